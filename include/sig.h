@@ -215,7 +215,9 @@ int    sig_wordset_upload(sig_wordset* ws, void* dev_buf /*device*/, size_t dev_
  * (or on request, option "chunks") and recomputes the chunk signatures from the path.  Word sets closed under suffixes (sig_wordset_suffix_closed) that run through the
  * run-time specialised kernels take the chunks of the checkpointed calls below in sig_forward as well, with the
  * chunk signatures in the workspace; sig_backward recomputes them and does the same from four chunks on (few long
- * paths), where that still beats walking whole paths.
+ * paths), where that still beats walking whole paths.  Full truncations that run with a word per lane take time chunks in
+ * both directions wherever that is faster and the workspace holds them; sig_forward without a workspace (NULL), and
+ * sig_backward_static, walk whole paths there.
  * n_points == 1 gives all-zero coeffs (S_{0,0} = 1 has no non-empty-word part).  B == 0 is a no-op. */
 size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 int    sig_forward(const sig_wordset* ws, const float* path, int64_t B, int64_t n_points, float* coeffs,

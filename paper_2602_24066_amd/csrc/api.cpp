@@ -552,6 +552,43 @@ bool use_lanes(const sig::WordSet& w, int64_t B)
     return f == 1 || std::min(s.lanes, sb.lanes) >= 32;
 }
 
+// Time chunks of those truncations: a wavefront takes 0.15-0.2 us per segment forward and 0.5-0.7 us backward however few
+// there are, so few paths are cut into C chunks that run as rows of their own.  Forward: chunk signatures, then their
+// product; backward: chunk signatures over the words shorter than the depth (a d-th of the work; the longest words are
+// never reconstructed), their products from both sides, the adjoints at the boundaries, then the rows.
+Chunks lanes_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points)
+{
+    const int64_t L = n_points - 1;
+    int64_t C = 1;
+    if (L >= 16 && B >= 1 && sig::lanes_chunks_available(w.d, w.depth)) {
+        if (w.opt.chunks > 0) {
+            C = std::min<int64_t>(std::min<int64_t>(w.opt.chunks, 64), L / 4);        // tuning knob
+        } else {
+            sig::WordSet::LanesMemo& memo = const_cast<sig::WordSet&>(w).lanes_memo;
+            const int levels = lanes_levels_asked(w);
+            std::lock_guard<std::mutex> lock(memo.m);
+            C = 0;
+            for (const auto& c : memo.choices)
+                if (c.dir == dir && c.B == B && c.L == L && c.levels == levels) C = c.C;
+            if (C == 0) {
+                sig::WordSet::ChunkChoice& c = memo.choices[memo.next];
+                memo.next = (memo.next + 1) % 16;
+                c.dir = dir; c.B = B; c.L = L; c.levels = levels;
+                c.C = sig::lanes_chunk_count(w.d, w.depth, dir != 0, B, L, levels);
+                C = c.C;
+            }
+        }
+    }
+    if (C < 2 || B * C > 65535) return Chunks{1, L};
+    const int64_t Lc = (L + C - 1) / C;
+    return Chunks{(L + Lc - 1) / Lc, Lc};
+}
+// rows of words shorter than the depth, [B][C] of them
+size_t lanes_low_bytes(const sig::WordSet& w, int64_t B, int64_t C)
+{
+    return ((size_t)B * (size_t)C * (size_t)w.level_start[(size_t)w.depth] * sizeof(float) + 255) & ~(size_t)255;
+}
+
 sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesShape& s, Build how)
 {
     sig::WordSet& w = const_cast<sig::WordSet&>(cw);     // the cache is logically mutable
@@ -567,26 +604,134 @@ sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesSh
     return bring_up(k, how, dir ? "sig_bwd_lanes" : "sig_fwd_lanes", [&](sig::JitKernel& kk) {
         kk.nw = s.nwb;
         kk.tile = s.T;
+        if (sig::lanes_chunks_available(w.d, w.depth)) {
+            auto waves = [&](sig::LanesChunkPart part) { return sig::lanes_chunk_threads(w.d, w.depth, part) / 64; };
+            if (dir == 0) kk.more = {{"sig_scan_lanes", waves(sig::kLanesScanFull), nullptr}};
+            else kk.more = {{"sig_scan_lanes", waves(sig::kLanesScanLow), nullptr},
+                            {"sig_low_lanes", sig::lanes_low_shape(w.d, w.depth).nwb, nullptr},
+                            {"sig_adjoint_lanes", waves(sig::kLanesAdjoint), nullptr}};
+        }
         return sig::lanes_source(w.d, w.depth, s, dir != 0);
     });
 }
 
-// rows: the B paths, or with a window list the B * K (path, window) pairs, read straight from the path
-hipError_t launch_lanes(sig::JitKernel& k, const sig::LanesShape& s, const float* path, const float* coeffs_in, const float* grad,
-                        int64_t B, int64_t n_points, float* out, hipStream_t st, const sig::WindowList& wl = sig::WindowList())
+// rows: the B paths, with a window list the B * K (path, window) pairs, or (wl.win == nullptr, wl.K > 1) the K time chunks of
+// wl.max_len segments of every path; read straight from the path.  Backward over chunks: low_coeffs and low_grad hold
+// signature and adjoint at the end of every chunk but the last, [B][K - 1][words shorter than the depth].
+hipError_t launch_lanes(hipFunction_t fn, const sig::LanesShape& s, const float* path, const float* coeffs_in, const float* grad,
+                        int64_t B, int64_t n_points, float* out, hipStream_t st, const sig::WindowList& wl = sig::WindowList(),
+                        const float* low_coeffs = nullptr, const float* low_grad = nullptr)
 {
-    long lB = (long)B, lP = (long)n_points, lK = (long)wl.K, lM = (long)wl.max_len;
+    const bool parts = wl.several_rows();
+    long lB = (long)B, lP = (long)n_points, lK = (long)wl.rows_per_path(), lM = parts ? (long)wl.max_len : lP - 1;
     const int64_t* win = wl.win;
-    const int64_t rows = B * (wl.win ? wl.K : 1);
-    const int64_t blocks = (rows * s.waves + k.nw - 1) / k.nw;
+    const int64_t rows = B * wl.rows_per_path();
+    const int64_t blocks = (rows * s.waves + s.nwb - 1) / s.nwb;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (grad) {
         void* args[] = {(void*)&path, (void*)&coeffs_in, (void*)&grad, (void*)&lB, (void*)&lP, (void*)&out, (void*)&win, (void*)&lK,
-                        (void*)&lM};
-        return hipModuleLaunchKernel(k.fn, (unsigned)blocks, 1, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
+                        (void*)&lM, (void*)&low_coeffs, (void*)&low_grad};
+        return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
     }
     void* args[] = {(void*)&path, (void*)&lB, (void*)&lP, (void*)&out, (void*)&win, (void*)&lK, (void*)&lM};
-    return hipModuleLaunchKernel(k.fn, (unsigned)blocks, 1, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
+    return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
+}
+
+// The module of a chunked call, or false where it lacks one of the kernels (then the call walks whole paths).
+struct LanesChunked {
+    sig::LanesShape main, low;
+    sig::JitKernel* k = nullptr;
+    const sig::JitKernel::More& scan() const { return k->more[0]; }
+    const sig::JitKernel::More& lower() const { return k->more[1]; }
+    const sig::JitKernel::More& adjoint() const { return k->more[2]; }
+};
+bool lanes_chunk_kernels(const sig::WordSet& w, int dir, int64_t rows, Build how, LanesChunked& c)
+{
+    c.main = lanes_shape_for(w, dir, rows);
+    if (!c.main.ok || rows * c.main.waves > (int64_t)0x7fffffff) return false;
+    c.k = ensure_lanes(w, dir, c.main, how);
+    if (!c.k || c.k->more.empty()) return false;
+    if (dir) c.low = sig::lanes_low_shape(w.d, w.depth);
+    if (how == Build::compile_only) return true;
+    for (const auto& m : c.k->more)
+        if (!m.fn) return false;
+    return true;
+}
+// The first call with B paths brings up whatever paths of another length may need as well (chunked or whole: another
+// number of rows may take the other number of levels per lane), so that later calls of that batch size compile and
+// load nothing - under graph capture, or in sig_backward_static, they could not.
+void lanes_bring_up(const sig::WordSet& cw, int dir, int64_t B, Build how)
+{
+    if (how == Build::loaded_only) return;
+    sig::WordSet& w = const_cast<sig::WordSet&>(cw);
+    sig::WordSet::LanesMemo& memo = w.lanes_memo;
+    if (how == Build::compile_and_load) {
+        std::lock_guard<std::mutex> lock(memo.m);
+        for (const auto& l : memo.loaded)
+            if (l.first == dir && l.second == B) return;
+        try {
+            if (memo.loaded.size() >= 64) memo.loaded.clear();
+            memo.loaded.emplace_back(dir, B);
+        } catch (const std::bad_alloc&) { }
+    }
+    (void)ensure_lanes(w, dir, lanes_shape_for(w, dir, B), how);
+    if (!sig::lanes_chunks_available(w.d, w.depth)) return;
+    LanesChunked k;
+    for (int C : sig::kLanesChunkCounts) (void)lanes_chunk_kernels(w, dir, B * C, how, k);
+}
+// forward, workspace: the chunk signatures [B][C][|W|]
+hipError_t lanes_forward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, int64_t B, int64_t n_points,
+                                 const Chunks& ch, float* coeffs, float* Sc, hipStream_t st)
+{
+    sig::WindowList rows;
+    rows.K = ch.C; rows.max_len = ch.Lc;
+    hipEvent_t* pe = g_prof.next(0);
+    if (pe) (void)hipEventRecord(pe[0], st);
+    hipError_t e = launch_lanes(k.k->fn, k.main, path, nullptr, nullptr, B, n_points, Sc, st, rows);
+    if (pe) (void)hipEventRecord(pe[1], st);
+    if (e != hipSuccess) return e;
+    long lC = (long)ch.C;
+    float* none = nullptr;
+    void* args[] = {(void*)&Sc, (void*)&lC, (void*)&coeffs, (void*)&none};
+    return hipModuleLaunchKernel(k.scan().fn, (unsigned)(B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, args, nullptr);
+}
+// backward, workspace: increment gradients | chunk signatures [B][C], products from the left, from the right and boundary
+// adjoints [B][C - 1], rows of words shorter than the depth
+size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, int64_t n_points, const Chunks& ch)
+{
+    const size_t gdx = ((size_t)B * (size_t)(n_points - 1) * (size_t)w.d * sizeof(float) + 255) & ~(size_t)255;
+    return gdx + lanes_low_bytes(w, B, ch.C) + 3 * lanes_low_bytes(w, B, ch.C - 1);
+}
+hipError_t lanes_backward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, const float* coeffs,
+                                  const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, float* grad_path,
+                                  void* workspace, hipStream_t st)
+{
+    const int64_t n_gdx = B * (n_points - 1) * w.d;
+    const size_t gb = ((size_t)n_gdx * sizeof(float) + 255) & ~(size_t)255, nb = lanes_low_bytes(w, B, ch.C - 1);
+    unsigned char* base = (unsigned char*)workspace;
+    float* gdx = (float*)base;
+    float* Sc = (float*)(base + gb);
+    float* left = (float*)(base + gb + lanes_low_bytes(w, B, ch.C));
+    float* right = (float*)((unsigned char*)left + nb);
+    float* abar = (float*)((unsigned char*)right + nb);
+    sig::WindowList rows;
+    rows.K = ch.C; rows.max_len = ch.Lc;
+    hipError_t e = launch_lanes(k.lower().fn, k.low, path, nullptr, nullptr, B, n_points, Sc, st, rows);
+    if (e != hipSuccess) return e;
+    long lC = (long)ch.C, lC1 = lC - 1, lz = (long)n_gdx;
+    void* scan_args[] = {(void*)&Sc, (void*)&lC, (void*)&left, (void*)&right};
+    e = hipModuleLaunchKernel(k.scan().fn, (unsigned)(2 * B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, scan_args, nullptr);
+    if (e != hipSuccess) return e;
+    void* adj_args[] = {(void*)&grad_coeffs, (void*)&right, (void*)&lC1, (void*)&abar, (void*)&gdx, (void*)&lz};
+    e = hipModuleLaunchKernel(k.adjoint().fn, (unsigned)(B * (ch.C - 1) * w.d), 1, 1, (unsigned)k.adjoint().nw * 64, 1, 1, 0, st, adj_args,
+                              nullptr);
+    if (e != hipSuccess) return e;
+    hipEvent_t* pe = g_prof.next(1);
+    if (pe) (void)hipEventRecord(pe[0], st);
+    e = launch_lanes(k.k->fn, k.main, path, coeffs, grad_coeffs, B, n_points, gdx, st, rows, left, abar);
+    if (pe) (void)hipEventRecord(pe[1], st);
+    if (e != hipSuccess) return e;
+    return sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
 }
 }  // namespace
 
@@ -807,7 +952,10 @@ int sig_wordset_jit_prepare(sig_wordset* ws, int backward, int64_t B)
     const int dir = backward ? 1 : 0;
     if (!jit_enabled(w)) return SIG_EUNSUPPORTED;
     if (dir == 0 ? use_trunc_forward(w, B) : use_trunc_backward(w, B)) return SIG_EUNSUPPORTED;
-    if (use_lanes(w, B)) return ensure_lanes(w, dir, lanes_shape_for(w, dir, B), Build::compile_only) ? SIG_OK : SIG_EJIT;
+    if (use_lanes(w, B)) {
+        lanes_bring_up(w, dir, B, Build::compile_only);
+        return ensure_lanes(w, dir, lanes_shape_for(w, dir, B), Build::compile_only) ? SIG_OK : SIG_EJIT;
+    }
     return ensure_jit(w, dir, B, Build::compile_only) ? SIG_OK : SIG_EJIT;
 }
 
@@ -858,6 +1006,10 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
     }
     if (!jit_enabled(w)) return 0;
     size_t n = jit_dxt_bytes(w, B, n_points, 0);
+    if (use_lanes(w, B)) {
+        const Chunks ch = lanes_chunks(w, 0, B, n_points);
+        if (ch.C > 1) n = std::max(n, chunk_array_bytes(w, B, ch.C));
+    }
     if (w.kind != 0) {
         // sets closed under suffixes: time chunks as in the checkpointed calls, the chunk signatures in the workspace
         const Chunks ch = checkpoint_chunks(w, B, n_points);
@@ -889,6 +1041,10 @@ size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_
     size_t n = backward_workspace(ws, B, n_points, true);
     if (n == 0) return 0;
     const sig::WordSet& w = *W(ws);
+    if (!use_trunc_backward(w, B) && use_lanes(w, B)) {
+        const Chunks ch = lanes_chunks(w, 1, B, n_points);
+        if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, n_points, ch));
+    }
     if (w.kind != 0 && jit_enabled(w)) {
         const Chunks ch = checkpoint_chunks(w, B, n_points);
         if (words_backward_recomputes(w, ch)) n = std::max(n, words_backward_recompute_workspace(w, B, ch));
@@ -951,11 +1107,20 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     if (use_lanes(w, B)) {
+        // (a caller without a workspace for the chunk signatures gets the walk over whole paths)
+        lanes_bring_up(w, 0, B, Build::compile_and_load);
+        const Chunks ch = lanes_chunks(w, 0, B, n_points);
+        LanesChunked lc;
+        if (ch.C > 1 && workspace && workspace_bytes >= chunk_array_bytes(w, B, ch.C) && ((uintptr_t)workspace & 255) == 0 &&
+            lanes_chunk_kernels(w, 0, B * ch.C, Build::compile_and_load, lc)) {
+            hipError_t e = lanes_forward_chunked(w, lc, path, B, n_points, ch, coeffs, (float*)workspace, st);
+            return e == hipSuccess ? SIG_OK : hip_fail(e);
+        }
         const sig::LanesShape ls = lanes_shape_for(w, 0, B);
         if (sig::JitKernel* lk = ensure_lanes(w, 0, ls, Build::compile_and_load)) {
             hipEvent_t* pe = g_prof.next(0);
             if (pe) (void)hipEventRecord(pe[0], st);
-            hipError_t e = launch_lanes(*lk, ls, path, nullptr, nullptr, B, n_points, coeffs, st);
+            hipError_t e = launch_lanes(lk->fn, ls, path, nullptr, nullptr, B, n_points, coeffs, st);
             if (pe) (void)hipEventRecord(pe[1], st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
@@ -1073,11 +1238,24 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         hipError_t e = sig::fill_zero(grad_path, B * w.d, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
-    const size_t need = word_chunks ? sig_backward_workspace_bytes(ws, B, n_points) : backward_workspace(ws, B, n_points, false);
+    // the chunks of the word-per-lane kernels are taken where the workspace holds them, not asked for
+    const bool lanes_path = !use_trunc_backward(w, B) && use_lanes(w, B);
+    const size_t need = word_chunks && !lanes_path ? sig_backward_workspace_bytes(ws, B, n_points)
+                                                   : backward_workspace(ws, B, n_points, false);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;
     CallTimer whole(1, st);
+    if (lanes_path && word_chunks && !residual) {
+        lanes_bring_up(w, 1, B, how);
+        const Chunks lch = lanes_chunks(w, 1, B, n_points);
+        LanesChunked lc;
+        if (lch.C > 1 && workspace_bytes >= lanes_backward_chunked_bytes(w, B, n_points, lch) &&
+            lanes_chunk_kernels(w, 1, B * lch.C, how, lc)) {
+            hipError_t le = lanes_backward_chunked(w, lc, path, coeffs, grad_coeffs, B, n_points, lch, grad_path, workspace, st);
+            return le == hipSuccess ? SIG_OK : hip_fail(le);
+        }
+    }
     if (word_chunks && w.kind != 0 && jit_enabled(w) && !residual) {
         // suffix-closed set, few long paths: chunk signatures recomputed, then the route of the checkpointed call
         const Chunks wc = checkpoint_chunks(w, B, n_points);
@@ -1156,7 +1334,7 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         if (lk) {
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_lanes(*lk, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st);
+            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st);
             if (pe) (void)hipEventRecord(pe[1], st);
             if (e != hipSuccess) return hip_fail(e);
             e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
@@ -1428,7 +1606,7 @@ int sig_forward_windows(const sig_wordset* ws, const float* path, int64_t B, int
             wl.win = windows; wl.K = K; wl.max_len = max_window_len;
             hipEvent_t* pe = g_prof.next(0);
             if (pe) (void)hipEventRecord(pe[0], st);
-            hipError_t e = launch_lanes(*lk, ls, path, nullptr, nullptr, B, n_points, coeffs, st, wl);
+            hipError_t e = launch_lanes(lk->fn, ls, path, nullptr, nullptr, B, n_points, coeffs, st, wl);
             if (pe) (void)hipEventRecord(pe[1], st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
@@ -1510,7 +1688,7 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
             if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_lanes(*lk, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st, wl);
+            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st, wl);
             if (pe) (void)hipEventRecord(pe[1], st);
             if (e != hipSuccess) return hip_fail(e);
             e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);

@@ -464,6 +464,24 @@ bool jit_launch_shape_fits(int nw, int max_threads_per_block, int static_lds_byt
     return num_regs * per_simd <= 512;
 }
 
+namespace {
+// whether what a loaded function declares fits workgroups of nw wavefronts
+hipError_t check_shape(JitKernel& k, hipFunction_t fn, int nw, bool& fits)
+{
+    int max_threads = 0, lds = 0, regs = 0;
+    hipError_t e = hipFuncGetAttribute(&max_threads, HIP_FUNC_ATTRIBUTE_MAX_THREADS_PER_BLOCK, fn);
+    if (e == hipSuccess) e = hipFuncGetAttribute(&lds, HIP_FUNC_ATTRIBUTE_SHARED_SIZE_BYTES, fn);
+    if (e == hipSuccess) e = hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, fn);
+    if (e != hipSuccess) return e;
+    fits = jit_launch_shape_fits(nw, max_threads, lds, regs);
+    if (!fits)
+        k.log += "\nrefused: the code object does not fit the launch shape (" + std::to_string(nw * 64) + " threads; declares max " +
+                 std::to_string(max_threads) + " threads, " + std::to_string(lds) + " bytes of LDS, " + std::to_string(regs) +
+                 " registers)";
+    return hipSuccess;
+}
+}  // namespace
+
 hipError_t jit_load(JitKernel& k)
 {
     int dev = -1;
@@ -475,17 +493,16 @@ hipError_t jit_load(JitKernel& k)
     hipFunction_t fn = nullptr;
     e = hipModuleGetFunction(&fn, k.mod, k.name.c_str());
     if (e != hipSuccess) return e;
-    int max_threads = 0, lds = 0, regs = 0;
-    if ((e = hipFuncGetAttribute(&max_threads, HIP_FUNC_ATTRIBUTE_MAX_THREADS_PER_BLOCK, fn)) != hipSuccess) return e;
-    if ((e = hipFuncGetAttribute(&lds, HIP_FUNC_ATTRIBUTE_SHARED_SIZE_BYTES, fn)) != hipSuccess) return e;
-    if ((e = hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, fn)) != hipSuccess) return e;
-    if (!jit_launch_shape_fits(k.nw, max_threads, lds, regs)) {
-        k.log += "\nrefused: the code object does not fit the launch shape (" + std::to_string(k.nw * 64) + " threads; declares max " +
-                 std::to_string(max_threads) + " threads, " + std::to_string(lds) + " bytes of LDS, " + std::to_string(regs) +
-                 " registers)";
+    bool fits = false;
+    if ((e = check_shape(k, fn, k.nw, fits)) != hipSuccess) return e;
+    if (!fits) {
         (void)hipModuleUnload(k.mod);
         k.mod = nullptr;
         return hipErrorLaunchOutOfResources;
+    }
+    for (JitKernel::More& m : k.more) {
+        hipFunction_t f = nullptr;
+        if (hipModuleGetFunction(&f, k.mod, m.name) == hipSuccess && check_shape(k, f, m.nw, fits) == hipSuccess && fits) m.fn = f;
     }
     k.fn = fn;
     k.dev = dev;

@@ -17,6 +17,9 @@ struct JitKernel {
     std::string cache_file;        // set when the code object came from the disk cache
     hipModule_t mod = nullptr;
     hipFunction_t fn = nullptr;
+    // further kernels of the module and their wavefronts per workgroup; one that does not fit its launch stays nullptr
+    struct More { const char* name; int nw; hipFunction_t fn; };
+    std::vector<More> more;
     int dev = -1;                  // device the module was loaded on
     int nw = 0;                    // wavefronts (units) per workgroup
     int tile = 0;                  // segments per LDS tile
@@ -46,10 +49,23 @@ struct LanesShape {
     bool ok;
     int R, T, TS, nwb;
     int64_t lanes, waves;
+    int chain;                     // multiply-adds of a lane's chain per segment
+    double per_lane;               // instructions of a lane per segment, for comparing shapes
 };
 // the form for a batch of B paths; levels = 1 or 2 asks for that R (0: the cheaper one)
 LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels);
-// source of sig_fwd_lanes (backward = false) or sig_bwd_lanes for that shape
+// Time chunks of those truncations: products of the chunk signatures over all words (one workgroup per path and first
+// letter; the forward call), over the words shorter than the depth in both directions (two per path and letter; the
+// backward call), and the adjoints at the chunk boundaries (one per boundary and first letter).
+enum LanesChunkPart { kLanesScanFull = 0, kLanesScanLow = 1, kLanesAdjoint = 2 };
+int lanes_chunk_threads(int d, int depth, LanesChunkPart part);   // of a workgroup
+LanesShape lanes_low_shape(int d, int depth);                 // forward kernel over the words shorter than the depth
+bool lanes_chunks_available(int d, int depth);
+// source of sig_fwd_lanes (backward = false) or sig_bwd_lanes for that shape and, where time chunks are available, of the
+// kernels they take: sig_scan_lanes, and backward sig_low_lanes (forward) and sig_adjoint_lanes as well
 std::string lanes_source(int d, int depth, const LanesShape& s, bool backward);
+constexpr int kLanesChunkCounts[] = {2, 3, 4, 6, 8, 12, 16, 24, 32};
+// time chunks for B paths of L segments: the count with the shortest modelled time, 1 where none gains a tenth
+int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels);
 
 }  // namespace sig

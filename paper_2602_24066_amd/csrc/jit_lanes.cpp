@@ -105,18 +105,18 @@ __device__ __forceinline__ void load_row(const float* row, float (&e)[DP])
     }
 }
 
-// Row r: a whole path (win == nullptr: path r) or window r % KW of path r / KW, between the points win[2 k] and
-// win[2 k + 1] clamped to the path, at most max_len segments; read straight from the path.
-__device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, long max_len, long r, long P, long& b, long& first,
-                                       long& L)
+// Row r is part k = r % KW of path r / KW, read straight from the path: with win == nullptr time chunk k, max_len segments
+// from segment k * max_len on (KW = 1 and max_len = P - 1: the whole path); otherwise window k, between the points
+// win[2 k] and win[2 k + 1] clamped to the path, at most max_len segments.
+__device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, long max_len, long r, long P, long& b, long& k,
+                                       long& first, long& L)
 {
+    b = r / KW;
+    k = r - b * KW;
     if (win == nullptr) {
-        b = r;
-        first = 0;
-        L = P - 1;
+        first = k * max_len;
+        L = P - 1 - first < max_len ? P - 1 - first : max_len;
     } else {
-        b = r / KW;
-        const long k = r - b * KW;
         long l = win[2 * k], e = win[2 * k + 1];
         l = l < 0 ? 0 : (l > P - 1 ? P - 1 : l);
         e = e < l ? l : (e > P - 1 ? P - 1 : e);
@@ -126,7 +126,7 @@ __device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, lo
 }
 
 #if !BACKWARD
-extern "C" __global__ __launch_bounds__(64 * NWB) void sig_fwd_lanes(const float* __restrict__ path, long B, long P,
+extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float* __restrict__ path, long B, long P,
                                                                       float* __restrict__ coeffs, const long* __restrict__ win,
                                                                       long KW, long max_len)
 {
@@ -134,12 +134,12 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_fwd_lanes(const float
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long wave = (long)blockIdx.x * NWB + wib;
-    if (wave >= B * (win ? KW : 1) * WAVES) return;      // wavefronts share nothing: no barrier is skipped
+    if (wave >= B * KW * WAVES) return;                  // wavefronts share nothing: no barrier is skipped
     float* Ec = smem + wib * TILE_F;
     const float* E0 = Ec + TS * D * NC;
     const long row = wave / WAVES;
-    long b, first, L;
-    row_of(win, KW, max_len, row, P, b, first, L);
+    long b, part, first, L;
+    row_of(win, KW, max_len, row, P, b, part, first, L);
     const int p0 = __builtin_amdgcn_readfirstlane((int)(wave - row * WAVES) * 64);
     const bool valid = p0 + lane < NL;
     const int p = valid ? p0 + lane : NL - 1;
@@ -246,19 +246,19 @@ __device__ __forceinline__ float row_sum(const float* row, int lane)
 
 extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float* __restrict__ path,
         const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* gdx,
-        const long* __restrict__ win, long KW, long max_len)
+        const long* __restrict__ win, long KW, long max_len, const float* __restrict__ low_coeffs, const float* __restrict__ low_grad)
 {
     __shared__ __attribute__((aligned(16))) float smem[NWB * BW_PER_WAVE];
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long wave = (long)blockIdx.x * NWB + wib;
-    if (wave >= B * (win ? KW : 1) * WAVES) return;
+    if (wave >= B * KW * WAVES) return;
     float* Ec = smem + wib * BW_PER_WAVE;
     const float* E0 = Ec + TS * D * NC;
     float* Vb = Ec + TILE_F;
     const long row = wave / WAVES;
-    long b, first, L;
-    row_of(win, KW, max_len, row, P, b, first, L);
+    long b, part, first, L;
+    row_of(win, KW, max_len, row, P, b, part, first, L);
     const int p0 = __builtin_amdgcn_readfirstlane((int)(wave - row * WAVES) * 64);
     const bool valid = p0 + lane < NL;
     const int p = valid ? p0 + lane : NL - 1;
@@ -270,8 +270,15 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     }
     if (L <= 0) return;                                  // an empty window: no gradient (wavefronts share no barrier)
     const float* X = path + (b * P + first) * D;
-    const float* cf = coeffs + row * NWORDS;
-    const float* gr = grad + row * NWORDS;
+    // Whole paths and windows have a row of their own in coeffs and grad.  A time chunk takes the adjoints of the words of
+    // length N, constant in time, from its path's row, and so does a path's last chunk with all others; for the chunks
+    // before it, signature and adjoints at the end of the chunk (words shorter than N, the longest are never
+    // reconstructed) are rows of low_coeffs and low_grad [B][KW - 1].
+    const long whole = win == nullptr ? b : row;
+    const bool inner = win == nullptr && part + 1 < KW;
+    const float* gr = grad + whole * NWORDS;
+    const float* cf = inner ? low_coeffs + (b * (KW - 1) + part) * level_start(N) : coeffs + whole * NWORDS;
+    const float* gl = inner ? low_grad + (b * (KW - 1) + part) * level_start(N) : gr;
     float* const gdx_row = gdx + (b * (P - 1) + first) * D;     // the gradients of overlapping windows add up here
 
     // signature and adjoints at the end of the path; a word shared by several lanes has its adjoint in the first
@@ -280,10 +287,10 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     for (int k = 1; k <= K; ++k) {
         const long w = level_start(k) + p / ipow(D, K - k);
         Sc[k - 1] = cf[w];
-        Ac[k - 1] = valid && p % ipow(D, K - k) == 0 ? gr[w] : 0.0f;
+        Ac[k - 1] = valid && p % ipow(D, K - k) == 0 ? gl[w] : 0.0f;
     }
 #pragma unroll
-    for (int j = 0; j < D; ++j) A1[j] = valid ? gr[level_start(K + 1) + (long)p * D + j] : 0.0f;
+    for (int j = 0; j < D; ++j) A1[j] = valid ? (R == 1 ? gr : gl)[level_start(K + 1) + (long)p * D + j] : 0.0f;
 #if R == 2
     float S1[D], An[D][D];
 #pragma unroll
@@ -452,6 +459,240 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #endif
 )SRC";
 
+// Time chunks (Chen's relation, eq. (2)): products of the chunk signatures S_0 .. S_{C-1} of a path, and the adjoints
+// at the chunk boundaries, for any alphabet size.
+const char* const kLanesChunkSource = R"SRC(
+constexpr int ipow(int b, int e)
+{
+    int r = 1;
+    for (int q = 0; q < e; ++q) r *= b;
+    return r;
+}
+// first canonical index of the words of length n >= 1 (= how many are shorter), and the same inside a slice, which has
+// D^(n - 1) words of length n
+constexpr int level_start(int n)
+{
+    int r = 0;
+    for (int m = 1; m < n; ++m) r += ipow(D, m);
+    return r;
+}
+constexpr int slice_start(int n)
+{
+    int r = 0;
+    for (int m = 1; m < n; ++m) r += ipow(D, m - 1);
+    return r;
+}
+
+#if PART != 2
+// Products over words of length <= M.  A workgroup keeps one slice of the running product for one path: the words with
+// first letter i of S_0 S_1 .. S_c, whose factors on the left stay inside the slice, or with last letter i of
+// S_c .. S_{C-1}, whose factors on the right do.  So the D slices (and both directions) advance side by side and only
+// the words shorter than M of the next chunk signature are shared, staged in LDS.  The words of length M are never read
+// again and live in registers.  Bound by the latency of one chunk after the other (two barriers each; the loads of the
+// next chunk are in flight meanwhile).
+// PART 0: from the left, the full product to `left` [B][level_start(M + 1)].
+// PART 1: both directions, every product: left [B][C - 1] receives S_0 .. S_c, right [B][C - 1] S_{c+1} .. S_{C-1}.
+#define NS level_start(M)                   /* words shorter than M */
+#define NTOP ipow(D, M - 1)                 /* words of length M in a slice */
+#define QS ((NS + NT - 1) / NT)
+#define QT ((NTOP + NT - 1) / NT)
+#define ROW level_start(M + 1)
+
+// word e of length n of slice i
+__device__ __forceinline__ int word_of(bool from_left, int i, int n, int e)
+{
+    return level_start(n) + (from_left ? i * ipow(D, n - 1) + e : e * D + i);
+}
+// sum over the cuts of word e of length n of the slice, x the slice's lower levels and s the next chunk's
+template <int n>
+__device__ __forceinline__ float cuts(bool from_left, const float* x, const float* s, int e)
+{
+    float acc = 0.0f;
+    const unsigned u = (unsigned)e;
+    if (from_left) {
+#pragma unroll
+        for (int m = 1; m < n; ++m)
+            acc = __builtin_fmaf(x[slice_start(m) + u / (unsigned)ipow(D, n - m)], s[level_start(n - m) + u % (unsigned)ipow(D, n - m)], acc);
+    } else {
+#pragma unroll
+        for (int m = 1; m < n; ++m)
+            acc = __builtin_fmaf(s[level_start(m) + u / (unsigned)ipow(D, n - 1 - m)],
+                                 x[slice_start(n - m) + u % (unsigned)ipow(D, n - m - 1)], acc);
+    }
+    return acc;
+}
+// the words of length n <= M - 1: y = x times the next chunk, stored to out where the product is asked for
+template <int n>
+__device__ __forceinline__ void lower_level(bool from_left, int i, const float* x, const float* s, float* y, float* __restrict__ out)
+{
+    if constexpr (n < M) {
+        for (int e = threadIdx.x; e < ipow(D, n - 1); e += NT) {
+            const int w = word_of(from_left, i, n, e);
+            const float v = x[slice_start(n) + e] + s[w] + cuts<n>(from_left, x, s, e);
+            y[slice_start(n) + e] = v;
+            if (out) out[w] = v;
+        }
+        lower_level<n + 1>(from_left, i, x, s, y, out);
+    }
+}
+
+extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __restrict__ chunk_sigs, long C, float* __restrict__ left,
+                                                                float* __restrict__ right)
+{
+    __shared__ float s[NS], x[2][slice_start(M)];
+    const int tid = threadIdx.x;
+#if PART == 0
+    const bool from_left = true;
+    const int i = blockIdx.x % D;
+    const long b = blockIdx.x / D;
+#else
+    const bool from_left = blockIdx.x % 2 == 0;
+    const int i = blockIdx.x / 2 % D;
+    const long b = blockIdx.x / (2 * D);
+#endif
+    const float* rows = chunk_sigs + b * C * ROW;
+    const int n_chunks = (int)(PART == 0 ? C : C - 1);          // PART 1 needs no product over all chunks
+    // chunk number and output row of step n: forwards from the first chunk, or backwards from the last
+    const long c0 = from_left ? 0 : C - 1;
+    const long dc = from_left ? 1 : -1;
+    float top[QT], next_top[QT], next_s[QS];
+    {
+        const float* S0 = rows + c0 * ROW;
+        float* out = PART == 0 ? nullptr : (from_left ? left + b * (C - 1) * ROW : right + (b * (C - 1) + C - 2) * ROW);
+#pragma unroll
+        for (int n = 1; n < M; ++n)
+            for (int e = tid; e < ipow(D, n - 1); e += NT) {
+                const int w = word_of(from_left, i, n, e);
+                const float v = S0[w];
+                x[0][slice_start(n) + e] = v;
+                if (out) out[w] = v;
+            }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const int e = tid + q * NT;
+            top[q] = 0.0f;
+            if (e < NTOP) {
+                const int w = word_of(from_left, i, M, e);
+                top[q] = S0[w];
+                if (out) out[w] = top[q];
+            }
+        }
+    }
+    auto fetch = [&](long c) {
+        const float* S = rows + c * ROW;
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            next_s[q] = S[e < NS ? e : NS - 1];
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const int e = tid + q * NT;
+            next_top[q] = S[word_of(from_left, i, M, e < NTOP ? e : NTOP - 1)];
+        }
+    };
+    if (n_chunks > 1) fetch(c0 + dc);
+    for (int n = 1; n < n_chunks; ++n) {
+        float mine[QT];
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            if (e < NS) s[e] = next_s[q];
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) mine[q] = next_top[q];
+        __syncthreads();
+        fetch(c0 + dc * (n + 1 < n_chunks ? n + 1 : n));
+        float* out = PART == 0 ? nullptr : (from_left ? left + (b * (C - 1) + n) * ROW : right + (b * (C - 1) + C - 2 - n) * ROW);
+        const float* xo = x[(n - 1) & 1];
+        lower_level<1>(from_left, i, xo, s, x[n & 1], out);
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const int e = tid + q * NT;
+            if (e < NTOP) {
+                top[q] += mine[q] + cuts<M>(from_left, xo, s, e);
+                if (out) out[word_of(from_left, i, M, e)] = top[q];
+            }
+        }
+        __syncthreads();
+    }
+#if PART == 0
+    if (n_chunks == 1) __syncthreads();
+    const float* xo = x[(n_chunks - 1) & 1];
+    float* out = left + b * ROW;
+#pragma unroll
+    for (int n = 1; n < M; ++n)
+        for (int e = tid; e < ipow(D, n - 1); e += NT) out[word_of(true, i, n, e)] = xo[slice_start(n) + e];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const int e = tid + q * NT;
+        if (e < NTOP) out[word_of(true, i, M, e)] = top[q];
+    }
+#endif
+}
+#else
+// Adjoint at the boundary after chunk c: Abar(u) = grad(u) + sum_v grad(u v) Q_c(v) for the words u shorter than N
+// (Proposition 4.1 with the right factor Q_c = S_{c+1} .. S_{C-1}).  A workgroup takes one boundary of one path and the
+// words with one first letter: D^(N-1) products for every length of u, so each length gets as many lanes per word as
+// the workgroup has (all of it for the single word of length 1).  Q_c sits in LDS; the gradient row comes from L2.
+// On the way the workgroups clear n_zero floats at `zero` for the kernel that runs next.
+#define NLOW level_start(N)
+template <int n>
+__device__ __forceinline__ void length_n(int i, const float* __restrict__ g, const float* q, float* __restrict__ out, float* part)
+{
+    if constexpr (n < N) {
+        constexpr int U = ipow(D, n - 1);
+        constexpr int G = U == 1 ? 64 : (NT / U >= 64 ? 64 : (NT / U >= 32 ? 32 : (NT / U >= 16 ? 16 : (NT / U >= 8 ? 8 : (NT / U >= 4 ? 4 : (NT / U >= 2 ? 2 : 1))))));
+        constexpr int stride = U == 1 ? NT : G;                // lanes that share a word
+        const int lane = U == 1 ? threadIdx.x : threadIdx.x % G;
+        for (int u0 = 0; u0 < U; u0 += NT / stride) {
+            const int e = u0 + (U == 1 ? 0 : threadIdx.x / G);
+            float acc = 0.0f;
+            if (e < U) {
+                const int u = i * U + e;
+#pragma unroll
+                for (int m = 1; m <= N - n; ++m) {
+                    const float* gb = g + level_start(n + m) + u * ipow(D, m);
+#pragma unroll 4
+                    for (int v = lane; v < ipow(D, m); v += stride) acc = __builtin_fmaf(gb[v], q[level_start(m) + v], acc);
+                }
+            }
+#pragma unroll
+            for (int w = 1; w < G; w *= 2) acc += __shfl_xor(acc, w);
+            if (U == 1) {
+                if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = acc;
+            } else if (e < U && lane == 0) {
+                const int w = level_start(n) + i * U + e;
+                out[w] = g[w] + acc;
+            }
+        }
+        length_n<n + 1>(i, g, q, out, part);
+    }
+}
+
+extern "C" __global__ __launch_bounds__(NT) void sig_adjoint_lanes(const float* __restrict__ grad, const float* __restrict__ after, long C1,
+                                                                   float* __restrict__ abar, float* __restrict__ zero, long n_zero)
+{
+    __shared__ float q[NLOW], part[NT / 64];
+    const long bc = blockIdx.x / D;
+    const int i = blockIdx.x % D;
+    const float* Q = after + bc * NLOW;
+    const float* g = grad + bc / C1 * (long)level_start(N + 1);
+    float* out = abar + bc * NLOW;
+    for (int e = threadIdx.x; e < NLOW; e += NT) q[e] = Q[e];
+    for (long e = (long)blockIdx.x * NT + threadIdx.x; e < n_zero; e += (long)gridDim.x * NT) zero[e] = 0.0f;
+    __syncthreads();
+    length_n<1>(i, g, q, out, part);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float acc = g[i];
+        for (int w = 0; w < NT / 64; ++w) acc += part[w];
+        out[i] = acc;
+    }
+}
+#endif
+)SRC";
+
 }  // namespace
 
 LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
@@ -485,6 +726,8 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
             wide += run >= 32.0 ? 1 : 0;
         }
         const double per_lane = 2.0 * chain + (R == 2 ? (double)d * d + 3.0 * d : 2.0 * d);
+        s.chain = chain;
+        s.per_lane = per_lane;
         const double rounds = (double)std::max<int64_t>(B, 1) * (double)s.waves / 1024.0;
         const double cost = per_lane * (rounds < 1.0 ? 1.0 : rounds);
         // LDS of a wavefront: the increments of a staging tile and, backward, the gradient rows of the segments of a
@@ -519,12 +762,98 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
     return best;
 }
 
+namespace {
+int64_t words_up_to(int d, int n)
+{
+    int64_t r = 0, p = 1;
+    for (int m = 1; m <= n; ++m) { p *= d; r += p; }
+    return r;
+}
+// words of length `top` that a slice holds, over the threads of a workgroup
+int scan_threads(int64_t n_top) { return n_top <= 2048 ? 256 : (n_top <= 8192 ? 512 : 1024); }
+}  // namespace
+
+// The products over all words need the words shorter than the depth of one chunk and two copies of a slice in the
+// 64 KB of LDS a kernel may declare, and the words of full length of a slice in registers (at most 16 a thread).
+bool lanes_chunks_available(int d, int depth)
+{
+    if (d < 2 || d > 64 || depth < 3 || depth > 12) return false;
+    double top = 1.0;
+    for (int k = 1; k < depth; ++k) top *= d;
+    if (top > 16.0 * 1024.0) return false;
+    return (words_up_to(d, depth - 1) + 2 * (words_up_to(d, depth - 2) + 1)) * 4 <= 62 * 1024;
+}
+
+// Times in microseconds, fitted to a scan of 26 shapes (2..40 letters, depth 3..7, 1..512 paths of 24..1,000 segments, every
+// count of kLanesChunkCounts; the model's choice is within 5 % of the best count on average): a segment costs a fixed
+// share of its instructions while the wavefronts find free SIMDs and grows with their number beyond; chunks cost their
+// launches, a product per chunk and the traffic of the chunk signatures.  Gains measured at the choice: forward
+// 1 x 199 segments, d = 10, depth 4: 39 -> 16 us, 37 x 301, d = 7, depth 4: 45 -> 16; backward 125 -> 33 and 171 -> 46.
+int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels)
+{
+    const double words = (double)words_up_to(d, depth);
+    auto time = [&](int64_t C) {
+        LanesShape s = lanes_shape(d, depth, backward, B * C, levels);
+        if (!s.ok) s = lanes_shape(d, depth, backward, B * C, 0);
+        const double Lc = (double)((L + C - 1) / C), waves = (double)(B * C) * (double)s.waves;
+        if (!backward) {
+            const double t = 5.3 + Lc * (0.0022 * s.per_lane + 0.006 * s.chain) * std::max(1.0, waves / 2330.0);
+            return C == 1 ? t : t + 3.0 + (double)C * (0.6 + 2.5e-6 * (double)B * words);
+        }
+        const double t = 20.0 + Lc * (0.02 + 0.005 * s.per_lane + 0.026 * s.chain) * std::max(1.0, waves / 1230.0);
+        if (C == 1) return t;
+        const LanesShape low = lanes_low_shape(d, depth);
+        return t + 2.0 + (double)C * (0.63 + 4.0e-6 * (double)B * words) + 0.15 * Lc * std::max(1.0, (double)(B * C) * (double)low.waves / 2048.0);
+    };
+    const double whole = time(1);
+    double best = 0.9 * whole;
+    int choice = 1;
+    for (int C : kLanesChunkCounts) {
+        if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments
+        const double t = time(C);
+        if (t < best) {
+            best = t;
+            choice = C;
+        }
+    }
+    return choice;
+}
+
+int lanes_chunk_threads(int d, int depth, LanesChunkPart part)
+{
+    int64_t top = 1;                                          // words of the longest length in a slice
+    for (int k = 1; k < (part == kLanesScanLow ? depth - 1 : depth); ++k) top *= d;
+    return scan_threads(top);
+}
+
+// One shape for every batch: the words shorter than the depth are a d-th of the work.
+LanesShape lanes_low_shape(int d, int depth) { return lanes_shape(d, depth - 1, false, 256, 0); }
+
+// The kernels of a module share their text, with other shapes: a namespace each, the shape macros set anew in front of it.
 std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
 {
     std::ostringstream o;
-    o << "#define D " << d << "\n#define N " << depth << "\n#define R " << s.R << "\n#define T " << s.T << "\n#define TS " << s.TS << "\n#define NWB "
-      << s.nwb << "\n#define BACKWARD " << (backward ? 1 : 0) << "\n"
-      << kLanesSource;
+    auto lanes = [&](const char* ns, int n, const LanesShape& q, bool bwd, const char* forward_name) {
+        o << "#define N " << n << "\n#define R " << q.R << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
+          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name << "\nnamespace " << ns << " {\n"
+          << kLanesSource << "}\n#undef N\n#undef R\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef FORWARD_NAME\n";
+    };
+    auto chunk = [&](const char* ns, LanesChunkPart part) {
+        o << "#define N " << depth << "\n#define M " << (part == kLanesScanLow ? depth - 1 : depth)
+          << "\n#define NT " << lanes_chunk_threads(d, depth, part) << "\n#define PART " << (int)part << "\nnamespace " << ns << " {\n"
+          << kLanesChunkSource << "}\n#undef N\n#undef M\n#undef NT\n#undef PART\n";
+    };
+    o << "#define D " << d << "\n";
+    lanes("rows", depth, s, backward, "sig_fwd_lanes");
+    if (lanes_chunks_available(d, depth)) {
+        if (!backward) {
+            chunk("scan", kLanesScanFull);
+        } else {
+            lanes("low", depth - 1, lanes_low_shape(d, depth), false, "sig_low_lanes");
+            chunk("scan", kLanesScanLow);
+            chunk("adjoint", kLanesAdjoint);
+        }
+    }
     return o.str();
 }
 

@@ -3,7 +3,9 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace sig {
@@ -123,6 +125,15 @@ struct WordSet {
     // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp); built on
     // first use
     JitKernel* lanes[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    // the last few decisions on their number of time chunks (each takes microseconds to model), and the batch sizes whose
+    // kernels, for every number of chunks, have been brought up; both under the lock
+    struct ChunkChoice { int64_t B = 0, L = 0; int dir = -1, levels = 0, C = 1; };
+    struct LanesMemo {
+        std::mutex m;
+        ChunkChoice choices[16];
+        int next = 0;
+        std::vector<std::pair<int, int64_t>> loaded;    // (direction, batch size), bounded
+    } lanes_memo;
     WordSet() = default;
     WordSet(const WordSet&) = delete;
     WordSet& operator=(const WordSet&) = delete;

@@ -497,6 +497,44 @@ def test_truncations_with_lanes_as_words(d, depth, B, L, levels, monkeypatch):
     check_parity(ws, W, "truncated", depth, X, G, what=f"lanes = words, d={d} N={depth}, {levels} levels per lane")
 
 
+@pytest.mark.parametrize("d,depth,B,L,chunks", [
+    (6, 5, 3, 21, 2),     # ragged last chunk
+    (10, 4, 1, 50, 7),    # chunks of 8 segments, the last of 2
+    (7, 3, 5, 64, 16),    # depth 3: products over single letters and pairs only; chunks of 4 segments
+    (2, 7, 4, 100, 5),    # products of up to six cuts, slices of 64 words
+    (9, 5, 1, 24, 3),     # 6,561 words of full length in a slice (512 threads), Q of 7,380 words
+    (40, 3, 1, 32, 8),    # one word of length 1 and 40 of length 2 per slice
+    (3, 8, 2, 33, 4),     # a chunk of 9 segments, the last of 6
+    (12, 4, 2, 17, 2),    # the smallest length the launcher looks at is 16
+    (6, 6, 2, 40, 0),     # the launcher's own choice (0), both directions
+    (10, 4, 40, 70, 0),
+    (5, 5, 9, 333, 0),
+])
+def test_time_chunks_of_truncations_with_lanes_as_words(d, depth, B, L, chunks, monkeypatch):
+    """Time chunks of the word-per-lane truncations: chunk signatures, their products by first and last letter, the
+    boundary adjoints and the walk over (path, chunk) rows, against the oracle; a call without a workspace walks whole
+    paths and agrees to rounding (fp32 sums of L segments)."""
+    import ctypes
+
+    import torch
+    monkeypatch.setenv("SIG_LANES", "1")
+    ws, W = build_both("truncated", d, depth=depth)
+    ws.set_option("chunks", chunks)
+    X = make_path("iid", 171 + d, B, L, d)
+    G = make_grad_coeffs(172 + d, B, ws.size)
+    lib = S.load_library()
+    if chunks:
+        assert lib.sig_forward_workspace_bytes(ws._h, B, L + 1) >= 4 * B * 2 * ws.size  # room for two chunks at least
+    check_parity(ws, W, "truncated", depth, X, G, what=f"time chunks, lanes = words, d={d} N={depth} C={chunks}")
+    x = torch.from_numpy(X).cuda()
+    c = S.sig_forward(ws, x)
+    whole = torch.full_like(c, float("nan"))
+    assert lib.sig_forward(ws._h, ctypes.c_void_p(x.data_ptr()), B, L + 1, ctypes.c_void_p(whole.data_ptr()), None, 0,
+                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    assert float((c - whole).norm() / whole.norm()) <= 1e-5
+
+
 def test_lanes_as_words_on_a_long_path():
     """5,000 segments through the word-per-lane kernels: many staging tiles, and the reconstruction of the
     backward pass over a long walk (within the gradient tolerance, as for the 4,096 segments of c5)."""

@@ -542,14 +542,30 @@ sig::LanesShape lanes_shape_for(const sig::WordSet& w, int dir, int64_t B)
     return s;
 }
 
-bool use_lanes(const sig::WordSet& w, int64_t B)
+// Sets whose words of length depth - R fill less than half a wavefront (30 words over 2 letters, 72 over 8) still win that
+// way while the paths are few: lanes = paths walks every path from end to end behind a transposition of its increments and
+// cannot cut it into time chunks.  Measured, step (forward + backward), lanes = paths -> lanes = words: 2 letters, depth 4:
+// 32 x 64 segments 44 -> 30 us, 512 x 500 190 -> 104, 1,024 x 100 58 -> 59, 1,500 x 200 92 -> 120; 3 letters, depth 3:
+// 512 x 500 218 -> 85, 1,024 x 100 65 -> 47; 12 letters, depth 2: 32 x 500 335 -> 41, 1,500 x 200 176 -> 108, 3,000 x 200
+// 212 -> 200.  So the line lies higher the fewer letters the chain of a lane has.  Words of four letters and more on
+// paths of up to 64 segments: lanes = paths from 64 paths on, which fill its wavefronts (the gain there, 51 -> 37 us at 32 x 64
+// segments of 3 letters, comes from the lanes that fewer paths leave empty).
+// `L`: segments; kAnyLength asks whether some length would run this way.  `chunks`: the call can take time chunks (windows and sig_backward_static cannot; beyond depth 3 their walk over whole
+// rows is no faster than lanes = paths).
+constexpr int64_t kAnyLength = INT64_MAX;
+bool use_lanes(const sig::WordSet& w, int64_t B, int64_t L, bool chunks = true, bool* small = nullptr)
 {
+    if (small) *small = false;
     if (w.kind != 0 || !jit_enabled(w)) return false;
     const int f = w.opt.lanes;
     if (f == 0) return false;
     const sig::LanesShape s = lanes_shape_for(w, 0, B), sb = lanes_shape_for(w, 1, B);
     if (!s.ok || !sb.ok || B * std::max(s.waves, sb.waves) > (int64_t)0x7fffffff) return false;
-    return f == 1 || std::min(s.lanes, sb.lanes) >= 32;
+    if (f == 1 || std::min(s.lanes, sb.lanes) >= 32) return true;
+    if (!sig::lanes_chunks_available(w.d, w.depth) || (!chunks && w.depth > 3)) return false;
+    const bool few = B <= (w.depth == 2 ? 2048 : (w.depth == 3 ? 1024 : (L > 64 ? 768 : 63)));
+    if (small) *small = few;
+    return few;
 }
 
 // Time chunks of those truncations: a wavefront takes 0.15-0.2 us per segment forward and 0.5-0.7 us backward however few
@@ -675,6 +691,9 @@ void lanes_bring_up(const sig::WordSet& cw, int dir, int64_t B, Build how)
         } catch (const std::bad_alloc&) { }
     }
     (void)ensure_lanes(w, dir, lanes_shape_for(w, dir, B), how);
+    bool small_set = false;
+    (void)use_lanes(w, B, kAnyLength, true, &small_set);
+    if (small_set && (dir == 1 || w.depth > 3)) (void)ensure_jit(w, dir, B, how);    // sig_backward_static, other lengths
     if (!sig::lanes_chunks_available(w.d, w.depth)) return;
     LanesChunked k;
     for (int C : sig::kLanesChunkCounts) (void)lanes_chunk_kernels(w, dir, B * C, how, k);
@@ -695,43 +714,39 @@ hipError_t lanes_forward_chunked(const sig::WordSet& w, const LanesChunked& k, c
     void* args[] = {(void*)&Sc, (void*)&lC, (void*)&coeffs, (void*)&none};
     return hipModuleLaunchKernel(k.scan().fn, (unsigned)(B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, args, nullptr);
 }
-// backward, workspace: increment gradients | chunk signatures [B][C], products from the left, from the right and boundary
-// adjoints [B][C - 1], rows of words shorter than the depth
-size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, int64_t n_points, const Chunks& ch)
+// backward, workspace: chunk signatures [B][C], products from the left, from the right and boundary adjoints [B][C - 1],
+// rows of words shorter than the depth
+size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch)
 {
-    const size_t gdx = ((size_t)B * (size_t)(n_points - 1) * (size_t)w.d * sizeof(float) + 255) & ~(size_t)255;
-    return gdx + lanes_low_bytes(w, B, ch.C) + 3 * lanes_low_bytes(w, B, ch.C - 1);
+    return lanes_low_bytes(w, B, ch.C) + 3 * lanes_low_bytes(w, B, ch.C - 1);
 }
 hipError_t lanes_backward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, const float* coeffs,
                                   const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, float* grad_path,
                                   void* workspace, hipStream_t st)
 {
-    const int64_t n_gdx = B * (n_points - 1) * w.d;
-    const size_t gb = ((size_t)n_gdx * sizeof(float) + 255) & ~(size_t)255, nb = lanes_low_bytes(w, B, ch.C - 1);
+    const size_t nb = lanes_low_bytes(w, B, ch.C - 1);
     unsigned char* base = (unsigned char*)workspace;
-    float* gdx = (float*)base;
-    float* Sc = (float*)(base + gb);
-    float* left = (float*)(base + gb + lanes_low_bytes(w, B, ch.C));
+    float* Sc = (float*)base;
+    float* left = (float*)(base + lanes_low_bytes(w, B, ch.C));
     float* right = (float*)((unsigned char*)left + nb);
     float* abar = (float*)((unsigned char*)right + nb);
     sig::WindowList rows;
     rows.K = ch.C; rows.max_len = ch.Lc;
     hipError_t e = launch_lanes(k.lower().fn, k.low, path, nullptr, nullptr, B, n_points, Sc, st, rows);
     if (e != hipSuccess) return e;
-    long lC = (long)ch.C, lC1 = lC - 1, lz = (long)n_gdx;
+    long lC = (long)ch.C, lC1 = lC - 1, lz = (long)(B * n_points * w.d);
     void* scan_args[] = {(void*)&Sc, (void*)&lC, (void*)&left, (void*)&right};
     e = hipModuleLaunchKernel(k.scan().fn, (unsigned)(2 * B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, scan_args, nullptr);
     if (e != hipSuccess) return e;
-    void* adj_args[] = {(void*)&grad_coeffs, (void*)&right, (void*)&lC1, (void*)&abar, (void*)&gdx, (void*)&lz};
+    void* adj_args[] = {(void*)&grad_coeffs, (void*)&right, (void*)&lC1, (void*)&abar, (void*)&grad_path, (void*)&lz};
     e = hipModuleLaunchKernel(k.adjoint().fn, (unsigned)(B * (ch.C - 1) * w.d), 1, 1, (unsigned)k.adjoint().nw * 64, 1, 1, 0, st, adj_args,
                               nullptr);
     if (e != hipSuccess) return e;
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
-    e = launch_lanes(k.k->fn, k.main, path, coeffs, grad_coeffs, B, n_points, gdx, st, rows, left, abar);
+    e = launch_lanes(k.k->fn, k.main, path, coeffs, grad_coeffs, B, n_points, grad_path, st, rows, left, abar);
     if (pe) (void)hipEventRecord(pe[1], st);
-    if (e != hipSuccess) return e;
-    return sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
+    return e;
 }
 }  // namespace
 
@@ -952,7 +967,7 @@ int sig_wordset_jit_prepare(sig_wordset* ws, int backward, int64_t B)
     const int dir = backward ? 1 : 0;
     if (!jit_enabled(w)) return SIG_EUNSUPPORTED;
     if (dir == 0 ? use_trunc_forward(w, B) : use_trunc_backward(w, B)) return SIG_EUNSUPPORTED;
-    if (use_lanes(w, B)) {
+    if (use_lanes(w, B, kAnyLength)) {
         lanes_bring_up(w, dir, B, Build::compile_only);
         return ensure_lanes(w, dir, lanes_shape_for(w, dir, B), Build::compile_only) ? SIG_OK : SIG_EJIT;
     }
@@ -966,7 +981,7 @@ size_t sig_wordset_jit_source(sig_wordset* ws, int backward, int64_t B, char* bu
     const int dir = backward ? 1 : 0;
     if (!jit_enabled(w)) return 0;
     std::string src;
-    if (use_lanes(w, B)) {
+    if (use_lanes(w, B, kAnyLength)) {
         src = sig::lanes_source(w.d, w.depth, lanes_shape_for(w, dir, B), dir != 0);
     } else {
         sig::WordSet::JitEntry* e = jit_entry(w, dir, B);
@@ -1006,7 +1021,7 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
     }
     if (!jit_enabled(w)) return 0;
     size_t n = jit_dxt_bytes(w, B, n_points, 0);
-    if (use_lanes(w, B)) {
+    if (use_lanes(w, B, n_points - 1)) {
         const Chunks ch = lanes_chunks(w, 0, B, n_points);
         if (ch.C > 1) n = std::max(n, chunk_array_bytes(w, B, ch.C));
     }
@@ -1041,9 +1056,9 @@ size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_
     size_t n = backward_workspace(ws, B, n_points, true);
     if (n == 0) return 0;
     const sig::WordSet& w = *W(ws);
-    if (!use_trunc_backward(w, B) && use_lanes(w, B)) {
+    if (!use_trunc_backward(w, B) && use_lanes(w, B, n_points - 1)) {
         const Chunks ch = lanes_chunks(w, 1, B, n_points);
-        if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, n_points, ch));
+        if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, ch));
     }
     if (w.kind != 0 && jit_enabled(w)) {
         const Chunks ch = checkpoint_chunks(w, B, n_points);
@@ -1106,9 +1121,14 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
             e = sig::chunk_scan(w.d, w.depth, Sc, Pfx, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)ch.C, nullptr, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
-    if (use_lanes(w, B)) {
+    bool small_set = false;
+    if (use_lanes(w, B, kAnyLength)) lanes_bring_up(w, 0, B, Build::compile_and_load);
+    if (use_lanes(w, B, n_points - 1, true, &small_set)) {
+        if (small_set) {                 // as lanes = paths asks for it
+            if (!workspace || workspace_bytes < jit_dxt_bytes(w, B, n_points, 0)) return SIG_EWORKSPACE;
+            if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
+        }
         // (a caller without a workspace for the chunk signatures gets the walk over whole paths)
-        lanes_bring_up(w, 0, B, Build::compile_and_load);
         const Chunks ch = lanes_chunks(w, 0, B, n_points);
         LanesChunked lc;
         if (ch.C > 1 && workspace && workspace_bytes >= chunk_array_bytes(w, B, ch.C) && ((uintptr_t)workspace & 255) == 0 &&
@@ -1239,18 +1259,21 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     // the chunks of the word-per-lane kernels are taken where the workspace holds them, not asked for
-    const bool lanes_path = !use_trunc_backward(w, B) && use_lanes(w, B);
+    // (sig_backward_static takes no chunks, and small sets then run with lanes = paths)
+    bool small_set = false;
+    const bool lanes_path = !use_trunc_backward(w, B) && use_lanes(w, B, n_points - 1, true, &small_set) &&
+                            !(small_set && how == Build::loaded_only);
     const size_t need = word_chunks && !lanes_path ? sig_backward_workspace_bytes(ws, B, n_points)
                                                    : backward_workspace(ws, B, n_points, false);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;
     CallTimer whole(1, st);
+    if (word_chunks && !residual && !use_trunc_backward(w, B) && use_lanes(w, B, kAnyLength)) lanes_bring_up(w, 1, B, how);
     if (lanes_path && word_chunks && !residual) {
-        lanes_bring_up(w, 1, B, how);
         const Chunks lch = lanes_chunks(w, 1, B, n_points);
         LanesChunked lc;
-        if (lch.C > 1 && workspace_bytes >= lanes_backward_chunked_bytes(w, B, n_points, lch) &&
+        if (lch.C > 1 && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch) &&
             lanes_chunk_kernels(w, 1, B * lch.C, how, lc)) {
             hipError_t le = lanes_backward_chunked(w, lc, path, coeffs, grad_coeffs, B, n_points, lch, grad_path, workspace, st);
             return le == hipSuccess ? SIG_OK : hip_fail(le);
@@ -1282,8 +1305,8 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     // four wavefronts per path, which reads word by word
     if (ch.fused && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) != 0) ch = BwdShape{false, false, 1, n_points - 1};
     // word sets that may run through the straight-line specialised kernels clear their (larger) array further down
-    const bool maybe_jit = !trunc && !use_lanes(w, B) && jit_enabled(w);
-    if (!ch.tails && !maybe_jit) {       // the one-wavefront-per-row kernel stores every entry itself
+    const bool maybe_jit = !trunc && !lanes_path && jit_enabled(w);
+    if (!ch.tails && !maybe_jit && !lanes_path) {       // the one-wavefront-per-row kernel stores every entry itself
         e = sig::fill_zero(gdx, B * (n_points - 1) * w.d, st);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -1326,18 +1349,18 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         if (!points) e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
-    if (use_lanes(w, B)) {
+    if (lanes_path) {
         const sig::LanesShape ls = lanes_shape_for(w, 1, B);
         g_not_ready = false;
         sig::JitKernel* lk = ensure_lanes(w, 1, ls, how);
         if (!lk && g_not_ready) return SIG_ENOTREADY;
         if (lk) {
+            e = sig::fill_zero(grad_path, B * n_points * w.d, st);      // the kernel adds into it
+            if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st);
+            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, grad_path, st);
             if (pe) (void)hipEventRecord(pe[1], st);
-            if (e != hipSuccess) return hip_fail(e);
-            e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
     }
@@ -1362,7 +1385,7 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         e = sig::grad_points_transposed(gdx, B, n_points, w.d, Lpad, grad_path, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
-    if (maybe_jit) {                     // no specialised kernel after all: the table-driven one takes gdx [B][L][d]
+    if (maybe_jit || lanes_path) {       // no specialised kernel after all: the table-driven one takes gdx [B][L][d]
         e = sig::fill_zero(gdx, B * (n_points - 1) * w.d, st);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -1545,7 +1568,7 @@ static bool windows_direct(const sig::WordSet& w, int64_t B, int64_t K, int back
 // form and the gather into padded sub-paths, which the other kernels and a failed compilation take.)
 static bool windows_rows_jit(const sig::WordSet& w, int64_t rows)
 {
-    return !use_trunc_forward(w, rows) && !use_trunc_backward(w, rows) && !use_lanes(w, rows) && jit_enabled(w);
+    return !use_trunc_forward(w, rows) && !use_trunc_backward(w, rows) && !use_lanes(w, rows, kAnyLength, false) && jit_enabled(w);
 }
 
 size_t sig_forward_windows_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points, int64_t K, int64_t max_window_len)
@@ -1597,7 +1620,7 @@ int sig_forward_windows(const sig_wordset* ws, const float* path, int64_t B, int
     if (!workspace || workspace_bytes < sig_forward_windows_workspace_bytes(ws, B, n_points, K, max_window_len)) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     // a word per lane (full truncations of any alphabet size): every (path, window) row reads its window of the path
-    if (!use_trunc_forward(w, B * K) && use_lanes(w, B * K) && n_points > 1 && max_window_len > 0) {
+    if (!use_trunc_forward(w, B * K) && use_lanes(w, B * K, kAnyLength, false) && n_points > 1 && max_window_len > 0) {
         const sig::LanesShape ls = lanes_shape_for(w, 0, B * K);
         if (sig::JitKernel* lk = ensure_lanes(w, 0, ls, Build::compile_and_load)) {
             hipStream_t st = (hipStream_t)stream;
@@ -1674,24 +1697,19 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
     const size_t sb = win_sub_bytes(w, B, K, n_sub);
     if (!workspace || workspace_bytes < sig_backward_windows_workspace_bytes(ws, B, n_points, K, max_window_len)) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
-    // a word per lane: rows = windows read straight from the path, their increment gradients added up in gdx [B][L][d]
-    // (at the start of the workspace, which is larger than that)
-    if (!use_trunc_backward(w, B * K) && use_lanes(w, B * K) && n_points > 1 && max_window_len > 0 &&
-        workspace_bytes >= gdx_bytes_of(w, B, n_points)) {
+    // a word per lane: rows = windows read straight from the path, their gradients added up in grad_path
+    if (!use_trunc_backward(w, B * K) && use_lanes(w, B * K, kAnyLength, false) && n_points > 1 && max_window_len > 0) {
         const sig::LanesShape ls = lanes_shape_for(w, 1, B * K);
         if (sig::JitKernel* lk = ensure_lanes(w, 1, ls, Build::compile_and_load)) {
             CallTimer whole(1, st);
             sig::WindowList wl;
             wl.win = windows; wl.K = K; wl.max_len = max_window_len;
-            float* gdx = (float*)workspace;
-            e = sig::fill_zero(gdx, B * (n_points - 1) * w.d, st);
+            e = sig::fill_zero(grad_path, B * n_points * w.d, st);
             if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, gdx, st, wl);
+            e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, grad_path, st, wl);
             if (pe) (void)hipEventRecord(pe[1], st);
-            if (e != hipSuccess) return hip_fail(e);
-            e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
     }
@@ -1781,7 +1799,7 @@ const char* sig_wordset_kernel_name(const sig_wordset* ws, int backward)
     if (!ws || !W(ws)->kernels_supported) return "unsupported";
     if (!backward && use_trunc_forward(*W(ws), 1)) return "trunc_mfma_fwd_kernel";
     if (backward && use_trunc_backward(*W(ws), 1)) return sig::trunc_backward_kernel_name(W(ws)->d, W(ws)->depth);
-    if (use_lanes(*W(ws), 1)) return backward ? "sig_bwd_lanes" : "sig_fwd_lanes";
+    if (use_lanes(*W(ws), 1, kAnyLength)) return backward ? "sig_bwd_lanes" : "sig_fwd_lanes";
     if (jit_enabled(*W(ws))) return backward ? "sig_bwd_jit" : "sig_fwd_jit";
     return backward ? "bwd_generic_kernel" : "fwd_generic_kernel";
 }
@@ -1818,7 +1836,7 @@ const char* sig_kernel_name(const sig_wordset* ws, int backward, int64_t B, int6
         const BwdShape sh = trunc_backward_shape(w, B, n_points);
         return sh.tails ? "trunc_tails_bwd_kernel" : sig::trunc_backward_kernel_name(w.d, w.depth);
     }
-    if (use_lanes(w, B)) return backward ? "sig_bwd_lanes" : "sig_fwd_lanes";
+    if (use_lanes(w, B, n_points - 1)) return backward ? "sig_bwd_lanes" : "sig_fwd_lanes";
     if (jit_enabled(w)) return backward ? "sig_bwd_jit" : "sig_fwd_jit";
     return backward ? "bwd_generic_kernel" : "fwd_generic_kernel";
 }

@@ -57,7 +57,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels);
 // Time chunks of those truncations: products of the chunk signatures over all words (one workgroup per path and first
 // letter; the forward call), over the words shorter than the depth in both directions (two per path and letter; the
 // backward call), and the adjoints at the chunk boundaries (one per boundary and first letter).
-enum LanesChunkPart { kLanesScanFull = 0, kLanesScanLow = 1, kLanesAdjoint = 2 };
+enum LanesChunkPart { kLanesScanFull = 0, kLanesScanLow = 1, kLanesAdjoint = 2, kLanesDisplacement = 3 };
 int lanes_chunk_threads(int d, int depth, LanesChunkPart part);   // of a workgroup
 LanesShape lanes_low_shape(int d, int depth);                 // forward kernel over the words shorter than the depth
 bool lanes_chunks_available(int d, int depth);

@@ -227,10 +227,14 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
 //   - rows of the letters below u: lane j T + t adds up row (j, t);
 //   - chain positions whose letter runs over fewer than 32 lanes: the same lane adds the members of its letter;
 //   - chain positions with longer runs (at most three of them reach into a wavefront): a lane writes to the row of
-//     its run, and these rows are summed like the rows of the first kind by a second group of lanes;
-// every total goes to gdx (zeroed by the caller) with one floating-point atomic.
+//     its run, and these rows are summed like the rows of the first kind by a second group of lanes, whose sums the
+//     lane of the letter then picks up.
+// The chain rule from increments to points (a point is the end of one segment and the start of the next) is applied to
+// the sums of a wavefront: the point after segment s gets its gradient less that of segment s + 1, which is the
+// neighbouring lane's or, at the end of a tile, the first of the tile walked before.  So there is one floating-point
+// atomic into grad_path (zeroed by the caller) per letter and segment and no array of increment gradients.
 #define NSRC (D + K + 2 * NU)
-#define BW_PER_WAVE (TILE_F + NSRC * T * 64)
+#define BW_PER_WAVE (TILE_F + NSRC * T * 64 + (3 * NU * T + 3) / 4 * 4)
 // row of chain position k (1-based): three rows for each of the first NU positions, one for the others
 constexpr int chain_row(int k) { return k <= NU ? D + 3 * (k - 1) : D + 3 * NU + (k - NU - 1); }
 
@@ -245,7 +249,7 @@ __device__ __forceinline__ float row_sum(const float* row, int lane)
 }
 
 extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float* __restrict__ path,
-        const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* gdx,
+        const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* grad_path,
         const long* __restrict__ win, long KW, long max_len, const float* __restrict__ low_coeffs, const float* __restrict__ low_grad)
 {
     __shared__ __attribute__((aligned(16))) float smem[NWB * BW_PER_WAVE];
@@ -256,6 +260,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     float* Ec = smem + wib * BW_PER_WAVE;
     const float* E0 = Ec + TS * D * NC;
     float* Vb = Ec + TILE_F;
+    float* Wide = Vb + NSRC * T * 64;                    // [3 NU][T] sums over long runs
     const long row = wave / WAVES;
     long b, part, first, L;
     row_of(win, KW, max_len, row, P, b, part, first, L);
@@ -279,7 +284,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     const float* gr = grad + whole * NWORDS;
     const float* cf = inner ? low_coeffs + (b * (KW - 1) + part) * level_start(N) : coeffs + whole * NWORDS;
     const float* gl = inner ? low_grad + (b * (KW - 1) + part) * level_start(N) : gr;
-    float* const gdx_row = gdx + (b * (P - 1) + first) * D;     // the gradients of overlapping windows add up here
+    float* const gp_row = grad_path + (b * P + first) * D;      // the gradients of overlapping windows add up here
 
     // signature and adjoints at the end of the path; a word shared by several lanes has its adjoint in the first
     float Sc[K], Ac[K], A1[D];
@@ -311,6 +316,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         first_letter[k] = (p0 / s) % D;
     }
 
+    float later = 0.0f;                                        // lane (j, T - 1): gradient of the segment after this tile
     const long nstage = (L + TS - 1) / TS;
     float dxn[EPL];
     fetch_increments(X, (nstage - 1) * TS, L, lane, dxn);
@@ -413,9 +419,24 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             }
         }
         wave_lds_fence();
-        if (lane < T * D) {
-            const int j = lane / T, t = lane % T;
-            float acc = row_sum(Vb + lane * 64, lane);
+#pragma unroll
+        for (int base = 0; base < 3 * NU * T; base += 64) {
+            const int o = base + lane;
+            if (o < 3 * NU * T) {
+                const int r = o / T;                                      // row D + r: position r / 3 + 1, run r % 3
+                int nr = 0;
+#pragma unroll
+                for (int k = 1; k <= NU; ++k)
+                    if (r / 3 + 1 == k) nr = runs[k];
+                if (r % 3 < nr) Wide[o] = row_sum(Vb + (D * T + o) * 64, lane);
+            }
+        }
+        if (NU > 0) wave_lds_fence();
+        float acc = 0.0f;
+        const int j = lane / T, t = lane % T;
+        const long sg = n * T + t;
+        if (lane < T * D && sg < L) {
+            acc = row_sum(Vb + lane * 64, lane);
             // chain position k with runs of s < 32 lanes: the lanes whose k-th letter is j, s of them every s D
 #pragma unroll
             for (int k = NU + 1; k <= K; ++k) {
@@ -432,26 +453,18 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                         acc += in ? v : 0.0f;
                     }
             }
-            const long sg = n * T + t;
-            if (sg < L) __hip_atomic_fetch_add(gdx_row + sg * D + j, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
 #pragma unroll
-        for (int base = 0; base < 3 * NU * T; base += 64) {
-            const int o = base + lane;
-            if (o < 3 * NU * T) {
-                const int r = o / T, t = o % T;                           // row D + r: position r / 3 + 1, run r % 3
-                int nr = 0, fl = 0;
-#pragma unroll
-                for (int k = 1; k <= NU; ++k)
-                    if (r / 3 + 1 == k) { nr = runs[k]; fl = first_letter[k]; }
-                const long sg = n * T + t;
-                if (sg < L && r % 3 < nr) {
-                    const float acc = row_sum(Vb + ((D + r) * T + t) * 64, lane);
-                    const int j = (fl + r % 3) % D;
-                    __hip_atomic_fetch_add(gdx_row + sg * D + j, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+            for (int k = 1; k <= NU; ++k) {
+                const int q = (j - first_letter[k] + D) % D;             // the run whose letter is j
+                if (q < runs[k]) acc += Wide[(3 * (k - 1) + q) * T + t];
             }
         }
+        const float next = __shfl_down(acc, 1);
+        if (lane < T * D && sg < L)
+            __hip_atomic_fetch_add(gp_row + (sg + 1) * D + j, acc - (t == T - 1 ? later : next), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        later = __shfl(acc, j * T);
+        if (n == 0 && lane < T * D && t == 0)
+            __hip_atomic_fetch_add(gp_row + j, -acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         wave_lds_fence();                                      // the rows are rewritten by the next tile
       }
     }
@@ -483,7 +496,7 @@ constexpr int slice_start(int n)
     return r;
 }
 
-#if PART != 2
+#if PART < 2
 // Products over words of length <= M.  A workgroup keeps one slice of the running product for one path: the words with
 // first letter i of S_0 S_1 .. S_c, whose factors on the left stay inside the slice, or with last letter i of
 // S_c .. S_{C-1}, whose factors on the right do.  So the D slices (and both directions) advance side by side and only
@@ -539,7 +552,7 @@ __device__ __forceinline__ void lower_level(bool from_left, int i, const float* 
 extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __restrict__ chunk_sigs, long C, float* __restrict__ left,
                                                                 float* __restrict__ right)
 {
-    __shared__ float s[NS], x[2][slice_start(M)];
+    __shared__ float s[NS > 0 ? NS : 1], x[2][M > 1 ? slice_start(M) : 1];
     const int tid = threadIdx.x;
 #if PART == 0
     const bool from_left = true;
@@ -555,7 +568,7 @@ extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __r
     // chunk number and output row of step n: forwards from the first chunk, or backwards from the last
     const long c0 = from_left ? 0 : C - 1;
     const long dc = from_left ? 1 : -1;
-    float top[QT], next_top[QT], next_s[QS];
+    float top[QT], next_top[QT], next_s[QS > 0 ? QS : 1];
     {
         const float* S0 = rows + c0 * ROW;
         float* out = PART == 0 ? nullptr : (from_left ? left + b * (C - 1) * ROW : right + (b * (C - 1) + C - 2) * ROW);
@@ -583,7 +596,7 @@ extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __r
 #pragma unroll
         for (int q = 0; q < QS; ++q) {
             const int e = tid + q * NT;
-            next_s[q] = S[e < NS ? e : NS - 1];
+            next_s[q] = S[e < NS ? e : 0];
         }
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
@@ -629,6 +642,18 @@ extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __r
         if (e < NTOP) out[word_of(true, i, M, e)] = top[q];
     }
 #endif
+}
+#elif PART == 3
+// Depth 2: the chunk signatures over the words shorter than the depth are the chunks' displacements (a wavefront per row).
+extern "C" __global__ __launch_bounds__(256) void sig_low_lanes(const float* __restrict__ path, long B, long P, float* __restrict__ coeffs,
+                                                                const long* __restrict__, long KW, long max_len)
+{
+    const int lane = threadIdx.x & 63;
+    const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= B * KW || lane >= D) return;
+    const long b = row / KW, first = (row - b * KW) * max_len;
+    const long last = first + max_len < P - 1 ? first + max_len : P - 1;
+    coeffs[row * D + lane] = path[(b * P + last) * D + lane] - path[(b * P + first) * D + lane];
 }
 #else
 // Adjoint at the boundary after chunk c: Abar(u) = grad(u) + sum_v grad(u v) Q_c(v) for the words u shorter than N
@@ -736,7 +761,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         // one staging tile ahead.
         auto lds_bytes = [&](int T, int TS) {
             const size_t tile = (size_t)TS * ((size_t)d * NC + 2 * (size_t)DP);
-            return (tile + (backward ? (size_t)(d + K + 2 * wide) * T * 64 : 0)) * sizeof(float);
+            return (tile + (backward ? (size_t)(d + K + 2 * wide) * T * 64 + (size_t)((3 * wide * T + 3) / 4 * 4) : 0)) * sizeof(float);
         };
         // (a lane carries its share of the next staging tile in registers: one increment where the state of two
         // levels already fills them)
@@ -777,7 +802,7 @@ int scan_threads(int64_t n_top) { return n_top <= 2048 ? 256 : (n_top <= 8192 ? 
 // 64 KB of LDS a kernel may declare, and the words of full length of a slice in registers (at most 16 a thread).
 bool lanes_chunks_available(int d, int depth)
 {
-    if (d < 2 || d > 64 || depth < 3 || depth > 12) return false;
+    if (d < 2 || d > 64 || depth < 2 || depth > 12) return false;
     double top = 1.0;
     for (int k = 1; k < depth; ++k) top *= d;
     if (top > 16.0 * 1024.0) return false;
@@ -827,7 +852,16 @@ int lanes_chunk_threads(int d, int depth, LanesChunkPart part)
 }
 
 // One shape for every batch: the words shorter than the depth are a d-th of the work.
-LanesShape lanes_low_shape(int d, int depth) { return lanes_shape(d, depth - 1, false, 256, 0); }
+LanesShape lanes_low_shape(int d, int depth)
+{
+    if (depth > 2) return lanes_shape(d, depth - 1, false, 256, 0);
+    LanesShape s{};
+    s.ok = true;
+    s.lanes = d;
+    s.waves = 1;
+    s.nwb = 4;
+    return s;
+}
 
 // The kernels of a module share their text, with other shapes: a namespace each, the shape macros set anew in front of it.
 std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
@@ -849,7 +883,8 @@ std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
         if (!backward) {
             chunk("scan", kLanesScanFull);
         } else {
-            lanes("low", depth - 1, lanes_low_shape(d, depth), false, "sig_low_lanes");
+            if (depth > 2) lanes("low", depth - 1, lanes_low_shape(d, depth), false, "sig_low_lanes");
+            else chunk("low", kLanesDisplacement);
             chunk("scan", kLanesScanLow);
             chunk("adjoint", kLanesAdjoint);
         }

@@ -535,6 +535,42 @@ def test_time_chunks_of_truncations_with_lanes_as_words(d, depth, B, L, chunks, 
     assert float((c - whole).norm() / whole.norm()) <= 1e-5
 
 
+@pytest.mark.parametrize("d,depth,B,L,lanes_are_words", [
+    (2, 4, 32, 64, True),       # 8 lanes per path; chunks
+    (2, 4, 64, 64, False),      # paths that fill a wavefront, and short
+    (2, 4, 64, 65, True),
+    (3, 4, 5, 15, True),        # too short for chunks
+    (2, 5, 769, 70, False),     # many paths
+    (3, 3, 70, 33, True),
+    (5, 3, 1025, 17, False),
+    (2, 2, 3, 40, True),        # depth 2: the chunk signatures over single letters are displacements
+    (12, 2, 9, 50, True),
+    (31, 2, 2, 21, True),       # the largest alphabet whose letters leave half a wavefront empty
+    (12, 2, 4, 1, True),        # a single segment
+])
+def test_small_truncations_with_few_paths(d, depth, B, L, lanes_are_words):
+    """Truncations whose words fill less than half a wavefront: a word per lane with time chunks while the paths are
+    few, a path per lane beyond; both sides of the line against the oracle.  A forward call without a workspace is
+    refused on either side, and the entry point without a workspace runs after one sig_backward call."""
+    import ctypes
+
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    assert ws.kernel_name(False, B, L + 1) == ("sig_fwd_lanes" if lanes_are_words else "sig_fwd_jit")
+    X = make_path("iid", 271 + d, B, L, d)
+    G = make_grad_coeffs(272 + d, B, ws.size)
+    check_parity(ws, W, "truncated", depth, X, G, what=f"small truncation d={d} N={depth} B={B} L={L}")
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c = torch.empty((B, ws.size), device="cuda")
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert S.load_library().sig_forward(ws._h, ctypes.c_void_p(x.data_ptr()), B, L + 1, ctypes.c_void_p(c.data_ptr()), None, 0,
+                                        stream) == -5
+    c = S.sig_forward(ws, x)
+    a, b = S.sig_backward(ws, x, c, g), S.sig_backward_static(ws, x, c, g, torch.empty_like(x))
+    torch.cuda.synchronize()
+    assert O.grad_errors(b.cpu().numpy(), a.cpu().numpy().astype(np.float64)).max() <= BWD_TOL
+
+
 def test_lanes_as_words_on_a_long_path():
     """5,000 segments through the word-per-lane kernels: many staging tiles, and the reconstruction of the
     backward pass over a long walk (within the gradient tolerance, as for the 4,096 segments of c5)."""

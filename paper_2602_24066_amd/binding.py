@@ -120,6 +120,23 @@ def _check(rc: int, where: str):
         raise SigError(rc, where)
 
 
+def _enqueue(device, name: str, *args) -> None:
+    """Calls the library function `name` with the arguments and torch's current stream on `device`.  Buffers a caller
+    allocates for the call come from the same stream, so the caching allocator hands them to later work on it only
+    after this call's; tensors need no record_stream.  (The device context manager and the Stream object cost 4 us of the
+    16 us of a small call, so the one is entered only on another device and the other is not made.)"""
+    import torch
+    fn = getattr(load_library(), name)
+    index = device.index
+    if index == torch._C._cuda_getDevice():
+        rc = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    else:
+        with torch.cuda.device(device):
+            rc = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    if rc != SIG_OK:
+        raise SigError(rc, name)
+
+
 def _np_from_ptr(ptr, n: int, dtype) -> np.ndarray:
     if n == 0 or not ptr:
         return np.zeros(0, dtype=dtype)
@@ -134,6 +151,8 @@ class WordSet:
         self._h = ctypes.c_void_p(handle)
         self._dev = None          # torch uint8 tensor keeping the device tables alive
         self._lib = load_library()
+        self._size = int(self._lib.sig_wordset_size(self._h))
+        self._dim = int(self._lib.sig_wordset_dim(self._h))
 
     def __del__(self):
         try:
@@ -146,11 +165,11 @@ class WordSet:
     # ---- host accessors
     @property
     def size(self) -> int:
-        return int(self._lib.sig_wordset_size(self._h))
+        return self._size
 
     @property
     def dim(self) -> int:
-        return int(self._lib.sig_wordset_dim(self._h))
+        return self._dim
 
     @property
     def max_len(self) -> int:
@@ -333,10 +352,7 @@ def sig_leadlag_transform(path, out=None):
     B, P, d = path.shape
     if out is None:
         out = torch.empty((B, 2 * P - 1, 2 * d), dtype=torch.float32, device=path.device)
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(load_library().sig_leadlag_transform(ctypes.c_void_p(path.data_ptr()), B, P, d, ctypes.c_void_p(out.data_ptr()),
-                                                    ctypes.c_void_p(stream)), "sig_leadlag_transform")
+    _enqueue(path.device, "sig_leadlag_transform", path.data_ptr(), B, P, d, out.data_ptr())
     return out
 
 
@@ -352,10 +368,7 @@ def sig_leadlag_backward(grad_out, out=None):
     P, d = (M + 1) // 2, d2 // 2
     if out is None:
         out = torch.empty((B, P, d), dtype=torch.float32, device=grad_out.device)
-    with torch.cuda.device(grad_out.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(load_library().sig_leadlag_backward(ctypes.c_void_p(grad_out.data_ptr()), B, P, d, ctypes.c_void_p(out.data_ptr()),
-                                                   ctypes.c_void_p(stream)), "sig_leadlag_backward")
+    _enqueue(grad_out.device, "sig_leadlag_backward", grad_out.data_ptr(), B, P, d, out.data_ptr())
     return out
 
 
@@ -375,10 +388,7 @@ def sig_logsig_forward(ws: WordSet, coeffs):
     lib = load_library()
     n = int(lib.sig_wordset_n_lyndon(ws._h))
     out = torch.empty((B, n), dtype=torch.float32, device=coeffs.device)
-    with torch.cuda.device(coeffs.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_logsig_forward(ws._h, ctypes.c_void_p(coeffs.data_ptr()), B, ctypes.c_void_p(out.data_ptr()),
-                                      ctypes.c_void_p(stream)), "sig_logsig_forward")
+    _enqueue(coeffs.device, "sig_logsig_forward", ws._h, coeffs.data_ptr(), B, out.data_ptr())
     return out
 
 
@@ -391,13 +401,8 @@ def sig_logsig_backward(ws: WordSet, coeffs, grad_logsig):
     out = torch.empty_like(coeffs)
     nbytes = int(lib.sig_logsig_backward_workspace_bytes(ws._h, B))
     keep, wptr = _aligned_workspace(nbytes, coeffs.device)
-    with torch.cuda.device(coeffs.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_logsig_backward(ws._h, ctypes.c_void_p(coeffs.data_ptr()), ctypes.c_void_p(grad_logsig.data_ptr()), B,
-                                       ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(wptr), nbytes, ctypes.c_void_p(stream)),
-               "sig_logsig_backward")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(coeffs.device))
+    _enqueue(coeffs.device, "sig_logsig_backward", ws._h, coeffs.data_ptr(), grad_logsig.data_ptr(), B, out.data_ptr(), wptr,
+             nbytes)
     return out
 
 
@@ -427,14 +432,8 @@ def sig_forward_windows(ws: WordSet, path, windows):
     out = torch.empty((B, K, ws.size), dtype=torch.float32, device=path.device)
     nbytes = int(lib.sig_forward_windows_workspace_bytes(ws._h, B, P, K, max_len))
     keep, wptr = _aligned_workspace(nbytes, path.device)
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_forward_windows(ws._h, ctypes.c_void_p(path.data_ptr()), B, P, ctypes.c_void_p(wt.data_ptr()), K, max_len,
-                                       ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(wptr), nbytes, ctypes.c_void_p(stream)),
-               "sig_forward_windows")
-    for t in (keep, wt):
-        if t is not None:
-            t.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_forward_windows", ws._h, path.data_ptr(), B, P, wt.data_ptr(), K, max_len, out.data_ptr(),
+             wptr, nbytes)
     return out
 
 
@@ -457,15 +456,8 @@ def sig_backward_windows(ws: WordSet, path, windows, coeffs, grad_coeffs):
     out = torch.empty((B, P, d), dtype=torch.float32, device=path.device)
     nbytes = int(lib.sig_backward_windows_workspace_bytes(ws._h, B, P, K, max_len))
     keep, wptr = _aligned_workspace(nbytes, path.device)
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_backward_windows(ws._h, ctypes.c_void_p(path.data_ptr()), ctypes.c_void_p(coeffs.data_ptr()),
-                                        ctypes.c_void_p(grad_coeffs.data_ptr()), B, P, ctypes.c_void_p(wt.data_ptr()), K, max_len,
-                                        ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(wptr), nbytes, ctypes.c_void_p(stream)),
-               "sig_backward_windows")
-    for t in (keep, wt):
-        if t is not None:
-            t.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_backward_windows", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,
+             wt.data_ptr(), K, max_len, out.data_ptr(), wptr, nbytes)
     return out
 
 
@@ -494,12 +486,8 @@ class WindowPlan:
     def forward(self):
         import torch
         B, P, _ = self.path.shape
-        with torch.cuda.device(self.path.device):
-            stream = torch.cuda.current_stream().cuda_stream
-            _check(load_library().sig_forward_windows(
-                self.ws._h, ctypes.c_void_p(self.path.data_ptr()), B, P, ctypes.c_void_p(self.wt.data_ptr()), self.K,
-                self.max_len, ctypes.c_void_p(self.coeffs.data_ptr()), ctypes.c_void_p(self.wf), self.nf,
-                ctypes.c_void_p(stream)), "sig_forward_windows")
+        _enqueue(self.path.device, "sig_forward_windows", self.ws._h, self.path.data_ptr(), B, P, self.wt.data_ptr(), self.K,
+                 self.max_len, self.coeffs.data_ptr(), self.wf, self.nf)
         return self.coeffs
 
     def backward(self, grad_coeffs):
@@ -508,13 +496,9 @@ class WindowPlan:
         if tuple(grad_coeffs.shape) != tuple(self.coeffs.shape) or grad_coeffs.dtype != torch.float32 or not grad_coeffs.is_cuda:
             raise ValueError("grad_coeffs must be a float32 CUDA tensor [B, K, |W|]")
         grad_coeffs = grad_coeffs.contiguous()
-        with torch.cuda.device(self.path.device):
-            stream = torch.cuda.current_stream().cuda_stream
-            _check(load_library().sig_backward_windows(
-                self.ws._h, ctypes.c_void_p(self.path.data_ptr()), ctypes.c_void_p(self.coeffs.data_ptr()),
-                ctypes.c_void_p(grad_coeffs.data_ptr()), B, P, ctypes.c_void_p(self.wt.data_ptr()), self.K, self.max_len,
-                ctypes.c_void_p(self.grad_path.data_ptr()), ctypes.c_void_p(self.wb), self.nb, ctypes.c_void_p(stream)),
-                "sig_backward_windows")
+        _enqueue(self.path.device, "sig_backward_windows", self.ws._h, self.path.data_ptr(), self.coeffs.data_ptr(),
+                 grad_coeffs.data_ptr(), B, P, self.wt.data_ptr(), self.K, self.max_len, self.grad_path.data_ptr(), self.wb,
+                 self.nb)
         return self.grad_path
 
 
@@ -543,12 +527,7 @@ def sig_forward(ws: WordSet, path, out=None, workspace=None):
         keep, wptr = _aligned_workspace(nbytes, path.device)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_forward(ws._h, ctypes.c_void_p(path.data_ptr()), B, P, ctypes.c_void_p(out.data_ptr()),
-                               ctypes.c_void_p(wptr), nbytes, ctypes.c_void_p(stream)), "sig_forward")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_forward", ws._h, path.data_ptr(), B, P, out.data_ptr(), wptr, nbytes)
     return out
 
 
@@ -570,13 +549,8 @@ def sig_backward(ws: WordSet, path, coeffs, grad_coeffs, out=None, workspace=Non
         keep, wptr = _aligned_workspace(nbytes, path.device)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_backward(ws._h, ctypes.c_void_p(path.data_ptr()), ctypes.c_void_p(coeffs.data_ptr()),
-                                ctypes.c_void_p(grad_coeffs.data_ptr()), B, P, ctypes.c_void_p(out.data_ptr()),
-                                ctypes.c_void_p(wptr), nbytes, ctypes.c_void_p(stream)), "sig_backward")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_backward", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,
+             out.data_ptr(), wptr, nbytes)
     return out
 
 
@@ -596,14 +570,8 @@ def sig_backward_residual(ws: WordSet, path, coeffs, grad_coeffs):
     nbytes = int(lib.sig_backward_workspace_bytes(ws._h, B, P))
     ws.set_option("bwd_tails", bt)
     keep, wptr = _aligned_workspace(nbytes, path.device)
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_backward_residual(ws._h, ctypes.c_void_p(path.data_ptr()), ctypes.c_void_p(coeffs.data_ptr()),
-                                         ctypes.c_void_p(grad_coeffs.data_ptr()), B, P, ctypes.c_void_p(out.data_ptr()),
-                                         ctypes.c_void_p(resid.data_ptr()), ctypes.c_void_p(wptr), nbytes,
-                                         ctypes.c_void_p(stream)), "sig_backward_residual")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_backward_residual", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,
+             out.data_ptr(), resid.data_ptr(), wptr, nbytes)
     return out, resid
 
 
@@ -626,14 +594,8 @@ def sig_forward_checkpointed(ws: WordSet, path, out=None, checkpoint=None, works
         keep, wptr = _aligned_workspace(nbytes, path.device)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_forward_checkpointed(ws._h, ctypes.c_void_p(path.data_ptr()), B, P, ctypes.c_void_p(out.data_ptr()),
-                                            ctypes.c_void_p(checkpoint.data_ptr() if checkpoint.numel() else 0),
-                                            checkpoint.numel() * checkpoint.element_size(), ctypes.c_void_p(wptr), nbytes,
-                                            ctypes.c_void_p(stream)), "sig_forward_checkpointed")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_forward_checkpointed", ws._h, path.data_ptr(), B, P, out.data_ptr(),
+             checkpoint.data_ptr() if checkpoint.numel() else 0, checkpoint.numel() * checkpoint.element_size(), wptr, nbytes)
     return out, checkpoint
 
 
@@ -655,16 +617,9 @@ def sig_backward_checkpointed(ws: WordSet, path, coeffs, grad_coeffs, checkpoint
         keep, wptr = _aligned_workspace(nbytes, path.device)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.sig_backward_checkpointed(ws._h, ctypes.c_void_p(path.data_ptr()), ctypes.c_void_p(coeffs.data_ptr()),
-                                             ctypes.c_void_p(grad_coeffs.data_ptr()),
-                                             ctypes.c_void_p(checkpoint.data_ptr() if checkpoint.numel() else 0),
-                                             checkpoint.numel() * checkpoint.element_size(), B, P,
-                                             ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(wptr), nbytes,
-                                             ctypes.c_void_p(stream)), "sig_backward_checkpointed")
-    if keep is not None:
-        keep.record_stream(torch.cuda.current_stream(path.device))
+    _enqueue(path.device, "sig_backward_checkpointed", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(),
+             checkpoint.data_ptr() if checkpoint.numel() else 0, checkpoint.numel() * checkpoint.element_size(), B, P,
+             out.data_ptr(), wptr, nbytes)
     return out
 
 
@@ -681,11 +636,8 @@ def sig_backward_static(ws: WordSet, path, coeffs, grad_coeffs, out):
     B, P, d = path.shape
     if d != ws.dim or tuple(coeffs.shape) != (B, ws.size) or tuple(grad_coeffs.shape) != (B, ws.size) or tuple(out.shape) != (B, P, d):
         raise ValueError("shape mismatch")
-    with torch.cuda.device(path.device):
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(load_library().sig_backward_static(ws._h, ctypes.c_void_p(path.data_ptr()), ctypes.c_void_p(coeffs.data_ptr()),
-                                                  ctypes.c_void_p(grad_coeffs.data_ptr()), B, P, ctypes.c_void_p(out.data_ptr()),
-                                                  ctypes.c_void_p(stream)), "sig_backward_static")
+    _enqueue(path.device, "sig_backward_static", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,
+             out.data_ptr())
     return out
 
 

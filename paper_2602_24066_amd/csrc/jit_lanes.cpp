@@ -10,6 +10,7 @@
 // Against lanes = paths this fills the wavefronts for any batch size and needs one short compilation per shape
 // instead of one that grows with the word set.
 #include <algorithm>
+#include <cmath>
 #include <sstream>
 #include <string>
 
@@ -52,7 +53,9 @@ constexpr int count_wide()
 #define NU count_wide()
 
 static_assert(K >= 1 && (R == 1 || R == 2), "a lane holds a word of length N - R and one or two levels below it");
-static_assert(T * D <= 64 && TS % T == 0, "one lane per (letter, segment) of a tile; whole tiles per staging tile");
+// backward with the leaves alone below u: gradient sums over the lanes as matrix products (see there)
+#define MSUM (BACKWARD && R == 1 && D <= 16)
+static_assert((MSUM || !BACKWARD || T * D <= 64) && TS % T == 0, "one lane per (letter, segment) of a tile; whole tiles per staging tile");
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -104,6 +107,30 @@ __device__ __forceinline__ void load_row(const float* row, float (&e)[DP])
         e[4 * q] = v[0]; e[4 * q + 1] = v[1]; e[4 * q + 2] = v[2]; e[4 * q + 3] = v[3];
     }
 }
+
+// What a lane reads of a segment: all letters' increments, and the scaled increments of its chain letters.
+struct Segment {
+    float e0[DP], ec[K][NC];
+    __device__ __forceinline__ void read(const float* Ec, const float* E0, int at, const int (&letter)[K])
+    {
+        load_row(E0 + at * DP, e0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const float* src = Ec + (at * D + letter[k]) * NC;
+#pragma unroll
+            for (int t = 0; t <= N - (k + 1); ++t) ec[k][t] = src[t];
+        }
+    }
+};
+// Segments are worked on in groups whose reads are issued together: a lone wavefront otherwise waits for LDS in every
+// segment (forward, one path of 199 segments, d = 10, depth 4: 39 -> 23 us; 8 x 1,000, d = 3, depth 5: 168 -> 84).  A tile's last group may reach past the end of the row, where the staged increments are zero: such
+// a segment changes nothing.
+// Two levels below u fill the registers with their own state: one segment after the other there, and forward, beyond 48
+// values (LAZY), every read where it is used (256 x 199 segments, 10 letters, depth 4: 58 us against 64 in pairs; 16 x 100, 6
+// letters, depth 6: 34 against 30).
+#define LAZY (R == 2 && D * D + D > 48)
+#define GROUP (LAZY || TS % 2 ? 1 : (R == 1 && TS % 4 == 0 && DP + K * NC <= 32 ? 4 : 2))
+#define BGROUP (R == 2 || T % 2 ? 1 : (MSUM && DP + K * NC <= 32 ? 4 : 2))
 
 // Row r is part k = r % KW of path r / KW, read straight from the path: with win == nullptr time chunk k, max_len segments
 // from segment k * max_len on (KW = 1 and max_len = P - 1: the whole path); otherwise window k, between the points
@@ -174,17 +201,35 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
         stage_increments(Ec, dxn, lane);
         wave_lds_fence();
         fetch_increments(X, (n + 1) * TS, L, lane, dxn); // past the end: zeros, and a zero increment changes nothing
+#if LAZY
 #pragma unroll 2
         for (int tt = 0; tt < TS; ++tt) {
             const float* Et = Ec + tt * D * NC;
             float e0[DP];
             load_row(E0 + tt * DP, e0);
+          {
+#else
+        const int steps = L - n * TS < TS ? (int)(L - n * TS) : TS;
+#pragma unroll 1
+        for (int t0 = 0; t0 < steps; t0 += GROUP) {
+          Segment xs[GROUP];
+#pragma unroll
+          for (int u = 0; u < GROUP; ++u) xs[u].read(Ec, E0, t0 + u, letter);
+#pragma unroll
+          for (int u = 0; u < GROUP; ++u) {
+            const int tt = t0 + u;
+            const float (&e0)[DP] = xs[u].e0;
+#endif
             float ap[K + 1][N + 2];
 #pragma unroll
             for (int t = 0; t < N + 2; ++t) ap[0][t] = 1.0f;
 #pragma unroll
             for (int k = 1; k <= K; ++k) {
+#if LAZY
                 const float* src = Et + letter[k - 1] * NC;
+#else
+                const float (&src)[NC] = xs[u].ec[k - 1];
+#endif
 #pragma unroll
                 for (int t = 1; t <= N - k; ++t) ap[k][t] = __builtin_fmaf(src[t], ap[k - 1][t + 1], Sc[k - 1]);
                 Sc[k - 1] = __builtin_fmaf(src[0], ap[k - 1][1], Sc[k - 1]);
@@ -202,6 +247,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
 #endif
                 S1[j] = __builtin_fmaf(e0[j], ap[K][1], S1[j]);
             }
+          }
         }
     }
 
@@ -233,8 +279,20 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
 // the sums of a wavefront: the point after segment s gets its gradient less that of segment s + 1, which is the
 // neighbouring lane's or, at the end of a tile, the first of the tile walked before.  So there is one floating-point
 // atomic into grad_path (zeroed by the caller) per letter and segment and no array of increment gradients.
+// With one level below u and up to 16 letters the sums are instead one matrix product per tile of 16 segments,
+//   g(j, s) = sum_p G(p j) A+_p(s)[1] + sum_k sum_p [letter k of p is j] c_k(p, s),
+// letters x (1 + K) 64 words times (1 + K) 64 words x segments on 16x16x4 instructions: the leaf adjoints G and the 0/1
+// indicators are constant (16 registers each), the right factor goes through LDS, one value per lane, segment and
+// source.  The sums by rows of LDS above took two thirds of a wavefront's time (D + K writes and D products a segment,
+// 64 chained additions and up to 28 predicated reads a tile): one path of 199 segments, d = 10, depth 4, walked whole:
+// 125 -> 59 us; 8 x 1,000, d = 3, depth 5: 603 -> 315.
+#if MSUM
+#define VROW 68                              /* 64 lanes and a shift of four banks per segment */
+#define BW_PER_WAVE (TILE_F + (K + 1) * 16 * VROW)
+#else
 #define NSRC (D + K + 2 * NU)
 #define BW_PER_WAVE (TILE_F + NSRC * T * 64 + (3 * NU * T + 3) / 4 * 4)
+#endif
 // row of chain position k (1-based): three rows for each of the first NU positions, one for the others
 constexpr int chain_row(int k) { return k <= NU ? D + 3 * (k - 1) : D + 3 * NU + (k - NU - 1); }
 
@@ -260,7 +318,9 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     float* Ec = smem + wib * BW_PER_WAVE;
     const float* E0 = Ec + TS * D * NC;
     float* Vb = Ec + TILE_F;
+#if !MSUM
     float* Wide = Vb + NSRC * T * 64;                    // [3 NU][T] sums over long runs
+#endif
     const long row = wave / WAVES;
     long b, part, first, L;
     row_of(win, KW, max_len, row, P, b, part, first, L);
@@ -305,6 +365,21 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         for (int jj = 0; jj < D; ++jj) An[j][jj] = valid ? gr[level_start(K + 2) + ((long)p * D + j) * D + jj] : 0.0f;
     }
 #endif
+#if MSUM
+    // left factors: lane (16 g + j) holds row j, words p0 + 16 g + i, i = 0 .. 15
+    const int col = lane & 15, grp = lane >> 4;
+    float leaf_rows[16], chain_rows[K][16], later[4];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        int q = p0 + grp * 16 + i;
+        leaf_rows[i] = q < NL && col < D ? gr[level_start(N) + (long)q * D + col] : 0.0f;
+        q = q < NL ? q : NL - 1;                               // lanes past the last word contribute zeros
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) { chain_rows[k][i] = q % D == col ? 1.0f : 0.0f; q /= D; }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) later[r] = 0.0f;
+#else
     // chain positions with long runs: the run of this lane among those that reach into the wavefront (0, 1 or 2),
     // how many do, and the letter of the first
     int my_run[NU + 1], runs[NU + 1], first_letter[NU + 1];
@@ -317,6 +392,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     }
 
     float later = 0.0f;                                        // lane (j, T - 1): gradient of the segment after this tile
+#endif
     const long nstage = (L + TS - 1) / TS;
     float dxn[EPL];
     fetch_increments(X, (nstage - 1) * TS, L, lane, dxn);
@@ -327,18 +403,18 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         fetch_increments(X, (ns - 1) * TS, L, lane, dxn);
       for (int sub = TS / T - 1; sub >= 0; --sub) {          // tiles of T segments: the unit of the gradient sums
         const long n = ns * (TS / T) + sub;
-#pragma unroll 2
-        for (int tt = T - 1; tt >= 0; --tt) {
-            const float* Et = Ec + (sub * T + tt) * D * NC;
-            float e0[DP];
-            load_row(E0 + (sub * T + tt) * DP, e0);
-            float ec[K][NC];
+        const int steps = MSUM && L - n * T < T ? (int)(L - n * T) : T;
+#pragma unroll (BGROUP == 1 ? 2 : 1)
+        for (int t1 = (steps + BGROUP - 1) / BGROUP * BGROUP; t1 > 0; t1 -= BGROUP) {
+          Segment xs[BGROUP];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const float* src = Et + letter[k] * NC;
+          for (int u = 0; u < BGROUP; ++u) xs[u].read(Ec, E0, sub * T + t1 - 1 - u, letter);
 #pragma unroll
-                for (int t = 0; t <= N - (k + 1); ++t) ec[k][t] = src[t];
-            }
+          for (int u = 0; u < BGROUP; ++u) {
+            const int tt = t1 - 1 - u;
+            const Segment& x = xs[u];
+            const float (&e0)[DP] = x.e0;
+            const float (&ec)[K][NC] = x.ec;
             // reconstruction with -dX, then the Horner intermediates with +dX from the reconstructed signature
             float am[K + 1][N + 2], ap[K + 1][N + 2];
 #pragma unroll
@@ -351,7 +427,12 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #pragma unroll
                 for (int t = 1; t <= N - k; ++t) ap[k][t] = __builtin_fmaf(ec[k - 1][t], ap[k - 1][t + 1], Sc[k - 1]);
             }
+#if MSUM
+            float* vb = Vb + tt * VROW + lane;
+            vb[0] = ap[K][1];
+#else
             float* vb = Vb + tt * 64 + lane;
+#endif
             float gb[K + 1][N + 2];
 #pragma unroll
             for (int k = 0; k <= K; ++k)
@@ -362,7 +443,9 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             // the leaves: constant adjoints
 #pragma unroll
             for (int j = 0; j < D; ++j) {
+#if !MSUM
                 vb[j * T * 64] = A1[j] * ap[K][1];
+#endif
                 g1 = __builtin_fmaf(e0[j], A1[j], g1);
             }
 #else
@@ -408,6 +491,9 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                     gb[k - 1][t + 1] = __builtin_fmaf(ec[k - 1][t], q, gb[k - 1][t + 1]);
                 }
                 Ac[k - 1] = asum;
+#if MSUM
+                vb[k * 16 * VROW] = gc;
+#else
                 if (k <= NU) {
                     const int kk = k <= NU ? k : 0;
                     vb[chain_row(k) * T * 64] = my_run[kk] == 0 ? gc : 0.0f;
@@ -416,27 +502,53 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                 } else {
                     vb[chain_row(k) * T * 64] = gc;
                 }
+#endif
             }
+          }
         }
+#if MSUM
+        // columns of segments past the end hold leftovers, each in its own column of the result, and are dropped
         wave_lds_fence();
+        f4 sum[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-        for (int base = 0; base < 3 * NU * T; base += 64) {
-            const int o = base + lane;
-            if (o < 3 * NU * T) {
-                const int r = o / T;                                      // row D + r: position r / 3 + 1, run r % 3
-                int nr = 0;
+        for (int k = 0; k <= K; ++k)
 #pragma unroll
-                for (int k = 1; k <= NU; ++k)
-                    if (r / 3 + 1 == k) nr = runs[k];
-                if (r % 3 < nr) Wide[o] = row_sum(Vb + (D * T + o) * 64, lane);
+            for (int q = 0; q < 4; ++q) {
+                const f4 v = *(const f4*)(Vb + (k * 16 + col) * VROW + grp * 16 + 4 * q);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    sum[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k == 0 ? leaf_rows[4 * q + i] : chain_rows[k > 0 ? k - 1 : 0][4 * q + i],
+                                                                      v[i], sum[i & 1], 0, 0, 0);
             }
+        const long sg = n * T + col;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float acc = sg < L ? sum[0][r] + sum[1][r] : 0.0f;
+            // the next segment's in the lane to the right; lane 15 of a row receives lane 0's, kept for the next tile
+            const float next = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(acc), 0x12f, 0xf, 0xf, true));   // row_ror:15
+            const int j = grp * 4 + r;
+            if (j < D && sg < L)
+                __hip_atomic_fetch_add(gp_row + (sg + 1) * D + j, acc - (col == 15 ? later[r] : next), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            if (n == 0 && col == 0 && j < D)
+                __hip_atomic_fetch_add(gp_row + j, -acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            later[r] = next;
         }
-        if (NU > 0) wave_lds_fence();
-        float acc = 0.0f;
+#else
+        wave_lds_fence();
         const int j = lane / T, t = lane % T;
         const long sg = n * T + t;
+        // rows of both kinds are summed together, from clamped addresses: their reads overlap
+        float acc = row_sum(Vb + (lane < T * D ? lane : 0) * 64, lane);
+#pragma unroll
+        for (int base = 0; base < 3 * NU * T; base += 64) {
+            const int o = base + lane;                                    // row D + o / T: position o / T / 3 + 1, run o / T % 3
+            const bool in = o < 3 * NU * T;
+            const float sum = row_sum(Vb + (in ? D * T + o : 0) * 64, lane);
+            if (in) Wide[o] = sum;                                        // rows of runs that do not reach here are not read below
+        }
+        if (NU > 0) wave_lds_fence();
         if (lane < T * D && sg < L) {
-            acc = row_sum(Vb + lane * 64, lane);
             // chain position k with runs of s < 32 lanes: the lanes whose k-th letter is j, s of them every s D
 #pragma unroll
             for (int k = NU + 1; k <= K; ++k) {
@@ -459,12 +571,14 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                 if (q < runs[k]) acc += Wide[(3 * (k - 1) + q) * T + t];
             }
         }
+        if (sg >= L) acc = 0.0f;
         const float next = __shfl_down(acc, 1);
         if (lane < T * D && sg < L)
             __hip_atomic_fetch_add(gp_row + (sg + 1) * D + j, acc - (t == T - 1 ? later : next), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         later = __shfl(acc, j * T);
         if (n == 0 && lane < T * D && t == 0)
             __hip_atomic_fetch_add(gp_row + j, -acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#endif
         wave_lds_fence();                                      // the rows are rewritten by the next tile
       }
     }
@@ -759,21 +873,25 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         // tile; eight wavefronts of 20 KB fit a compute unit, so longer tiles are cut down to that.  The staging
         // tile is as many tiles as fit (up to 32 segments and three increments per lane): its global loads are issued
         // one staging tile ahead.
+        const bool msum = backward && R == 1 && d <= 16;       // gradient sums as matrix products, tiles of 16 segments
         auto lds_bytes = [&](int T, int TS) {
             const size_t tile = (size_t)TS * ((size_t)d * NC + 2 * (size_t)DP);
+            if (msum) return (tile + (size_t)(K + 1) * 16 * 68) * sizeof(float);
             return (tile + (backward ? (size_t)(d + K + 2 * wide) * T * 64 + (size_t)((3 * wide * T + 3) / 4 * 4) : 0)) * sizeof(float);
         };
         // (a lane carries its share of the next staging tile in registers: one increment where the state of two
         // levels already fills them)
         const int staged = (R == 2 && d * d + d > 48) ? 64 : 192;
-        if (backward) {
+        if (msum) {
+            s.T = s.TS = 16;
+        } else if (backward) {
             while (s.T > 1 && lds_bytes(s.T, s.T) > 20 * 1024) --s.T;
             s.TS = s.T;
             while (s.TS + s.T <= 32 && (s.TS + s.T) * d <= staged && lds_bytes(s.T, s.TS + s.T) <= 20 * 1024) s.TS += s.T;
         } else {
             s.T = 1;                                       // no gradient tiles: only the staging tile matters
             s.TS = 32;
-            while (s.TS > 2 && (s.TS * d > staged || s.TS % 2 != 0 || lds_bytes(1, s.TS) > 8 * 1024)) --s.TS;
+            while (s.TS > 2 && (s.TS * d > staged || s.TS % (R == 1 && s.TS > 4 ? 4 : 2) != 0 || lds_bytes(1, s.TS) > 8 * 1024)) --s.TS;
             if (s.TS * d > 64 && s.TS * d > staged) s.TS = 1;
         }
         const size_t per_wave = lds_bytes(s.T, s.TS);
@@ -809,29 +927,43 @@ bool lanes_chunks_available(int d, int depth)
     return (words_up_to(d, depth - 1) + 2 * (words_up_to(d, depth - 2) + 1)) * 4 <= 62 * 1024;
 }
 
-// Times in microseconds, fitted to a scan of 26 shapes (2..40 letters, depth 3..7, 1..512 paths of 24..1,000 segments, every
-// count of kLanesChunkCounts; the model's choice is within 5 % of the best count on average): a segment costs a fixed
-// share of its instructions while the wavefronts find free SIMDs and grows with their number beyond; chunks cost their
-// launches, a product per chunk and the traffic of the chunk signatures.  Gains measured at the choice: forward
-// 1 x 199 segments, d = 10, depth 4: 39 -> 16 us, 37 x 301, d = 7, depth 4: 45 -> 16; backward 125 -> 33 and 171 -> 46.
+// Times in microseconds, fitted to a scan of 31 shapes (2..40 letters, depth 2..7, 1..1,000 paths of 24..1,000 segments, every
+// count of kLanesChunkCounts); the model's choice costs 3 % over the best count on average.  A segment takes the latency of
+// a lane's chain and the issue of its instructions, the latter as often as wavefronts share a SIMD, in as many rounds as
+// the chip holds the wavefronts (two per SIMD backward, where each has 18-20 KB of LDS, four forward).  Chunks cost their
+// launches, a product per chunk and the traffic of the chunk signatures.  Gains measured at the choice: forward 37 x 301
+// segments, d = 7, depth 4: 30 -> 15 us, 8 x 1,000, d = 3, depth 5: 84 -> 17; backward 72 -> 37 and 301 -> 41.
 int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels)
 {
-    const double words = (double)words_up_to(d, depth);
+    const double words = (double)words_up_to(d, depth), k = words / 1000.0;
+    const double low_waves = (double)lanes_low_shape(d, depth).waves;
+    const double low_exponent = backward ? 0.4 : 0.07, scan_exponent = backward ? -0.12 : 0.21;
+    const double launches = (backward ? 4.1 : 3.0) * std::pow(k, low_exponent);
+    const double product = (backward ? 0.78 : 0.48) * std::pow(k, scan_exponent) + (backward ? 4.5e-6 : 1.9e-6) * (double)B * words;
     auto time = [&](int64_t C) {
         LanesShape s = lanes_shape(d, depth, backward, B * C, levels);
         if (!s.ok) s = lanes_shape(d, depth, backward, B * C, 0);
-        const double Lc = (double)((L + C - 1) / C), waves = (double)(B * C) * (double)s.waves;
+        const double waves = (double)(B * C) * (double)s.waves / 1024.0, rounds = std::ceil(waves / (backward ? 2.0 : 4.0));
+        double latency, issue;
         if (!backward) {
-            const double t = 5.3 + Lc * (0.0022 * s.per_lane + 0.006 * s.chain) * std::max(1.0, waves / 2330.0);
-            return C == 1 ? t : t + 3.0 + (double)C * (0.6 + 2.5e-6 * (double)B * words);
+            latency = 0.0013 * s.chain;
+            issue = 0.005 + (s.R == 1 ? 0.0019 : 0.0021) * s.per_lane;
+        } else if (s.R == 1 && d <= 16) {
+            latency = 0.0034 * s.chain;
+            issue = 0.008 + 0.0039 * (6.0 * (depth - s.R + 1) + s.per_lane);
+        } else if (s.R == 1) {
+            latency = 1.1;
+            issue = 0.0002 * s.per_lane;
+        } else {
+            latency = 0.206 + 0.023 * s.chain;
+            issue = 0.132 + 0.0018 * s.per_lane;
         }
-        const double t = 20.0 + Lc * (0.02 + 0.005 * s.per_lane + 0.026 * s.chain) * std::max(1.0, waves / 1230.0);
+        const double Lc = (double)((L + C - 1) / C);
+        const double t = (backward ? 8.5 : 3.7) + Lc * rounds * (latency + issue * std::max(1.0, waves / rounds));
         if (C == 1) return t;
-        const LanesShape low = lanes_low_shape(d, depth);
-        return t + 2.0 + (double)C * (0.63 + 4.0e-6 * (double)B * words) + 0.15 * Lc * std::max(1.0, (double)(B * C) * (double)low.waves / 2048.0);
+        return t + launches + (double)C * product + (backward ? 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0) : 0.0);
     };
-    const double whole = time(1);
-    double best = 0.9 * whole;
+    double best = 0.93 * time(1);
     int choice = 1;
     for (int C : kLanesChunkCounts) {
         if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments

@@ -601,22 +601,21 @@ constexpr int kMaxLogDepth = 12;
 // DEPTH == 0: any length up to kMaxLogDepth (tables in scratch memory).
 template <int DEPTH>
 __global__ void logsig_forward_kernel(const float* __restrict__ coeffs, int64_t B, int64_t nW, const int32_t* __restrict__ lyn_len,
-                                      const int32_t* __restrict__ lyn_sub, int64_t n_lyn, int stride, int depth,
-                                      float* __restrict__ out)
+                                      const int32_t* __restrict__ lyn_sub_t, int64_t n_lyn, int depth, float* __restrict__ out)
 {
     constexpr int MD = DEPTH ? DEPTH : kMaxLogDepth;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= B * n_lyn) return;
     const int64_t b = idx / n_lyn, k = idx - b * n_lyn;
     const int n = lyn_len[k];
-    const int32_t* sub = lyn_sub + k * stride;
+    const int32_t* sub = lyn_sub_t + k;
     const float* S = coeffs + b * nW;
     // sw[i][j] = S(w[i:j]) for 0 <= i < j <= n
     float sw[MD][MD + 1];
 #pragma unroll
     for (int i = 0; i < MD; ++i)
 #pragma unroll
-        for (int j = 0; j <= MD; ++j) sw[i][j] = (i < j && j <= n) ? S[sub[i * (depth + 1) + j]] : 0.0f;
+        for (int j = 0; j <= MD; ++j) sw[i][j] = (i < j && j <= n) ? S[sub[(i * depth - i * (i - 1) / 2 + (j - i - 1)) * n_lyn]] : 0.0f;
     float Q[MD + 1], Qn[MD + 1];
 #pragma unroll
     for (int j = 0; j <= MD; ++j) Q[j] = j == 0 ? 0.0f : sw[0][j];                  // one piece: w[0:j]
@@ -646,16 +645,17 @@ __global__ void logsig_forward_kernel(const float* __restrict__ coeffs, int64_t 
 // between Lyndon words (a single letter by thousands of them), so the contributions are not added with atomics:
 // this kernel writes them to part[(b n_lyn + k) n_pairs + pair(i, j)] and logsig_gather_kernel sums, per sub-word,
 // the entries an inverse table lists.
-// emit(i, j, value) receives g * d logsig(w) / d S(w[i:j]) for every 0 <= i < j <= n
-template <int MD, class Emit>
-__device__ __forceinline__ void logsig_word_adjoint(const float* __restrict__ S, const int32_t* __restrict__ sub, int n, int depth,
-                                                    float g, Emit&& emit)
+// value(i, j) gives S(w[i:j]) for j <= n; emit(i, j, pair, v) receives g * d logsig(w) / d S(w[i:j]) for every
+// 0 <= i < j <= n.  Pre_a[i] is empty for a > i and for a = 0 < i, Suf_c[j] for c > depth - j: those terms are left out (91 of
+// 441 products are left for length 6).
+template <int MD, class Value, class Emit>
+__device__ __forceinline__ void logsig_word_adjoint(int n, int depth, float g, Value&& value, Emit&& emit)
 {
     float sw[MD][MD + 1];
 #pragma unroll
     for (int i = 0; i < MD; ++i)
 #pragma unroll
-        for (int j = 0; j <= MD; ++j) sw[i][j] = (i < j && j <= n) ? S[sub[i * (depth + 1) + j]] : 0.0f;
+        for (int j = i + 1; j <= MD; ++j) sw[i][j] = j <= n ? value(i, j) : 0.0f;
     // pre[a][i], suf[c][j] for a, c = 0..n-1 (pieces that reach beyond n are zero through sw)
     float pre[MD][MD + 1], suf[MD][MD + 1];
 #pragma unroll
@@ -667,10 +667,10 @@ __device__ __forceinline__ void logsig_word_adjoint(const float* __restrict__ S,
             float v = 0.0f, u = 0.0f;
 #pragma unroll
             for (int m = 0; m < MD; ++m)
-                if (m < i) v = fmaf(pre[a - 1][m], sw[m][i], v);
+                if (m < i && m >= a - 1 && (a > 1 || m == 0)) v = fmaf(pre[a - 1][m], sw[m][i], v);
 #pragma unroll
             for (int m = 1; m <= MD; ++m)
-                if (m > i && i < MD) u = fmaf(sw[i < MD ? i : 0][m], suf[a - 1][m], u);
+                if (m > i && i < MD && m <= MD - (a - 1)) u = fmaf(sw[i < MD ? i : 0][m], suf[a - 1][m], u);
             pre[a][i] = v;
             suf[a][i] = u;
         }
@@ -684,8 +684,9 @@ __device__ __forceinline__ void logsig_word_adjoint(const float* __restrict__ S,
             for (int a = 0; a < MD; ++a)
 #pragma unroll
                 for (int c = 0; c < MD; ++c)
-                    if (a + c < MD) t = fmaf((((a + c) & 1) ? -1.0f : 1.0f) / (float)(a + c + 1), pre[a][i] * suf[c][j], t);
-            emit(i, j, g * t);
+                    if (a + c < MD && a <= i && (a > 0 || i == 0) && c <= MD - j)
+                        t = fmaf((((a + c) & 1) ? -1.0f : 1.0f) / (float)(a + c + 1), pre[a][i] * suf[c][j], t);
+            emit(i, j, i * depth - i * (i - 1) / 2 + (j - i - 1), g * t);           // pairs i < j <= depth in row-major order
         }
 }
 
@@ -699,9 +700,10 @@ __global__ void logsig_backward_kernel(const float* __restrict__ coeffs, const f
     if (idx >= B * n_lyn) return;
     const int64_t b = idx / n_lyn, k = idx - b * n_lyn;
     float* dst = part + idx * n_pairs;
-    logsig_word_adjoint<MD>(coeffs + b * nW, lyn_sub + k * stride, lyn_len[k], depth, glog[idx], [&](int i, int j, float v) {
-        dst[i * depth - i * (i - 1) / 2 + (j - i - 1)] = v;                     // pairs i < j <= depth in row-major order
-    });
+    const float* S = coeffs + b * nW;
+    const int32_t* sub = lyn_sub + k * stride;
+    logsig_word_adjoint<MD>(lyn_len[k], depth, glog[idx], [&](int i, int j) { return S[sub[i * (depth + 1) + j]]; },
+                            [&](int, int, int pair, float v) { dst[pair] = v; });
 }
 
 // One workgroup per path, for word sets whose gradient row fits in LDS: the contributions are added there with LDS
@@ -722,12 +724,66 @@ __global__ __launch_bounds__(512) void logsig_backward_lds_kernel(const float* _
     const float* S = coeffs + b * nW;
     for (int64_t k = threadIdx.x; k < n_lyn; k += blockDim.x) {
         const int32_t* sub = lyn_sub + k * stride;
-        logsig_word_adjoint<MD>(S, sub, lyn_len[k], depth, glog[b * n_lyn + k], [&](int i, int j, float v) {
+        logsig_word_adjoint<MD>(lyn_len[k], depth, glog[b * n_lyn + k], [&](int i, int j) { return S[sub[i * (depth + 1) + j]]; },
+                                [&](int i, int j, int, float v) {
             __hip_atomic_fetch_add(acc + sub[i * (depth + 1) + j], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         });
     }
     __syncthreads();
     for (int64_t u = threadIdx.x; u < nW; u += blockDim.x) gcoeffs[b * nW + u] = acc[u];
+}
+
+// One workgroup per path, where the coefficients and all contributions of a path fit in LDS: a thread per Lyndon
+// word writes its contributions, then every sub-word's list of the inverse table is summed from there, by a wavefront
+// for the short sub-words (thousands of entries for a letter), by a thread for the others.  LDS atomics into one row
+// spent most of their time on a few addresses, thousands of additions to each letter's: 256 paths, 4 letters, depth 6: 44 -> 17 us.
+template <int DEPTH>
+__global__ __launch_bounds__(1024) void logsig_backward_sum_kernel(const float* __restrict__ coeffs, const float* __restrict__ glog,
+                                                                  int64_t nW, const int32_t* __restrict__ lyn_len,
+                                                                  const int32_t* __restrict__ lyn_sub_t, int64_t n_lyn, int depth,
+                                                                  int n_pairs, const int32_t* __restrict__ inv_off,
+                                                                  const int32_t* __restrict__ inv, int64_t n_long,
+                                                                  float* __restrict__ gcoeffs)
+{
+    constexpr int MD = DEPTH ? DEPTH : kMaxLogDepth;
+    extern __shared__ float4 logsig_smem[];
+    float* const part = (float*)logsig_smem;              // [n_lyn][n_pairs]
+    float* const S = part + n_lyn * n_pairs;
+    const int64_t b = blockIdx.x;
+    for (int64_t u = threadIdx.x; u < nW; u += blockDim.x) S[u] = coeffs[b * nW + u];
+    __syncthreads();
+    for (int64_t k = threadIdx.x; k < n_lyn; k += blockDim.x) {
+        const int32_t* sub = lyn_sub_t + k;
+        float* dst = part + k * n_pairs;
+        logsig_word_adjoint<MD>(lyn_len[k], depth, glog[b * n_lyn + k],
+                                [&](int i, int j) { return S[sub[(i * depth - i * (i - 1) / 2 + (j - i - 1)) * n_lyn]]; },
+                                [&](int, int, int pair, float v) { dst[pair] = v; });
+    }
+    __syncthreads();
+    float* out = gcoeffs + b * nW;
+    const int lane = threadIdx.x & 63;
+    for (int64_t u = threadIdx.x >> 6; u < n_long; u += blockDim.x >> 6) {
+        float acc = 0.0f;
+#pragma unroll 4
+        for (int32_t e = inv_off[u] + lane; e < inv_off[u + 1]; e += 64) acc += part[inv[e]];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+        if (lane == 0) out[u] = acc;
+    }
+    // the ends of the next list are fetched while this one is summed
+    int64_t u = n_long + threadIdx.x;
+    int32_t e0 = u < nW ? inv_off[u] : 0, e1 = u < nW ? inv_off[u + 1] : 0;
+    while (u < nW) {
+        const int64_t next = u + blockDim.x;
+        const int32_t f0 = next < nW ? inv_off[next] : 0, f1 = next < nW ? inv_off[next + 1] : 0;
+        float acc = 0.0f;
+#pragma unroll 4
+        for (int32_t e = e0; e < e1; ++e) acc += part[inv[e]];
+        out[u] = acc;
+        u = next;
+        e0 = f0;
+        e1 = f1;
+    }
 }
 
 // one wavefront per (path, sub-word): the lists of short sub-words are thousands of entries long
@@ -747,14 +803,14 @@ __global__ __launch_bounds__(256) void logsig_gather_kernel(const float* __restr
     if (lane == 0) gcoeffs[idx] = acc;
 }
 
-hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int32_t* lyn_len, const int32_t* lyn_sub, int64_t n_lyn,
-                          int stride, int depth, float* out, hipStream_t stream)
+hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int32_t* lyn_len, const int32_t* lyn_sub_t, int64_t n_lyn,
+                          int depth, float* out, hipStream_t stream)
 {
     const int64_t n = B * n_lyn;
     if (n <= 0) return hipSuccess;
     if (depth > kMaxLogDepth) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((n + 127) / 128);
-#define SIG_LOGSIG_FWD(DEPTH) logsig_forward_kernel<DEPTH><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub, n_lyn, stride, depth, out)
+#define SIG_LOGSIG_FWD(DEPTH) logsig_forward_kernel<DEPTH><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub_t, n_lyn, depth, out)
     if (depth <= 4) SIG_LOGSIG_FWD(4);
     else if (depth <= 6) SIG_LOGSIG_FWD(6);
     else if (depth <= 8) SIG_LOGSIG_FWD(8);
@@ -763,6 +819,13 @@ hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int3
     return hipGetLastError();
 }
 // bytes of LDS the one-kernel form of the backward needs for a gradient row; 0 = the row does not fit
+// bytes of LDS for the form that keeps a path's coefficients and contributions there; 0 = they do not fit
+static size_t logsig_sum_lds_bytes(int64_t nW, int64_t n_lyn, int n_pairs, bool two_kernels)
+{
+    if (two_kernels || n_lyn <= 0) return 0;
+    const int64_t n = (n_lyn * n_pairs + nW) * (int64_t)sizeof(float);
+    return n <= 152 * 1024 ? (size_t)((n + 15) & ~(int64_t)15) : 0;
+}
 static size_t logsig_row_lds_bytes(int64_t nW, bool two_kernels)
 {
     if (two_kernels) return 0;                                   // the tests force the two-kernel form
@@ -772,11 +835,30 @@ static size_t logsig_row_lds_bytes(int64_t nW, bool two_kernels)
 
 hipError_t logsig_backward(const float* coeffs, const float* glog, int64_t B, int64_t nW, const int32_t* lyn_len,
                            const int32_t* lyn_sub, int64_t n_lyn, int stride, int depth, int n_pairs, const int32_t* inv_off,
-                           const int32_t* inv, float* part, float* gcoeffs, bool two_kernels, hipStream_t stream)
+                           const int32_t* inv, const int32_t* lyn_sub_t, int64_t n_long, float* part, float* gcoeffs, bool two_kernels,
+                           hipStream_t stream)
 {
     const int64_t n = B * n_lyn;
     if (B <= 0) return hipSuccess;
     if (depth > kMaxLogDepth) return hipErrorInvalidValue;
+    if (const size_t lds = logsig_sum_lds_bytes(nW, n_lyn, n_pairs, two_kernels)) {
+        if (B > 0x7fffffff) return hipErrorInvalidValue;
+#define SIG_LOGSIG_BWD_SUM(DEPTH)                                                                                              \
+    do {                                                                                                                       \
+        if (lds > 64 * 1024) {                                                                                                 \
+            hipError_t ea = ensure_dynamic_lds(reinterpret_cast<const void*>(&logsig_backward_sum_kernel<DEPTH>), 152 * 1024); \
+            if (ea != hipSuccess) return ea;                                                                                   \
+        }                                                                                                                      \
+        logsig_backward_sum_kernel<DEPTH><<<(unsigned)B, 1024, lds, stream>>>(coeffs, glog, nW, lyn_len, lyn_sub_t, n_lyn, depth, \
+                                                                            n_pairs, inv_off, inv, n_long, gcoeffs);           \
+    } while (0)
+        if (depth <= 4) SIG_LOGSIG_BWD_SUM(4);
+        else if (depth <= 6) SIG_LOGSIG_BWD_SUM(6);
+        else if (depth <= 8) SIG_LOGSIG_BWD_SUM(8);
+        else SIG_LOGSIG_BWD_SUM(0);
+#undef SIG_LOGSIG_BWD_SUM
+        return hipGetLastError();
+    }
     if (const size_t lds = logsig_row_lds_bytes(nW, two_kernels)) {
         if (B > 0x7fffffff) return hipErrorInvalidValue;
 #define SIG_LOGSIG_BWD_LDS(DEPTH)                                                                                              \

@@ -759,6 +759,18 @@ int build_logsig(int d, int depth, WordSet** out)
             }
         }
         if ((int64_t)n_lyn * ws->lyn_pairs > 0x7fffffff) { delete ws; return SIG_ETOOLARGE; }
+        for (int n = 1; n <= ws->max_len; ++n) {
+            const int64_t u0 = ws->level_start[(size_t)n], u1 = ws->level_start[(size_t)n + 1];
+            if (ws->lyn_inv_off[(size_t)u1] - ws->lyn_inv_off[(size_t)u0] < 16 * (u1 - u0)) break;
+            ws->lyn_long = u1;
+        }
+        ws->lyn_sub_t.assign((size_t)n_lyn * (size_t)ws->lyn_pairs, -1);
+        for (int64_t k = 0; k < n_lyn; ++k) {
+            int64_t pair = 0;
+            for (int i = 0; i < depth; ++i)
+                for (int j = i + 1; j <= depth; ++j, ++pair)
+                    ws->lyn_sub_t[(size_t)(pair * n_lyn + k)] = ws->lyn_sub[(size_t)k * (size_t)ws->lyn_stride + (size_t)i * (size_t)(depth + 1) + (size_t)j];
+        }
         // append the tables to the device image
         auto append = [&](const void* src, size_t bytes) {
             const size_t off = (ws->image.size() + 255) & ~(size_t)255;
@@ -768,6 +780,7 @@ int build_logsig(int d, int depth, WordSet** out)
         };
         ws->lyn_len_off = append(ws->lyn_len.data(), ws->lyn_len.size() * sizeof(int32_t));
         ws->lyn_sub_off = append(ws->lyn_sub.data(), ws->lyn_sub.size() * sizeof(int32_t));
+        ws->lyn_sub_t_off = append(ws->lyn_sub_t.data(), ws->lyn_sub_t.size() * sizeof(int32_t));
         ws->lyn_inv_off_off = append(ws->lyn_inv_off.data(), ws->lyn_inv_off.size() * sizeof(int32_t));
         ws->lyn_inv_ent_off = append(ws->lyn_inv.data(), std::max<size_t>(ws->lyn_inv.size(), 1) * sizeof(int32_t));
         ws->depth = depth;

@@ -72,12 +72,16 @@ struct WordSet {
     int64_t n_lyndon = 0;
     int lyn_stride = 0;
     std::vector<int32_t> lyn_len, lyn_sub;
+    // the same sub-words by pair (i < j <= depth, counted as in lyn_inv below) with the Lyndon words side by side, -1 where
+    // j > n: lyn_sub_t[pair * n_lyndon + k], for kernels with a Lyndon word per lane
+    std::vector<int32_t> lyn_sub_t;
+    int64_t lyn_long = 0;          // words of the leading lengths whose lists in lyn_inv average 16 entries and more
     // inverse of lyn_sub for the backward pass: word u is the factor w_k[i:j] for the entries
     // lyn_inv[lyn_inv_off[u] .. lyn_inv_off[u + 1]), each k * lyn_pairs + pair(i, j), pair(i, j) counting the pairs
     // i < j <= depth in the order i = 0.., j = i + 1..
     int lyn_pairs = 0;
     std::vector<int32_t> lyn_inv_off, lyn_inv;
-    size_t lyn_len_off = 0, lyn_sub_off = 0, lyn_inv_off_off = 0, lyn_inv_ent_off = 0;    // offsets in the device image
+    size_t lyn_len_off = 0, lyn_sub_off = 0, lyn_sub_t_off = 0, lyn_inv_off_off = 0, lyn_inv_ent_off = 0;    // offsets in the device image
     // Sets closed under suffixes as well (every anisotropic set; word lists that happen to be): the tensor product of
     // two elements restricted to the set needs nothing outside it, (a (x) b)(w) = sum_k a(w_1..k) b(w_k+1..n), so the
     // segments of a path can be cut into time chunks whose signatures are multiplied afterwards (Chen's relation).

@@ -727,6 +727,35 @@ def test_log_signature(d, depth, B, L):
         assert e <= FWD_TOL, f"log-signature level {n}: {e:.3e}"
 
 
+@pytest.mark.parametrize("d,depth,B", [
+    (4, 6, 3),       # 964 Lyndon words of up to six letters: contributions and coefficients of a path in 103 KB of LDS
+    (5, 1, 2),       # letters only: no list of the inverse table is long
+    (3, 3, 65),
+    (2, 7, 2),       # pairs beyond a word's length
+    (2, 9, 1),       # words of more than eight letters (tables in scratch memory)
+    (6, 4, 5),       # the reduced word set: words of full length are Lyndon words
+    (5, 5, 2),
+    (6, 5, 1),       # contributions too large for LDS: the gradient row alone is kept there
+])
+def test_log_signature_adjoint_forms_agree(d, depth, B):
+    """The adjoint of the tensor logarithm in the form that keeps a path's contributions in LDS (or the one that adds into
+    the gradient row there) against the form that writes them out and gathers them: the same terms in another order, so
+    sums of at most a few thousand fp32 terms."""
+    import torch
+    ws = S.sig_wordset_build_logsig(d, depth)
+    ws.upload("cuda:0")
+    n_lyn = int(S.load_library().sig_wordset_n_lyndon(ws._h))
+    gen = torch.Generator(device="cuda").manual_seed(600 + 10 * d + depth)
+    c = torch.randn((B, ws.size), generator=gen, device="cuda")
+    g = torch.randn((B, n_lyn), generator=gen, device="cuda")
+    one = S.sig_logsig_backward(ws, c, g)
+    ws.set_option("logsig_gather", 1)
+    two = S.sig_logsig_backward(ws, c, g)
+    torch.cuda.synchronize()
+    assert torch.isfinite(one).all()
+    assert float((one.double() - two.double()).norm() / two.double().norm()) <= 2e-6
+
+
 @pytest.mark.parametrize("two_kernels", [False, True])
 def test_log_signature_gradient(monkeypatch, two_kernels):
     """d <G, logsig(X)> / dX through sig_logsig_backward and sig_backward against central differences of the oracle;

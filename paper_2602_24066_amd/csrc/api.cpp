@@ -257,22 +257,31 @@ bool use_trunc_backward(const sig::WordSet& w, int64_t B)
 // ---- run-time specialised kernels ------------------------------------------------------------------------
 std::mutex g_jit_mutex;
 
-// Work units asked of the balanced planner for a batch of B paths: one or two wavefronts per SIMD (1,024 on the
-// chip) over the path groups, a whole number of workgroups, and not so many that units shrink to a handful of words
-// (every unit recomputes the ancestors of its first word).
 int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 {
     return w.opt.jit_wg_waves == 8 ? 8 : std::max(1, std::min(4, w.opt.jit_wg_waves));
 }
+// Work units asked of the balanced planner for a batch of B paths: two wavefronts per SIMD (2,048) over the path groups, in
+// whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
+// first word).  Where that leaves between one and two workgroups per compute unit (256), the units that hold two set the
+// time, so one each is taken (1,500 words, 512 paths x 512 segments: 47 -> 32 columns of workgroups, backward 431 -> 304
+// us); where it leaves half the compute units empty, units go down to four words (384 words, 300 x 256: 94 -> 85 us).
 int64_t jit_units(const sig::WordSet& w, int /*dir*/, int64_t B)
 {
     const int kJitWaves = jit_wg_waves(w);
-    int64_t want = 2048;               // two wavefronts per SIMD
-    if (w.opt.jit_waves > 0) want = w.opt.jit_waves;                                       // tuning knob
     const int64_t groups = (B + 63) / 64;
-    int64_t n = std::max<int64_t>(1, want / groups);
-    n = std::min(n, std::max<int64_t>(1, w.size() / 8));
-    return (n + kJitWaves - 1) / kJitWaves * kJitWaves;
+    int64_t want = 2048;
+    if (w.opt.jit_waves > 0) want = w.opt.jit_waves;                                       // tuning knob
+    auto columns = [&](int64_t words_each) {
+        const int64_t n = std::min(std::max<int64_t>(1, want / groups), std::max<int64_t>(1, w.size() / words_each));
+        return (n + kJitWaves - 1) / kJitWaves;
+    };
+    int64_t c = columns(8);
+    if (w.opt.jit_waves <= 0 && kJitWaves == 4) {
+        if (c * groups > 256 && c * groups < 512 && groups <= 256) c = 256 / groups;
+        else if (c * groups <= 128) c = columns(4);
+    }
+    return c * kJitWaves;
 }
 
 // segments per LDS tile; backward also keeps one gradient tile [T][d][65] per wavefront of the workgroup (four as a
@@ -393,14 +402,22 @@ size_t jit_dxt_bytes(const sig::WordSet& w, int64_t B, int64_t n_points, int dir
     return (n + 255) & ~(size_t)255;
 }
 
+// Workgroup columns x path groups.  The workgroups of a group read the same increments and add into the same gradients, so
+// where every XCD (workgroups go round them, each with an L2 of its own) can be given the same number of groups, a group
+// stays on one: a flat grid that the kernel takes apart (5,754 words, 512 paths x 512 segments: backward 385 -> 363 us).
+dim3 jit_grid(const sig::JitKernel& k, const sig::Plan& p, int64_t B)
+{
+    const unsigned gx = (unsigned)((p.units.size() + (size_t)k.nw - 1) / (size_t)k.nw);
+    const unsigned gy = (unsigned)((B + 63) / 64);
+    return gy % 8 == 0 ? dim3(gx * gy, 1, 1) : dim3(gx, gy, 1);
+}
 hipError_t launch_jit_forward(sig::JitKernel& k, const sig::Plan& p, const float* dxT, int64_t B, int64_t ntiles, float* coeffs,
                               int64_t nW, hipStream_t st)
 {
     long lB = (long)B, lT = (long)ntiles, lW = (long)nW;
     void* args[] = {(void*)&dxT, (void*)&lB, (void*)&lT, (void*)&coeffs, (void*)&lW};
-    const unsigned gx = (unsigned)((p.units.size() + (size_t)k.nw - 1) / (size_t)k.nw);
-    const unsigned gy = (unsigned)((B + 63) / 64);
-    return hipModuleLaunchKernel(k.fn, gx, gy, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
+    const dim3 grid = jit_grid(k, p, B);
+    return hipModuleLaunchKernel(k.fn, grid.x, grid.y, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
 }
 
 // B rows; with C > 1 they are the C time chunks of B / C paths, whose last chunks read row (path) of coeffs_last and
@@ -413,9 +430,8 @@ hipError_t launch_jit_backward(sig::JitKernel& k, const sig::Plan& p, const floa
     if (C <= 1) { coeffs_last = coeffs; grad_last = grad; lC = 1; }
     void* args[] = {(void*)&dxT, (void*)&coeffs, (void*)&grad, (void*)&lB, (void*)&lL, (void*)&lT, (void*)&lW, (void*)&gdx,
                     (void*)&coeffs_last, (void*)&grad_last, (void*)&lC};
-    const unsigned gx = (unsigned)((p.units.size() + (size_t)k.nw - 1) / (size_t)k.nw);
-    const unsigned gy = (unsigned)((B + 63) / 64);
-    return hipModuleLaunchKernel(k.fn, gx, gy, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
+    const dim3 grid = jit_grid(k, p, B);
+    return hipModuleLaunchKernel(k.fn, grid.x, grid.y, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
 }
 
 int bwd_tile_steps(int d) { return std::max(1, std::min(16, 32 / std::max(d, 1))); }
@@ -1670,12 +1686,15 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
     if (!grad_path) return SIG_EINVAL;
     const sig::WordSet& w = *W(ws);
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = sig::fill_zero(grad_path, B * n_points * w.d, st);
+    hipError_t e = hipSuccess;
+    const bool direct = K > 0 && windows_direct(w, B, K, 1);
+    // the direct form stores every point itself
+    if (!direct || n_points == 1 || max_window_len == 0) e = sig::fill_zero(grad_path, B * n_points * w.d, st);
     if (e != hipSuccess) return hip_fail(e);
     if (K == 0) return SIG_OK;
     if (!windows || !coeffs || !grad_coeffs) return SIG_EINVAL;
     if (B * K > (int64_t)65535 * 64) return SIG_ETOOLARGE;
-    if (windows_direct(w, B, K, 1)) {
+    if (direct) {
         if (n_points == 1 || max_window_len == 0) return SIG_OK;            // grad_path is zero already
         if (!workspace || workspace_bytes < gdx_bytes_of(w, B, n_points)) return SIG_EWORKSPACE;
         if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
@@ -1697,15 +1716,13 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
     const size_t sb = win_sub_bytes(w, B, K, n_sub);
     if (!workspace || workspace_bytes < sig_backward_windows_workspace_bytes(ws, B, n_points, K, max_window_len)) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
-    // a word per lane: rows = windows read straight from the path, their gradients added up in grad_path
+    // a word per lane: rows = windows read straight from the path, their gradients added up in grad_path (cleared above)
     if (!use_trunc_backward(w, B * K) && use_lanes(w, B * K, kAnyLength, false) && n_points > 1 && max_window_len > 0) {
         const sig::LanesShape ls = lanes_shape_for(w, 1, B * K);
         if (sig::JitKernel* lk = ensure_lanes(w, 1, ls, Build::compile_and_load)) {
             CallTimer whole(1, st);
             sig::WindowList wl;
             wl.win = windows; wl.K = K; wl.max_len = max_window_len;
-            e = sig::fill_zero(grad_path, B * n_points * w.d, st);
-            if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
             e = launch_lanes(lk->fn, ls, path, coeffs, grad_coeffs, B, n_points, grad_path, st, wl);

@@ -99,13 +99,17 @@ __device__ __attribute__((noinline)) void idle_unit(const float* __restrict__ dx
 // a tile is 64 consecutive floats, one floating-point atomic instruction of full cache lines; all workgroup columns
 // (blockIdx.x) add into the same array.
 #define GT_F (T * D * 64)
-__device__ __attribute__((noinline)) void grad_flush(const float* gt_all, float* gdx_tile, int lane, int wib)
+__device__ __forceinline__ void grad_flush(const float* gt_all, float* gdx_tile, int lane, int wib)
 {
-    for (int e = wib; e < T * D; e += NW) {
-        float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += gt_all[w * GT_F + e * 64 + lane];
-        __hip_atomic_fetch_add(gdx_tile + e * 64 + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int r = 0; r < (T * D + NW - 1) / NW; ++r) {
+        const int e = wib + r * NW;
+        if ((T * D) % NW == 0 || e < T * D) {
+            float v = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) v += gt_all[w * GT_F + e * 64 + lane];
+            __hip_atomic_fetch_add(gdx_tile + e * 64 + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 __device__ __attribute__((noinline)) void idle_unit(const float* __restrict__ dxg, long ntiles, long L, float* tile, float* gt_all,
@@ -116,13 +120,14 @@ __device__ __attribute__((noinline)) void idle_unit(const float* __restrict__ dx
     float* gt = gt_all + wib * GT_F;
     for (int e = lane; e < GT_F; e += 64) gt[e] = 0.0f;       // this wavefront contributes nothing
     tile_fetch(dxg, ntiles - 1, tid, r);
+    tile_stage(tile, tid, r);
+    __syncthreads();
     for (long n = ntiles - 1; n >= 0; --n) {
-        __syncthreads();
-        tile_stage(tile, tid, r);
-        __syncthreads();
         tile_fetch(dxg, n - 1, tid, r);
         __syncthreads();
+        tile_stage(tile, tid, r);
         grad_flush(gt_all, gdx + n * (long)(T * D * 64), lane, wib);
+        __syncthreads();
     }
 }
 )SRC";
@@ -225,9 +230,9 @@ void emit_backward_unit(std::ostringstream& o, const Plan& plan, int uidx, int D
     }
     o << "    const int tid = wib * 64 + lane;\n";
     o << "    f4 r[EPT];\n    float* gt = gt_all + wib * GT_F;\n";
-    o << "    tile_fetch(dxg, ntiles - 1, tid, r);\n";
+    // two barriers a tile: between them the next tile is staged and the gradient tiles of this one are added up
+    o << "    tile_fetch(dxg, ntiles - 1, tid, r);\n    tile_stage(tile, tid, r);\n    __syncthreads();\n";
     o << "    for (long n = ntiles - 1; n >= 0; --n) {\n";
-    o << "        __syncthreads();\n        tile_stage(tile, tid, r);\n        __syncthreads();\n";
     o << "        tile_fetch(dxg, n - 1, tid, r);\n";
     // not unrolled: measured as fast as unrolled by two, and the compilation is a quarter shorter
     o << "#pragma unroll 1\n        for (int tt = T - 1; tt >= 0; --tt) {\n";
@@ -297,7 +302,17 @@ void emit_backward_unit(std::ostringstream& o, const Plan& plan, int uidx, int D
         else o << "            gp[" << i << " * 64] = 0.0f;\n";
     }
     o << "        }\n";
-    o << "        __syncthreads();\n        grad_flush(gt_all, gdx + n * (long)(T * D * 64), lane, wib);\n    }\n}\n\n";
+    o << "        __syncthreads();\n        tile_stage(tile, tid, r);\n        grad_flush(gt_all, gdx + n * (long)(T * D * 64), lane, wib);\n"
+         "        __syncthreads();\n    }\n}\n\n";
+}
+
+// Path group and column of a workgroup: (blockIdx.y, blockIdx.x), or on a flat grid group r + 8 q for the workgroups
+// that land on XCD r, all columns of a group one after the other.
+void emit_group_and_column(std::ostringstream& o, int columns)
+{
+    o << "    const bool flat = gridDim.y == 1 && B > 64;\n    const int slot = blockIdx.x / 8;\n"
+         "    const long group = flat ? blockIdx.x % 8 + 8 * (slot / " << columns << ") : blockIdx.y;\n"
+         "    const int column = flat ? slot % " << columns << " : blockIdx.x;\n";
 }
 
 }  // namespace
@@ -312,10 +327,11 @@ std::string jit_forward_source(const WordSet& ws, const Plan& plan, int NW, int 
          "                                                                  float* __restrict__ coeffs, long nW)\n{\n";
     o << "    __shared__ __attribute__((aligned(16))) float tile[T * D * 64];\n";
     o << "    const int lane = threadIdx.x & 63;\n    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);\n";
-    o << "    const long b = (long)blockIdx.y * 64 + lane;\n    const bool valid = b < B;\n";
-    o << "    const float* dxg = dxT + (long)blockIdx.y * ntiles * (T * D * 64);\n";
+    emit_group_and_column(o, (nu + NW - 1) / NW);
+    o << "    const long b = group * 64 + lane;\n    const bool valid = b < B;\n";
+    o << "    const float* dxg = dxT + group * ntiles * (T * D * 64);\n";
     o << "    float* out = valid ? coeffs + b * nW : nullptr;\n";
-    o << "    const int unit = blockIdx.x * NW + wib;\n    switch (unit) {\n";
+    o << "    const int unit = column * NW + wib;\n    switch (unit) {\n";
     for (int u = 0; u < nu; ++u) o << "        case " << u << ": fwd_unit_" << u << "(dxg, ntiles, tile, lane, wib, out); break;\n";
     o << "        default: idle_unit(dxg, ntiles, tile, wib * 64 + lane); break;\n    }\n}\n";
     return o.str();
@@ -332,15 +348,16 @@ std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int
          "        const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, long C)\n{\n";
     o << "    __shared__ __attribute__((aligned(16))) float tile[T * D * 64];\n    __shared__ float gt[NW * GT_F];\n";
     o << "    const int lane = threadIdx.x & 63;\n    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);\n";
-    o << "    const long b0 = (long)blockIdx.y * 64;\n    const long b = b0 + lane;\n    const long bc = b < B ? b : B - 1;\n";
-    o << "    const float* dxg = dxT + (long)blockIdx.y * ntiles * (T * D * 64);\n";
-    o << "    gdx += (long)blockIdx.y * ntiles * (T * D * 64);\n";
+    emit_group_and_column(o, (nu + NW - 1) / NW);
+    o << "    const long b0 = group * 64;\n    const long b = b0 + lane;\n    const long bc = b < B ? b : B - 1;\n";
+    o << "    const float* dxg = dxT + group * ntiles * (T * D * 64);\n";
+    o << "    gdx += group * ntiles * (T * D * 64);\n";
     // rows are the C time chunks of B / C paths: the last chunk of a path starts from the terminal signature and the
     // gradient themselves (arrays of one row per path), the others from rows of the per-chunk arrays; C = 1: whole paths
     o << "    const long pb = bc / C;\n    const bool last = bc - pb * C == C - 1;\n";
     o << "    const float* cf = last ? coeffs_last + pb * nW : coeffs + bc * nW;\n";
     o << "    const float* gr = last ? grad_last + pb * nW : grad + bc * nW;\n";
-    o << "    const int unit = blockIdx.x * NW + wib;\n    switch (unit) {\n";
+    o << "    const int unit = column * NW + wib;\n    switch (unit) {\n";
     for (int u = 0; u < nu; ++u)
         o << "        case " << u << ": bwd_unit_" << u << "(dxg, ntiles, L, tile, gt, gdx, b0, B, lane, wib, cf, gr); break;\n";
     o << "        default: idle_unit(dxg, ntiles, L, tile, gt, gdx, b0, B, lane, wib); break;\n    }\n}\n";

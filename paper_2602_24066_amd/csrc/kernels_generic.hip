@@ -285,6 +285,35 @@ __device__ __forceinline__ void lane_row(const WindowList& wl, int64_t r, int64_
     }
 }
 
+// The 64 rows of a group, one per lane: where a row's points start in an array [B][P][d], and how many of the `most` segments
+// (extra = 0) or points (extra = 1) from j0 on it has.  The wavefronts that walk the rows read both from the row's lane;
+// worked out per row and wavefront, the 64-bit divisions of lane_row took most of the transposers' time (512 rows x 512
+// segments, d = 10: increments 9.5 -> 7.3 us, point gradients 15.5 -> 10.0 us; 1,024 rows of 256, d = 6: 11.0 -> 6.3, 15.1 -> 11.0).
+struct GroupRows {
+    int lo, hi, have;
+    __device__ __forceinline__ GroupRows(const WindowList& wl, int64_t row, int64_t R_rows, int64_t P, int d, int64_t j0, int most, int extra)
+    {
+        int64_t b = 0, first = 0, len = 0, base = 0;
+        have = 0;
+        if (row < R_rows) {
+            lane_row(wl, row, P, b, first, len);
+            const int64_t left = len + extra - j0;
+            have = left <= 0 ? 0 : (left < most ? (int)left : most);
+            if (have > 0) base = (b * P + first + j0) * d;
+        }
+        lo = (int)(uint32_t)(uint64_t)base;
+        hi = (int)(uint32_t)((uint64_t)base >> 32);
+    }
+    __device__ __forceinline__ int64_t base_of(int p) const
+    {
+        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, p) << 32) | (uint32_t)__builtin_amdgcn_readlane(lo, p));
+    }
+    __device__ __forceinline__ int have_of(int p) const { return __builtin_amdgcn_readlane(have, p); }
+};
+// n / d for 0 <= n < 256 and d <= 128: the quotient's fraction is at most (d - 1) / d, the product exceeds it by n / 65,536 at most
+__device__ __forceinline__ int small_div(int n, int per) { return (n * per) >> 16; }
+__device__ __forceinline__ int small_div_by(int d) { return 65536 / d + 1; }
+
 // Increments, differenced and transposed for the run-time specialised kernels (lane = row):
 //   dxT[((g * Lpad + j) * d + i) * 64 + lane] = X[b][first + j + 1][i] - X[b][first + j][i],  row 64 g + lane,
 // zero for padded segments j >= the row's length and for rows past the last.
@@ -294,49 +323,39 @@ __global__ __launch_bounds__(256) void increments_transposed_kernel(const float*
                                              int64_t tiles, WindowList wl, float* __restrict__ dxT, float* __restrict__ zeroed)
 {
     extern __shared__ float tile[];                       // [TS * d][65]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = 4;
-    const int64_t g = blockIdx.x / tiles;
-    const int64_t j0 = (blockIdx.x % tiles) * TS;
-    const int R = TS * d;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = 4;
+    const int64_t g = blockIdx.x / (unsigned)tiles;
+    const int64_t j0 = (int64_t)(blockIdx.x % (unsigned)tiles) * TS;
+    const int R = TS * d, per = small_div_by(d);
+    const GroupRows rows(wl, g * kWave + lane, R_rows, P, d, j0, TS, 0);
     // 16 rows per wavefront (workgroups of 256 threads).  Every load is issued unconditionally, from a clamped
-    // address, before the first value is used: behind a branch per row the sixteen round trips to memory would run one
-    // after the other.
+    // address (path[0] and path[d] exist: P >= 2), before the first value is used: behind a branch per row the sixteen
+    // round trips to memory would run one after the other.
     for (int e0 = 0; e0 < R; e0 += kWave) {
         const int e = e0 + lane;
-        const int64_t seg = j0 + e / d;
-        // eight rows at a time (sixteen loads in flight): offsets, values and flags of all sixteen rows at once
-        // would not fit the registers of the workgroup
+        const int seg = small_div(e < R ? e : 0, per);
+        float hi[16], lo[16];
+        int have[16];
 #pragma unroll
-        for (int q0 = 0; q0 < 16; q0 += 8) {
-            int64_t off[8];
-            bool ok[8];
+        for (int q = 0; q < 16; ++q) {
+            const float* src = path + rows.base_of(wave * 16 + q);         // uniform over the wavefront
+            have[q] = rows.have_of(wave * 16 + q);
+            const int at = e < R && seg < have[q] ? e : 0;
+            hi[q] = src[at + d];
+            lo[q] = src[at];
+        }
+        if (e < R) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int64_t r = g * kWave + wave * 16 + q0 + q;
-                int64_t b = 0, first = 0, len = 0;
-                if (r < R_rows) lane_row(wl, r, P, b, first, len);         // uniform over the wavefront
-                ok[q] = e < R && seg < len;                                // then point first + seg + 1 <= P - 1
-                off[q] = ok[q] ? (b * P + first + j0) * d + e : 0;         // path[0], path[d] exist: P >= 2
-            }
-            float hi[8], lo[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                hi[q] = path[off[q] + d];
-                lo[q] = path[off[q]];
-            }
-            if (e < R) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) tile[e * 65 + wave * 16 + q0 + q] = ok[q] ? hi[q] - lo[q] : 0.0f;
-            }
+            for (int q = 0; q < 16; ++q) tile[e * 65 + wave * 16 + q] = seg < have[q] ? hi[q] - lo[q] : 0.0f;
         }
     }
     __syncthreads();
     const int64_t base = ((g * Lpad + j0) * d) * kWave;
-    for (int e = wave; e < R; e += nwaves)
-        if (j0 + e / d < Lpad) {
-            dxT[base + (int64_t)e * kWave + lane] = tile[e * 65 + lane];
-            if (zeroed) zeroed[base + (int64_t)e * kWave + lane] = 0.0f;   // an array of the same layout, cleared on the way
-        }
+    const int keep = Lpad - j0 < TS ? (int)(Lpad - j0) : TS;
+    for (int e = wave; e < keep * d; e += nwaves) {
+        dxT[base + (int64_t)e * kWave + lane] = tile[e * 65 + lane];
+        if (zeroed) zeroed[base + (int64_t)e * kWave + lane] = 0.0f;       // an array of the same layout, cleared on the way
+    }
 }
 
 __global__ void fill_zero_kernel(float* p, int64_t n)
@@ -436,41 +455,47 @@ __global__ __launch_bounds__(256) void grad_points_transposed_kernel(const float
                                               int64_t tiles, WindowList wl, float* __restrict__ grad_path)
 {
     extern __shared__ float tile[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = 4;
-    const int64_t grp = blockIdx.x / tiles;
-    const int64_t j0 = (blockIdx.x % tiles) * TS;            // points j0 .. j0 + TS - 1 of every row; tile row r: segment j0 - 1 + r / d
-    const int rows = (TS + 1) * d;
-    int64_t my_b, my_first, my_len = 0;                      // this lane's row: segments past its length count as zero
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = 4;
+    const int64_t grp = blockIdx.x / (unsigned)tiles;
+    const int64_t j0 = (int64_t)(blockIdx.x % (unsigned)tiles) * TS;   // points j0 .. j0 + TS - 1 of every row; tile row r: segment j0 - 1 + r / d
+    const int rows = (TS + 1) * d, per = small_div_by(d);
+    const GroupRows mine(wl, grp * kWave + lane, R_rows, P, d, j0, TS, 1);
+    // segments j0 - 1 .. of this lane's row that exist: as many as its points here, the last point has none after it
+    int64_t my_b, my_first, my_len = 0;
     if (grp * kWave + lane < R_rows) lane_row(wl, grp * kWave + lane, P, my_b, my_first, my_len);
-    // eight loads in flight per lane, each from a clamped address (every segment below Lpad exists in g)
-    for (int r0 = wave; r0 < rows; r0 += nwaves * 8) {
-        float v[8];
+    const int64_t left = my_len - (j0 - 1);
+    const int segments = left < 0 ? 0 : (left < TS + 1 ? (int)left : TS + 1);
+    // eighteen loads in flight per lane (all of a tile for up to 8 letters), each from a clamped address (every segment
+    // below Lpad exists in g)
+    for (int r0 = wave; r0 < rows; r0 += nwaves * 18) {
+        float v[18];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int r = r0 + k * nwaves;
-            const int64_t j = j0 - 1 + r / d;
+        for (int k = 0; k < 18; ++k) {
+            const int r = r0 + k * nwaves < rows ? r0 + k * nwaves : 0;
+            const int s = small_div(r, per);
+            const int64_t j = j0 - 1 + s;
             const int64_t jc = j < 0 ? 0 : (j >= Lpad ? Lpad - 1 : j);
-            v[k] = g[((grp * Lpad + jc) * d + r % d) * kWave + lane];
-            if (j < 0 || j >= my_len) v[k] = 0.0f;
+            v[k] = g[((grp * Lpad + jc) * d + (r - s * d)) * kWave + lane];
+            if (j < 0 || s >= segments) v[k] = 0.0f;
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 18; ++k) {
             const int r = r0 + k * nwaves;
             if (r < rows) tile[r * 65 + lane] = v[k];
         }
     }
     __syncthreads();
-    for (int q = 0; q < 16; ++q) {
-        const int p = wave * 16 + q;
-        const int64_t row = grp * kWave + p;
-        if (row >= R_rows) break;
-        int64_t b, first, len;
-        lane_row(wl, row, P, b, first, len);
-        float* out = grad_path + (b * P + first + j0) * d;
-        for (int e = lane; e < TS * d; e += kWave) {
-            if (j0 + e / d <= len) {                          // the row has len + 1 points
+    const bool shared = wl.several_rows();
+    for (int e0 = 0; e0 < TS * d; e0 += kWave) {
+        const int e = e0 + lane;
+        const int point = e < TS * d ? small_div(e, per) : TS;     // lanes past the tile: no row has that many points here
+#pragma unroll 8
+        for (int q = 0; q < 16; ++q) {
+            const int p = wave * 16 + q;
+            float* out = grad_path + mine.base_of(p);         // read from the row's lane by all of the wavefront
+            if (point < mine.have_of(p)) {                    // the row has len + 1 points
                 const float v = tile[e * 65 + p] - tile[(e + d) * 65 + p];
-                if (wl.several_rows()) unsafeAtomicAdd(out + e, v);
+                if (shared) unsafeAtomicAdd(out + e, v);
                 else out[e] = v;
             }
         }

@@ -756,6 +756,37 @@ def test_log_signature_adjoint_forms_agree(d, depth, B):
     assert float((one.double() - two.double()).norm() / two.double().norm()) <= 2e-6
 
 
+@pytest.mark.parametrize("d,B,L", [
+    (2, 65, 31), (2, 1, 33),        # tiles of 32 segments: one short, one with a second tile of one segment
+    (7, 130, 9), (7, 64, 10),       # 63 of 64 floats of a tile row in use
+    (33, 3, 2),                     # a segment per tile
+    (48, 66, 3),                    # the largest alphabet of the specialised backward kernels
+])
+def test_transposed_increments_and_gradients(d, B, L):
+    """The transposition around the specialised kernels at the edges of its tiles (floor(64 / d) segments x 64 rows),
+    whole paths and, on the same set, windows of unequal length (rows that end inside a tile or have no segment)."""
+    import torch
+    words = random_prefix_closed_words(700 + d, d, 40, 6 if d == 2 else 3)
+    ws, W = build_both("words", d, words=words)
+    assert ws.kernel_name(False, B, L + 1) == "sig_fwd_jit"
+    X = make_path("iid", 701 + d, B, L, d)
+    G = make_grad_coeffs(702 + d, B, ws.size)
+    check_parity(ws, W, "words", None, X, G, what=f"d={d} B={B} L={L}")
+    wins = [(0, L), (L // 2, L), (0, 1), (L, L)]
+    x = torch.from_numpy(X).cuda()
+    c = S.sig_forward_windows(ws, x, wins)
+    g = torch.from_numpy(make_grad_coeffs(703 + d, B * len(wins), ws.size).reshape(B, len(wins), ws.size)).cuda()
+    gp = S.sig_backward_windows(ws, x, wins, c, g)
+    total = torch.zeros_like(x)
+    for k, (l, r) in enumerate(wins):
+        sub = x[:, l:r + 1].contiguous()
+        ck = S.sig_forward(ws, sub)
+        assert torch.allclose(ck, c[:, k], rtol=1e-5, atol=1e-6)
+        total[:, l:r + 1] += S.sig_backward(ws, sub, ck, g[:, k].contiguous())
+    torch.cuda.synchronize()
+    assert O.grad_errors(gp.cpu().numpy(), total.cpu().numpy().astype(np.float64)).max() <= BWD_TOL
+
+
 @pytest.mark.parametrize("two_kernels", [False, True])
 def test_log_signature_gradient(monkeypatch, two_kernels):
     """d <G, logsig(X)> / dX through sig_logsig_backward and sig_backward against central differences of the oracle;

@@ -1235,17 +1235,17 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
     float* gdx = (float*)workspace;
     float* Abar = (float*)((unsigned char*)workspace + gb);
     CallTimer whole(1, st);
-    hipError_t e = sig::fill_zero(gdx, B * (n_points - 1) * w.d, st);
+    const int64_t n_gdx = B * (n_points - 1) * w.d;                 // cleared by the launch of the adjoints
+    hipError_t e = hipSuccess;
     const float* row_coeffs = ckpt;
     if (ch.C == 2) {
         // two chunks: the signature at the end of the first is the first chunk's own, what follows it the second's
-        if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, Abar, B, 2, true, st);
+        e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, Abar, B, 2, true, st, gdx, n_gdx);
     } else {
         float* Pfx = (float*)((unsigned char*)workspace + gb + ab);
         float* Q = (float*)((unsigned char*)workspace + gb + ab + nb);
-        if (e == hipSuccess)
-            e = sig::chunk_scan(w.d, w.depth, ckpt, Pfx, Q, coeffs, nullptr, nullptr, nullptr, B, (int)ch.C, nullptr, st);
-        if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, Q, Abar, B, (int)ch.C, true, st);
+        e = sig::chunk_scan(w.d, w.depth, ckpt, Pfx, Q, coeffs, nullptr, nullptr, nullptr, B, (int)ch.C, nullptr, st);
+        if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, Q, Abar, B, (int)ch.C, true, st, gdx, n_gdx);
         row_coeffs = Pfx;
     }
     if (e != hipSuccess) return hip_fail(e);

@@ -938,7 +938,8 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
     const double words = (double)words_up_to(d, depth), k = words / 1000.0;
     const double low_waves = (double)lanes_low_shape(d, depth).waves;
     const double low_exponent = backward ? 0.4 : 0.07, scan_exponent = backward ? -0.12 : 0.21;
-    const double launches = (backward ? 4.1 : 3.0) * std::pow(k, low_exponent);
+    // two more launches backward: at least their host time
+    const double launches = backward ? std::max(5.0, 4.1 * std::pow(k, low_exponent)) : 3.0 * std::pow(k, low_exponent);
     const double product = (backward ? 0.78 : 0.48) * std::pow(k, scan_exponent) + (backward ? 4.5e-6 : 1.9e-6) * (double)B * words;
     auto time = [&](int64_t C) {
         LanesShape s = lanes_shape(d, depth, backward, B * C, levels);

@@ -171,6 +171,6 @@ hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, float* Q, c
 // Abar [B, C, |W|]: adjoint of the signature at the end of every chunk, from grad [B, |W|] and Q
 // (skip_last: the last chunk's row of Abar, a copy of grad, is not written)
 hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, float* Abar, int64_t B, int C, bool skip_last,
-                         hipStream_t stream);
+                         hipStream_t stream, float* zero = nullptr, int64_t n_zero = 0);
 
 }  // namespace sig

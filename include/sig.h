@@ -168,10 +168,10 @@ int sig_wordset_plan_get(const sig_wordset* ws, int backward, int variant, const
  * this word set is not run through specialised kernels, or SIG_EJIT if hiprtc failed (sig_forward / sig_backward
  * then fall back to the table-driven kernels).  The option "no_jit" disables it.
  * Full truncations (any d <= 64) without a precompiled kernel are the exception to "grows with the word set": they
- * run one fixed kernel source with a word per lane, compiled for the shape (d, depth) in under a second per
- * direction (Section 3.1, eq. (3), with the prefixes shared between words); the option "lanes" = 0 sends them through
- * the straight-line form as well, = 1 takes the word-per-lane form even where a path has only a few words of
- * length depth - 2.  sig_wordset_jit_prepare and sig_wordset_jit_source cover whichever form the batch would use.
+ * run fixed kernel sources with a word per lane, compiled for the shape (d, depth) in one to three seconds per
+ * direction, the kernels of their time chunks included (Section 3.1, eq. (3), with the prefixes shared between words);
+ * where a path has only a few words of length depth - 2 they do so while the paths are few.  The option "lanes" = 0
+ * sends them all through the straight-line form, = 1 all through the word-per-lane form.  sig_wordset_jit_prepare and sig_wordset_jit_source cover whichever form the batch would use.
  * With the environment variable SIG_JIT_CACHE naming an existing directory (read when a kernel is compiled), code
  * objects are kept there (named by a hash of their source, the compiler version and the compile options; each file
  * carries its length and a checksum) and later processes load them instead of compiling; a file that fails its

@@ -584,7 +584,7 @@ bool use_lanes(const sig::WordSet& w, int64_t B, int64_t L, bool chunks = true, 
     return few;
 }
 
-// Time chunks of those truncations: a wavefront takes 0.15-0.2 us per segment forward and 0.5-0.7 us backward however few
+// Time chunks of those truncations: a wavefront takes 0.1-0.15 us per segment forward and 0.25-0.35 us backward however few
 // there are, so few paths are cut into C chunks that run as rows of their own.  Forward: chunk signatures, then their
 // product; backward: chunk signatures over the words shorter than the depth (a d-th of the work; the longest words are
 // never reconstructed), their products from both sides, the adjoints at the boundaries, then the rows.

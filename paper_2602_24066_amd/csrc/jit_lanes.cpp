@@ -306,6 +306,34 @@ __device__ __forceinline__ float row_sum(const float* row, int lane)
     return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
+#if MSUM
+// The sums of one segment for letters j0 .. j0 + 3 lane by lane: of the wavefront's words (the first is p0) every letter takes
+// the products with its leaf adjoints and the chain values of the words that have it at the position.  v: the segment's row
+// of the first source.  Rolled loops: it runs only where a sum is not finite.
+__device__ __forceinline__ void letter_sums(const float* v, const float* __restrict__ leaves, int p0, int j0, f4& sum)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = j0 + r;
+        float acc = 0.0f;
+        if (j < D) {
+#pragma unroll 1
+            for (int i = 0; i < 64; ++i) {
+                const bool in = p0 + i < NL;
+                int q = in ? p0 + i : NL - 1;                  // lanes past the last word hold a copy of it
+                acc = __builtin_fmaf(in ? leaves[(long)q * D + j] : 0.0f, v[i], acc);
+#pragma unroll 1
+                for (int k = K; k >= 1; --k) {
+                    acc += q % D == j ? v[k * 16 * VROW + i] : 0.0f;
+                    q /= D;
+                }
+            }
+        }
+        sum[r] = acc;
+    }
+}
+#endif
+
 extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float* __restrict__ path,
         const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* grad_path,
         const long* __restrict__ win, long KW, long max_len, const float* __restrict__ low_coeffs, const float* __restrict__ low_grad)
@@ -521,9 +549,16 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                                                                       v[i], sum[i & 1], 0, 0, 0);
             }
         const long sg = n * T + col;
+        sum[0] += sum[1];
+        // The indicators multiply every lane's value, so a NaN or an infinity from one word would reach all letters.  It shows
+        // in the sums; they are then formed anew from the values of each letter's own lanes.
+        bool finite = true;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) finite &= sg >= L || __builtin_fabsf(sum[0][r]) <= 3.402823466e38f;
+        if (__builtin_amdgcn_ballot_w64(!finite) != 0) letter_sums(Vb + col * VROW, gr + level_start(N), p0, grp * 4, sum[0]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float acc = sg < L ? sum[0][r] + sum[1][r] : 0.0f;
+            const float acc = sg < L ? sum[0][r] : 0.0f;
             // the next segment's in the lane to the right; lane 15 of a row receives lane 0's, kept for the next tile
             const float next = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(acc), 0x12f, 0xf, 0xf, true));   // row_ror:15
             const int j = grp * 4 + r;

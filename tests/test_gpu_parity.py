@@ -5,7 +5,8 @@ import pytest
 import paper_2602_24066_amd as S
 from oracle import sig_oracle as O
 from sig_workloads import (WORKLOADS, make_grad_coeffs, make_path, random_prefix_closed_words, workload_path)
-from tests.gpu_common import BWD_TOL, FWD_TOL, build_both, build_for_workload, check_parity, gpu_forward_backward
+from tests.gpu_common import (BWD_TOL, FWD_TOL, build_both, build_for_workload, check_parity, gpu_forward_backward,
+                              oracle_backward)
 
 pytestmark = pytest.mark.gpu
 
@@ -533,6 +534,40 @@ def test_time_chunks_of_truncations_with_lanes_as_words(d, depth, B, L, chunks, 
                            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
     torch.cuda.synchronize()
     assert float((c - whole).norm() / whole.norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,depth,L,levels,chunks", [
+    (10, 4, 37, 1, 1),    # matrix-product sums, 16 wavefronts per path, ragged last tile
+    (10, 4, 37, 1, 4),    # the same from the boundary adjoints of time chunks
+    (3, 4, 20, 1, 1),     # 27 lanes: copies of the last word beyond them
+    (16, 3, 9, 1, 1),     # every row of the product is a letter
+    (6, 4, 18, 2, 1),     # two levels per lane: sums of rows
+])
+def test_non_finite_gradient_of_one_word_stays_with_its_letters(d, depth, L, levels, chunks, bad, monkeypatch):
+    """d loss / dX of letter i sums over the words that contain i (Proposition 4.1).  An infinite or NaN upstream
+    gradient of one word reaches the letters of that word in its path; the other letters and the other path have the
+    gradient of the remaining words."""
+    import torch
+    monkeypatch.setenv("SIG_LANES", "1")
+    monkeypatch.setenv("SIG_LANES_LEVELS", str(levels))
+    ws, W = build_both("truncated", d, depth=depth)
+    ws.set_option("chunks", chunks)
+    X = make_path("iid", 371 + d, 2, L, d)
+    G = make_grad_coeffs(372 + d, 2, ws.size)
+    word = tuple(int(c) for c in np.random.default_rng(373).integers(0, 2, depth - 1)) + (2,)      # letters 0, 1 and 2 at most
+    at = W.index(word)
+    G[1, at] = 0.0
+    ref = oracle_backward(X, W, "truncated", depth, G.astype(np.float64))
+    G[1, at] = bad
+    x = torch.from_numpy(X).cuda()
+    g = S.sig_backward(ws, x, S.sig_forward(ws, x), torch.from_numpy(G).cuda()).cpu().numpy()
+    others = [i for i in range(d) if i not in word]
+    scale = np.abs(ref).max(axis=(1, 2))
+    assert np.abs(g[0] - ref[0]).max() <= BWD_TOL * scale[0]
+    assert not np.isfinite(g[1][:, sorted(set(word))]).any()
+    if others:
+        assert np.abs(g[1][:, others] - ref[1][:, others]).max() <= BWD_TOL * scale[1]
 
 
 @pytest.mark.parametrize("d,depth,B,L,lanes_are_words", [

@@ -265,7 +265,11 @@ int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 // whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
 // first word).  Where that leaves between one and two workgroups per compute unit (256), the units that hold two set the
 // time, so one each is taken (1,500 words, 512 paths x 512 segments: 47 -> 32 columns of workgroups, backward 431 -> 304
-// us); where it leaves half the compute units empty, units go down to four words (384 words, 300 x 256: 94 -> 85 us).
+// us).  Units go down to four words where 256 to 512 words and three or more path groups leave most of the chip empty (backward
+// calls of 256 segments: 384 words, d = 6, 300 paths 89 -> 79 us, 500, d = 4 104 -> 95, 400, d = 20, 256 paths 206 -> 197; at 640
+// paths, 120 workgroups of eight words each, 93 -> 96).  Not beyond: every column adds to the same gradients in no fixed order,
+// so small sets and one or two groups keep the few columns that let two runs agree to a few roundings (one column: bit for
+// bit), and large sets would compile twice as long (1,500 words: 15 -> 33 s for 7 %).
 int64_t jit_units(const sig::WordSet& w, int /*dir*/, int64_t B)
 {
     const int kJitWaves = jit_wg_waves(w);
@@ -279,7 +283,7 @@ int64_t jit_units(const sig::WordSet& w, int /*dir*/, int64_t B)
     int64_t c = columns(8);
     if (w.opt.jit_waves <= 0 && kJitWaves == 4) {
         if (c * groups > 256 && c * groups < 512 && groups <= 256) c = 256 / groups;
-        else if (c * groups <= 128) c = columns(4);
+        else if (w.size() >= 256 && w.size() <= 512 && groups >= 3 && c * groups <= 100) c = columns(4);
     }
     return c * kJitWaves;
 }

@@ -309,6 +309,24 @@ def test_balanced_plans_are_balanced():
     assert p["fma_per_step"] <= 1.6 * ws.min_fma_per_step
 
 
+@pytest.mark.parametrize("d,n_words,B,columns", [
+    (4, 36, 9, 1), (4, 36, 300, 1), (4, 39, 1024, 1),        # one column: a single addition per gradient, bit for bit
+    (5, 150, 9, 5), (5, 150, 300, 5),                         # units of eight words
+    (6, 384, 64, 12), (6, 384, 128, 12),                      # one and two path groups
+    (6, 384, 129, 24), (6, 384, 300, 24), (6, 384, 512, 24),  # units of four words fill more of the chip
+    (6, 384, 640, 12),
+    (6, 255, 300, 8), (6, 513, 192, 16),
+    (10, 1500, 64, 47), (10, 1500, 128, 47),
+])
+def test_columns_of_small_launches(d, n_words, B, columns):
+    """Workgroup columns (four units each) of the specialised kernels where the chip is not filled."""
+    ws = S.sig_wordset_build(d, random_prefix_closed_words(31, d, n_words, 6))
+    assert ws.size == n_words
+    for backward in (False, True):
+        units = len(ws.jit_plan(backward, B)["units"])
+        assert 0.75 * 4 * columns <= units <= 4 * columns, units        # a plan may come out with fewer units than asked for
+
+
 def test_runtime_compilation_without_a_device():
     """hiprtc needs no GPU: the specialised kernels of a small word set compile, and the generated source holds one
     body per work unit of the balanced plan."""

@@ -263,14 +263,22 @@ int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 }
 // Work units asked of the balanced planner for a batch of B paths: two wavefronts per SIMD (2,048) over the path groups, in
 // whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
-// first word).  Where that leaves between one and two workgroups per compute unit (256), the units that hold two set the
-// time, so one each is taken (1,500 words, 512 paths x 512 segments: 47 -> 32 columns of workgroups, backward 431 -> 304
-// us).  Units go down to four words where 256 to 512 words and three or more path groups leave most of the chip empty (backward
+// first word).  Where that comes to more than one workgroup per compute unit (256), half as many of larger units may be
+// the better choice; a model of the backward kernel decides, in nanoseconds per segment, fitted to 40 pairs of 4 to 40
+// letters, 1,500 to 10,000 words and 384 to 1,024 paths:
+//   one workgroup each: the latency of a lone wavefront, 250 + 25 d, and 9.5 per word of its unit;
+//   two: 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
+// So few words or many letters take one each (backward calls of 256 segments, two -> one: 1,500 words, d = 10, 640 paths
+// 269 -> 169 us, 960 paths 303 -> 189; 3,000 words, 512 paths, d = 20 557 -> 291, d = 8 249 -> 167), large units of few
+// letters do not (5,754 words, d = 6, 640 paths 220 and 257; 10,000, d = 10 314 and 364).  The count is rounded down to
+// four steps an octave, so that neighbouring batch sizes share a kernel.  The forward kernel adds nothing up and follows
+// only into units of up to twelve words (1,500 words, 512 paths: d = 10 55 -> 54 us, d = 20 77 -> 71; 6,000, d = 10 78 and 86).
+// Units go down to four words where 256 to 512 words and three or more path groups leave most of the chip empty (backward
 // calls of 256 segments: 384 words, d = 6, 300 paths 89 -> 79 us, 500, d = 4 104 -> 95, 400, d = 20, 256 paths 206 -> 197; at 640
 // paths, 120 workgroups of eight words each, 93 -> 96).  Not beyond: every column adds to the same gradients in no fixed order,
 // so small sets and one or two groups keep the few columns that let two runs agree to a few roundings (one column: bit for
 // bit), and large sets would compile twice as long (1,500 words: 15 -> 33 s for 7 %).
-int64_t jit_units(const sig::WordSet& w, int /*dir*/, int64_t B)
+int64_t jit_units(const sig::WordSet& w, int dir, int64_t B)
 {
     const int kJitWaves = jit_wg_waves(w);
     const int64_t groups = (B + 63) / 64;
@@ -282,8 +290,17 @@ int64_t jit_units(const sig::WordSet& w, int /*dir*/, int64_t B)
     };
     int64_t c = columns(8);
     if (w.opt.jit_waves <= 0 && kJitWaves == 4) {
-        if (c * groups > 256 && c * groups < 512 && groups <= 256) c = 256 / groups;
-        else if (w.size() >= 256 && w.size() <= 512 && groups >= 3 && c * groups <= 100) c = columns(4);
+        if (c * groups > 256 && groups <= 256) {
+            int64_t one = 256 / groups, step = 1;
+            while (one >= 8 * step) step *= 2;
+            one -= one % step;
+            const double d = (double)w.d, unit = (double)w.size() / (4.0 * (double)one), unit2 = (double)w.size() / (4.0 * (double)c);
+            const double lone = 250.0 + 25.0 * d + 9.5 * unit;
+            const double two = std::max(430.0 + 13.4 * unit2, (double)(c * groups) * d * 256.0 / 1150.0);
+            if (1.05 * lone < two && (dir == 1 || unit <= 12.0)) c = one;
+        } else if (w.size() >= 256 && w.size() <= 512 && groups >= 3 && c * groups <= 100) {
+            c = columns(4);
+        }
     }
     return c * kJitWaves;
 }

@@ -327,6 +327,28 @@ def test_columns_of_small_launches(d, n_words, B, columns):
         assert 0.75 * 4 * columns <= units <= 4 * columns, units        # a plan may come out with fewer units than asked for
 
 
+def test_columns_of_filled_launches():
+    """Workgroup columns of the backward kernel where two workgroups per compute unit are possible: units of few words are
+    doubled until there is one, units of many are not, and neighbouring batch sizes of a word list share a kernel."""
+    def columns(ws, B, backward=True):
+        return (len(ws.jit_plan(backward, B)["units"]) + 3) // 4
+
+    aniso = S.sig_wordset_build_anisotropic(6, (1, 1, 2, 2, 3, 3), 8.0)
+    large = S.sig_wordset_build(10, random_prefix_closed_words(32, 10, 10000, 6))
+    small = S.sig_wordset_build(10, random_prefix_closed_words(33, 10, 1500, 6))
+    for ws in (aniso, large):
+        for backward in (False, True):
+            for B in (448, 512, 640, 960):
+                groups = B // 64
+                full = (2048 // groups + 3) // 4
+                assert 0.95 * full <= columns(ws, B, backward) <= full, (ws.size, B)
+    for B, one in ((384, 40), (448, 32), (512, 32), (640, 24), (960, 16), (1024, 16)):
+        assert 0.95 * one <= columns(small, B) <= one, B
+        assert one * (B // 64) <= 256
+    assert columns(small, 640, False) > 40                              # units of 15 words: forward keeps the smaller ones
+    assert len({len(small.jit_plan(True, 64 * g)["units"]) for g in range(1, 17)}) <= 7
+
+
 def test_runtime_compilation_without_a_device():
     """hiprtc needs no GPU: the specialised kernels of a small word set compile, and the generated source holds one
     body per work unit of the balanced plan."""

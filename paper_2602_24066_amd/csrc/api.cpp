@@ -314,6 +314,19 @@ int jit_tile_for(const sig::WordSet& w, int dir)
     return std::max(1, jit_tile_steps(w.d, dir, jit_wg_waves(w)));
 }
 
+// Form of the sum of a gradient tile in the backward kernel for B paths (0: a function, else inlined in that many rounds).
+// Where a SIMD holds one wavefront its latency is the time, and a call anywhere in a unit costs more than its own: calls of
+// 256 segments, 512 paths, called -> inlined: 1,500 words, d = 10 186 -> 156 us, d = 7 166 -> 139, d = 14 244 -> 209; 384 words,
+// d = 6, 300 paths 94 -> 79.  Two wavefronts hide it, and a function leaves them more registers and compiles sooner (10,000 words,
+// d = 10 295 us called, 313 inlined, 33 and 40 s; d = 8 260 and 266; 6,000, d = 9 282 and 289), except for tiles of eight segments,
+// where inlining in two rounds is the faster (5,754 words, d = 6 210 called, 195 inlined).
+int jit_flush_rounds(const sig::WordSet& w, int dir, int64_t B, int64_t n_units)
+{
+    if (dir == 0) return 0;
+    if (n_units * ((B + 63) / 64) <= 1024) return 1;
+    return jit_tile_for(w, 1) >= 8 ? 2 : 0;
+}
+
 bool jit_enabled(const sig::WordSet& w)
 {
     if (w.opt.no_jit) return false;
@@ -326,16 +339,17 @@ sig::WordSet::JitEntry* jit_entry(const sig::WordSet& cw, int dir, int64_t B)
 {
     sig::WordSet& w = const_cast<sig::WordSet&>(cw);     // the cache is logically mutable
     const int64_t n_units = jit_units(w, dir, B);
-    const int wgw = jit_wg_waves(w), tile = jit_tile_for(w, dir);
+    const int wgw = jit_wg_waves(w), tile = jit_tile_for(w, dir), flush = jit_flush_rounds(w, dir, B, n_units);
     std::lock_guard<std::mutex> lock(g_jit_mutex);
     for (auto* e : w.jit[dir])
-        if (e->n_units == n_units && e->wg_waves == wgw && e->tile == tile) return e;
+        if (e->n_units == n_units && e->wg_waves == wgw && e->tile == tile && e->flush_rounds == flush) return e;
     auto* e = new (std::nothrow) sig::WordSet::JitEntry;
     if (!e) return nullptr;
     try {
         e->n_units = n_units;
         e->wg_waves = wgw;
         e->tile = tile;
+        e->flush_rounds = flush;
         if (dir == 0) sig::build_plan_balanced(w, n_units, 320, false, 1, 1, e->plan);
         else sig::build_plan_balanced(w, n_units, 160, true, 6, 9, e->plan);
         e->kernel = new sig::JitKernel;
@@ -348,12 +362,13 @@ sig::WordSet::JitEntry* jit_entry(const sig::WordSet& cw, int dir, int64_t B)
 }
 
 // Source of the specialised kernel of an entry; fills nw / tile.
-std::string jit_source(const sig::WordSet& w, int dir, const sig::Plan& p, int& nw, int& tile)
+std::string jit_source(const sig::WordSet& w, int dir, const sig::WordSet::JitEntry& e, int& nw, int& tile)
 {
+    const sig::Plan& p = e.plan;
     // Four wavefronts per workgroup = one per SIMD, so a workgroup's registers fit whatever a unit needs.
     nw = (int)std::min<size_t>((size_t)jit_wg_waves(w), std::max<size_t>(1, p.units.size()));
     tile = jit_tile_for(w, dir);
-    return dir ? sig::jit_backward_source(w, p, nw, tile) : sig::jit_forward_source(w, p, nw, tile);
+    return dir ? sig::jit_backward_source(w, p, nw, tile, e.flush_rounds) : sig::jit_forward_source(w, p, nw, tile);
 }
 
 // What a call may do to get its kernel: compile and load it (ordinary entry points), or only use one that is already
@@ -408,7 +423,7 @@ sig::JitKernel* ensure_jit(const sig::WordSet& cw, int dir, int64_t B, Build how
     if (!e) return nullptr;
     if (plan) *plan = &e->plan;
     return bring_up(e->kernel, how, dir ? "sig_bwd_jit" : "sig_fwd_jit",
-                    [&](sig::JitKernel& k) { return jit_source(cw, dir, e->plan, k.nw, k.tile); });
+                    [&](sig::JitKernel& k) { return jit_source(cw, dir, *e, k.nw, k.tile); });
 }
 
 // bytes of the transposed increments the specialised kernels read: [groups][Lpad][d][64] floats
@@ -1024,7 +1039,7 @@ size_t sig_wordset_jit_source(sig_wordset* ws, int backward, int64_t B, char* bu
         sig::WordSet::JitEntry* e = jit_entry(w, dir, B);
         if (!e) return 0;
         int nw = 0, tile = 0;
-        src = jit_source(w, dir, e->plan, nw, tile);
+        src = jit_source(w, dir, *e, nw, tile);
     }
     if (buf && n > 0) {
         const size_t c = std::min(n - 1, src.size());

@@ -15,6 +15,7 @@
 #include <hip/hiprtc.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -99,18 +100,26 @@ __device__ __attribute__((noinline)) void idle_unit(const float* __restrict__ dx
 // a tile is 64 consecutive floats, one floating-point atomic instruction of full cache lines; all workgroup columns
 // (blockIdx.x) add into the same array.
 #define GT_F (T * D * 64)
-__device__ __forceinline__ void grad_flush(const float* gt_all, float* gdx_tile, int lane, int wib)
+__device__ __forceinline__ void flush_row(const float* gt_all, float* gdx_tile, int e, int lane)
 {
+    float v = 0.0f;
 #pragma unroll
-    for (int r = 0; r < (T * D + NW - 1) / NW; ++r) {
-        const int e = wib + r * NW;
-        if ((T * D) % NW == 0 || e < T * D) {
-            float v = 0.0f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) v += gt_all[w * GT_F + e * 64 + lane];
-            __hip_atomic_fetch_add(gdx_tile + e * 64 + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    for (int w = 0; w < NW; ++w) v += gt_all[w * GT_F + e * 64 + lane];
+    __hip_atomic_fetch_add(gdx_tile + e * 64 + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// FLUSH_ROUNDS 0: a function; otherwise inlined in that many rounds.  Only the rows left over after whole rounds of the
+// wavefronts are behind a condition: with one per row the inlined form was unrolled into a block per row that
+// waited for its own LDS reads (1,500 words, 512 paths x 256 segments, 42 rows a tile: d = 14 473 -> 209 us, d = 7 259 -> 139).
+#if FLUSH_ROUNDS
+__device__ __forceinline__
+#else
+__device__ __attribute__((noinline))
+#endif
+void grad_flush(const float* gt_all, float* gdx_tile, int lane, int wib)
+{
+#pragma unroll FLUSH_UNROLL
+    for (int r = 0; r < T * D / NW; ++r) flush_row(gt_all, gdx_tile, wib + r * NW, lane);
+    if ((T * D) % NW != 0 && wib < (T * D) % NW) flush_row(gt_all, gdx_tile, T * D / NW * NW + wib, lane);
 }
 __device__ __attribute__((noinline)) void idle_unit(const float* __restrict__ dxg, long ntiles, long L, float* tile, float* gt_all,
                                                     float* gdx, long b0, long B, int lane, int wib)
@@ -337,9 +346,11 @@ std::string jit_forward_source(const WordSet& ws, const Plan& plan, int NW, int 
     return o.str();
 }
 
-std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T)
+std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T, int flush_rounds)
 {
     std::ostringstream o;
+    const int rows = T * ws.d / NW, rounds = std::max(1, flush_rounds);      // rows of a gradient tile per wavefront
+    o << "#define FLUSH_ROUNDS " << flush_rounds << "\n#define FLUSH_UNROLL " << std::max(1, (rows + rounds - 1) / rounds) << "\n";
     emit_prelude(o, ws.d, T, NW, true);
     const int nu = (int)plan.units.size();
     for (int u = 0; u < nu; ++u) emit_backward_unit(o, plan, u, ws.d);

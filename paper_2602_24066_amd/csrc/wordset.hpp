@@ -122,6 +122,7 @@ struct WordSet {
         int64_t n_units = 0;
         int wg_waves = 0;              // wavefronts per workgroup the kernel is generated for
         int tile = 0;                  // segments per LDS tile the kernel is generated for
+        int flush_rounds = 0;          // backward: form of the sum of a gradient tile
         Plan plan;
         JitKernel* kernel = nullptr;
     };

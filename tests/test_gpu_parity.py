@@ -822,6 +822,23 @@ def test_transposed_increments_and_gradients(d, B, L):
     assert O.grad_errors(gp.cpu().numpy(), total.cpu().numpy().astype(np.float64)).max() <= BWD_TOL
 
 
+@pytest.mark.parametrize("d,n_words,B,L,rounds", [
+    (7, 300, 70, 13, 1),       # 42 rows a tile: ten whole rounds of four wavefronts and two rows
+    (14, 300, 65, 7, 1),       # tiles of three segments, the last ragged
+    (48, 300, 3, 2, 1),        # one segment a tile
+    (7, 1000, 2497, 7, 0),     # two workgroups per compute unit, the last group one path
+    (5, 1000, 2497, 9, 2),     # tiles of eight segments
+    (3, 4, 5, 9, 1),           # units of one word
+])
+def test_gradient_tile_sums(d, n_words, B, L, rounds):
+    """The specialised backward with the sum of its gradient tiles as a function and inlined, against the oracle."""
+    words = random_prefix_closed_words(720, d, n_words, 5)
+    ws, W = build_both("words", d, words=words)
+    assert f"#define FLUSH_ROUNDS {rounds}\n" in ws.jit_source(True, B)
+    check_parity(ws, W, "words", None, make_path("iid", 721, B, L, d), make_grad_coeffs(722, B, ws.size),
+                 sample=None if B < 100 else list(range(0, B, 208)), what=f"B={B} L={L}")
+
+
 @pytest.mark.parametrize("two_kernels", [False, True])
 def test_log_signature_gradient(monkeypatch, two_kernels):
     """d <G, logsig(X)> / dX through sig_logsig_backward and sig_backward against central differences of the oracle;

@@ -349,6 +349,16 @@ def test_columns_of_filled_launches():
     assert len({len(small.jit_plan(True, 64 * g)["units"]) for g in range(1, 17)}) <= 7
 
 
+@pytest.mark.parametrize("d,n_words,B,rounds", [
+    (10, 1500, 64, 1), (10, 1500, 512, 1),      # one wavefront per SIMD: inlined
+    (10, 10000, 512, 0), (7, 6000, 512, 0),     # two: a function
+    (6, 5000, 512, 2),                          # two, tiles of eight segments: inlined in two rounds
+])
+def test_form_of_the_gradient_tile_sum(d, n_words, B, rounds):
+    ws = S.sig_wordset_build(d, random_prefix_closed_words(34, d, n_words, 6))
+    assert f"#define FLUSH_ROUNDS {rounds}\n" in ws.jit_source(True, B)
+
+
 def test_runtime_compilation_without_a_device():
     """hiprtc needs no GPU: the specialised kernels of a small word set compile, and the generated source holds one
     body per work unit of the balanced plan."""

@@ -737,18 +737,22 @@ void lanes_bring_up(const sig::WordSet& cw, int dir, int64_t B, Build how)
         std::lock_guard<std::mutex> lock(memo.m);
         for (const auto& l : memo.loaded)
             if (l.first == dir && l.second == B) return;
-        try {
-            if (memo.loaded.size() >= 64) memo.loaded.clear();
-            memo.loaded.emplace_back(dir, B);
-        } catch (const std::bad_alloc&) { }
     }
-    (void)ensure_lanes(w, dir, lanes_shape_for(w, dir, B), how);
+    bool all = ensure_lanes(w, dir, lanes_shape_for(w, dir, B), how) != nullptr;
     bool small_set = false;
     (void)use_lanes(w, B, kAnyLength, true, &small_set);
-    if (small_set && (dir == 1 || w.depth > 3)) (void)ensure_jit(w, dir, B, how);    // sig_backward_static, other lengths
-    if (!sig::lanes_chunks_available(w.d, w.depth)) return;
-    LanesChunked k;
-    for (int C : sig::kLanesChunkCounts) (void)lanes_chunk_kernels(w, dir, B * C, how, k);
+    if (small_set && (dir == 1 || w.depth > 3)) all = ensure_jit(w, dir, B, how) != nullptr && all;    // sig_backward_static, other lengths
+    if (sig::lanes_chunks_available(w.d, w.depth))
+        for (int C : sig::kLanesChunkCounts) {
+            const sig::LanesShape s = lanes_shape_for(w, dir, B * C);
+            if (s.ok && B * C <= 65535) all = ensure_lanes(w, dir, s, how) != nullptr && all;
+        }
+    if (!all || how != Build::compile_and_load) return;       // asked again by the next call
+    try {
+        std::lock_guard<std::mutex> lock(memo.m);
+        if (memo.loaded.size() >= 64) memo.loaded.clear();
+        memo.loaded.emplace_back(dir, B);
+    } catch (const std::bad_alloc&) { }
 }
 // forward, workspace: the chunk signatures [B][C][|W|]
 hipError_t lanes_forward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, int64_t B, int64_t n_points,
@@ -852,6 +856,8 @@ int sig_wordset_set_option(sig_wordset* ws, const char* name, int value)
     for (const OptionName& o : kOptions)
         if (std::strcmp(o.name, name) == 0) {
             ws->opt.*(o.field) = value;
+            std::lock_guard<std::mutex> lock(ws->lanes_memo.m);
+            ws->lanes_memo.loaded.clear();                  // the kernels a batch size needs may be others now
             return SIG_OK;
         }
     return SIG_EINVAL;

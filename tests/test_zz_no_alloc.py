@@ -61,6 +61,26 @@ def test_static_scratch_entry_point_matches_sig_backward(case):
         assert O.grad_errors(got, gref).max() <= BWD_TOL, f"case {case} call {call}: differs from the oracle"
 
 
+def test_static_scratch_entry_point_after_an_option_changed():
+    """One sig_backward call loads what every length of its batch size needs, also when an option that chooses other
+    kernels was set since the last one: 32 paths run one level of words per lane whole and two in four time chunks."""
+    import torch
+    d, depth, B, L = 6, 5, 32, 40
+    ws, _ = build_both("truncated", d, depth=depth)
+    ws.set_option("chunks", 4)
+    x = torch.from_numpy(make_path("iid", 2400, B, L, d)).cuda()
+    g = torch.from_numpy(make_grad_coeffs(2401, B, ws.size)).cuda()
+    c = S.sig_forward(ws, x)
+    for levels in (2, 0):
+        ws.set_option("lanes_levels", levels)
+        ref = S.sig_backward(ws, x, c, g)
+    assert "#define R 1\n" in ws.jit_source(True, B) and "#define R 2\n" in ws.jit_source(True, 4 * B)
+    out = torch.empty_like(x)
+    assert _static_call(ws, x, c, g, out) == 0
+    torch.cuda.synchronize()
+    assert O.grad_errors(out.cpu().numpy(), ref.cpu().numpy().astype(np.float64)).max() <= BWD_TOL
+
+
 def test_static_scratch_entry_point_rejects_what_does_not_fit():
     import torch
     ws, _ = build_both("truncated", 8, depth=5)

@@ -6,7 +6,7 @@ import paper_2602_24066_amd as S
 from oracle import sig_oracle as O
 from sig_workloads import (WORKLOADS, make_grad_coeffs, make_path, random_prefix_closed_words, workload_path)
 from tests.gpu_common import (BWD_TOL, FWD_TOL, build_both, build_for_workload, check_parity, gpu_forward_backward,
-                              oracle_backward)
+                              oracle_backward, oracle_forward)
 
 pytestmark = pytest.mark.gpu
 
@@ -534,6 +534,80 @@ def test_time_chunks_of_truncations_with_lanes_as_words(d, depth, B, L, chunks, 
                            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
     torch.cuda.synchronize()
     assert float((c - whole).norm() / whole.norm()) <= 1e-5
+
+
+def nan_workspace(nbytes):
+    """A float32 tensor of nbytes, 256-byte aligned, every entry NaN."""
+    import torch
+    buf = torch.full((nbytes // 4 + 64,), float("nan"), device="cuda")
+    first = (-buf.data_ptr() % 256) // 4
+    return buf[first:first + nbytes // 4]
+
+
+@pytest.mark.parametrize("d,depth,B,L,chunks", [
+    (6, 5, 3, 21, 2),
+    (7, 3, 5, 64, 16),
+    (2, 4, 9, 40, 5),     # a small truncation
+    (12, 2, 3, 33, 4),    # depth 2: displacements
+    (9, 5, 1, 24, 3),     # scan and adjoints of 512 threads
+    (10, 5, 1, 17, 3),    # 10^4 words of full length in a slice: 1,024 threads
+    (24, 4, 1, 16, 2),    # 24^3, the largest slice but one: 14 words a thread, 61 KB of LDS
+])
+def test_time_chunk_kernels_write_their_workspace(d, depth, B, L, chunks, monkeypatch):
+    """The chunked calls of the word-per-lane truncations leave the chunk signatures (forward) and their products and
+    boundary adjoints (backward) in the workspace; nothing of it is missing, and the results are the oracle's."""
+    import torch
+    monkeypatch.setenv("SIG_LANES", "1")
+    ws, W = build_both("truncated", d, depth=depth)
+    ws.set_option("chunks", chunks)
+    X, G = make_path("iid", 471 + d, B, L, d), make_grad_coeffs(472 + d, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    lib = S.load_library()
+    Lc = -(-L // chunks)
+    C = -(-L // Lc)
+    work = nan_workspace(int(lib.sig_forward_workspace_bytes(ws._h, B, L + 1)))
+    c = S.sig_forward(ws, x, workspace=work)
+    torch.cuda.synchronize()
+    rows = work[:B * C * ws.size].reshape(B, C, ws.size)
+    ws.set_option("chunks", 1)
+    for k in range(C):
+        part = S.sig_forward(ws, x[:, k * Lc:min((k + 1) * Lc, L) + 1].contiguous())
+        assert float((rows[:, k] - part).norm() / part.norm()) <= 1e-5, k
+    ws.set_option("chunks", chunks)
+    low = int(ws.level_start[depth])
+    work = nan_workspace(int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1)))
+    gp = S.sig_backward(ws, x, c, g, workspace=work)
+    torch.cuda.synchronize()
+    at = 0
+    for n_rows in (C, C - 1, C - 1, C - 1):          # chunk signatures, products from the left, from the right, adjoints
+        assert torch.isfinite(work[at:at + B * n_rows * low]).all(), (n_rows, at)
+        at += -(-B * n_rows * low * 4 // 256) * 64
+    errs = O.level_errors(c.cpu().numpy(), oracle_forward(X, W, "truncated", depth), np.array([len(w) for w in W]))
+    assert max(errs.values()) <= FWD_TOL, errs
+    assert O.grad_errors(gp.cpu().numpy(), oracle_backward(X, W, "truncated", depth, G.astype(np.float64))).max() <= BWD_TOL
+
+
+def test_backward_with_the_workspace_of_whole_paths():
+    """sig_backward takes time chunks where the workspace holds them; with the size a call over whole paths asks for it
+    walks whole paths, leaves the workspace alone and agrees to rounding."""
+    import torch
+    d, depth, B, L = 9, 5, 1, 24
+    ws, W = build_both("truncated", d, depth=depth)
+    X, G = make_path("iid", 571, B, L, d), make_grad_coeffs(572, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    lib = S.load_library()
+    c = S.sig_forward(ws, x)
+    ws.set_option("chunks", 1)
+    whole = int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1))
+    ws.set_option("chunks", 3)
+    assert int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1)) > whole
+    work = nan_workspace(whole)
+    gp = S.sig_backward(ws, x, c, g, workspace=work)
+    torch.cuda.synchronize()
+    assert torch.isnan(work).all()
+    assert O.grad_errors(gp.cpu().numpy(), oracle_backward(X, W, "truncated", depth, G.astype(np.float64))).max() <= BWD_TOL
+    with pytest.raises(S.SigError):
+        S.sig_backward(ws, x, c, g, workspace=work[:whole // 4 - 64])
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])

@@ -599,11 +599,13 @@ sig::LanesShape lanes_shape_for(const sig::WordSet& w, int dir, int64_t B)
 // cannot cut it into time chunks.  Measured, step (forward + backward), lanes = paths -> lanes = words: 2 letters, depth 4:
 // 32 x 64 segments 44 -> 30 us, 512 x 500 190 -> 104, 1,024 x 100 58 -> 59, 1,500 x 200 92 -> 120; 3 letters, depth 3:
 // 512 x 500 218 -> 85, 1,024 x 100 65 -> 47; 12 letters, depth 2: 32 x 500 335 -> 41, 1,500 x 200 176 -> 108, 3,000 x 200
-// 212 -> 200.  So the line lies higher the fewer letters the chain of a lane has.  Words of four letters and more on
-// paths of up to 64 segments: lanes = paths from 64 paths on, which fill its wavefronts (the gain there, 51 -> 37 us at 32 x 64
-// segments of 3 letters, comes from the lanes that fewer paths leave empty).
-// `L`: segments; kAnyLength asks whether some length would run this way.  `chunks`: the call can take time chunks (windows and sig_backward_static cannot; beyond depth 3 their walk over whole
-// rows is no faster than lanes = paths).
+// 212 -> 200.  So the line lies higher the fewer letters the chain of a lane has.  Depth 5: 3 letters, 256 paths
+// x 256 segments 106 -> 67 us, 512 106 -> 132, 768 124 -> 164; 2 letters, 512 x 256 108 -> 89, 768 110 -> 124.  Words of four letters on paths of up to 64 segments stay with lanes = paths from 64 paths on.  That is not
+// where the times lie: lanes = words is the faster there too (3 letters, depth 4, 64 x 64 42 -> 25 us, 768 x 64 43 -> 31; 2 letters
+// 64 x 16 21 -> 12, 768 x 64 37 -> 30); a host test fixes the kernel of 64 paths of 64 segments.
+// `L`: segments; kAnyLength asks whether some length would run this way.  `chunks`: the call can take time chunks (windows and
+// sig_backward_static cannot; beyond depth 3 their walk over whole rows gains little over lanes = paths or loses: static
+// call, 2 letters, depth 4, 64 paths x 256 segments 67 and 63 us, 768 x 1,000 233 and 293).
 constexpr int64_t kAnyLength = INT64_MAX;
 bool use_lanes(const sig::WordSet& w, int64_t B, int64_t L, bool chunks = true, bool* small = nullptr)
 {
@@ -615,7 +617,7 @@ bool use_lanes(const sig::WordSet& w, int64_t B, int64_t L, bool chunks = true, 
     if (!s.ok || !sb.ok || B * std::max(s.waves, sb.waves) > (int64_t)0x7fffffff) return false;
     if (f == 1 || std::min(s.lanes, sb.lanes) >= 32) return true;
     if (!sig::lanes_chunks_available(w.d, w.depth) || (!chunks && w.depth > 3)) return false;
-    const bool few = B <= (w.depth == 2 ? 2048 : (w.depth == 3 ? 1024 : (L > 64 ? 768 : 63)));
+    const bool few = B <= (w.depth == 2 ? 2048 : (w.depth == 3 ? 1024 : (L <= 64 ? 63 : (w.depth == 4 ? 768 : (w.d == 2 ? 512 : 256)))));
     if (small) *small = few;
     return few;
 }

@@ -684,3 +684,14 @@ def test_kernel_selection_for_full_truncations(monkeypatch):
     monkeypatch.delenv("SIG_LANES")
     # batches beyond the row limit of the register-resident kernels take the run-time compiled ones
     assert ws46.kernel_name(False, 70000, 17) == "sig_fwd_lanes"
+
+
+@pytest.mark.parametrize("d,depth,B,lanes_are_words", [
+    (3, 5, 256, True), (3, 5, 257, False), (3, 5, 768, False),
+    (2, 5, 512, True), (2, 5, 513, False),
+    (2, 4, 768, True), (2, 4, 769, False), (3, 4, 768, True),
+])
+def test_batch_size_up_to_which_small_truncations_run_a_word_per_lane(d, depth, B, lanes_are_words):
+    ws = S.sig_wordset_build_truncated(d, depth)
+    for backward in (False, True):
+        assert ws.kernel_name(backward, B, 257) == ("sig_bwd" if backward else "sig_fwd") + ("_lanes" if lanes_are_words else "_jit")

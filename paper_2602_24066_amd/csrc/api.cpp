@@ -599,8 +599,9 @@ sig::LanesShape lanes_shape_for(const sig::WordSet& w, int dir, int64_t B)
 // cannot cut it into time chunks.  Measured, step (forward + backward), lanes = paths -> lanes = words: 2 letters, depth 4:
 // 32 x 64 segments 44 -> 30 us, 512 x 500 190 -> 104, 1,024 x 100 58 -> 59, 1,500 x 200 92 -> 120; 3 letters, depth 3:
 // 512 x 500 218 -> 85, 1,024 x 100 65 -> 47; 12 letters, depth 2: 32 x 500 335 -> 41, 1,500 x 200 176 -> 108, 3,000 x 200
-// 212 -> 200.  So the line lies higher the fewer letters the chain of a lane has.  Depth 5: 3 letters, 256 paths
-// x 256 segments 106 -> 67 us, 512 106 -> 132, 768 124 -> 164; 2 letters, 512 x 256 108 -> 89, 768 110 -> 124.  Words of four letters on paths of up to 64 segments stay with lanes = paths from 64 paths on.  That is not
+// 212 -> 200.  So the line lies higher the fewer letters the chain of a lane has.  Depth 5: 2 letters, 512 x 256
+// 108 -> 89 us, 768 x 256 110 -> 124; 3 letters, 768 x 256 124 -> 164 (with up to some 600 paths they have one level below the
+// lane's word, 81 lanes, and don't come here).  Words of four letters on paths of up to 64 segments stay with lanes = paths from 64 paths on.  That is not
 // where the times lie: lanes = words is the faster there too (3 letters, depth 4, 64 x 64 42 -> 25 us, 768 x 64 43 -> 31; 2 letters
 // 64 x 16 21 -> 12, 768 x 64 37 -> 30); a host test fixes the kernel of 64 paths of 64 segments.
 // `L`: segments; kAnyLength asks whether some length would run this way.  `chunks`: the call can take time chunks (windows and

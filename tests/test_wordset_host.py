@@ -687,7 +687,7 @@ def test_kernel_selection_for_full_truncations(monkeypatch):
 
 
 @pytest.mark.parametrize("d,depth,B,lanes_are_words", [
-    (3, 5, 256, True), (3, 5, 257, False), (3, 5, 768, False),
+    (3, 5, 512, True), (3, 5, 768, False),                          # 81 lanes and 27
     (2, 5, 512, True), (2, 5, 513, False),
     (2, 4, 768, True), (2, 4, 769, False), (3, 4, 768, True),
 ])

@@ -695,3 +695,15 @@ def test_batch_size_up_to_which_small_truncations_run_a_word_per_lane(d, depth, 
     ws = S.sig_wordset_build_truncated(d, depth)
     for backward in (False, True):
         assert ws.kernel_name(backward, B, 257) == ("sig_bwd" if backward else "sig_fwd") + ("_lanes" if lanes_are_words else "_jit")
+
+
+@pytest.mark.parametrize("d,depth,backward,B,kernels", [
+    (31, 2, True, 32, 1), (31, 2, False, 32, 1),     # a word per lane whatever the length, sig_backward_static included
+    (3, 4, False, 32, 1), (3, 4, False, 64, 2),      # from 64 paths on short paths take a path per lane
+    (3, 3, True, 32, 2),                             # sig_backward_static does
+])
+def test_small_truncations_compile_what_some_call_of_the_batch_size_runs(d, depth, backward, B, kernels, tmp_path, monkeypatch):
+    import os
+    monkeypatch.setenv("SIG_JIT_CACHE", str(tmp_path))
+    assert S.sig_wordset_build_truncated(d, depth).jit_prepare(backward, B) == 0
+    assert len(os.listdir(tmp_path)) == kernels

@@ -666,12 +666,12 @@ sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesSh
     sig::JitKernel* k = nullptr;
     {
         std::lock_guard<std::mutex> lock(g_jit_mutex);
-        sig::JitKernel*& slot = w.lanes[dir][s.R - 1];
+        sig::JitKernel*& slot = w.lanes[dir][dir == 1 && s.R == 1 && w.d == 2 && !s.msum ? 2 : s.R - 1];
         if (!slot) slot = new (std::nothrow) sig::JitKernel;
         k = slot;
     }
     if (!k) return nullptr;
-    // everything but the levels per lane follows from (d, depth, direction): one kernel per slot
+    // everything but the levels per lane and, for two letters, the form of the sums follows from (d, depth, direction)
     return bring_up(k, how, dir ? "sig_bwd_lanes" : "sig_fwd_lanes", [&](sig::JitKernel& kk) {
         kk.nw = s.nwb;
         kk.tile = s.T;

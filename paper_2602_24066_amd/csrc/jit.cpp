@@ -548,7 +548,7 @@ WordSet::~WordSet()
             delete e;
         }
     for (int dir = 0; dir < 2; ++dir)
-        for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < 3; ++r)
             if (lanes[dir][r]) {
                 jit_release(*lanes[dir][r]);
                 delete lanes[dir][r];

@@ -47,7 +47,7 @@ void jit_release(JitKernel& k);
 // it, `lanes` = d^(depth - R) of them per path in `waves` wavefronts, nwb wavefronts per workgroup, T segments per
 // gradient tile, TS segments of increments staged at a time.
 struct LanesShape {
-    bool ok;
+    bool ok, msum;                 // msum: gradient sums as matrix products
     int R, T, TS, nwb;
     int64_t lanes, waves;
     int chain;                     // multiply-adds of a lane's chain per segment

@@ -53,8 +53,7 @@ constexpr int count_wide()
 #define NU count_wide()
 
 static_assert(K >= 1 && (R == 1 || R == 2), "a lane holds a word of length N - R and one or two levels below it");
-// backward with the leaves alone below u: gradient sums over the lanes as matrix products (see there)
-#define MSUM (BACKWARD && R == 1 && D <= 16)
+// MSUM: backward with the leaves alone below u, gradient sums over the lanes as matrix products (see there)
 static_assert((MSUM || !BACKWARD || T * D <= 64) && TS % T == 0, "one lane per (letter, segment) of a tile; whole tiles per staging tile");
 
 __device__ __forceinline__ void wave_lds_fence()
@@ -130,6 +129,11 @@ struct Segment {
 // letters, depth 6: 34 against 30).
 #define LAZY (R == 2 && D * D + D > 48)
 #define GROUP (LAZY || TS % 2 ? 1 : (R == 1 && TS % 4 == 0 && DP + K * NC <= 32 ? 4 : 2))
+// Two letters and a chain of seven or more: the addresses of the 190 predicated reads that sum the short runs do not change
+// from tile to tile, and held in registers over the loop they cost half the speed, as do two segments or two row sums in flight
+// (100 segments, two wavefronts per SIMD: depth 9 446 -> 163 us, depth 10 553 -> 211, 12 823 -> 304).  So there they are formed
+// anew, and one thing is done after the other.
+#define ONE_BY_ONE (!MSUM && D == 2 && K >= 7)
 #define BGROUP (R == 2 || T % 2 ? 1 : (MSUM && DP + K * NC <= 32 ? 4 : 2))
 
 // Row r is part k = r % KW of path r / KW, read straight from the path: with win == nullptr time chunk k, max_len segments
@@ -432,7 +436,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
       for (int sub = TS / T - 1; sub >= 0; --sub) {          // tiles of T segments: the unit of the gradient sums
         const long n = ns * (TS / T) + sub;
         const int steps = MSUM && L - n * T < T ? (int)(L - n * T) : T;
-#pragma unroll (BGROUP == 1 ? 2 : 1)
+#pragma unroll (BGROUP == 1 && !ONE_BY_ONE ? 2 : 1)
         for (int t1 = (steps + BGROUP - 1) / BGROUP * BGROUP; t1 > 0; t1 -= BGROUP) {
           Segment xs[BGROUP];
 #pragma unroll
@@ -573,6 +577,17 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         wave_lds_fence();
         const int j = lane / T, t = lane % T;
         const long sg = n * T + t;
+#if ONE_BY_ONE
+        float acc = 0.0f;
+        if (lane < T * D) acc = row_sum(Vb + lane * 64, lane);
+#pragma unroll
+        for (int base = 0; base < 3 * NU * T; base += 64) {
+            const int o = base + lane;
+            if (o < 3 * NU * T) Wide[o] = row_sum(Vb + (D * T + o) * 64, lane);
+        }
+        int jr = j;
+        asm volatile("" : "+v"(jr));                           // keeps what follows from it inside the loop
+#else
         // rows of both kinds are summed together, from clamped addresses: their reads overlap
         float acc = row_sum(Vb + (lane < T * D ? lane : 0) * 64, lane);
 #pragma unroll
@@ -582,14 +597,18 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             const float sum = row_sum(Vb + (in ? D * T + o : 0) * 64, lane);
             if (in) Wide[o] = sum;                                        // rows of runs that do not reach here are not read below
         }
+        const int jr = j;
+#endif
         if (NU > 0) wave_lds_fence();
-        if (lane < T * D && sg < L) {
+        // (for two letters segments past the end are summed too: behind a condition that changes from tile to tile the reads took
+        // 78 registers more; depth 8, two wavefronts per SIMD 110 -> 96 us.  Three letters and more are faster with it.)
+        if (lane < T * D && ((D == 2 && !ONE_BY_ONE) || sg < L)) {
             // chain position k with runs of s < 32 lanes: the lanes whose k-th letter is j, s of them every s D
 #pragma unroll
             for (int k = NU + 1; k <= K; ++k) {
                 const int s = ipow(D, K - k), period = s * D;
                 const float* V = Vb + (chain_row(k) * T + t) * 64;
-                const int rs0 = (p0 / period) * period + j * s - p0;     // first run that can reach this wavefront
+                const int rs0 = (p0 / period) * period + jr * s - p0;     // first run that can reach this wavefront
 #pragma unroll
                 for (int r = 0; r < (64 + period - 1) / period + 1; ++r)
 #pragma unroll
@@ -908,7 +927,11 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         // tile; eight wavefronts of 20 KB fit a compute unit, so longer tiles are cut down to that.  The staging
         // tile is as many tiles as fit (up to 32 segments and three increments per lane): its global loads are issued
         // one staging tile ahead.
-        const bool msum = backward && R == 1 && d <= 16;       // gradient sums as matrix products, tiles of 16 segments
+        // gradient sums as matrix products, tiles of 16 segments: 4.4 KB of LDS for every source.  Two letters and depth 7 and
+        // more are then left with one wavefront per SIMD, so batches of more than that sum rows (depth 7, 100 segments: 1,024
+        // paths 57 us as products, 72 as rows; 2,048 111 and 85; 8,192 434 and 366)
+        const bool msum = backward && R == 1 && d <= 16 && !(d == 2 && K >= 6 && rounds > 1.0);
+        s.msum = msum;
         auto lds_bytes = [&](int T, int TS) {
             const size_t tile = (size_t)TS * ((size_t)d * NC + 2 * (size_t)DP);
             if (msum) return (tile + (size_t)(K + 1) * 16 * 68) * sizeof(float);
@@ -984,9 +1007,13 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         if (!backward) {
             latency = 0.0013 * s.chain;
             issue = 0.005 + (s.R == 1 ? 0.0019 : 0.0021) * s.per_lane;
-        } else if (s.R == 1 && d <= 16) {
+        } else if (s.msum) {
             latency = 0.0034 * s.chain;
             issue = 0.008 + 0.0039 * (6.0 * (depth - s.R + 1) + s.per_lane);
+        } else if (s.R == 1 && d == 2) {
+            latency = 0.59;                                  // sums by rows: the chip is full, more rows gain nothing
+            issue = 0.13;
+            if (C > 1) return 1.0e9;
         } else if (s.R == 1) {
             latency = 1.1;
             issue = 0.0002 * s.per_lane;
@@ -1037,8 +1064,8 @@ std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
     std::ostringstream o;
     auto lanes = [&](const char* ns, int n, const LanesShape& q, bool bwd, const char* forward_name) {
         o << "#define N " << n << "\n#define R " << q.R << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
-          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name << "\nnamespace " << ns << " {\n"
-          << kLanesSource << "}\n#undef N\n#undef R\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef FORWARD_NAME\n";
+          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name << "\nnamespace " << ns << " {\n"
+          << kLanesSource << "}\n#undef N\n#undef R\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n";
     };
     auto chunk = [&](const char* ns, LanesChunkPart part) {
         o << "#define N " << depth << "\n#define M " << (part == kLanesScanLow ? depth - 1 : depth)

@@ -127,9 +127,9 @@ struct WordSet {
         JitKernel* kernel = nullptr;
     };
     std::vector<JitEntry*> jit[2];
-    // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp); built on
-    // first use
-    JitKernel* lanes[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp), the third one level
+    // with sums by rows where that is one of two forms; built on first use
+    JitKernel* lanes[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
     // the last few decisions on their number of time chunks (each takes microseconds to model), and the batch sizes whose
     // kernels, for every number of chunks, have been brought up; both under the lock
     struct ChunkChoice { int64_t B = 0, L = 0; int dir = -1, levels = 0, C = 1; };

@@ -498,6 +498,25 @@ def test_truncations_with_lanes_as_words(d, depth, B, L, levels, monkeypatch):
     check_parity(ws, W, "truncated", depth, X, G, what=f"lanes = words, d={d} N={depth}, {levels} levels per lane")
 
 
+@pytest.mark.parametrize("depth,B,L,levels,msum", [
+    (7, 1024, 11, 0, 1),     # one wavefront per SIMD: matrix products
+    (7, 1025, 11, 0, 0),     # more: sums by rows
+    (8, 1300, 9, 0, 0),      # two levels per lane, a chain of six
+    (9, 520, 19, 0, 0),      # chains of seven and of ten: one segment after the other, three long runs
+    (12, 64, 5, 0, 0),
+    (8, 1030, 17, 1, 0),     # one level, a chain of seven
+])
+def test_two_letters_with_many_paths(depth, B, L, levels, msum):
+    """Backward of the truncations over two letters where their wavefronts fill the chip, against the oracle."""
+    ws, W = build_both("truncated", 2, depth=depth)
+    ws.set_option("lanes", 1)
+    ws.set_option("lanes_levels", levels)
+    ws.set_option("chunks", 1)
+    assert f"#define BACKWARD 1\n#define MSUM {msum}\n" in ws.jit_source(True, B)
+    check_parity(ws, W, "truncated", depth, make_path("iid", 671, B, L, 2), make_grad_coeffs(672, B, ws.size),
+                 sample=sorted({0, 1, B // 2, B - 2, B - 1}), what=f"two letters, depth {depth}, B={B}")
+
+
 @pytest.mark.parametrize("d,depth,B,L,chunks", [
     (6, 5, 3, 21, 2),     # ragged last chunk
     (10, 4, 1, 50, 7),    # chunks of 8 segments, the last of 2

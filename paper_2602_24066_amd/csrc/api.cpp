@@ -890,8 +890,8 @@ int sig_logsig_forward(const sig_wordset* ws, const float* coeffs, int64_t B, fl
     if (!coeffs || !logsig) return SIG_EINVAL;
     const unsigned char* base = (const unsigned char*)w.dev;
     hipError_t e = sig::logsig_forward(coeffs, B, w.size(), (const int32_t*)(base + w.lyn_len_off),
-                                       (const int32_t*)(base + w.lyn_sub_t_off), w.n_lyndon, w.depth, logsig,
-                                       (hipStream_t)stream);
+                                       (const int32_t*)(base + w.lyn_sub_off), (const int32_t*)(base + w.lyn_sub_t_off), w.n_lyndon,
+                                       w.lyn_stride, w.depth, logsig, (hipStream_t)stream);
     return e == hipSuccess ? SIG_OK : hip_fail(e);
 }
 

@@ -635,23 +635,29 @@ constexpr int kMaxLogDepth = 12;
 
 // DEPTH > 0: compile-time bound on the word length, all loops unrolled so that the small tables stay in registers;
 // DEPTH == 0: any length up to kMaxLogDepth (tables in scratch memory).
-template <int DEPTH>
+// BY_WORD: lyn_sub holds the places of a Lyndon word side by side, `stride` apart; otherwise those of a pair (i, j), n_lyn apart.
+template <int DEPTH, bool BY_WORD>
 __global__ void logsig_forward_kernel(const float* __restrict__ coeffs, int64_t B, int64_t nW, const int32_t* __restrict__ lyn_len,
-                                      const int32_t* __restrict__ lyn_sub_t, int64_t n_lyn, int depth, float* __restrict__ out)
+                                      const int32_t* __restrict__ lyn_sub, int64_t n_lyn, int stride, int depth, float* __restrict__ out)
 {
     constexpr int MD = DEPTH ? DEPTH : kMaxLogDepth;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= B * n_lyn) return;
     const int64_t b = idx / n_lyn, k = idx - b * n_lyn;
     const int n = lyn_len[k];
-    const int32_t* sub = lyn_sub_t + k;
+    const int32_t* sub = BY_WORD ? lyn_sub + k * stride : lyn_sub + k;
     const float* S = coeffs + b * nW;
-    // sw[i][j] = S(w[i:j]) for 0 <= i < j <= n
+    const int nl = (int)n_lyn;                            // the table has fewer than 2^31 entries
+    // sw[i][j] = S(w[i:j]) for 0 <= i < j <= n; `row` is the place of pair (i, i + 1)
     float sw[MD][MD + 1];
+    int row = 0;
 #pragma unroll
-    for (int i = 0; i < MD; ++i)
+    for (int i = 0; i < MD; ++i) {
 #pragma unroll
-        for (int j = 0; j <= MD; ++j) sw[i][j] = (i < j && j <= n) ? S[sub[(i * depth - i * (i - 1) / 2 + (j - i - 1)) * n_lyn]] : 0.0f;
+        for (int j = 0; j <= MD; ++j)
+            sw[i][j] = (i < j && j <= n) ? S[sub[BY_WORD ? i * (depth + 1) + j : row + (j - i - 1) * nl]] : 0.0f;
+        row += (depth - i) * nl;
+    }
     float Q[MD + 1], Qn[MD + 1];
 #pragma unroll
     for (int j = 0; j <= MD; ++j) Q[j] = j == 0 ? 0.0f : sw[0][j];                  // one piece: w[0:j]
@@ -788,11 +794,12 @@ __global__ __launch_bounds__(1024) void logsig_backward_sum_kernel(const float* 
     const int64_t b = blockIdx.x;
     for (int64_t u = threadIdx.x; u < nW; u += blockDim.x) S[u] = coeffs[b * nW + u];
     __syncthreads();
+    const int nl = (int)n_lyn;
     for (int64_t k = threadIdx.x; k < n_lyn; k += blockDim.x) {
         const int32_t* sub = lyn_sub_t + k;
         float* dst = part + k * n_pairs;
         logsig_word_adjoint<MD>(lyn_len[k], depth, glog[b * n_lyn + k],
-                                [&](int i, int j) { return S[sub[(i * depth - i * (i - 1) / 2 + (j - i - 1)) * n_lyn]]; },
+                                [&](int i, int j) { return S[sub[(i * depth - i * (i - 1) / 2 + (j - i - 1)) * nl]]; },
                                 [&](int, int, int pair, float v) { dst[pair] = v; });
     }
     __syncthreads();
@@ -839,14 +846,20 @@ __global__ __launch_bounds__(256) void logsig_gather_kernel(const float* __restr
     if (lane == 0) gcoeffs[idx] = acc;
 }
 
-hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int32_t* lyn_len, const int32_t* lyn_sub_t, int64_t n_lyn,
-                          int depth, float* out, hipStream_t stream)
+hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int32_t* lyn_len, const int32_t* lyn_sub,
+                          const int32_t* lyn_sub_t, int64_t n_lyn, int stride, int depth, float* out, hipStream_t stream)
 {
     const int64_t n = B * n_lyn;
     if (n <= 0) return hipSuccess;
     if (depth > kMaxLogDepth) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((n + 127) / 128);
-#define SIG_LOGSIG_FWD(DEPTH) logsig_forward_kernel<DEPTH><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub_t, n_lyn, depth, out)
+    // With one wavefront or so per SIMD the time is that of a lane's reads, in fewer instructions where they lie side by side; with
+    // more, that of the cache lines a wavefront touches, fewer where its lanes' do (3 letters, depth 4, by word and by pair: one
+    // path 2.2 and 2.5 us, 20,000 8.8 and 5.7; 4 letters, depth 5: 64 paths 3.4 and 3.6, 256 4.5 and 3.8).
+    const bool by_word = n < 65536;
+#define SIG_LOGSIG_FWD(DEPTH)                                                                                                       \
+    (by_word ? logsig_forward_kernel<DEPTH, true><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub, n_lyn, stride, depth, out) \
+             : logsig_forward_kernel<DEPTH, false><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub_t, n_lyn, stride, depth, out))
     if (depth <= 4) SIG_LOGSIG_FWD(4);
     else if (depth <= 6) SIG_LOGSIG_FWD(6);
     else if (depth <= 8) SIG_LOGSIG_FWD(8);
@@ -854,14 +867,20 @@ hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int3
 #undef SIG_LOGSIG_FWD
     return hipGetLastError();
 }
-// bytes of LDS the one-kernel form of the backward needs for a gradient row; 0 = the row does not fit
-// bytes of LDS for the form that keeps a path's coefficients and contributions there; 0 = they do not fit
-static size_t logsig_sum_lds_bytes(int64_t nW, int64_t n_lyn, int n_pairs, bool two_kernels)
+// Bytes of LDS for the form that keeps a path's coefficients and contributions there; 0 = they do not fit, or there are too few
+// Lyndon words for its 1,024 threads.  Measured, atomics -> lists: from 256 words on (385 words, 10 letters, depth 3: one path 5.7 ->
+// 4.5 us, 4,096 paths 68 -> 34; 406, 6 letters, depth 4: 8.0 -> 6.2, 102 -> 50), for pairs of letters, in lists of a few entries, from
+// 640 (300 words: 3.2 -> 4.2, 25 -> 32; 820: 5.4 -> 5.3, 64 -> 46); below (90 words, 4 letters, depth 4: 3.4 -> 4.8, 25 -> 32) the
+// atomics are faster.  Between, around 200 words of three and four letters and 500 pairs, the lists win where there are many paths
+// (205 words, 5 letters, depth 4: one path 4.9 -> 5.2, 1,024 14.5 -> 11.1; 496 pairs: 4.0 -> 4.3, 11.0 -> 10.0).
+static size_t logsig_sum_lds_bytes(int64_t B, int64_t nW, int64_t n_lyn, int n_pairs, int depth, bool two_kernels)
 {
-    if (two_kernels || n_lyn <= 0) return 0;
+    if (two_kernels || n_lyn < (depth > 2 ? 200 : 400)) return 0;
+    if (n_lyn < (depth > 2 ? 256 : 640) && (depth > 4 || B <= 512)) return 0;
     const int64_t n = (n_lyn * n_pairs + nW) * (int64_t)sizeof(float);
     return n <= 152 * 1024 ? (size_t)((n + 15) & ~(int64_t)15) : 0;
 }
+// bytes of LDS the form with atomics needs for a gradient row; 0 = the row does not fit
 static size_t logsig_row_lds_bytes(int64_t nW, bool two_kernels)
 {
     if (two_kernels) return 0;                                   // the tests force the two-kernel form
@@ -877,7 +896,7 @@ hipError_t logsig_backward(const float* coeffs, const float* glog, int64_t B, in
     const int64_t n = B * n_lyn;
     if (B <= 0) return hipSuccess;
     if (depth > kMaxLogDepth) return hipErrorInvalidValue;
-    if (const size_t lds = logsig_sum_lds_bytes(nW, n_lyn, n_pairs, two_kernels)) {
+    if (const size_t lds = logsig_sum_lds_bytes(B, nW, n_lyn, n_pairs, depth, two_kernels)) {
         if (B > 0x7fffffff) return hipErrorInvalidValue;
 #define SIG_LOGSIG_BWD_SUM(DEPTH)                                                                                              \
     do {                                                                                                                       \

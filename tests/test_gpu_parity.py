@@ -884,6 +884,40 @@ def test_log_signature_adjoint_forms_agree(d, depth, B):
     assert float((one.double() - two.double()).norm() / two.double().norm()) <= 2e-6
 
 
+@pytest.mark.parametrize("d,depth,B,n_lyndon", [
+    (4, 4, 3, 90),                          # few words: atomics
+    (5, 4, 512, 205), (5, 4, 513, 205),     # around 200: by the number of paths
+    (9, 3, 2, 285), (2, 10, 600, 226),
+    (20, 2, 4, 210), (31, 2, 512, 496), (31, 2, 513, 496), (36, 2, 2, 666),      # pairs of letters
+])
+def test_log_signature_adjoint_on_either_side_of_its_lines(d, depth, B, n_lyndon):
+    """The forms of the log-signature adjoint by the number of Lyndon words, against the form that gathers (the same terms in
+    another order)."""
+    import torch
+    ws = S.sig_wordset_build_logsig(d, depth).upload("cuda:0")
+    assert int(S.load_library().sig_wordset_n_lyndon(ws._h)) == n_lyndon
+    gen = torch.Generator(device="cuda").manual_seed(700 + 10 * d + depth)
+    c, g = torch.randn((B, ws.size), generator=gen, device="cuda"), torch.randn((B, n_lyndon), generator=gen, device="cuda")
+    one = S.sig_logsig_backward(ws, c, g)
+    ws.set_option("logsig_gather", 1)
+    two = S.sig_logsig_backward(ws, c, g)
+    torch.cuda.synchronize()
+    assert float((one.double() - two.double()).norm() / two.double().norm()) <= 2e-6
+
+
+@pytest.mark.parametrize("d,depth", [(4, 4), (3, 6), (2, 8), (2, 9), (5, 1)])
+def test_log_signature_tables_by_word_and_by_pair(d, depth):
+    """Few and many Lyndon words of a call read their places in another order (from 65,536 on): the same arithmetic."""
+    import torch
+    ws = S.sig_wordset_build_logsig(d, depth).upload("cuda:0")
+    n_lyn = int(S.load_library().sig_wordset_n_lyndon(ws._h))
+    B = -(-65536 // n_lyn)
+    c = torch.randn((B, ws.size), generator=torch.Generator(device="cuda").manual_seed(800 + d), device="cuda")
+    many = S.sig_logsig_forward(ws, c)
+    few = torch.cat([S.sig_logsig_forward(ws, c[:B // 2]), S.sig_logsig_forward(ws, c[B // 2:])])
+    assert torch.equal(many, few)
+
+
 @pytest.mark.parametrize("d,B,L", [
     (2, 65, 31), (2, 1, 33),        # tiles of 32 segments: one short, one with a second tile of one segment
     (7, 130, 9), (7, 64, 10),       # 63 of 64 floats of a tile row in use

@@ -273,11 +273,12 @@ int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 // letters do not (5,754 words, d = 6, 640 paths 220 and 257; 10,000, d = 10 314 and 364).  The count is rounded down to
 // four steps an octave, so that neighbouring batch sizes share a kernel.  The forward kernel adds nothing up and follows
 // only into units of up to twelve words (1,500 words, 512 paths: d = 10 55 -> 54 us, d = 20 77 -> 71; 6,000, d = 10 78 and 86).
-// Units go down to four words where 256 to 512 words and three or more path groups leave most of the chip empty (backward
-// calls of 256 segments: 384 words, d = 6, 300 paths 89 -> 79 us, 500, d = 4 104 -> 95, 400, d = 20, 256 paths 206 -> 197; at 640
-// paths, 120 workgroups of eight words each, 93 -> 96).  Not beyond: every column adds to the same gradients in no fixed order,
-// so small sets and one or two groups keep the few columns that let two runs agree to a few roundings (one column: bit for
-// bit), and large sets would compile twice as long (1,500 words: 15 -> 33 s for 7 %).
+// Units go down to four words where 128 to 512 words and three or more path groups leave most of the chip empty (calls of 256
+// segments, forward + backward: 150 words, d = 5, 256 paths 144 -> 136 us; 384, d = 6, 300 paths 124 -> 111; 500, d = 4 143 -> 133;
+// 400, d = 20, 256 paths 264 -> 248; at 640 paths, 120 workgroups of eight words each, no gain).  Not beyond: every column adds to the
+// same gradients in no fixed order, so fewer words and one or two groups keep the few columns that let two runs agree to a few
+// roundings (up to 39 words, one column: bit for bit; 150 words on 9 paths gained 6 % from ten columns and differed by twice as
+// much), and large sets would compile twice as long (1,500 words: 15 -> 33 s for 7 %).
 int64_t jit_units(const sig::WordSet& w, int dir, int64_t B)
 {
     const int kJitWaves = jit_wg_waves(w);
@@ -298,7 +299,7 @@ int64_t jit_units(const sig::WordSet& w, int dir, int64_t B)
             const double lone = 250.0 + 25.0 * d + 9.5 * unit;
             const double two = std::max(430.0 + 13.4 * unit2, (double)(c * groups) * d * 256.0 / 1150.0);
             if (1.05 * lone < two && (dir == 1 || unit <= 12.0)) c = one;
-        } else if (w.size() >= 256 && w.size() <= 512 && groups >= 3 && c * groups <= 100) {
+        } else if (w.size() >= 128 && w.size() <= 512 && groups >= 3 && c * groups <= 100) {
             c = columns(4);
         }
     }

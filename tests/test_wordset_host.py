@@ -311,11 +311,12 @@ def test_balanced_plans_are_balanced():
 
 @pytest.mark.parametrize("d,n_words,B,columns", [
     (4, 36, 9, 1), (4, 36, 300, 1), (4, 39, 1024, 1),        # one column: a single addition per gradient, bit for bit
-    (5, 150, 9, 5), (5, 150, 300, 5),                         # units of eight words
+    (5, 150, 9, 5), (5, 150, 128, 5), (5, 127, 300, 4),       # units of eight words: one or two path groups, few words
+    (5, 150, 129, 10), (5, 150, 300, 10),                     # of four
     (6, 384, 64, 12), (6, 384, 128, 12),                      # one and two path groups
     (6, 384, 129, 24), (6, 384, 300, 24), (6, 384, 512, 24),  # units of four words fill more of the chip
     (6, 384, 640, 12),
-    (6, 255, 300, 8), (6, 513, 192, 16),
+    (6, 255, 300, 16), (6, 513, 192, 16),
     (10, 1500, 64, 47), (10, 1500, 128, 47),
 ])
 def test_columns_of_small_launches(d, n_words, B, columns):

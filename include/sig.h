@@ -129,7 +129,7 @@ int64_t        sig_wordset_term_tables(const sig_wordset* ws, const uint32_t** p
  *   "lanes"         [SIG_LANES]          word-per-lane kernels for full truncations: -1 auto, 0 off, 1 wherever defined
  *   "lanes_levels"  [SIG_LANES_LEVELS]   levels below the lane's word: 0 auto, 1, 2
  *   "logsig_gather" [SIG_LOGSIG_GATHER]  1: two-kernel form of sig_logsig_backward
- *   "jit_wg_waves"  [SIG_JIT_WG_WAVES]   wavefronts per workgroup of the specialised kernels, 1..4 (default 4)
+ *   "jit_wg_waves"  [SIG_JIT_WG_WAVES]   wavefronts per workgroup of the specialised kernels, 1..4 or 8 (default 4)
  *   "bwd_tile"      [SIG_BWD_TILE]       LDS tile of the backward kernels, 0 = launcher's rule.  d = 8: 4, 8 or 16 segments;
  *                                        d = 16: 8, 12 or 16 segments, or 4 = 16 segments with the gradient sources
  *                                        summed every 4 (the form that fits two workgroups on a compute unit)
@@ -281,8 +281,8 @@ int    sig_backward_checkpointed(const sig_wordset* ws, const float* path, const
  * (gradient with respect to the increments, transposed increments, chunk arrays) live in a static device array of
  * SIG_STATIC_SCRATCH_BYTES that each GPU the library runs on holds until the process ends.  The call allocates nothing
  * and frees nothing; it only enqueues kernels on `stream` (what must start at zero is cleared by a kernel first).
- * Errors beyond those of sig_backward: SIG_ETOOLARGE when sig_backward_workspace_bytes(ws, B, n_points) exceeds
- * SIG_STATIC_SCRATCH_BYTES; SIG_ENOTREADY when the word set runs through a run-time compiled kernel that this process
+ * Errors beyond those of sig_backward: SIG_ETOOLARGE when what sig_backward needs over whole paths (its workspace without
+ * time chunks of its own) exceeds SIG_STATIC_SCRATCH_BYTES; SIG_ENOTREADY when the word set runs through a run-time compiled kernel that this process
  * has not loaded yet (loading a code object allocates): one sig_backward call of the same batch size loads it.
  * All calls on one GPU share that GPU's array: calls that overlap in time on the same device (different streams or
  * host threads) race; calls on one stream are ordered and safe. */

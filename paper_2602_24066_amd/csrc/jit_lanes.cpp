@@ -556,10 +556,10 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         sum[0] += sum[1];
         // The indicators multiply every lane's value, so a NaN or an infinity from one word would reach all letters.  It shows
         // in the sums; they are then formed anew from the values of each letter's own lanes.
-        bool finite = true;
+        float zero = 0.0f;                                     // NaN as soon as one of the four is not finite
 #pragma unroll
-        for (int r = 0; r < 4; ++r) finite &= sg >= L || __builtin_fabsf(sum[0][r]) <= 3.402823466e38f;
-        if (__builtin_amdgcn_ballot_w64(!finite) != 0) letter_sums(Vb + col * VROW, gr + level_start(N), p0, grp * 4, sum[0]);
+        for (int r = 0; r < 4; ++r) zero = __builtin_fmaf(sum[0][r], 0.0f, zero);
+        if (__builtin_amdgcn_ballot_w64(sg < L && !(zero == 0.0f)) != 0) letter_sums(Vb + col * VROW, gr + level_start(N), p0, grp * 4, sum[0]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float acc = sg < L ? sum[0][r] : 0.0f;

@@ -51,6 +51,7 @@ void options_from_environment(sig::WordSet& w)
         const char* e = std::getenv(o.env);
         if (e && e[0]) w.opt.*(o.field) = std::atoi(e);
     }
+    if (w.closure) w.closure->opt = w.opt;
 }
 int finish_build(int rc, sig::WordSet* w, sig_wordset** out)
 {
@@ -448,11 +449,12 @@ dim3 jit_grid(const sig::JitKernel& k, const sig::Plan& p, int64_t B)
     const unsigned gy = (unsigned)((B + 63) / 64);
     return gy % 8 == 0 ? dim3(gx * gy, 1, 1) : dim3(gx, gy, 1);
 }
-hipError_t launch_jit_forward(sig::JitKernel& k, const sig::Plan& p, const float* dxT, int64_t B, int64_t ntiles, float* coeffs,
+// L segments of a row, Lpad of them in dxT (whole tiles of the kernel fit)
+hipError_t launch_jit_forward(sig::JitKernel& k, const sig::Plan& p, const float* dxT, int64_t B, int64_t L, int64_t Lpad, float* coeffs,
                               int64_t nW, hipStream_t st)
 {
-    long lB = (long)B, lT = (long)ntiles, lW = (long)nW;
-    void* args[] = {(void*)&dxT, (void*)&lB, (void*)&lT, (void*)&coeffs, (void*)&lW};
+    long lB = (long)B, lT = (long)((L + k.tile - 1) / k.tile), lW = (long)nW, lP = (long)Lpad;
+    void* args[] = {(void*)&dxT, (void*)&lB, (void*)&lT, (void*)&coeffs, (void*)&lW, (void*)&lP};
     const dim3 grid = jit_grid(k, p, B);
     return hipModuleLaunchKernel(k.fn, grid.x, grid.y, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
 }
@@ -460,13 +462,13 @@ hipError_t launch_jit_forward(sig::JitKernel& k, const sig::Plan& p, const float
 // B rows; with C > 1 they are the C time chunks of B / C paths, whose last chunks read row (path) of coeffs_last and
 // grad_last and the others row (path * C + chunk) of coeffs and grad.  C = 1: coeffs and grad hold a row per path.
 hipError_t launch_jit_backward(sig::JitKernel& k, const sig::Plan& p, const float* dxT, const float* coeffs, const float* grad,
-                               int64_t B, int64_t L, int64_t ntiles, int64_t nW, float* gdx, hipStream_t st,
+                               int64_t B, int64_t L, int64_t Lpad, int64_t nW, float* gdx, hipStream_t st,
                                const float* coeffs_last = nullptr, const float* grad_last = nullptr, int64_t C = 1)
 {
-    long lB = (long)B, lL = (long)L, lT = (long)ntiles, lW = (long)nW, lC = (long)C;
+    long lB = (long)B, lL = (long)L, lT = (long)((L + k.tile - 1) / k.tile), lW = (long)nW, lC = (long)C, lP = (long)Lpad;
     if (C <= 1) { coeffs_last = coeffs; grad_last = grad; lC = 1; }
     void* args[] = {(void*)&dxT, (void*)&coeffs, (void*)&grad, (void*)&lB, (void*)&lL, (void*)&lT, (void*)&lW, (void*)&gdx,
-                    (void*)&coeffs_last, (void*)&grad_last, (void*)&lC};
+                    (void*)&coeffs_last, (void*)&grad_last, (void*)&lC, (void*)&lP};
     const dim3 grid = jit_grid(k, p, B);
     return hipModuleLaunchKernel(k.fn, grid.x, grid.y, 1, (unsigned)k.nw * 64, 1, 1, 0, st, args, nullptr);
 }
@@ -489,6 +491,27 @@ sig::WordTables word_tables(const sig::WordSet& w)
     t.N = w.max_len;
     t.W = (int)w.size();
     return t;
+}
+// the tables of the closure of a set that lacks suffixes, with its words and terms marked
+sig::WordTables closure_tables(const sig::WordSet& w)
+{
+    sig::WordTables t = word_tables(*w.closure);
+    const unsigned char* base = (const unsigned char*)w.dev;
+    t.prod_pairs = (const uint32_t*)(base + w.dev_closure_prod_off);
+    t.adj_pairs = (const uint32_t*)(base + w.dev_closure_adj_pairs_off);
+    t.adj_key = (const uint32_t*)(base + w.dev_closure_adj_key_off);
+    t.adj_groups = (int)(w.closure_adj_pairs.size() / 256);
+    t.own = (const int32_t*)(base + w.dev_closure_own_off);
+    t.W_own = (int)w.size();
+    return t;
+}
+// products of the chunk signatures: from the left into rows and last, from the right into rows_reverse, as far as given
+hipError_t words_products(const sig::WordTables& t, const float* S, int64_t B, int64_t C, float* rows, float* last, float* rows_reverse,
+                          hipStream_t st)
+{
+    if (sig::words_scan_small_available(t)) return sig::words_scan_small(t, S, B, (int)C, rows, last, rows_reverse, st);
+    if (rows_reverse) return sig::words_scan_both(t, S, B, (int)C, rows, rows_reverse, st);
+    return sig::words_scan(t, S, B, (int)C, false, rows, last, st);
 }
 // Both kernels for B * C rows, compiled and loaded, or false: then the checkpointed calls run as the plain ones (the
 // outcome of a compilation is remembered, so the forward and the backward call of a pair decide alike).
@@ -517,9 +540,9 @@ hipError_t words_forward_chunked(const sig::WordSet& w, const float* path, int64
     if (e != hipSuccess) return e;
     hipEvent_t* pe = g_prof.next(0);
     if (pe) (void)hipEventRecord(pe[0], st);
-    e = launch_jit_forward(fk, fp, dxT, B * ch.C, Lpad / fk.tile, Sc, w.size(), st);
+    e = launch_jit_forward(fk, fp, dxT, B * ch.C, ch.Lc, Lpad, Sc, w.size(), st);
     if (pe) (void)hipEventRecord(pe[1], st);
-    if (e == hipSuccess && coeffs) e = sig::words_scan(word_tables(w), Sc, B, (int)ch.C, false, nullptr, coeffs, st);
+    if (e == hipSuccess && coeffs) e = words_products(word_tables(w), Sc, B, ch.C, nullptr, coeffs, nullptr, st);
     return e;
 }
 size_t words_backward_ckpt_workspace(const sig::WordSet& w, int64_t B, const Chunks& ch)
@@ -552,7 +575,7 @@ hipError_t words_backward_chunked(const sig::WordSet& w, const float* path, cons
         if (e == hipSuccess) e = sig::words_adjoint(tab, grad_coeffs, Sc + w.size(), B, 2, Abar, grad_path, n_gp, st);
     } else {
         float* P = (float*)((unsigned char*)workspace + 2 * t_bytes + nb);
-        if (e == hipSuccess) e = sig::words_scan_both(tab, Sc, B, (int)ch.C, P, Abar, st);
+        if (e == hipSuccess) e = words_products(tab, Sc, B, ch.C, P, nullptr, Abar, st);
         if (e == hipSuccess) e = sig::words_adjoint(tab, grad_coeffs, Abar, B, (int)ch.C, Abar, grad_path, n_gp, st);   // in place, row by row
         Pfx = P;
     }
@@ -560,7 +583,7 @@ hipError_t words_backward_chunked(const sig::WordSet& w, const float* path, cons
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
     // the rows of the last chunk are the caller's terminal signature and gradient themselves
-    e = launch_jit_backward(bk, bp, dxT, Pfx, Abar, B * ch.C, ch.Lc, Lpad / bk.tile, w.size(), gdx, st, coeffs, grad_coeffs, ch.C);
+    e = launch_jit_backward(bk, bp, dxT, Pfx, Abar, B * ch.C, ch.Lc, Lpad, w.size(), gdx, st, coeffs, grad_coeffs, ch.C);
     if (pe) (void)hipEventRecord(pe[1], st);
     if (e != hipSuccess) return e;
     return sig::grad_points_transposed(gdx, B, n_points, w.d, Lpad, grad_path, st, rows);
@@ -577,6 +600,161 @@ size_t words_backward_recompute_first(const sig::WordSet& w, int64_t B, const Ch
 size_t words_backward_recompute_workspace(const sig::WordSet& w, int64_t B, const Chunks& ch)
 {
     return words_backward_recompute_first(w, B, ch) + chunk_array_bytes(w, B, ch.C);
+}
+
+// ---- time chunks of sig_forward and sig_backward on small launches ---------------------------------------------------
+// A specialised kernel takes 0.08-0.16 us per segment forward and 0.2-0.45 backward however few paths there are, so where the
+// wavefronts of whole paths fill at most three quarters of the SIMDs the plain calls cut every path into chunks, for sets that
+// lack suffixes as well: the chunk signatures are then those of the closure, and the backward rows run over the set itself.
+// Which kernels that takes follows from the batch size alone: they are planned for plain_rows(B).
+const sig::WordSet& chunk_set(const sig::WordSet& w) { return w.closure ? *w.closure : w; }
+sig::WordTables chunk_tables(const sig::WordSet& w) { return w.closure ? closure_tables(w) : word_tables(w); }
+int64_t plain_rows(int64_t B) { return std::min<int64_t>(std::max<int64_t>(2048, B), 8 * B); }
+bool plain_chunks_available(const sig::WordSet& w, int64_t B)
+{
+    if (w.kind == 0 || B < 1 || !jit_enabled(w) || !(w.closure || w.pair_tables)) return false;
+    const sig::WordSet& c = chunk_set(w);
+    if (c.size() > 4096 || c.max_len > 8) return false;
+    return jit_units(w, 1, B) * ((B + 63) / 64) <= 768;
+}
+// Modelled time in microseconds of a call (kForward, kBackward, which runs the chunks' forward pass again, kBackwardKept, which
+// finds their signatures in a checkpoint) with C chunks, fitted to a scan of ten sets (36 to 432 words, closures up to 1,195, 4 to 9
+// letters, 22 to 300 paths of 66 to 819 segments, counts up to 32): a segment's latency by letters and words of a unit, as often
+// as the wavefronts fill the SIMDs; a product per chunk, by words of the closure and paths; the launches.
+enum PlainCall { kForward, kBackward, kBackwardKept };
+double plain_time(const sig::WordSet& w, PlainCall call, int64_t B, int64_t L, int64_t C)
+{
+    const sig::WordSet& c = chunk_set(w);
+    const double d = (double)w.d, words = (double)c.size(), own = (double)w.size(), paths = (double)B;
+    const int64_t R = C > 1 ? plain_rows(B) : B;
+    const double units = (double)jit_units(w, call == kForward ? 0 : 1, R);
+    const double seg_b = 0.05 + 0.04 * d + 0.0095 * std::max(0.0, own / units - 8.0);
+    auto forward = [&](double per_unit) { return 0.05 + 0.008 * d + 0.003 * std::max(0.0, per_unit - 8.0); };
+    if (C == 1) return (double)L * (call == kForward ? forward(own / units) : seg_b);
+    const double Lc = (double)((L + C - 1) / C), groups = (double)((B * C + 63) / 64), uf = (double)jit_units(c, 0, R);
+    double t = call == kBackwardKept ? 0.0 : Lc * forward(words / uf) * std::max(1.0, groups * uf / 2048.0);
+    if (call == kForward) return t + 5.5 + (double)C * (0.3 + 0.0005 * words + 0.0006 * paths + 2.0e-6 * paths * words);
+    t += Lc * seg_b * std::max(1.0, groups * units / 1024.0) + (double)C * (0.4 + 0.001 * words + 0.0024 * paths + 1.0e-5 * paths * words);
+    return t + (call == kBackwardKept ? 10.0 : 15.0);
+}
+// The count with the shortest modelled time.  Forward + backward, whole paths -> at the choice, us: 226 words, d = 9, 22 paths x
+// 819 segments 534 -> 87; 432, d = 8, 46 x 526 319 -> 99; 384 (lead-lag, d = 6), 300 x 256 111 -> 82; 36 (lead-lag), 39 x 388
+// 130 -> 52; 240, d = 11, 258 x 969 615 -> 221; 209 (anisotropic), 101 x 322 148 -> 62.
+int plain_chunk_count(const sig::WordSet& w, PlainCall call, int64_t B, int64_t L)
+{
+    double best = 0.93 * plain_time(w, call, B, L, 1);
+    int choice = 1;
+    for (int C : sig::kLanesChunkCounts) {
+        if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments
+        const double t = plain_time(w, call, B, L, C);
+        if (t < best) {
+            best = t;
+            choice = C;
+        }
+    }
+    return choice;
+}
+Chunks plain_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points)
+{
+    const int64_t L = n_points - 1;
+    int64_t C = 1;
+    if (plain_chunks_available(w, B)) {
+        if (w.opt.chunks > 0) {
+            C = std::min<int64_t>(std::min<int64_t>(w.opt.chunks, 64), L / 4);        // tuning knob
+        } else {
+            C = plain_chunk_count(w, dir ? kBackward : kForward, B, L);
+        }
+        if (B * C > (int64_t)65535 * 64) C = 1;
+    }
+    if (C < 2) return Chunks{1, L};
+    const int64_t Lc = (L + C - 1) / C;
+    return Chunks{(L + Lc - 1) / Lc, Lc};
+}
+int64_t plain_lpad(const sig::WordSet& w, const Chunks& ch)    // one transposed copy serves both directions
+{
+    return std::max(jit_lpad(w, ch.Lc + 1, 0), jit_lpad(w, ch.Lc + 1, 1));
+}
+size_t plain_dxt_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return ((size_t)((B * ch.C + 63) / 64) * (size_t)plain_lpad(w, ch) * (size_t)w.d * 64 * sizeof(float) + 255) & ~(size_t)255;
+}
+size_t plain_forward_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return plain_dxt_bytes(w, B, ch) + chunk_array_bytes(chunk_set(w), B, ch.C);
+}
+// increment gradients | increments | chunk signatures | products from the left | from the right | boundary adjoints (without a
+// closure in place of the products from the right)
+size_t plain_backward_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return 2 * plain_dxt_bytes(w, B, ch) + 2 * chunk_array_bytes(chunk_set(w), B, ch.C) + (w.closure ? 2 : 1) * chunk_array_bytes(w, B, ch.C);
+}
+struct PlainKernels {
+    sig::JitKernel *chunk = nullptr, *rows = nullptr;      // signatures of the chunks; backward: the rows
+    const sig::Plan *chunk_plan = nullptr, *rows_plan = nullptr;
+};
+bool plain_kernels(const sig::WordSet& w, int dir, int64_t B, Build how, PlainKernels& k)
+{
+    k.chunk = ensure_jit(chunk_set(w), 0, plain_rows(B), how, &k.chunk_plan);
+    k.rows = k.chunk && dir ? ensure_jit(w, 1, plain_rows(B), how, &k.rows_plan) : nullptr;
+    return k.chunk && (dir == 0 || k.rows);
+}
+// The kernels of a chunked call.  A call that takes chunks loads those of whole paths as well, for calls of the batch size that
+// don't (other lengths, sig_backward_static); under graph capture, where nothing can be loaded, kernels that no call has brought
+// up yet mean whole paths.
+bool plain_kernels_for(const sig::WordSet& w, int dir, int64_t B, Build how, hipStream_t st, PlainKernels& k)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (how == Build::compile_and_load && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+        how = Build::loaded_only;
+    return ensure_jit(w, dir, B, how) && plain_kernels(w, dir, B, how, k);
+}
+hipError_t plain_forward_chunked(const sig::WordSet& w, const PlainKernels& k, const float* path, int64_t B, int64_t n_points,
+                                 const Chunks& ch, float* coeffs, void* workspace, hipStream_t st)
+{
+    const sig::WordSet& c = chunk_set(w);
+    sig::WindowList rows;
+    rows.K = ch.C; rows.max_len = ch.Lc;
+    float* dxT = (float*)workspace;
+    float* Sc = (float*)((unsigned char*)workspace + plain_dxt_bytes(w, B, ch));
+    const int64_t Lpad = plain_lpad(w, ch);
+    hipError_t e = sig::increments_transposed(path, B, n_points, w.d, Lpad, dxT, nullptr, st, rows);
+    if (e != hipSuccess) return e;
+    hipEvent_t* pe = g_prof.next(0);
+    if (pe) (void)hipEventRecord(pe[0], st);
+    e = launch_jit_forward(*k.chunk, *k.chunk_plan, dxT, B * ch.C, ch.Lc, Lpad, Sc, c.size(), st);
+    if (pe) (void)hipEventRecord(pe[1], st);
+    if (e != hipSuccess) return e;
+    return words_products(chunk_tables(w), Sc, B, ch.C, nullptr, coeffs, nullptr, st);
+}
+hipError_t plain_backward_chunked(const sig::WordSet& w, const PlainKernels& k, const float* path, const float* coeffs,
+                                  const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, float* grad_path,
+                                  void* workspace, hipStream_t st)
+{
+    const sig::WordSet& c = chunk_set(w);
+    const sig::WordTables tab = chunk_tables(w);
+    sig::WindowList rows;
+    rows.K = ch.C; rows.max_len = ch.Lc;
+    const size_t t = plain_dxt_bytes(w, B, ch), nc = chunk_array_bytes(c, B, ch.C), nw = chunk_array_bytes(w, B, ch.C);
+    unsigned char* base = (unsigned char*)workspace;
+    float* gdx = (float*)base;
+    float* dxT = (float*)(base + t);
+    float* Sc = (float*)(base + 2 * t);
+    float* left = (float*)(base + 2 * t + nc);
+    float* right = (float*)(base + 2 * t + nc + nw);
+    float* Abar = w.closure ? (float*)(base + 2 * t + 2 * nc + nw) : right;
+    const int64_t Lpad = plain_lpad(w, ch);
+    hipError_t e = sig::increments_transposed(path, B, n_points, w.d, Lpad, dxT, gdx, st, rows);
+    if (e == hipSuccess) e = launch_jit_forward(*k.chunk, *k.chunk_plan, dxT, B * ch.C, ch.Lc, Lpad, Sc, c.size(), st);
+    if (e == hipSuccess) e = words_products(tab, Sc, B, ch.C, left, nullptr, right, st);
+    // rows of one path share the points between their chunks: the chain rule adds into grad_path, cleared here
+    if (e == hipSuccess) e = sig::words_adjoint(tab, grad_coeffs, right, B, (int)ch.C, Abar, grad_path, B * n_points * w.d, st);
+    if (e != hipSuccess) return e;
+    hipEvent_t* pe = g_prof.next(1);
+    if (pe) (void)hipEventRecord(pe[0], st);
+    e = launch_jit_backward(*k.rows, *k.rows_plan, dxT, left, Abar, B * ch.C, ch.Lc, Lpad, w.size(), gdx, st, coeffs, grad_coeffs, ch.C);
+    if (pe) (void)hipEventRecord(pe[1], st);
+    if (e != hipSuccess) return e;
+    return sig::grad_points_transposed(gdx, B, n_points, w.d, Lpad, grad_path, st, rows);
 }
 
 // ---- full truncations without a register-resident kernel of their own: lanes = words -----------------------
@@ -861,6 +1039,7 @@ int sig_wordset_set_option(sig_wordset* ws, const char* name, int value)
     for (const OptionName& o : kOptions)
         if (std::strcmp(o.name, name) == 0) {
             ws->opt.*(o.field) = value;
+            if (ws->closure) ws->closure->opt = ws->opt;
             std::lock_guard<std::mutex> lock(ws->lanes_memo.m);
             ws->lanes_memo.loaded.clear();                  // the kernels a batch size needs may be others now
             return SIG_OK;
@@ -1088,7 +1267,10 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
         const Chunks ch = lanes_chunks(w, 0, B, n_points);
         if (ch.C > 1) n = std::max(n, chunk_array_bytes(w, B, ch.C));
     }
-    if (w.kind != 0) {
+    if (plain_chunks_available(w, B)) {
+        const Chunks ch = plain_chunks(w, 0, B, n_points);
+        if (ch.C > 1) n = std::max(n, plain_forward_bytes(w, B, ch));
+    } else if (w.kind != 0) {
         // sets closed under suffixes: time chunks as in the checkpointed calls, the chunk signatures in the workspace
         const Chunks ch = checkpoint_chunks(w, B, n_points);
         if (ch.C >= 2) n = std::max(n, words_forward_ckpt_workspace(w, B, ch) + chunk_array_bytes(w, B, ch.C));
@@ -1123,7 +1305,10 @@ size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_
         const Chunks ch = lanes_chunks(w, 1, B, n_points);
         if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, ch));
     }
-    if (w.kind != 0 && jit_enabled(w)) {
+    if (plain_chunks_available(w, B)) {
+        const Chunks ch = plain_chunks(w, 1, B, n_points);
+        if (ch.C > 1) n = std::max(n, plain_backward_bytes(w, B, ch));
+    } else if (w.kind != 0 && jit_enabled(w)) {
         const Chunks ch = checkpoint_chunks(w, B, n_points);
         if (words_backward_recomputes(w, ch)) n = std::max(n, words_backward_recompute_workspace(w, B, ch));
     }
@@ -1208,7 +1393,19 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
     }
-    if (w.kind != 0 && word_chunks) {
+    const bool small_launch = plain_chunks_available(w, B);
+    if (small_launch && word_chunks) {
+        // (a smaller workspace gets the walk over whole paths, unless the set's own chunks have always been asked for)
+        const Chunks ch = plain_chunks(w, 0, B, n_points);
+        const bool fits = workspace && workspace_bytes >= sig_forward_workspace_bytes(ws, B, n_points);
+        if (!fits && checkpoint_chunks(w, B, n_points).C >= 2) return SIG_EWORKSPACE;
+        PlainKernels k;
+        if (ch.C > 1 && fits && plain_kernels_for(w, 0, B, Build::compile_and_load, st, k)) {
+            if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
+            hipError_t e = plain_forward_chunked(w, k, path, B, n_points, ch, coeffs, workspace, st);
+            return e == hipSuccess ? SIG_OK : hip_fail(e);
+        }
+    } else if (w.kind != 0 && word_chunks) {
         // sets closed under suffixes: the time chunks of the checkpointed calls, with the chunk signatures in the workspace
         const Chunks ch = checkpoint_chunks(w, B, n_points);
         const sig::Plan* cp = nullptr;
@@ -1232,7 +1429,7 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
         if (e != hipSuccess) return hip_fail(e);
         hipEvent_t* pe = g_prof.next(0);
         if (pe) (void)hipEventRecord(pe[0], st);
-        e = launch_jit_forward(*jk, *jp, dxT, B, Lpad / jk->tile, coeffs, w.size(), st);
+        e = launch_jit_forward(*jk, *jp, dxT, B, n_points - 1, Lpad, coeffs, w.size(), st);
         if (pe) (void)hipEventRecord(pe[1], st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
@@ -1327,8 +1524,10 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     bool small_set = false;
     const bool lanes_path = !use_trunc_backward(w, B) && use_lanes(w, B, n_points - 1, true, &small_set) &&
                             !(small_set && w.depth > 2 && how == Build::loaded_only);
-    const size_t need = word_chunks && !lanes_path ? sig_backward_workspace_bytes(ws, B, n_points)
-                                                   : backward_workspace(ws, B, n_points, false);
+    // the same holds for the chunks of small launches, except where a suffix-closed set has always asked for its chunks
+    const bool small_launch = plain_chunks_available(w, B);
+    const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points)));
+    const size_t need = word_chunks && !optional ? sig_backward_workspace_bytes(ws, B, n_points) : backward_workspace(ws, B, n_points, false);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;
@@ -1343,7 +1542,14 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
             return le == hipSuccess ? SIG_OK : hip_fail(le);
         }
     }
-    if (word_chunks && w.kind != 0 && jit_enabled(w) && !residual) {
+    if (small_launch && word_chunks && !residual) {
+        const Chunks pc = plain_chunks(w, 1, B, n_points);
+        PlainKernels k;
+        if (pc.C > 1 && workspace_bytes >= plain_backward_bytes(w, B, pc) && plain_kernels_for(w, 1, B, how, st, k)) {
+            hipError_t ce = plain_backward_chunked(w, k, path, coeffs, grad_coeffs, B, n_points, pc, grad_path, workspace, st);
+            return ce == hipSuccess ? SIG_OK : hip_fail(ce);
+        }
+    } else if (word_chunks && w.kind != 0 && jit_enabled(w) && !residual) {
         // suffix-closed set, few long paths: chunk signatures recomputed, then the route of the checkpointed call
         const Chunks wc = checkpoint_chunks(w, B, n_points);
         sig::JitKernel *fk, *bk;
@@ -1442,8 +1648,7 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         if (e != hipSuccess) return hip_fail(e);
         hipEvent_t* pe = g_prof.next(1);
         if (pe) (void)hipEventRecord(pe[0], st);
-        e = launch_jit_backward(*jk, *jp, dxT, coeffs, grad_coeffs, B, n_points - 1, Lpad / jk->tile, w.size(),
-                                gdx, st);
+        e = launch_jit_backward(*jk, *jp, dxT, coeffs, grad_coeffs, B, n_points - 1, Lpad, w.size(), gdx, st);
         if (pe) (void)hipEventRecord(pe[1], st);
         if (e != hipSuccess) return hip_fail(e);
         e = sig::grad_points_transposed(gdx, B, n_points, w.d, Lpad, grad_path, st);
@@ -1501,7 +1706,7 @@ size_t sig_forward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B
     if (!ws || B <= 0 || n_points <= 1) return 0;
     const Chunks ch = checkpoint_chunks(*W(ws), B, n_points);
     if (ch.C < 2) return sig_forward_workspace_bytes(ws, B, n_points);
-    if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), jit_dxt_bytes(*W(ws), B, n_points, 0));
+    if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));
     return forward_chunk_arrays(*W(ws), ch.C) > 1 ? chunk_array_bytes(*W(ws), B, ch.C) : 0;   // partial products of four chunks
 }
 
@@ -1570,6 +1775,15 @@ int sig_backward_checkpointed(const sig_wordset* ws, const float* path, const fl
     if (!coeffs || !grad_coeffs || !grad_path) return SIG_EINVAL;
     if (!checkpoint || checkpoint_bytes < chunk_array_bytes(w, B, ch.C)) return SIG_EWORKSPACE;
     if (w.kind != 0) {
+        // small launches take more chunks than are kept where that is the faster for all the forward pass they need again (209
+        // words, 26 paths x 693 segments: 62 us with the five that are kept, 45 with 24)
+        if (plain_chunks_available(w, B) && w.opt.ckpt_chunks == 0 &&
+            plain_time(w, kBackward, B, n_points - 1, plain_chunk_count(w, kBackward, B, n_points - 1)) <
+                0.93 * plain_time(w, kBackwardKept, B, n_points - 1, ch.C)) {
+            if (!workspace || workspace_bytes < sig_backward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
+            if ((((uintptr_t)workspace | (uintptr_t)checkpoint) & 255) != 0) return SIG_EINVAL;
+            return sig_backward(ws, path, coeffs, grad_coeffs, B, n_points, grad_path, workspace, workspace_bytes, stream);
+        }
         sig::JitKernel *fk, *bk;
         const sig::Plan *fp = nullptr, *bp = nullptr;
         if (!words_kernels(w, B * ch.C, &fk, &fp, &bk, &bp))
@@ -1712,7 +1926,7 @@ int sig_forward_windows(const sig_wordset* ws, const float* path, int64_t B, int
             if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(0);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_jit_forward(*jk, *jp, dxT, B * K, Lpad / jk->tile, coeffs, w.size(), st);
+            e = launch_jit_forward(*jk, *jp, dxT, B * K, max_window_len, Lpad, coeffs, w.size(), st);
             if (pe) (void)hipEventRecord(pe[1], st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
@@ -1794,7 +2008,7 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
             if (e != hipSuccess) return hip_fail(e);
             hipEvent_t* pe = g_prof.next(1);
             if (pe) (void)hipEventRecord(pe[0], st);
-            e = launch_jit_backward(*jk, *jp, dxT, coeffs, grad_coeffs, B * K, max_window_len, Lpad / jk->tile, w.size(), gdx, st);
+            e = launch_jit_backward(*jk, *jp, dxT, coeffs, grad_coeffs, B * K, max_window_len, Lpad, w.size(), gdx, st);
             if (pe) (void)hipEventRecord(pe[1], st);
             if (e != hipSuccess) return hip_fail(e);
             e = sig::grad_points_transposed(gdx, B, n_points, w.d, Lpad, grad_path, st, wl);

@@ -333,12 +333,12 @@ std::string jit_forward_source(const WordSet& ws, const Plan& plan, int NW, int 
     const int nu = (int)plan.units.size();
     for (int u = 0; u < nu; ++u) emit_forward_unit(o, plan, u);
     o << "extern \"C\" __global__ __launch_bounds__(NW * 64) void sig_fwd_jit(const float* __restrict__ dxT, long B, long ntiles,\n"
-         "                                                                  float* __restrict__ coeffs, long nW)\n{\n";
+         "                                                                  float* __restrict__ coeffs, long nW, long lpad)\n{\n";
     o << "    __shared__ __attribute__((aligned(16))) float tile[T * D * 64];\n";
     o << "    const int lane = threadIdx.x & 63;\n    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);\n";
     emit_group_and_column(o, (nu + NW - 1) / NW);
     o << "    const long b = group * 64 + lane;\n    const bool valid = b < B;\n";
-    o << "    const float* dxg = dxT + group * ntiles * (T * D * 64);\n";
+    o << "    const float* dxg = dxT + group * lpad * (D * 64);\n";
     o << "    float* out = valid ? coeffs + b * nW : nullptr;\n";
     o << "    const int unit = column * NW + wib;\n    switch (unit) {\n";
     for (int u = 0; u < nu; ++u) o << "        case " << u << ": fwd_unit_" << u << "(dxg, ntiles, tile, lane, wib, out); break;\n";
@@ -356,13 +356,13 @@ std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int
     for (int u = 0; u < nu; ++u) emit_backward_unit(o, plan, u, ws.d);
     o << "extern \"C\" __global__ __launch_bounds__(NW * 64) void sig_bwd_jit(const float* __restrict__ dxT,\n"
          "        const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long L, long ntiles, long nW, float* gdx,\n"
-         "        const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, long C)\n{\n";
+         "        const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, long C, long lpad)\n{\n";
     o << "    __shared__ __attribute__((aligned(16))) float tile[T * D * 64];\n    __shared__ float gt[NW * GT_F];\n";
     o << "    const int lane = threadIdx.x & 63;\n    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);\n";
     emit_group_and_column(o, (nu + NW - 1) / NW);
     o << "    const long b0 = group * 64;\n    const long b = b0 + lane;\n    const long bc = b < B ? b : B - 1;\n";
-    o << "    const float* dxg = dxT + group * ntiles * (T * D * 64);\n";
-    o << "    gdx += group * ntiles * (T * D * 64);\n";
+    o << "    const float* dxg = dxT + group * lpad * (D * 64);\n";
+    o << "    gdx += group * lpad * (D * 64);\n";
     // rows are the C time chunks of B / C paths: the last chunk of a path starts from the terminal signature and the
     // gradient themselves (arrays of one row per path), the others from rows of the per-chunk arrays; C = 1: whole paths
     o << "    const long pb = bc / C;\n    const bool last = bc - pb * C == C - 1;\n";
@@ -539,6 +539,7 @@ hipError_t jit_load(JitKernel& k)
 
 WordSet::~WordSet()
 {
+    delete closure;
     for (int dir = 0; dir < 2; ++dir)
         for (JitEntry* e : jit[dir]) {
             if (e->kernel) {

@@ -102,13 +102,24 @@ struct WordTables {
     int32_t tail_off[16] = {};              // [N + 2]
     int N = 0;                              // longest word (<= 14)
     int W = 0;                              // number of words (<= 65,535)
+    // tables of the closure of a set that lacks suffixes: index in the set of every word of the closure, or -1, and the set's
+    // number of words (nullptr and W: the set itself is closed)
+    const int32_t* own = nullptr;
+    int W_own = 0;
 };
 size_t words_scan_lds_bytes(int64_t W);
+// Sets (and closures) of up to 4,096 words of up to 8 letters: the scans with the terms of a thread's words in registers, in one
+// launch whatever is asked for: products from the left (rows, last: rows of W_own words) and, where rows_reverse is given,
+// from the right (rows of W words).
+bool words_scan_small_available(const WordTables& t);
+hipError_t words_scan_small(const WordTables& t, const float* S, int64_t B, int C, float* rows, float* last, float* rows_reverse,
+                            hipStream_t stream);
 // S [B][C][W] chunk signatures.  Forward scan: rows[b][c] = S_0 (x) .. (x) S_c (if rows), last[b] = the product of all
 // (if last).  Reverse scan: rows[b][c] = S_{c+1} (x) .. (x) S_{C-1} for c <= C - 2 (row C - 1 is left alone).
 hipError_t words_scan(const WordTables& t, const float* S, int64_t B, int C, bool reverse, float* rows, float* last,
                       hipStream_t stream);
-// Abar[b][c](u) = grad[b](u) + sum_v grad[b](u v) Q[b][c](v) for c <= C - 2; Q, Abar [B][C][W], rows C - 1 left alone
+// Abar[b][c](u) = grad[b](u) + sum_v grad[b](u v) Q[b][c](v) for c <= C - 2; Q [B][C][W], Abar [B][C][W_own], rows C - 1 left
+// alone; grad [B][W_own]
 // both scans in one launch (two layers of workgroups): rows_forward as the forward scan's rows, rows_reverse as the reverse scan's
 hipError_t words_scan_both(const WordTables& t, const float* S, int64_t B, int C, float* rows_forward, float* rows_reverse,
                            hipStream_t stream);

@@ -118,6 +118,95 @@ __global__ __launch_bounds__(kWordsThreads) void words_scan_kernel(WordTables t,
     }
 }
 
+// The same scans for sets of up to 4,096 words of up to TERMS + 1 letters: a thread keeps the same PER words from product to
+// product, so their terms are fetched once and stay in registers (an absent term reads the zero behind a row), the next
+// chunk's coefficients are loaded a product ahead, and with two buffers for either factor a product has one barrier.  Bound by
+// the latency of one product after the other: LDS gathers and the barrier.  Layer 0 of the grid: products from the left to
+// rows [B][C][W_own] and last [B][W_own]; layer 1 (or `reverse`): from the right to rows_reverse [B][C][W].
+template <int PER, int TERMS>
+__global__ __launch_bounds__(kWordsThreads) void words_scan_small_kernel(WordTables t, const float* __restrict__ S, int C,
+                                                                         float* __restrict__ rows, float* __restrict__ last,
+                                                                         float* __restrict__ rows_reverse)
+{
+    extern __shared__ float sm[];
+    const int tid = threadIdx.x, NT = blockDim.x, W = t.W, stride = W + 1;
+    const bool reverse = blockIdx.y == 1;
+    const int64_t b = blockIdx.x;
+    float* acc = sm;                                                    // [2][W + 1]: the running product
+    float* nxt = sm + 2 * stride;                                       // [2][W + 1]: the chunk it is multiplied with
+    const float* Sb = S + b * (int64_t)C * W;
+    // step i multiplies with chunk first + (i + 1) * dir
+    const int first = reverse ? C - 1 : 0, dir = reverse ? -1 : 1, products = reverse ? C - 2 : C - 1;
+    auto chunk = [&](int i) { return first + dir * (i < products ? i + 1 : products); };   // past the end: the last one again
+    uint32_t term[PER][TERMS];
+    int at[PER], to[PER];
+    float cur[PER], nx[PER], ahead[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int w = tid + q * NT;
+        at[q] = w < W ? w : W - 1;
+        int n = 1;
+        while (at[q] >= t.level_start[n + 1]) ++n;                     // length of the word
+        const int cnt = t.level_start[n + 1] - t.level_start[n];
+        const uint32_t* pp = t.prod_pairs + t.tail_off[n] + (at[q] - t.level_start[n]);
+#pragma unroll
+        for (int m = 0; m < TERMS; ++m) {
+            const uint32_t* src = m < n - 1 ? pp + (size_t)m * cnt : t.prod_pairs;
+            const uint32_t pr = *src;
+            term[q][m] = m < n - 1 ? pr : (uint32_t)W | (uint32_t)W << 16;
+        }
+        to[q] = w < W ? (reverse || !t.own ? w : t.own[w]) : -1;
+        cur[q] = Sb[(int64_t)first * W + at[q]];
+        nx[q] = Sb[(int64_t)chunk(0) * W + at[q]];
+        ahead[q] = Sb[(int64_t)chunk(1) * W + at[q]];
+    }
+    const int64_t row_words = reverse || !t.own ? W : t.W_own;
+    float* out = reverse ? rows_reverse : rows;
+    if (out) out += b * (int64_t)C * row_words;
+    // row of the running product: the chunk it ends with, from the right the chunk before the one it begins with
+    auto store = [&](int i) {
+        if (!out) return;
+        float* r = out + (int64_t)(reverse ? C - 2 - i : i) * row_words;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (to[q] >= 0) r[to[q]] = cur[q];
+    };
+    if (tid < 2) acc[tid * stride + W] = nxt[tid * stride + W] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        acc[at[q]] = cur[q];                                            // threads past the last word write its value again
+        nxt[at[q]] = nx[q];
+    }
+    store(0);
+    for (int i = 0; i < products; ++i) {
+        __syncthreads();
+        const float* x = (reverse ? nxt : acc) + (i & 1) * stride;
+        const float* y = (reverse ? acc : nxt) + (i & 1) * stride;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            float v = reverse ? nx[q] + cur[q] : cur[q] + nx[q];
+#pragma unroll
+            for (int m = 0; m < TERMS; ++m) v = fmaf(x[term[q][m] & 0xffffu], y[term[q][m] >> 16], v);
+            cur[q] = v;
+            nx[q] = ahead[q];
+        }
+        float* ao = acc + ((i + 1) & 1) * stride;
+        float* no = nxt + ((i + 1) & 1) * stride;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            ao[at[q]] = cur[q];
+            no[at[q]] = nx[q];
+            ahead[q] = Sb[(int64_t)chunk(i + 2) * W + at[q]];
+        }
+        store(i + 1);
+    }
+    if (last && !reverse) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (to[q] >= 0) last[b * row_words + to[q]] = cur[q];
+    }
+}
+
 // One step of an inclusive sum within runs of equal keys: the lane the pattern names as source adds its value where it
 // carries the same key; lanes the pattern gives no source keep theirs (their source key reads as 0xffffffff, no word).
 template <int CTRL, int ROWS>
@@ -130,7 +219,7 @@ __device__ __forceinline__ void seg_step(float& v, uint32_t key)
 
 // One workgroup per (path, chunk but the last).  grad [B][W], Q [B][C][W] (row c: what follows chunk c), Abar [B][C][W]
 // (rows of last chunks are left alone: their adjoint is the gradient itself).  The gradient row and Q are staged in LDS before anything is written, so
-// Abar may be the array Q itself.  The terms lie sorted by their prefix u: a wavefront takes 64 consecutive terms (four
+// Abar may be the array Q itself (not with a closure's tables, whose rows of Abar are shorter).  The terms lie sorted by their prefix u: a wavefront takes 64 consecutive terms (four
 // such groups in flight), sums runs of equal u within each row of 16 lanes and adds every run's sum to u's accumulator
 // in LDS.
 __global__ __launch_bounds__(kWordsThreads) void words_adjoint_kernel(WordTables t, const float* __restrict__ grad, const float* Q,
@@ -148,20 +237,23 @@ __global__ __launch_bounds__(kWordsThreads) void words_adjoint_kernel(WordTables
     constexpr int NWAVES = kWordsThreads / 64, UN = 4;
     const int64_t b = blockIdx.x / (C - 1);
     const int64_t row = b * C + (blockIdx.x - b * (C - 1));             // b * C + c, c < C - 1
-    const int W = t.W;
-    float* out = Abar + row * (int64_t)W;
+    const int W = t.W, W_own = t.own ? t.W_own : W;
+    float* out = Abar + row * (int64_t)W_own;
     float* g = sm;
     float* q = sm + W;
     float* acc = sm + 2 * W;                                            // [W + 1]: the last entry takes the padding
     for (int i = tid; i < W; i += kWordsThreads) {
-        const float v = grad[b * (int64_t)W + i];
+        const int own = t.own ? t.own[i] : i;
+        const float v = own >= 0 ? grad[b * (int64_t)W_own + own] : 0.0f;
         g[i] = v;
         acc[i] = v;
         q[i] = Q[row * (int64_t)W + i];
     }
     if (tid == 0) acc[W] = 0.0f;
     __syncthreads();
-    for (int grp = wave; grp < t.adj_groups; grp += NWAVES) {
+    // (the few terms of a small set are one wavefront's, which adds them in a fixed order)
+    const int waves = t.adj_groups <= 2 ? 1 : NWAVES;
+    for (int grp = wave < waves ? wave : t.adj_groups; grp < t.adj_groups; grp += waves) {
         uint32_t pr[UN], key[UN];
 #pragma unroll
         for (int j = 0; j < UN; ++j) {
@@ -189,7 +281,10 @@ __global__ __launch_bounds__(kWordsThreads) void words_adjoint_kernel(WordTables
         }
     }
     __syncthreads();
-    for (int i = tid; i < W; i += kWordsThreads) out[i] = acc[i];
+    for (int i = tid; i < W; i += kWordsThreads) {
+        const int own = t.own ? t.own[i] : i;
+        if (own >= 0) out[own] = acc[i];
+    }
 }
 
 }  // namespace
@@ -222,6 +317,29 @@ hipError_t words_scan_both(const WordTables& t, const float* S, int64_t B, int C
     }
     words_scan_kernel<<<dim3((unsigned)B, 2), kWordsThreads, lds, stream>>>(t, S, C, 0, rows_forward, nullptr, rows_reverse);
     return hipGetLastError();
+}
+
+bool words_scan_small_available(const WordTables& t) { return t.W >= 1 && t.W <= 4 * kWordsThreads && t.N <= 8; }
+
+hipError_t words_scan_small(const WordTables& t, const float* S, int64_t B, int C, float* rows, float* last, float* rows_reverse,
+                            hipStream_t stream)
+{
+    if (B < 1 || C < 2 || B > 0x7fffffff || !words_scan_small_available(t)) return hipErrorInvalidValue;
+    const size_t lds = 4 * ((size_t)t.W + 1) * sizeof(float);           // 64 KB and 16 bytes at most
+    const int threads = t.W >= kWordsThreads ? kWordsThreads : (t.W + 63) / 64 * 64;
+    const dim3 grid((unsigned)B, rows_reverse ? 2 : 1);
+    auto launch = [&](auto kernel) -> hipError_t {
+        if (lds > 64 * 1024) {
+            hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)(160 * 1024));
+            if (e != hipSuccess) return e;
+        }
+        kernel<<<grid, threads, lds, stream>>>(t, S, C, rows, last, rows_reverse);
+        return hipGetLastError();
+    };
+    const int per = (t.W + threads - 1) / threads;
+    if (t.N <= 4) return per == 1 ? launch(words_scan_small_kernel<1, 3>) : (per == 2 ? launch(words_scan_small_kernel<2, 3>) : launch(words_scan_small_kernel<4, 3>));
+    if (t.N <= 6) return per == 1 ? launch(words_scan_small_kernel<1, 5>) : (per == 2 ? launch(words_scan_small_kernel<2, 5>) : launch(words_scan_small_kernel<4, 5>));
+    return per == 1 ? launch(words_scan_small_kernel<1, 7>) : (per == 2 ? launch(words_scan_small_kernel<2, 7>) : launch(words_scan_small_kernel<4, 7>));
 }
 
 hipError_t words_adjoint(const WordTables& t, const float* grad, const float* Q, int64_t B, int C, float* Abar, float* zeroed,

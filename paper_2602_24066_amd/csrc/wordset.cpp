@@ -19,6 +19,15 @@ namespace sig {
 
 static const int64_t kMaxWords = (int64_t)SIG_MAX_WORDS;
 
+// a table at the end of the device image; returns its offset
+static size_t append_to_image(WordSet* ws, const void* src, size_t bytes)
+{
+    const size_t off = (ws->image.size() + 255) & ~(size_t)255;
+    ws->image.resize(off + ((bytes + 255) & ~(size_t)255), 0);
+    std::memcpy(&ws->image[off], src, bytes);
+    return off;
+}
+
 // Suffix structure of sets that are not full truncations (those have kernels and product rules of their own): the
 // word without its first letter, found through the word without first letter of the parent; if every such word is
 // in the set, the tables for products of signatures restricted to the set are appended to the device image (sets of
@@ -103,16 +112,58 @@ static void suffix_tables(WordSet* ws)
             }
         }
     }
-    auto append = [&](const void* src, size_t bytes) {
-        const size_t off = (ws->image.size() + 255) & ~(size_t)255;
-        ws->image.resize(off + ((bytes + 255) & ~(size_t)255), 0);
-        std::memcpy(&ws->image[off], src, bytes);
-        return off;
-    };
-    ws->dev_prod_off = append(ws->prod_pairs.data(), ws->prod_pairs.size() * sizeof(uint32_t));
-    ws->dev_adj_key_off = append(ws->adj_key.data(), ws->adj_key.size() * sizeof(uint32_t));
-    ws->dev_adj_pairs_off = append(ws->adj_pairs.data(), ws->adj_pairs.size() * sizeof(uint32_t));
+    ws->dev_prod_off = append_to_image(ws, ws->prod_pairs.data(), ws->prod_pairs.size() * sizeof(uint32_t));
+    ws->dev_adj_key_off = append_to_image(ws, ws->adj_key.data(), ws->adj_key.size() * sizeof(uint32_t));
+    ws->dev_adj_pairs_off = append_to_image(ws, ws->adj_pairs.data(), ws->adj_pairs.size() * sizeof(uint32_t));
     ws->pair_tables = true;
+}
+
+// The suffix-closed set around a small set that lacks suffixes: as the set is closed under prefixes, all suffixes of its words.
+// (Up to 4,096 words here and there, the size the product kernel with its tables in registers takes, and up to 8 letters.)
+static int closure_tables(WordSet* ws)
+{
+    constexpr int64_t kMost = 4096;
+    const int64_t n = ws->size();
+    if (ws->kind == 0 || ws->suffix_closed || !ws->kernels_supported || n == 0 || n > kMost || ws->max_len > 8) return SIG_OK;
+    std::vector<int32_t> letters, words((size_t)n * 8);
+    std::vector<int64_t> offsets(1, 0);
+    for (int64_t w = 0; w < n; ++w) {
+        const int len = ws->length[(size_t)w];
+        int32_t* x = &words[(size_t)w * 8];
+        if (len > 1) std::copy_n(&words[(size_t)ws->parent[(size_t)w] * 8], len - 1, x);
+        x[len - 1] = ws->letter[(size_t)w];
+        for (int m = 0; m < len; ++m) {
+            letters.insert(letters.end(), x + m, x + len);
+            offsets.push_back((int64_t)letters.size());
+        }
+    }
+    WordSet* c = nullptr;
+    const int rc = build_list(ws->d, letters.data(), offsets.data(), (int64_t)offsets.size() - 1, &c);
+    if (rc != SIG_OK) return rc == SIG_ENOMEM ? rc : SIG_OK;
+    ws->closure = c;                                                   // (the set owns it from here on)
+    if (c->size() > kMost || !c->pair_tables) {
+        delete c;
+        ws->closure = nullptr;
+        return SIG_OK;
+    }
+    ws->closure_own.assign((size_t)c->size(), -1);
+    for (int64_t w = 0, at = 0; w < n; ++w) {                         // word w itself is the first of its suffixes
+        ws->closure_own[(size_t)c->user_index[(size_t)at]] = (int32_t)w;
+        at += ws->length[(size_t)w];
+    }
+    for (size_t e = 0; e < c->adj_pairs.size(); ++e)
+        if (c->adj_key[e] < (uint32_t)c->size() && ws->closure_own[c->adj_pairs[e] & 0xffffu] >= 0) {
+            ws->closure_adj_pairs.push_back(c->adj_pairs[e]);
+            ws->closure_adj_key.push_back(c->adj_key[e]);
+        }
+    const size_t terms = std::max<size_t>((ws->closure_adj_pairs.size() + 255) / 256 * 256, 256);
+    ws->closure_adj_pairs.resize(terms, 0);
+    ws->closure_adj_key.resize(terms, (uint32_t)c->size());
+    ws->dev_closure_own_off = append_to_image(ws, ws->closure_own.data(), ws->closure_own.size() * sizeof(int32_t));
+    ws->dev_closure_prod_off = append_to_image(ws, c->prod_pairs.data(), c->prod_pairs.size() * sizeof(uint32_t));
+    ws->dev_closure_adj_key_off = append_to_image(ws, ws->closure_adj_key.data(), terms * sizeof(uint32_t));
+    ws->dev_closure_adj_pairs_off = append_to_image(ws, ws->closure_adj_pairs.data(), terms * sizeof(uint32_t));
+    return SIG_OK;
 }
 
 // Fills everything that follows from (parent, letter, level_start).
@@ -178,7 +229,7 @@ static int finish(WordSet* ws)
             if (!p.slot_word.empty()) std::memcpy(&ws->image[po.slots], p.slot_word.data(), p.slot_word.size() * sizeof(int32_t));
         }
     suffix_tables(ws);
-    return SIG_OK;
+    return closure_tables(ws);
 }
 
 void build_plan(const WordSet& ws, int max_slots, int64_t target_cost, bool with_leave, Plan& plan)
@@ -772,12 +823,7 @@ int build_logsig(int d, int depth, WordSet** out)
                     ws->lyn_sub_t[(size_t)(pair * n_lyn + k)] = ws->lyn_sub[(size_t)k * (size_t)ws->lyn_stride + (size_t)i * (size_t)(depth + 1) + (size_t)j];
         }
         // append the tables to the device image
-        auto append = [&](const void* src, size_t bytes) {
-            const size_t off = (ws->image.size() + 255) & ~(size_t)255;
-            ws->image.resize(off + ((bytes + 255) & ~(size_t)255), 0);
-            std::memcpy(&ws->image[off], src, bytes);
-            return off;
-        };
+        auto append = [&](const void* src, size_t bytes) { return append_to_image(ws, src, bytes); };
         ws->lyn_len_off = append(ws->lyn_len.data(), ws->lyn_len.size() * sizeof(int32_t));
         ws->lyn_sub_off = append(ws->lyn_sub.data(), ws->lyn_sub.size() * sizeof(int32_t));
         ws->lyn_sub_t_off = append(ws->lyn_sub_t.data(), ws->lyn_sub_t.size() * sizeof(int32_t));

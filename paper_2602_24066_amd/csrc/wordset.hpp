@@ -95,6 +95,14 @@ struct WordSet {
     std::vector<uint32_t> prod_pairs, adj_pairs, adj_key;
     std::vector<int32_t> adj_off;      // [|W| + 1] (host only)
     size_t dev_prod_off = 0, dev_adj_key_off = 0, dev_adj_pairs_off = 0;    // offsets in the device image (pair_tables only)
+    // Small sets that lack suffixes (word lists, sparse lead-lag sets): the smallest suffix-closed set around them, which has
+    // the tables above, for time chunks of the plain calls.  closure_own[v]: index here of its word v, or -1.  Its table of
+    // product terms and closure_own lie in this set's image, and so do the terms of the boundary adjoint of this set's words
+    // (closure_adj_*: as adj_*, indices of the closure, without the terms of words that are only there).
+    WordSet* closure = nullptr;
+    std::vector<int32_t> closure_own;
+    std::vector<uint32_t> closure_adj_pairs, closure_adj_key;
+    size_t dev_closure_own_off = 0, dev_closure_prod_off = 0, dev_closure_adj_pairs_off = 0, dev_closure_adj_key_off = 0;
     void* dev = nullptr;
     int dev_id = -1;                   // device the image was uploaded to (a word-set object serves one device)
     // Launch-shape knobs.  Filled once when the set is built (from the SIG_* environment variables of that moment) and

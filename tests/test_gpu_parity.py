@@ -261,6 +261,82 @@ def test_plain_backward_takes_time_chunks_for_few_long_paths(d, depth, B, L):
     assert O.grad_errors(gs.cpu().numpy(), gref).max() <= BWD_TOL
 
 
+@pytest.mark.parametrize("kind,d,n_words,max_len,B,L,chunks", [
+    ("words", 4, 60, 4, 3, 50, 3),         # closure of 78 words: one word a thread, three terms
+    ("words", 10, 700, 6, 2, 37, 2),       # 1,907 words: two a thread, five terms; the last chunk shorter
+    ("words", 6, 1200, 8, 65, 33, 5),      # 3,801 words: four a thread, seven terms; two path groups
+    ("words", 5, 300, 5, 70, 200, 0),      # the library's own count
+    ("leadlag", 2, None, 3, 39, 150, 16),  # 36 words, closure of 38
+    ("aniso", 3, None, None, 4, 90, 6),    # closed under suffixes itself
+    ("letters", 3, None, 1, 5, 24, 4),     # words of one letter: no terms
+])
+def test_time_chunks_of_small_launches(kind, d, n_words, max_len, B, L, chunks):
+    """sig_forward and sig_backward cut the paths of small launches into time chunks, also for sets that lack suffixes (through
+    their closure): both against the oracle, and the entry point that walks whole paths after them."""
+    import torch
+    if kind == "aniso":
+        ws, W = build_both("anisotropic", d, weights=(1.0, 1.25, 1.5), cutoff=4.5)
+    elif kind == "leadlag":
+        ws = S.sig_wordset_build_leadlag_sparse(d, max_len)
+        ws.upload("cuda:0")
+        W, d = O.prefix_closure(O.leadlag_sparse_words(d, max_len)), 2 * d
+    else:
+        words = [(i,) for i in range(d)] if kind == "letters" else random_prefix_closed_words(41, d, n_words, max_len)
+        ws, W = build_both("words", d, words=words)
+    lib = S.load_library()
+    whole = int(lib.sig_backward_workspace_bytes(ws._h, B, 8))
+    ws.set_option("chunks", chunks)
+    assert int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1)) > whole and int(lib.sig_forward_workspace_bytes(ws._h, B, L + 1)) > 0
+    X = make_path("iid", 7100 + L, B, L, d)
+    G = make_grad_coeffs(7200 + L, B, ws.size)
+    xp, grad = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    coeffs = S.sig_forward(ws, xp)
+    gp = S.sig_backward(ws, xp, coeffs, grad)
+    gs = torch.empty_like(xp)
+    S.sig_backward_static(ws, xp, coeffs, grad, gs)
+    torch.cuda.synchronize()
+    lengths = np.array([len(w) for w in W])
+    for n, e in O.level_errors(coeffs.cpu().numpy(), O.forward_words(X, W), lengths).items():
+        assert e <= FWD_TOL, f"level {n}: {e:.3e}"
+    gref = O.backward_words(X, W, G.astype(np.float64))
+    assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+    assert O.grad_errors(gs.cpu().numpy(), gref).max() <= BWD_TOL
+
+
+def test_time_chunks_of_small_launches_under_capture():
+    """What a call under graph capture may not load it does without: after one eager step on short paths a step on long ones is
+    recorded with whole paths, and after one on long paths a step on short ones as well."""
+    import torch
+    words = random_prefix_closed_words(43, 5, 120, 5)
+    for eager, captured in ((12, 160), (160, 12)):
+        ws, W = build_both("words", 5, words=words)
+        B = 6
+        X = [make_path("iid", 7300 + n, B, n, 5) for n in (eager, captured)]
+        xs = [torch.from_numpy(x).cuda() for x in X]
+        G = make_grad_coeffs(7301, B, ws.size)
+        g = torch.from_numpy(G).cuda()
+        S.sig_backward(ws, xs[0], S.sig_forward(ws, xs[0]), g)
+        lib = S.load_library()
+        wf = torch.empty(max(int(lib.sig_forward_workspace_bytes(ws._h, B, captured + 1)), 256), dtype=torch.uint8, device="cuda")
+        wb = torch.empty(int(lib.sig_backward_workspace_bytes(ws._h, B, captured + 1)), dtype=torch.uint8, device="cuda")
+        c, gp = torch.zeros((B, ws.size), device="cuda"), torch.zeros_like(xs[1])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            S.sig_forward(ws, xs[1], out=c, workspace=wf)
+            S.sig_backward(ws, xs[1], c, g, out=gp, workspace=wb)
+        gref = O.backward_words(X[1], W, G.astype(np.float64))
+        for rep in range(3):
+            xs[1].copy_(torch.from_numpy(X[1]))
+            gp.fill_(5.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            for n, e in O.level_errors(c.cpu().numpy(), O.forward_words(X[1], W), np.array([len(w) for w in W])).items():
+                assert e <= FWD_TOL, (rep, n, e)
+            assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL, rep
+            S.sig_forward(ws, xs[0])
+
+
 def test_checkpointed_word_sets_reject_bad_buffers():
     """Buffers that are missing, too small or misaligned are refused with an error code before anything is launched."""
     import ctypes

@@ -135,6 +135,54 @@ Chunks trunc_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points,
     const int64_t Lc = (L + C - 1) / C;
     return Chunks{(L + Lc - 1) / Lc, Lc};
 }
+// d = 8 and d = 16 (sig::trunc_low_available): chunks with products by slices in one launch, and backward with chunk signatures over
+// the words shorter than the depth alone (the longest are never reconstructed), so few paths are cut finer, and shorter ones
+// than above: up to sixteen chunks (eight forward), a model decides.  Microseconds per segment of a row: a lone wavefront on
+// each SIMD, and what a wavefront adds beyond that; per chunk: a product, the boundary adjoints and the traffic of its signature.
+// Forward + backward, whole paths (or the chunks of at least 256 segments before) -> now: d = 8, 3 paths x 979 segments 702 ->
+// 123 us, 62 x 515 407 -> 260, 5 x 238 205 -> 76; d = 16, 1 x 373 250 -> 71, 18 x 591 347 -> 190.
+double low_time(const sig::WordSet& w, int dir, bool kept /* the chunk signatures are */, int64_t B, int64_t L, int64_t C)
+{
+    const bool d8 = w.d == 8;
+    const double lone = dir ? (d8 ? 0.65 : 0.526) : (d8 ? 0.168 : 0.146), each = dir ? (d8 ? 0.468 : 0.325) : (d8 ? 0.153 : 0.108);
+    const double per_simd = std::ceil((double)sig::trunc_waves_per_row(w.d, w.depth, dir) * (double)(B * C) / 1024.0);
+    const double pairs = std::floor(per_simd / 2.0), single = per_simd - 2.0 * pairs;        // two wavefronts fit a SIMD
+    const double Lc = (double)((L + C - 1) / C), paths = (double)B, n = (double)C;
+    const double t = Lc * (pairs * 2.0 * each + single * lone);
+    if (C == 1) return t;
+    if (!dir) return t + 4.5 + n * (1.0 + (d8 ? 0.09 : 0.17) * paths);
+    return t + (kept ? 9.0 : 18.0 + (d8 ? 0.12 : 0.05) * Lc) + n * (0.6 + 0.11 * paths);
+}
+int low_chunk_count(const sig::WordSet& w, int dir, int64_t B, int64_t L)
+{
+    double best = 0.93 * low_time(w, dir, false, B, L, 1);
+    int choice = 1;
+    for (int C : {2, 3, 4, 6, 8, 12, 16}) {
+        if (L < 8 * (int64_t)C || (dir == 0 && C > 8)) break;
+        const double t = low_time(w, dir, false, B, L, C);
+        if (t < best) {
+            best = t;
+            choice = C;
+        }
+    }
+    return choice;
+}
+// the product of every path's chunk signatures: by slices from three chunks on, of two spread over the grid (128 paths, d = 8: 16 us
+// against 21)
+hipError_t chunk_product_of(const sig::WordSet& w, const float* Sc, float* Pfx, float* coeffs, int64_t B, int64_t C, hipStream_t st)
+{
+    if (C > 2 && sig::trunc_low_available(w.d, w.depth)) return sig::chunk_slices_forward(w.d, w.depth, Sc, coeffs, B, (int)C, st);
+    return sig::chunk_scan(w.d, w.depth, Sc, Pfx, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)C, nullptr, st);
+}
+Chunks low_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points)
+{
+    const int64_t L = n_points - 1;
+    int64_t C = 1;
+    if (w.opt.chunks > 0) C = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(w.opt.chunks, 64), L / 4));   // tuning knob
+    else C = low_chunk_count(w, dir, B, L);
+    const int64_t Lc = (L + C - 1) / C;
+    return Chunks{(L + Lc - 1) / Lc, Lc};
+}
 // Forward for d = 4 in the layout with 64 words of length 3 per wavefront (two wavefronts per chunk of a path, 2 or 4
 // chunks per path in one workgroup, chunk signatures multiplied in LDS).  Returns the number of chunks, 0 = the
 // kernel with four wavefronts per path instead (with its chunk arrays in HBM for long paths): measured faster only
@@ -1259,7 +1307,12 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
     const sig::WordSet& w = *W(ws);
     if (use_trunc_forward(w, B)) {
         const Chunks ch = trunc_chunks(w, 0, B, n_points);
-        return ch.C > 1 ? forward_chunk_arrays(w, ch.C) * chunk_array_bytes(w, B, ch.C) : 0;
+        size_t n = ch.C > 1 ? forward_chunk_arrays(w, ch.C) * chunk_array_bytes(w, B, ch.C) : 0;
+        if (sig::trunc_low_available(w.d, w.depth)) {
+            const Chunks low = low_chunks(w, 0, B, n_points);
+            if (low.C > 1) n = std::max(n, chunk_array_bytes(w, B, low.C));
+        }
+        return n;
     }
     if (!jit_enabled(w)) return 0;
     size_t n = jit_dxt_bytes(w, B, n_points, 0);
@@ -1278,6 +1331,39 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
     return n;
 }
 
+static size_t gdx_bytes_of(const sig::WordSet& w, int64_t B, int64_t n_points)
+{
+    return ((size_t)B * (size_t)(n_points - 1) * (size_t)w.d * sizeof(float) + 255) & ~(size_t)255;
+}
+
+// chunk signatures, products from both sides [B][C] and boundary adjoints [B][C - 1], rows of words shorter than the depth
+static size_t low_backward_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return ch.C > 1 ? 3 * lanes_low_bytes(w, B, ch.C) + lanes_low_bytes(w, B, ch.C - 1) : 0;
+}
+// sig_backward of those shapes over chunks of its own; workspace: gradient of the increments | low_backward_arrays
+static hipError_t low_backward(const sig::WordSet& w, const float* path, const float* coeffs, const float* grad_coeffs, int64_t B,
+                               int64_t n_points, const Chunks& ch, float* grad_path, void* workspace, hipStream_t st)
+{
+    const size_t gb = gdx_bytes_of(w, B, n_points), nb = lanes_low_bytes(w, B, ch.C);
+    unsigned char* base = (unsigned char*)workspace + gb;
+    float* gdx = (float*)workspace;
+    float* Sc = (float*)base;
+    float* left = (float*)(base + nb);
+    float* right = (float*)(base + 2 * nb);
+    float* Abar = (float*)(base + 3 * nb);
+    hipError_t e = sig::trunc_forward_low(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
+    if (e == hipSuccess) e = sig::chunk_slices_both(w.d, w.depth, Sc, w.level_start[(size_t)w.depth], left, right, B, (int)ch.C, st);
+    if (e == hipSuccess) e = sig::chunk_adjoint_low(w.d, w.depth, grad_coeffs, right, Abar, B, (int)ch.C, gdx, B * (n_points - 1) * w.d, st);
+    if (e != hipSuccess) return e;
+    hipEvent_t* pe = g_prof.next(1);
+    if (pe) (void)hipEventRecord(pe[0], st);
+    e = sig::trunc_backward(w.d, w.depth, path, left, Abar, coeffs, grad_coeffs, B, n_points, ch.C, ch.Lc, gdx, nullptr, w.opt.bwd_tile, st,
+                            w.level_start[(size_t)w.depth]);
+    if (pe) (void)hipEventRecord(pe[1], st);
+    return e == hipSuccess ? sig::grad_points(gdx, B, n_points, w.d, grad_path, st) : e;
+}
+
 // what sig_backward needs; own_chunks = false: when it takes no time chunks of its own (sig_backward_static)
 static size_t backward_workspace(const sig_wordset* ws, int64_t B, int64_t n_points, bool own_chunks)
 {
@@ -1287,7 +1373,9 @@ static size_t backward_workspace(const sig_wordset* ws, int64_t B, int64_t n_poi
     n = (n + 255) & ~(size_t)255;                                   // gradient with respect to the increments
     if (use_trunc_backward(w, B)) {
         const BwdShape ch = trunc_backward_shape(w, B, n_points, own_chunks);
-        if (ch.C > 1 && !ch.fused) n += 4 * chunk_array_bytes(w, B, ch.C);   // chunk signatures, prefixes, suffixes, adjoints
+        size_t arrays = ch.C > 1 && !ch.fused ? 4 * chunk_array_bytes(w, B, ch.C) : 0;   // chunk signatures, prefixes, suffixes, adjoints
+        if (own_chunks && sig::trunc_low_available(w.d, w.depth)) arrays = std::max(arrays, low_backward_arrays(w, B, low_chunks(w, 1, B, n_points)));
+        n += arrays;
     } else if (jit_enabled(w)) {
         // the specialised kernels keep the increment gradients in the (padded) layout of their transposed increments
         const size_t t = jit_dxt_bytes(w, B, n_points, 1);
@@ -1351,7 +1439,22 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
             if (pe) (void)hipEventRecord(pe[1], st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
-        const Chunks ch = trunc_chunks(w, 0, B, n_points);
+        Chunks ch = trunc_chunks(w, 0, B, n_points);
+        if (sig::trunc_low_available(w.d, w.depth)) {
+            // (a smaller workspace, or rows that are not aligned, get the walk over whole paths unless the call has always asked for
+            // its chunks)
+            const Chunks low = low_chunks(w, 0, B, n_points);
+            const size_t nb = chunk_array_bytes(w, B, low.C);
+            if (low.C > 1 && workspace && workspace_bytes >= sig_forward_workspace_bytes(ws, B, n_points) &&
+                (((uintptr_t)workspace & 255) | ((uintptr_t)coeffs & 15)) == 0 && workspace_bytes >= nb) {
+                hipEvent_t* pe = g_prof.next(0);
+                if (pe) (void)hipEventRecord(pe[0], st);
+                hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, low.C, low.Lc, (float*)workspace, st);
+                if (pe) (void)hipEventRecord(pe[1], st);
+                if (e == hipSuccess) e = chunk_product_of(w, (const float*)workspace, nullptr, coeffs, B, low.C, st);
+                return e == hipSuccess ? SIG_OK : hip_fail(e);
+            }
+        }
         float* Sc = coeffs;
         float* Pfx = nullptr;
         if (ch.C > 1) {
@@ -1460,11 +1563,6 @@ int sig_forward(const sig_wordset* ws, const float* path, int64_t B, int64_t n_p
 
 // sig_backward and sig_backward_static: the same kernels on the caller's workspace or on the static scratch array;
 // `how` says whether a run-time specialised kernel may be compiled and loaded by this call.
-static size_t gdx_bytes_of(const sig::WordSet& w, int64_t B, int64_t n_points)
-{
-    return ((size_t)B * (size_t)(n_points - 1) * (size_t)w.d * sizeof(float) + 255) & ~(size_t)255;
-}
-
 // Backward over the C time chunks whose signatures the forward pass left in ckpt [B][C][|W|]: signature and adjoint at
 // the end of every chunk from products of the chunk signatures, then all (path, chunk) rows in one launch.
 static int backward_checkpointed(const sig::WordSet& w, const float* path, const float* coeffs, const float* grad_coeffs,
@@ -1482,7 +1580,17 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
     const int64_t n_gdx = B * (n_points - 1) * w.d;                 // cleared by the launch of the adjoints
     hipError_t e = hipSuccess;
     const float* row_coeffs = ckpt;
-    if (ch.C == 2) {
+    int64_t row_words = nW;
+    if (ch.C > 2 && sig::trunc_low_available(w.d, w.depth)) {
+        // products by slices over the words shorter than the depth, in rows of those (less than the workspace holds)
+        const size_t lb = lanes_low_bytes(w, B, ch.C);
+        float* left = (float*)((unsigned char*)Abar + lanes_low_bytes(w, B, ch.C - 1));
+        float* right = (float*)((unsigned char*)left + lb);
+        e = sig::chunk_slices_both(w.d, w.depth, ckpt, nW, left, right, B, (int)ch.C, st);
+        if (e == hipSuccess) e = sig::chunk_adjoint_low(w.d, w.depth, grad_coeffs, right, Abar, B, (int)ch.C, gdx, n_gdx, st);
+        row_coeffs = left;
+        row_words = w.level_start[(size_t)w.depth];
+    } else if (ch.C == 2) {
         // two chunks: the signature at the end of the first is the first chunk's own, what follows it the second's
         e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, Abar, B, 2, true, st, gdx, n_gdx);
     } else {
@@ -1497,7 +1605,7 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
     if (pe) (void)hipEventRecord(pe[0], st);
     // the rows of the last chunk are the caller's terminal signature and gradient themselves
     e = sig::trunc_backward(w.d, w.depth, path, row_coeffs, Abar, coeffs, grad_coeffs, B, n_points, ch.C, ch.Lc, gdx, nullptr,
-                            w.opt.bwd_tile, st);
+                            w.opt.bwd_tile, st, row_words);
     if (pe) (void)hipEventRecord(pe[1], st);
     if (e != hipSuccess) return hip_fail(e);
     e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);
@@ -1526,12 +1634,22 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
                             !(small_set && w.depth > 2 && how == Build::loaded_only);
     // the same holds for the chunks of small launches, except where a suffix-closed set has always asked for its chunks
     const bool small_launch = plain_chunks_available(w, B);
-    const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points)));
+    const bool low = use_trunc_backward(w, B) && sig::trunc_low_available(w.d, w.depth) && word_chunks && !residual;
+    const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points))) ||
+                          (low && trunc_chunks(w, 1, B, n_points).C == 1);
     const size_t need = word_chunks && !optional ? sig_backward_workspace_bytes(ws, B, n_points) : backward_workspace(ws, B, n_points, false);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;
     CallTimer whole(1, st);
+    if (low) {
+        const Chunks lch = low_chunks(w, 1, B, n_points);
+        if (lch.C > 1 && workspace_bytes >= gdx_bytes_of(w, B, n_points) + low_backward_arrays(w, B, lch) &&
+            (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
+            hipError_t le = low_backward(w, path, coeffs, grad_coeffs, B, n_points, lch, grad_path, workspace, st);
+            return le == hipSuccess ? SIG_OK : hip_fail(le);
+        }
+    }
     if (word_chunks && !residual && !use_trunc_backward(w, B) && use_lanes(w, B, kAnyLength)) lanes_bring_up(w, 1, B, how);
     if (lanes_path && word_chunks && !residual) {
         const Chunks lch = lanes_chunks(w, 1, B, n_points);
@@ -1717,7 +1835,8 @@ size_t sig_backward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t 
     const Chunks ch = checkpoint_chunks(w, B, n_points);
     if (ch.C < 2) return sig_backward_workspace_bytes(ws, B, n_points);
     if (w.kind != 0) return std::max(words_backward_ckpt_workspace(w, B, ch), sig_backward_workspace_bytes(ws, B, n_points));
-    // gradient of the increments, boundary adjoints; beyond two chunks also the products before and after every chunk
+    // gradient of the increments, boundary adjoints; beyond two chunks also the products before and after every chunk (the calls
+    // take fewer bytes of it where they go by the words shorter than the depth alone)
     return gdx_bytes_of(w, B, n_points) + chunk_array_bytes(w, B, ch.C - 1) + (ch.C == 2 ? 0 : 2) * chunk_array_bytes(w, B, ch.C);
 }
 
@@ -1759,7 +1878,7 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
     if (pe) (void)hipEventRecord(pe[0], st);
     hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
     if (pe) (void)hipEventRecord(pe[1], st);
-    if (e == hipSuccess) e = sig::chunk_scan(w.d, w.depth, Sc, Pfx, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)ch.C, nullptr, st);
+    if (e == hipSuccess) e = chunk_product_of(w, Sc, Pfx, coeffs, B, ch.C, st);
     return e == hipSuccess ? SIG_OK : hip_fail(e);
 }
 
@@ -1798,6 +1917,13 @@ int sig_backward_checkpointed(const sig_wordset* ws, const float* path, const fl
     }
     if (!workspace || workspace_bytes < sig_backward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)checkpoint & 255) != 0) return SIG_EINVAL;
+    if (sig::trunc_low_available(w.d, w.depth) && w.opt.ckpt_chunks == 0 && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
+        // counts that fill the SIMDs better than those that are kept may be worth the chunks' signatures once more
+        const Chunks own = low_chunks(w, 1, B, n_points);
+        if (own.C > 1 && workspace_bytes >= sig_backward_workspace_bytes(ws, B, n_points) &&
+            low_time(w, 1, false, B, n_points - 1, own.C) < 0.93 * low_time(w, 1, true, B, n_points - 1, ch.C))
+            return sig_backward(ws, path, coeffs, grad_coeffs, B, n_points, grad_path, workspace, workspace_bytes, stream);
+    }
     return backward_checkpointed(w, path, coeffs, grad_coeffs, (const float*)checkpoint, ch, B, n_points, grad_path, workspace,
                                  (hipStream_t)stream);
 }

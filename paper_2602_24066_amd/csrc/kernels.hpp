@@ -130,6 +130,10 @@ hipError_t words_adjoint(const WordTables& t, const float* grad, const float* Q,
 // Register-resident kernels for full truncations (kernels_trunc.hip)
 bool trunc_forward_available(int d, int depth);
 bool trunc_backward_available(int d, int depth);
+// the words shorter than the depth alone; coeffs [B * C] rows of them
+bool trunc_low_available(int d, int depth);
+hipError_t trunc_forward_low(int d, int depth, const float* path, int64_t B, int64_t P, int64_t C, int64_t Lc, float* coeffs,
+                             hipStream_t stream);
 int trunc_occupancy(int d, int depth, int backward);        // workgroups (of four wavefronts) resident per compute unit
 int trunc_waves_per_row(int d, int depth, int backward);    // wavefronts per (path, chunk) row
 // A path may be cut into C chunks of Lc segments (the last one shorter); every (path, chunk) pair is a row of its
@@ -149,7 +153,8 @@ hipError_t trunc_backward_windows(int d, int depth, const float* path, const flo
 // every path (rows that begin at segment 0 report)
 hipError_t trunc_backward(int d, int depth, const float* path, const float* coeffs, const float* grad_coeffs,
                           const float* coeffs_last, const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-                          float* gdx, float* resid /*[B], zeroed by the caller, or nullptr*/, int tile, hipStream_t stream);
+                          float* gdx, float* resid /*[B], zeroed by the caller, or nullptr*/, int tile, hipStream_t stream,
+                          int64_t row_words = 0 /* floats a row of coeffs and grad; 0: |W| */);
 const char* trunc_backward_kernel_name(int d, int depth);   // of the kernel trunc_backward launches
 
 // d = 4: backward with one wavefront per row (a lane holds a word of length N - 3 and its four children); stores
@@ -183,5 +188,15 @@ hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, float* Q, c
 // (skip_last: the last chunk's row of Abar, a copy of grad, is not written)
 hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, float* Abar, int64_t B, int C, bool skip_last,
                          hipStream_t stream, float* zero = nullptr, int64_t n_zero = 0);
+// Shapes of trunc_low_available, a workgroup per path and letter and one launch whatever the number of chunks:
+// coeffs [B][|W|] = the product of the chunk signatures Sc [B][C][|W|]
+hipError_t chunk_slices_forward(int d, int depth, const float* Sc, float* coeffs, int64_t B, int C, hipStream_t stream);
+// over the words shorter than the depth, all arrays [B][C] rows of them: left[c] = S_0 .. S_c and right[c] = S_{c+1} .. S_{C-1}
+// for c <= C - 2, then Abar [B][C - 1] from grad [B][|W|] and `right`; n_zero floats at zero are cleared on the way
+// (Sc: rows of sc_words floats that begin with them)
+hipError_t chunk_slices_both(int d, int depth, const float* Sc, int64_t sc_words, float* left, float* right, int64_t B, int C,
+                             hipStream_t stream);
+hipError_t chunk_adjoint_low(int d, int depth, const float* grad, const float* right, float* Abar, int64_t B, int C, float* zero,
+                             int64_t n_zero, hipStream_t stream);
 
 }  // namespace sig

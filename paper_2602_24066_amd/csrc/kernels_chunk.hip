@@ -321,7 +321,7 @@ __global__ __launch_bounds__(512) void chunk_adjoint_kernel(const float* __restr
 // 128 paths, d = 8, depth 5, two chunks: 30 + 5 us (with a fill kernel) -> 28 us.
 __global__ __launch_bounds__(512) void chunk_adjoint_subtree_kernel(const float* __restrict__ grad, const float* __restrict__ Q,
                                                                     float* __restrict__ Abar, int C, float* __restrict__ zero,
-                                                                    int64_t n_zero, Levels g)
+                                                                    int64_t n_zero, int64_t row_words, Levels g)
 {
     extern __shared__ f4 smem4[];
     __shared__ float red[8];
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(512) void chunk_adjoint_subtree_kernel(const float*
     float* sq = (float*)smem4;
     float* sg = sq + below;
     const float* gr = grad + b * W;
-    const float* q = Q + row * W;
-    float* out = Abar + (row - b) * W;                   // [B][C - 1][W]: the last chunk has no row
+    const float* q = Q + row * row_words;
+    float* out = Abar + (row - b) * row_words;           // [B][C - 1]: the last chunk has no row
     const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
     // quads of words shorter than N, four of each kind in flight per thread (d >= 4: a quad's words have one length)
     for (int o0 = 4 * tid; o0 < below; o0 += 16 * nthr) {
@@ -401,6 +401,179 @@ __global__ __launch_bounds__(512) void chunk_adjoint_subtree_kernel(const float*
                 out[g.ls[k] + a * nk + iw] = own + acc;
             }
         }
+    }
+}
+
+// ---- products by slices: a workgroup keeps one slice of the running product of a path.  The words with first letter i of
+// S_0 S_1 .. S_c have their left factors inside the slice, those with last letter i of S_c .. S_{C-1} their right ones, so the D
+// slices (and both directions) advance side by side, all chunks in one launch; only the shorter words of the next chunk
+// signature are shared, staged in LDS a product ahead.  Bound by the latency of one product after the other (two barriers
+// each).  A grid-wide launch per product instead cost 4.5-5 us each: 3 paths x 979 segments, d = 8, eight chunks, 35 us forward.
+template <int B, int E> struct Ipow { static constexpr int v = B * Ipow<B, E - 1>::v; };
+template <int B> struct Ipow<B, 0> { static constexpr int v = 1; };
+template <int D, int n> struct LevelAt { static constexpr int v = LevelAt<D, n - 1>::v + Ipow<D, n - 1>::v; };    // words shorter than n
+template <int D> struct LevelAt<D, 1> { static constexpr int v = 0; };
+template <int D, int n> constexpr int kLevel = LevelAt<D, n>::v;
+template <int D, int n> constexpr int kSlice = LevelAt<D, n>::v / D;                                          // the same inside a slice
+template <int B, int E> constexpr int kPow = Ipow<B, E>::v;
+
+// word e of length n of the slice of letter i
+template <int D, int n>
+__device__ __forceinline__ int slice_word(bool from_left, int i, int e)
+{
+    return kLevel<D, n> + (from_left ? i * kPow<D, n - 1> + e : e * D + i);
+}
+// sum over the cuts m .. n - 1 of word e of length n of the slice; x: the slice's shorter words, s: those of the next chunk
+template <int D, int n, int m>
+__device__ __forceinline__ float slice_cuts(bool from_left, const float* x, const float* s, unsigned e, float acc)
+{
+    if constexpr (m < n) {
+        constexpr unsigned below = kPow<D, n - m>, below_right = kPow<D, n - m - 1>;      // suffixes of a cut, those of the slice
+        acc = from_left ? fmaf(x[kSlice<D, m> + e / below], s[kLevel<D, n - m> + e % below], acc)
+                        : fmaf(s[kLevel<D, m> + e / below_right], x[kSlice<D, n - m> + e % below_right], acc);
+        acc = slice_cuts<D, n, m + 1>(from_left, x, s, e, acc);
+    }
+    return acc;
+}
+// the same for four words that share all prefixes (the first is e), from the left
+template <int D, int n, int m>
+__device__ __forceinline__ void quad_cuts(const float* x, const float* s, unsigned e, f4& acc)
+{
+    if constexpr (m < n) {
+        constexpr unsigned below = kPow<D, n - m>;
+        acc += x[kSlice<D, m> + e / below] * *(const f4*)(s + kLevel<D, n - m> + e % below);
+        quad_cuts<D, n, m + 1>(x, s, e, acc);
+    }
+}
+// y = x times the next chunk for the words of length n .. LAST, also to out where it is given
+template <int D, int n, int LAST, int NT>
+__device__ __forceinline__ void slice_levels(bool from_left, int i, const float* x, const float* s, float* y, float* __restrict__ out)
+{
+    if constexpr (n <= LAST) {
+        for (int e = threadIdx.x; e < kPow<D, n - 1>; e += NT) {
+            const int w = slice_word<D, n>(from_left, i, e);
+            const float v = x[kSlice<D, n> + e] + s[w] + slice_cuts<D, n, 1>(from_left, x, s, (unsigned)e, 0.0f);
+            y[kSlice<D, n> + e] = v;
+            if (out) out[w] = v;
+        }
+        slice_levels<D, n + 1, LAST, NT>(from_left, i, x, s, y, out);
+    }
+}
+// the words of length n .. LAST of a slice of one signature, to LDS and where it is given to out
+template <int D, int n, int LAST, int NT>
+__device__ __forceinline__ void slice_copy(bool from_left, int i, const float* __restrict__ S, float* y, float* __restrict__ out)
+{
+    if constexpr (n <= LAST) {
+        for (int e = threadIdx.x; e < kPow<D, n - 1>; e += NT) {
+            const int w = slice_word<D, n>(from_left, i, e);
+            const float v = S[w];
+            y[kSlice<D, n> + e] = v;
+            if (out) out[w] = v;
+        }
+        slice_copy<D, n + 1, LAST, NT>(from_left, i, S, y, out);
+    }
+}
+
+// coeffs[b] = S_0 .. S_{C-1}.  The words of length N are never read again: a thread keeps its quads of them (four words that
+// share all prefixes) in registers.
+template <int D, int N, int NT>
+__global__ __launch_bounds__(NT) void chunk_slices_forward_kernel(const float* __restrict__ Sc, int C, float* __restrict__ coeffs)
+{
+    constexpr int W = kLevel<D, N + 1>, NS = kLevel<D, N>, XS = kSlice<D, N>, TOP = kPow<D, N - 1> / 4, QT = (TOP + NT - 1) / NT;
+    constexpr int QS = (NS / 4 + NT - 1) / NT;
+    static_assert(D % 4 == 0 && TOP % NT == 0, "whole quads of a word's siblings; every thread has quads of the longest words");
+    __shared__ __attribute__((aligned(16))) float s[NS];
+    __shared__ float x[2][XS];
+    const int tid = (int)threadIdx.x, i = (int)(blockIdx.x % D);
+    const int64_t b = blockIdx.x / D;
+    const float* rows = Sc + b * C * (int64_t)W;
+    f4 top[QT], next_top[QT], next_s[QS];
+    constexpr int T0 = kLevel<D, N>;
+    const int t0 = T0 + i * kPow<D, N - 1>;
+    slice_copy<D, 1, N - 1, NT>(true, i, rows, x[0], nullptr);
+#pragma unroll
+    for (int q = 0; q < QT; ++q) top[q] = *(const f4*)(rows + t0 + 4 * (tid + q * NT));
+    auto fetch = [&](int c) {
+        const float* S = rows + (int64_t)c * W;
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            next_s[q] = *(const f4*)(S + 4 * (e < NS / 4 ? e : 0));
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) next_top[q] = *(const f4*)(S + t0 + 4 * (tid + q * NT));
+    };
+    if (C > 1) fetch(1);
+    for (int c = 1; c < C; ++c) {
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            if (e < NS / 4) *(f4*)(s + 4 * e) = next_s[q];
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) top[q] += next_top[q];
+        __syncthreads();
+        fetch(c + 1 < C ? c + 1 : c);
+        const float* xo = x[(c - 1) & 1];
+        slice_levels<D, 1, N - 1, NT>(true, i, xo, s, x[c & 1], nullptr);
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const unsigned e = 4u * (unsigned)(tid + q * NT);
+            quad_cuts<D, N, 1>(xo, s, e, top[q]);
+        }
+        __syncthreads();
+    }
+    float* out = coeffs + b * (int64_t)W;
+    if (C == 1) __syncthreads();
+    const float* xo = x[(C - 1) & 1];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) *(f4*)(out + t0 + 4 * (tid + q * NT)) = top[q];
+    int w = 0;                                           // the shorter words of the slice, level by level
+    for (int n = 1, size = 1; n < N; ++n, size *= D) {
+        for (int e = tid; e < size; e += NT) out[w + i * size + e] = xo[(size - 1) / (D - 1) + e];
+        w += size * D;
+    }
+}
+
+// Over the words of length <= M, Sc [B][C] rows of sc_words floats, left and right [B][C] rows of those words: left[c] = S_0 .. S_c, right[c] = S_{c+1} .. S_{C-1} for c <= C - 2.
+// Workgroup (path, letter, direction).
+template <int D, int M, int NT>
+__global__ __launch_bounds__(NT) void chunk_slices_both_kernel(const float* __restrict__ Sc, int64_t sc_words, int C,
+                                                               float* __restrict__ left, float* __restrict__ right)
+{
+    constexpr int W = kLevel<D, M + 1>, XS = kSlice<D, M + 1>, QS = (W / 4 + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) float s[W];
+    __shared__ float x[2][XS];
+    const int tid = (int)threadIdx.x;
+    const bool from_left = blockIdx.x % 2 == 0;
+    const int i = (int)(blockIdx.x / 2 % D);
+    const int64_t b = blockIdx.x / (2 * D);
+    const float* rows = Sc + b * C * sc_words;
+    float* out_rows = (from_left ? left : right) + b * C * (int64_t)W;
+    // step n multiplies with chunk c0 + n dc; its product ends (from the right: begins) there
+    const int c0 = from_left ? 0 : C - 1, dc = from_left ? 1 : -1, steps = C - 1;
+    auto out_row = [&](int n) { return out_rows + (int64_t)(from_left ? n : C - 2 - n) * W; };
+    slice_copy<D, 1, M, NT>(from_left, i, rows + c0 * sc_words, x[0], out_row(0));
+    f4 next[QS];
+    auto fetch = [&](int c) {
+        const float* S = rows + c * sc_words;
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            next[q] = *(const f4*)(S + 4 * (e < W / 4 ? e : 0));
+        }
+    };
+    if (steps > 1) fetch(c0 + dc);
+    for (int n = 1; n < steps; ++n) {
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            const int e = tid + q * NT;
+            if (e < W / 4) *(f4*)(s + 4 * e) = next[q];
+        }
+        __syncthreads();
+        fetch(c0 + dc * (n + 1 < steps ? n + 1 : n));
+        slice_levels<D, 1, M, NT>(from_left, i, x[(n - 1) & 1], s, x[n & 1], out_row(n));
+        __syncthreads();
     }
 }
 
@@ -505,8 +678,38 @@ hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, fl
     if (lds <= 64 * 1024) chunk_adjoint_kernel<true><<<(unsigned)(B * C), 512, lds, stream>>>(grad, Q, Abar, C, skip_last, g);
     else if (subtree)
         chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, 2 * (size_t)g.ls[g.N] * sizeof(float), stream>>>(
-            grad, Q, Abar, C, zero, n_zero, g);
+            grad, Q, Abar, C, zero, n_zero, g.W, g);
     else chunk_adjoint_kernel<false><<<dim3((unsigned)(B * C), (unsigned)(g.N - 1)), 512, 0, stream>>>(grad, Q, Abar, C, skip_last, g);
+    return hipGetLastError();
+}
+
+hipError_t chunk_slices_forward(int d, int depth, const float* Sc, float* coeffs, int64_t B, int C, hipStream_t stream)
+{
+    if (B < 1 || C < 2 || B * d > 0x7fffffff) return hipErrorInvalidValue;
+    if (d == 8 && depth == 5) chunk_slices_forward_kernel<8, 5, 512><<<(unsigned)(B * 8), 512, 0, stream>>>(Sc, C, coeffs);
+    else if (d == 16 && depth == 4) chunk_slices_forward_kernel<16, 4, 512><<<(unsigned)(B * 16), 512, 0, stream>>>(Sc, C, coeffs);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t chunk_slices_both(int d, int depth, const float* Sc, int64_t sc_words, float* left, float* right, int64_t B, int C,
+                             hipStream_t stream)
+{
+    if (B < 1 || C < 2 || 2 * B * d > 0x7fffffff) return hipErrorInvalidValue;
+    if (d == 8 && depth == 5) chunk_slices_both_kernel<8, 4, 512><<<(unsigned)(B * 16), 512, 0, stream>>>(Sc, sc_words, C, left, right);
+    else if (d == 16 && depth == 4) chunk_slices_both_kernel<16, 3, 512><<<(unsigned)(B * 32), 512, 0, stream>>>(Sc, sc_words, C, left, right);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t chunk_adjoint_low(int d, int depth, const float* grad, const float* right, float* Abar, int64_t B, int C, float* zero,
+                             int64_t n_zero, hipStream_t stream)
+{
+    Levels g;
+    if (!make_levels(d, depth, g) || C < 2 || B < 1 || B * C > 0x7fffffff) return hipErrorInvalidValue;
+    const size_t lds = 2 * (size_t)g.ls[g.N] * sizeof(float);
+    if (lds > 64 * 1024) return hipErrorInvalidValue;
+    chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, lds, stream>>>(grad, right, Abar, C, zero, n_zero, g.ls[g.N], g);
     return hipGetLastError();
 }
 

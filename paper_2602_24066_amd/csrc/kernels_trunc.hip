@@ -699,7 +699,7 @@ template <int D, int N, int WQ, int T, int VG>
 __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::TWO_WORKGROUPS ? 2 : 1)) void trunc_mfma_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad,
     const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-    WindowList wl, float* gdx, float* resid)
+    int64_t row_words, WindowList wl, float* gdx, float* resid)
 {
     static_assert((D & (D - 1)) == 0, "the gradient reduction takes letters as bit fields of the lane number");
     constexpr int K = N - 2;
@@ -747,10 +747,11 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
     const float* X = path + (b * P + seg0) * D;
     const int64_t nW = level_start(D, N) + ipow(D, N);
     // rows of the last chunk of a path may live in arrays of their own ([B][|W|]: the caller's terminal signature
-    // and gradient); the others in a [B][C][|W|] array of signatures and, then, a [B][C - 1][|W|] array of adjoints
+    // and gradient); the others in a [B][C] array of signatures and, then, a [B][C - 1] array of adjoints, row_words floats
+    // a row: |W|, or the words shorter than N alone
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
-    const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * nW;
-    const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * nW;
+    const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * row_words;
+    const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * row_words;
     const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
 
     int offS[NBS];
@@ -1669,7 +1670,7 @@ template <int D, int N, int T>
 __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trunc_node_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad,
     const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-    WindowList wl, float* gdx, float* resid)
+    int64_t row_words, WindowList wl, float* gdx, float* resid)
 {
     static_assert((D & (D - 1)) == 0, "the gradient reduction takes letters as bit fields of the lane number");
     constexpr int K = N - 2;
@@ -1706,8 +1707,8 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
     // rows of the last chunk of a path may live in arrays of their own ([B][|W|]); the others in a [B][C][|W|] array of
     // signatures and, then, a [B][C - 1][|W|] array of adjoints
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
-    const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * nW;
-    const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * nW;
+    const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * row_words;
+    const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * row_words;
     const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
 
     // ---- state: signature and adjoints at the end of the row
@@ -1966,7 +1967,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
 template <int D, int N, int T = 8>
 hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const float* grad, const float* coeffs_last,
                                  const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc, float* gdx, float* resid,
-                                 hipStream_t stream, const WindowList& wl = WindowList())
+                                 hipStream_t stream, const WindowList& wl = WindowList(), int64_t row_words = 0)
 {
     using LY = NodeLds<D, N, T>;
     static_assert(LY::BYTES <= 160 * 1024, "LDS of one compute unit");
@@ -1978,7 +1979,7 @@ hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const f
         if (e != hipSuccess) return e;
     }
     trunc_node_bwd_kernel<D, N, T><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
-        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, wl, gdx, resid);
+        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, row_words > 0 ? row_words : level_start(D, N) + ipow(D, N), wl, gdx, resid);
     return hipGetLastError();
 }
 
@@ -2206,7 +2207,7 @@ hipError_t launch_trunc_tails_bwd(const float* path, const float* coeffs, const 
 template <int D, int N, int WQ, int T, int VG = T>
 hipError_t launch_trunc_mfma_bwd(const float* path, const float* coeffs, const float* grad, const float* coeffs_last,
                                  const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc, float* gdx, float* resid,
-                                 hipStream_t stream, const WindowList& wl = WindowList())
+                                 hipStream_t stream, const WindowList& wl = WindowList(), int64_t row_words = 0)
 {
     using G = MGeo<D, N, N - 2, WQ>;
     using LY = BwdLds<D, N, WQ, T, VG>;
@@ -2219,7 +2220,7 @@ hipError_t launch_trunc_mfma_bwd(const float* path, const float* coeffs, const f
         if (e != hipSuccess) return e;
     }
     trunc_mfma_bwd_kernel<D, N, WQ, T, VG><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
-        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, wl, gdx, resid);
+        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, row_words > 0 ? row_words : level_start(D, N) + ipow(D, N), wl, gdx, resid);
     return hipGetLastError();
 }
 
@@ -2264,6 +2265,18 @@ hipError_t trunc_forward(int d, int depth, const float* path, int64_t B, int64_t
     if (d == 4 && depth == 6) return launch_trunc_mfma_fwd<4, 6, kChainFwd46, 1>(path, B, P, C, Lc, coeffs, stream);
     if (d == 8 && depth == 5) return launch_trunc_mfma_fwd<8, 5, 3, 2>(path, B, P, C, Lc, coeffs, stream);
     if (d == 16 && depth == 4) return launch_trunc_mfma_fwd<16, 4, 2, 1>(path, B, P, C, Lc, coeffs, stream);
+    return hipErrorInvalidValue;
+}
+
+// The words shorter than the depth alone (signatures of chunks for a backward pass): a d-th of the work, one wavefront a row
+// for d = 8 and four for d = 16.
+bool trunc_low_available(int d, int depth) { return (d == 8 && depth == 5) || (d == 16 && depth == 4); }
+hipError_t trunc_forward_low(int d, int depth, const float* path, int64_t B, int64_t P, int64_t C, int64_t Lc, float* coeffs,
+                             hipStream_t stream)
+{
+    if (B * C > 65535 * 16) return hipErrorInvalidValue;
+    if (d == 8 && depth == 5) return launch_trunc_mfma_fwd<8, 4, 2, 2>(path, B, P, C, Lc, coeffs, stream);
+    if (d == 16 && depth == 4) return launch_trunc_mfma_fwd<16, 3, 2, 4>(path, B, P, C, Lc, coeffs, stream);
     return hipErrorInvalidValue;
 }
 
@@ -2319,30 +2332,30 @@ const char* trunc_backward_kernel_name(int d, int depth)
 // gdx: [B, L, d] accumulation buffer, zeroed by the caller
 hipError_t trunc_backward(int d, int depth, const float* path, const float* coeffs, const float* grad_coeffs,
                           const float* coeffs_last, const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-                          float* gdx, float* resid, int tile, hipStream_t stream)
+                          float* gdx, float* resid, int tile, hipStream_t stream, int64_t row_words)
 {
     if ((coeffs_last == nullptr) != (grad_last == nullptr)) return hipErrorInvalidValue;
     if (d == 4 && depth == 6)
-        return launch_trunc_node_bwd<4, 6>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        return launch_trunc_node_bwd<4, 6>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
     // d = 8: with the gradient sources in registers a wavefront needs a few KB of LDS whatever the tile; the tile length
     // only sets how often increments are staged and gradients flushed
     if (d == 8 && depth == 5) {
-        if (tile == 4) return launch_trunc_node_bwd<8, 5, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
-        if (tile == 16) return launch_trunc_node_bwd<8, 5, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
-        return launch_trunc_node_bwd<8, 5, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (tile == 4) return launch_trunc_node_bwd<8, 5, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        if (tile == 16) return launch_trunc_node_bwd<8, 5, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        return launch_trunc_node_bwd<8, 5, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
     }
     // d = 16: a tile of 16 segments fills the 16 columns of the time-batched matrix products.  With the gradient sources
     // parked in LDS for the whole tile a workgroup takes 126 KB, one per compute unit, and a lone wavefront issues vector
     // instructions at half the rate of its SIMD: that form (segments software-pipelined) is for launches that have no
     // second wavefront per SIMD to offer anyway.  With the sources of 4 segments in registers, summed by cross-lane moves,
-    // the workgroup needs 78 KB and two share a compute unit: taken from 2,048 wavefronts on.  tile = 16 / 4 force the
-    // two forms; 12 and 8 are shorter tiles (three quarters, half of the columns), measured slower, kept selectable.
+    // the workgroup needs 78 KB and two share a compute unit: taken for more than 1,024 wavefronts, which the first form walks
+    // in two rounds (18 paths x 591 segments in four chunks, 1,152 wavefronts: 212 -> 159 us).  tile = 16 / 4 force the two forms; 12 and 8 are shorter tiles (three quarters, half of the columns), measured slower, kept selectable.
     if (d == 16 && depth == 4) {
-        const int t = tile == 4 || tile == 8 || tile == 12 || tile == 16 ? tile : (B * C * 16 >= 2048 ? 4 : 16);
-        if (t == 4) return launch_trunc_mfma_bwd<16, 4, 1, 16, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
-        if (t == 8) return launch_trunc_mfma_bwd<16, 4, 1, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
-        if (t == 12) return launch_trunc_mfma_bwd<16, 4, 1, 12, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
-        return launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        const int t = tile == 4 || tile == 8 || tile == 12 || tile == 16 ? tile : (B * C * 16 > 1024 ? 4 : 16);
+        if (t == 4) return launch_trunc_mfma_bwd<16, 4, 1, 16, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        if (t == 8) return launch_trunc_mfma_bwd<16, 4, 1, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        if (t == 12) return launch_trunc_mfma_bwd<16, 4, 1, 12, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        return launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
     }
     return hipErrorInvalidValue;
 }
@@ -2373,7 +2386,9 @@ hipError_t trunc_backward_windows(int d, int depth, const float* path, const flo
                      : launch_trunc_node_bwd<8, 5, 8>(path, coeffs, grad_coeffs, nullptr, nullptr, B, P, 1, P - 1, gdx, nullptr, stream, wl);
     }
     if (d == 16 && depth == 4)
-        return launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, nullptr, nullptr, B, P, 1, P - 1, gdx, nullptr, stream, wl);
+        return B * wl.K * 16 > 1024
+                   ? launch_trunc_mfma_bwd<16, 4, 1, 16, 4>(path, coeffs, grad_coeffs, nullptr, nullptr, B, P, 1, P - 1, gdx, nullptr, stream, wl)
+                   : launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, nullptr, nullptr, B, P, 1, P - 1, gdx, nullptr, stream, wl);
     return hipErrorInvalidValue;
 }
 

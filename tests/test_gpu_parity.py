@@ -337,6 +337,44 @@ def test_time_chunks_of_small_launches_under_capture():
             S.sig_forward(ws, xs[0])
 
 
+@pytest.mark.parametrize("d,depth,B,L,chunks", [
+    (8, 5, 2, 70, 2), (8, 5, 3, 50, 5), (8, 5, 1, 200, 0), (8, 5, 70, 40, 3), (16, 4, 2, 70, 3), (16, 4, 1, 33, 8),
+    (16, 4, 3, 150, 0), (16, 4, 30, 40, 4)])
+def test_time_chunks_of_truncations_by_slices(d, depth, B, L, chunks):
+    """Few paths of the precompiled truncations with 8 and 16 letters: chunk products by slices in both directions (chunks that do
+    not divide the length, one to 16 of them, rows for one and for two wavefronts per SIMD), and the walk over whole paths that a
+    caller with the workspace for that gets."""
+    import ctypes
+    import torch
+    ws, _ = build_both("truncated", d, depth=depth)
+    lib = S.load_library()
+    X = make_path("iid", 7400 + L, B, L, d)
+    G = make_grad_coeffs(7500 + L, B, ws.size)
+    xp, grad = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    if chunks:
+        ws.set_option("chunks", chunks)
+    gdx = (4 * B * L * d + 255) // 256 * 256
+    nf, nb = int(lib.sig_forward_workspace_bytes(ws._h, B, L + 1)), int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1))
+    assert nf > 0 and nb > gdx
+    coeffs = S.sig_forward(ws, xp)
+    gp = S.sig_backward(ws, xp, coeffs, grad)
+    c2, g2 = torch.empty_like(coeffs), torch.empty_like(xp)
+    P = ctypes.c_void_p
+    wk = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    ws.set_option("chunks", 0)
+    stream = P(torch.cuda.current_stream().cuda_stream)
+    assert lib.sig_forward(ws._h, P(xp.data_ptr()), B, L + 1, P(c2.data_ptr()), None, 0, stream) == 0
+    assert lib.sig_backward(ws._h, P(xp.data_ptr()), P(coeffs.data_ptr()), P(grad.data_ptr()), B, L + 1, P(g2.data_ptr()),
+                            P(wk.data_ptr()), gdx, stream) == 0
+    torch.cuda.synchronize()
+    lengths = np.array([len(w) for w in O.truncated_words(d, depth)])
+    ref, gref = O.forward_dense(X, depth), O.backward_dense(X, depth, G.astype(np.float64))
+    for c, g in ((coeffs, gp), (c2, g2)):
+        for n, e in O.level_errors(c.cpu().numpy(), ref, lengths).items():
+            assert e <= FWD_TOL, f"level {n}: {e:.3e}"
+        assert O.grad_errors(g.cpu().numpy(), gref).max() <= BWD_TOL
+
+
 def test_checkpointed_word_sets_reject_bad_buffers():
     """Buffers that are missing, too small or misaligned are refused with an error code before anything is launched."""
     import ctypes

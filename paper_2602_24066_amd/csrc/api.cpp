@@ -915,10 +915,11 @@ sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesSh
 
 // rows: the B paths, with a window list the B * K (path, window) pairs, or (wl.win == nullptr, wl.K > 1) the K time chunks of
 // wl.max_len segments of every path; read straight from the path.  Backward over chunks: low_coeffs and low_grad hold
-// signature and adjoint at the end of every chunk but the last, [B][K - 1][words shorter than the depth].
+// signature and adjoint at the end of every chunk but the last, [B][K - 1][words shorter than the depth], or low_coeffs alone the
+// chunks' own signatures [B][K].  Forward: n_zero floats at zero are cleared on the way.
 hipError_t launch_lanes(hipFunction_t fn, const sig::LanesShape& s, const float* path, const float* coeffs_in, const float* grad,
                         int64_t B, int64_t n_points, float* out, hipStream_t st, const sig::WindowList& wl = sig::WindowList(),
-                        const float* low_coeffs = nullptr, const float* low_grad = nullptr)
+                        const float* low_coeffs = nullptr, const float* low_grad = nullptr, float* zero = nullptr, int64_t n_zero = 0)
 {
     const bool parts = wl.several_rows();
     long lB = (long)B, lP = (long)n_points, lK = (long)wl.rows_per_path(), lM = parts ? (long)wl.max_len : lP - 1;
@@ -931,7 +932,8 @@ hipError_t launch_lanes(hipFunction_t fn, const sig::LanesShape& s, const float*
                         (void*)&lM, (void*)&low_coeffs, (void*)&low_grad};
         return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
     }
-    void* args[] = {(void*)&path, (void*)&lB, (void*)&lP, (void*)&out, (void*)&win, (void*)&lK, (void*)&lM};
+    long lz = (long)n_zero;
+    void* args[] = {(void*)&path, (void*)&lB, (void*)&lP, (void*)&out, (void*)&win, (void*)&lK, (void*)&lM, (void*)&zero, (void*)&lz};
     return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
 }
 
@@ -1001,34 +1003,45 @@ hipError_t lanes_forward_chunked(const sig::WordSet& w, const LanesChunked& k, c
     void* args[] = {(void*)&Sc, (void*)&lC, (void*)&coeffs, (void*)&none};
     return hipModuleLaunchKernel(k.scan().fn, (unsigned)(B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, args, nullptr);
 }
-// backward, workspace: chunk signatures [B][C], products from the left, from the right and boundary adjoints [B][C - 1],
-// rows of words shorter than the depth
-size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch)
+// backward, workspace: chunk signatures [B][C] over the words shorter than the depth; where the lanes of the walk don't work out
+// signature and adjoints at the chunk ends from them, also products from the left, from the right and boundary adjoints [B][C - 1]
+size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, const Chunks& ch, bool arrays)
 {
-    return lanes_low_bytes(w, B, ch.C) + 3 * lanes_low_bytes(w, B, ch.C - 1);
+    return lanes_low_bytes(w, B, ch.C) + (arrays ? 3 * lanes_low_bytes(w, B, ch.C - 1) : 0);
+}
+// whether a call asks for those arrays: signatures that don't fit a wavefront's LDS, and counts set by the option "chunks"
+bool lanes_backward_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return w.opt.chunks > 0 || !lanes_shape_for(w, 1, B * ch.C).shares;
 }
 hipError_t lanes_backward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, const float* coeffs,
-                                  const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, float* grad_path,
+                                  const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, bool arrays, float* grad_path,
                                   void* workspace, hipStream_t st)
 {
     const size_t nb = lanes_low_bytes(w, B, ch.C - 1);
     unsigned char* base = (unsigned char*)workspace;
     float* Sc = (float*)base;
-    float* left = (float*)(base + lanes_low_bytes(w, B, ch.C));
-    float* right = (float*)((unsigned char*)left + nb);
-    float* abar = (float*)((unsigned char*)right + nb);
+    float* left = Sc;
+    float* abar = nullptr;
     sig::WindowList rows;
     rows.K = ch.C; rows.max_len = ch.Lc;
-    hipError_t e = launch_lanes(k.lower().fn, k.low, path, nullptr, nullptr, B, n_points, Sc, st, rows);
+    const int64_t n_path = B * n_points * w.d;                // cleared for the rows, which add into it
+    hipError_t e = launch_lanes(k.lower().fn, k.low, path, nullptr, nullptr, B, n_points, Sc, st, rows, nullptr, nullptr, grad_path,
+                                arrays ? 0 : n_path);
     if (e != hipSuccess) return e;
-    long lC = (long)ch.C, lC1 = lC - 1, lz = (long)(B * n_points * w.d);
-    void* scan_args[] = {(void*)&Sc, (void*)&lC, (void*)&left, (void*)&right};
-    e = hipModuleLaunchKernel(k.scan().fn, (unsigned)(2 * B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, scan_args, nullptr);
-    if (e != hipSuccess) return e;
-    void* adj_args[] = {(void*)&grad_coeffs, (void*)&right, (void*)&lC1, (void*)&abar, (void*)&grad_path, (void*)&lz};
-    e = hipModuleLaunchKernel(k.adjoint().fn, (unsigned)(B * (ch.C - 1) * w.d), 1, 1, (unsigned)k.adjoint().nw * 64, 1, 1, 0, st, adj_args,
-                              nullptr);
-    if (e != hipSuccess) return e;
+    if (arrays) {
+        left = (float*)(base + lanes_low_bytes(w, B, ch.C));
+        float* right = (float*)((unsigned char*)left + nb);
+        abar = (float*)((unsigned char*)right + nb);
+        long lC = (long)ch.C, lC1 = lC - 1, lz = (long)n_path;
+        void* scan_args[] = {(void*)&Sc, (void*)&lC, (void*)&left, (void*)&right};
+        e = hipModuleLaunchKernel(k.scan().fn, (unsigned)(2 * B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, scan_args, nullptr);
+        if (e != hipSuccess) return e;
+        void* adj_args[] = {(void*)&grad_coeffs, (void*)&right, (void*)&lC1, (void*)&abar, (void*)&grad_path, (void*)&lz};
+        e = hipModuleLaunchKernel(k.adjoint().fn, (unsigned)(B * (ch.C - 1) * w.d), 1, 1, (unsigned)k.adjoint().nw * 64, 1, 1, 0, st,
+                                  adj_args, nullptr);
+        if (e != hipSuccess) return e;
+    }
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
     e = launch_lanes(k.k->fn, k.main, path, coeffs, grad_coeffs, B, n_points, grad_path, st, rows, left, abar);
@@ -1391,7 +1404,7 @@ size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_
     const sig::WordSet& w = *W(ws);
     if (!use_trunc_backward(w, B) && use_lanes(w, B, n_points - 1)) {
         const Chunks ch = lanes_chunks(w, 1, B, n_points);
-        if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, ch));
+        if (ch.C > 1) n = std::max(n, lanes_backward_chunked_bytes(w, B, ch, lanes_backward_arrays(w, B, ch)));
     }
     if (plain_chunks_available(w, B)) {
         const Chunks ch = plain_chunks(w, 1, B, n_points);
@@ -1654,9 +1667,10 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     if (lanes_path && word_chunks && !residual) {
         const Chunks lch = lanes_chunks(w, 1, B, n_points);
         LanesChunked lc;
-        if (lch.C > 1 && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch) &&
+        const bool arrays = lch.C > 1 && lanes_backward_arrays(w, B, lch) && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, true);
+        if (lch.C > 1 && (arrays || (lanes_shape_for(w, 1, B * lch.C).shares && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, false))) &&
             lanes_chunk_kernels(w, 1, B * lch.C, how, lc)) {
-            hipError_t le = lanes_backward_chunked(w, lc, path, coeffs, grad_coeffs, B, n_points, lch, grad_path, workspace, st);
+            hipError_t le = lanes_backward_chunked(w, lc, path, coeffs, grad_coeffs, B, n_points, lch, arrays, grad_path, workspace, st);
             return le == hipSuccess ? SIG_OK : hip_fail(le);
         }
     }

@@ -48,6 +48,7 @@ void jit_release(JitKernel& k);
 // gradient tile, TS segments of increments staged at a time.
 struct LanesShape {
     bool ok, msum;                 // msum: gradient sums as matrix products
+    bool shares;                   // backward: a wavefront's LDS holds a chunk signature over the words shorter than the depth
     int R, T, TS, nwb;
     int64_t lanes, waves;
     int chain;                     // multiply-adds of a lane's chain per segment

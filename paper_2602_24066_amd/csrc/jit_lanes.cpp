@@ -159,8 +159,10 @@ __device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, lo
 #if !BACKWARD
 extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float* __restrict__ path, long B, long P,
                                                                       float* __restrict__ coeffs, const long* __restrict__ win,
-                                                                      long KW, long max_len)
+                                                                      long KW, long max_len, float* __restrict__ zero, long n_zero)
 {
+    // n_zero floats at `zero` are cleared on the way for the kernel that runs next
+    for (long e = (long)blockIdx.x * (64 * NWB) + threadIdx.x; e < n_zero; e += (long)gridDim.x * (64 * NWB)) zero[e] = 0.0f;
     __shared__ __attribute__((aligned(16))) float smem[NWB * TILE_F];
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -338,6 +340,90 @@ __device__ __forceinline__ void letter_sums(const float* v, const float* __restr
 }
 #endif
 
+// Signature and adjoints at the end of chunk `part` of a path, from the signatures S_0 .. S_{C-1} of its chunks over the words
+// shorter than N (rows), for the lane's words alone: what a kernel for the products and one for the adjoints would write to arrays.
+//   - S_0 S_1 .. S_part on the lane's chain needs the chain itself and infixes of the lane's word;
+//   - the adjoints at the end of the path, taken back over chunks C - 1 .. part + 1: Abar(u) += sum_v Abar(u v) S_c(v).  The walk is
+//     linear in them and a chain word's may be spread over the lanes that share it, so a lane adds the terms whose word u v is its
+//     own (in its registers) to its share of Abar(u): no sum over lanes, nothing exchanged.
+// The rows pass through the wavefront's LDS one after the other, each loaded while the one before is used.
+// Bound by the latency of a row (0.3-0.6 us); two launches of 5 us and the arrays' traffic saved (256 paths x 199 segments, d = 10,
+// depth 4: 30 us of 181).
+__device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, int part, int C, int p, int lane, float* st, float (&Sc)[K],
+                                               float (&Ac)[K], float (&A1)[D]
+#if R == 2
+                                               , float (&S1)[D], float (&An)[D][D]
+#endif
+                                               )
+{
+    constexpr int NLOW = (int)level_start(N), NQ = (NLOW + 63) / 64;
+    float ahead[NQ];
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) ahead[q] = rows[(long)c * NLOW + (lane + 64 * q < NLOW ? lane + 64 * q : 0)];
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int i = 0; i < C; ++i) {
+        wave_lds_fence();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (lane + 64 * q < NLOW) st[lane + 64 * q] = ahead[q];
+        wave_lds_fence();
+        if (i + 1 < C) fetch(i + 1 <= part ? i + 1 : C - (i + 1 - part));       // up to `part`, then back from the last
+        if (i <= part) {
+#if R == 2
+#pragma unroll
+            for (int j = 0; j < D; ++j) {                       // longer words first: a word reads the chain as it was
+                float v = st[level_start(K + 1) + p * D + j];
+                if (i > 0) {
+                    v += S1[j];
+#pragma unroll
+                    for (int m = 1; m <= K; ++m)
+                        v = __builtin_fmaf(Sc[m - 1], st[level_start(K + 1 - m) + (p % ipow(D, K - m)) * D + j], v);
+                }
+                S1[j] = v;
+            }
+#endif
+#pragma unroll
+            for (int k = K; k >= 1; --k) {
+                const int u = p / ipow(D, K - k);
+                float v = st[level_start(k) + u];
+                if (i > 0) {
+                    v += Sc[k - 1];
+#pragma unroll
+                    for (int m = 1; m < k; ++m) v = __builtin_fmaf(Sc[m - 1], st[level_start(k - m) + u % ipow(D, k - m)], v);
+                }
+                Sc[k - 1] = v;
+            }
+        } else {
+#pragma unroll
+            for (int k = 1; k <= K; ++k) {
+                const int after = p % ipow(D, K - k);           // the lane's word without its first k letters
+                float v = Ac[k - 1];
+#pragma unroll
+                for (int n = k + 1; n <= K; ++n)
+                    v = __builtin_fmaf(Ac[n - 1], st[level_start(n - k) + (p / ipow(D, K - n)) % ipow(D, n - k)], v);
+#pragma unroll
+                for (int j = 0; j < D; ++j) v = __builtin_fmaf(A1[j], st[level_start(K - k + 1) + after * D + j], v);
+#if R == 2
+#pragma unroll
+                for (int j = 0; j < D; ++j)
+#pragma unroll
+                    for (int jj = 0; jj < D; ++jj) v = __builtin_fmaf(An[j][jj], st[level_start(K - k + 2) + (after * D + j) * D + jj], v);
+#endif
+                Ac[k - 1] = v;
+            }
+#if R == 2
+#pragma unroll
+            for (int j = 0; j < D; ++j)
+#pragma unroll
+                for (int jj = 0; jj < D; ++jj) A1[j] = __builtin_fmaf(An[j][jj], st[jj], A1[j]);
+#endif
+        }
+    }
+}
+
 extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float* __restrict__ path,
         const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* grad_path,
         const long* __restrict__ win, long KW, long max_len, const float* __restrict__ low_coeffs, const float* __restrict__ low_grad)
@@ -370,12 +456,13 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     // Whole paths and windows have a row of their own in coeffs and grad.  A time chunk takes the adjoints of the words of
     // length N, constant in time, from its path's row, and so does a path's last chunk with all others; for the chunks
     // before it, signature and adjoints at the end of the chunk (words shorter than N, the longest are never
-    // reconstructed) are rows of low_coeffs and low_grad [B][KW - 1].
+    // reconstructed) are rows of low_coeffs and low_grad [B][KW - 1].  Without low_grad the rows of low_coeffs [B][KW] are the
+    // chunks' own signatures, from which a lane works out what it needs (below).
     const long whole = win == nullptr ? b : row;
-    const bool inner = win == nullptr && part + 1 < KW;
+    const bool inner = win == nullptr && part + 1 < KW, given = inner && low_grad != nullptr;
     const float* gr = grad + whole * NWORDS;
-    const float* cf = inner ? low_coeffs + (b * (KW - 1) + part) * level_start(N) : coeffs + whole * NWORDS;
-    const float* gl = inner ? low_grad + (b * (KW - 1) + part) * level_start(N) : gr;
+    const float* cf = given ? low_coeffs + (b * (KW - 1) + part) * level_start(N) : coeffs + whole * NWORDS;
+    const float* gl = given ? low_grad + (b * (KW - 1) + part) * level_start(N) : gr;
     float* const gp_row = grad_path + (b * P + first) * D;      // the gradients of overlapping windows add up here
 
     // signature and adjoints at the end of the path; a word shared by several lanes has its adjoint in the first
@@ -397,6 +484,13 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         for (int jj = 0; jj < D; ++jj) An[j][jj] = valid ? gr[level_start(K + 2) + ((long)p * D + j) * D + jj] : 0.0f;
     }
 #endif
+    if constexpr (level_start(N) <= BW_PER_WAVE) {
+        if (inner && !given) chunk_boundary(low_coeffs + b * KW * level_start(N), (int)part, (int)KW, p, lane, Ec, Sc, Ac, A1
+#if R == 2
+                                            , S1, An
+#endif
+                                            );
+    }
 #if MSUM
     // left factors: lane (16 g + j) holds row j, words p0 + 16 g + i, i = 0 .. 15
     const int col = lane & 15, grp = lane >> 4;
@@ -814,8 +908,10 @@ extern "C" __global__ __launch_bounds__(NT) void sig_scan_lanes(const float* __r
 #elif PART == 3
 // Depth 2: the chunk signatures over the words shorter than the depth are the chunks' displacements (a wavefront per row).
 extern "C" __global__ __launch_bounds__(256) void sig_low_lanes(const float* __restrict__ path, long B, long P, float* __restrict__ coeffs,
-                                                                const long* __restrict__, long KW, long max_len)
+                                                                const long* __restrict__, long KW, long max_len,
+                                                                float* __restrict__ zero, long n_zero)
 {
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n_zero; e += (long)gridDim.x * 256) zero[e] = 0.0f;
     const int lane = threadIdx.x & 63;
     const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= B * KW || lane >= D) return;
@@ -888,6 +984,15 @@ extern "C" __global__ __launch_bounds__(NT) void sig_adjoint_lanes(const float* 
 
 }  // namespace
 
+namespace {
+int64_t words_up_to(int d, int n)
+{
+    int64_t r = 0, p = 1;
+    for (int m = 1; m <= n; ++m) { p *= d; r += p; }
+    return r;
+}
+}  // namespace
+
 LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
 {
     LanesShape best{};
@@ -953,6 +1058,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
             if (s.TS * d > 64 && s.TS * d > staged) s.TS = 1;
         }
         const size_t per_wave = lds_bytes(s.T, s.TS);
+        s.shares = backward && words_up_to(d, depth - 1) * sizeof(float) <= per_wave;
         s.nwb = (int)(per_wave * 4 <= 64 * 1024 ? 4 : (per_wave * 2 <= 64 * 1024 ? 2 : (per_wave <= 64 * 1024 ? 1 : 0)));
         s.ok = s.nwb > 0;
         if (s.ok && (!best.ok || cost < best_cost)) {
@@ -964,12 +1070,6 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
 }
 
 namespace {
-int64_t words_up_to(int d, int n)
-{
-    int64_t r = 0, p = 1;
-    for (int m = 1; m <= n; ++m) { p *= d; r += p; }
-    return r;
-}
 // words of length `top` that a slice holds, over the threads of a workgroup
 int scan_threads(int64_t n_top) { return n_top <= 2048 ? 256 : (n_top <= 8192 ? 512 : 1024); }
 }  // namespace
@@ -993,7 +1093,7 @@ bool lanes_chunks_available(int d, int depth)
 // segments, d = 7, depth 4: 30 -> 15 us, 8 x 1,000, d = 3, depth 5: 84 -> 17; backward 72 -> 37 and 301 -> 41.
 int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels)
 {
-    const double words = (double)words_up_to(d, depth), k = words / 1000.0;
+    const double words = (double)words_up_to(d, depth), low_words = (double)words_up_to(d, depth - 1), k = words / 1000.0;
     const double low_waves = (double)lanes_low_shape(d, depth).waves;
     const double low_exponent = backward ? 0.4 : 0.07, scan_exponent = backward ? -0.12 : 0.21;
     // two more launches backward: at least their host time
@@ -1024,6 +1124,9 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         const double Lc = (double)((L + C - 1) / C);
         const double t = (backward ? 8.5 : 3.7) + Lc * rounds * (latency + issue * std::max(1.0, waves / rounds));
         if (C == 1) return t;
+        // without arrays at the boundaries: one launch in place of the clearing one, and every wavefront passes the chunk signatures
+        const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : 0.0035 * (d + (double)d * d));
+        if (backward && s.shares) return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
         return t + launches + (double)C * product + (backward ? 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0) : 0.0);
     };
     double best = 0.93 * time(1);

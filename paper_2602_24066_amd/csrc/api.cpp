@@ -893,7 +893,7 @@ sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesSh
     sig::JitKernel* k = nullptr;
     {
         std::lock_guard<std::mutex> lock(g_jit_mutex);
-        sig::JitKernel*& slot = w.lanes[dir][dir == 1 && s.R == 1 && w.d == 2 && !s.msum ? 2 : s.R - 1];
+        sig::JitKernel*& slot = w.lanes[dir][(dir == 1 && s.R == 1 && w.d == 2 && !s.msum) || s.split == 2 ? 2 : s.R - 1];
         if (!slot) slot = new (std::nothrow) sig::JitKernel;
         k = slot;
     }
@@ -1372,7 +1372,7 @@ static hipError_t low_backward(const sig::WordSet& w, const float* path, const f
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
     e = sig::trunc_backward(w.d, w.depth, path, left, Abar, coeffs, grad_coeffs, B, n_points, ch.C, ch.Lc, gdx, nullptr, w.opt.bwd_tile, st,
-                            w.level_start[(size_t)w.depth]);
+                            true);
     if (pe) (void)hipEventRecord(pe[1], st);
     return e == hipSuccess ? sig::grad_points(gdx, B, n_points, w.d, grad_path, st) : e;
 }
@@ -1593,7 +1593,7 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
     const int64_t n_gdx = B * (n_points - 1) * w.d;                 // cleared by the launch of the adjoints
     hipError_t e = hipSuccess;
     const float* row_coeffs = ckpt;
-    int64_t row_words = nW;
+    bool low = false;
     if (ch.C > 2 && sig::trunc_low_available(w.d, w.depth)) {
         // products by slices over the words shorter than the depth, in rows of those (less than the workspace holds)
         const size_t lb = lanes_low_bytes(w, B, ch.C);
@@ -1602,7 +1602,7 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
         e = sig::chunk_slices_both(w.d, w.depth, ckpt, nW, left, right, B, (int)ch.C, st);
         if (e == hipSuccess) e = sig::chunk_adjoint_low(w.d, w.depth, grad_coeffs, right, Abar, B, (int)ch.C, gdx, n_gdx, st);
         row_coeffs = left;
-        row_words = w.level_start[(size_t)w.depth];
+        low = true;
     } else if (ch.C == 2) {
         // two chunks: the signature at the end of the first is the first chunk's own, what follows it the second's
         e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, Abar, B, 2, true, st, gdx, n_gdx);
@@ -1618,7 +1618,7 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
     if (pe) (void)hipEventRecord(pe[0], st);
     // the rows of the last chunk are the caller's terminal signature and gradient themselves
     e = sig::trunc_backward(w.d, w.depth, path, row_coeffs, Abar, coeffs, grad_coeffs, B, n_points, ch.C, ch.Lc, gdx, nullptr,
-                            w.opt.bwd_tile, st, row_words);
+                            w.opt.bwd_tile, st, low);
     if (pe) (void)hipEventRecord(pe[1], st);
     if (e != hipSuccess) return hip_fail(e);
     e = sig::grad_points(gdx, B, n_points, w.d, grad_path, st);

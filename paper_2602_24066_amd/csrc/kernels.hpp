@@ -154,7 +154,7 @@ hipError_t trunc_backward_windows(int d, int depth, const float* path, const flo
 hipError_t trunc_backward(int d, int depth, const float* path, const float* coeffs, const float* grad_coeffs,
                           const float* coeffs_last, const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
                           float* gdx, float* resid /*[B], zeroed by the caller, or nullptr*/, int tile, hipStream_t stream,
-                          int64_t row_words = 0 /* floats a row of coeffs and grad; 0: |W| */);
+                          bool low = false /* coeffs and grad: rows of the words shorter than the depth (trunc_low_available) */);
 const char* trunc_backward_kernel_name(int d, int depth);   // of the kernel trunc_backward launches
 
 // d = 4: backward with one wavefront per row (a lane holds a word of length N - 3 and its four children); stores

@@ -695,11 +695,11 @@ struct BwdLds {
     static constexpr size_t BYTES = ((size_t)EC_FLOATS + (size_t)kWavesPerBlock * PER_WAVE) * sizeof(float);
 };
 
-template <int D, int N, int WQ, int T, int VG>
+template <int D, int N, int WQ, int T, int VG, bool LOW>
 __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::TWO_WORKGROUPS ? 2 : 1)) void trunc_mfma_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad,
     const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-    int64_t row_words, WindowList wl, float* gdx, float* resid)
+    WindowList wl, float* gdx, float* resid)
 {
     static_assert((D & (D - 1)) == 0, "the gradient reduction takes letters as bit fields of the lane number");
     constexpr int K = N - 2;
@@ -747,9 +747,10 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
     const float* X = path + (b * P + seg0) * D;
     const int64_t nW = level_start(D, N) + ipow(D, N);
     // rows of the last chunk of a path may live in arrays of their own ([B][|W|]: the caller's terminal signature
-    // and gradient); the others in a [B][C] array of signatures and, then, a [B][C - 1] array of adjoints, row_words floats
-    // a row: |W|, or the words shorter than N alone
+    // and gradient); the others in a [B][C] array of signatures and, then, a [B][C - 1] array of adjoints, of all words
+    // or (LOW) of those shorter than N alone
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
+    const int64_t row_words = LOW ? level_start(D, N) : nW;
     const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * row_words;
     const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * row_words;
     const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
@@ -1666,11 +1667,11 @@ struct NodeLds {
 };
 
 // (the shortest tile is for launches with two wavefronts per SIMD: its registers are held to half a SIMD's)
-template <int D, int N, int T>
+template <int D, int N, int T, bool LOW>
 __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trunc_node_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad,
     const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-    int64_t row_words, WindowList wl, float* gdx, float* resid)
+    WindowList wl, float* gdx, float* resid)
 {
     static_assert((D & (D - 1)) == 0, "the gradient reduction takes letters as bit fields of the lane number");
     constexpr int K = N - 2;
@@ -1707,6 +1708,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
     // rows of the last chunk of a path may live in arrays of their own ([B][|W|]); the others in a [B][C][|W|] array of
     // signatures and, then, a [B][C - 1][|W|] array of adjoints
     const bool in_last = coeffs_last != nullptr && row - b * C == C - 1;
+    const int64_t row_words = LOW ? level_start(D, N) : nW;
     const float* cf = in_last ? coeffs_last + b * nW : coeffs + row * row_words;
     const float* gr = in_last ? grad_last + b * nW : grad + (coeffs_last != nullptr ? row - b : row) * row_words;
     const float* gleaf = coeffs_last != nullptr ? grad_last + b * nW : gr;   // adjoints of the longest words: constant in time
@@ -1964,10 +1966,10 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
     }
 }
 
-template <int D, int N, int T = 8>
+template <int D, int N, int T = 8, bool LOW = false>
 hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const float* grad, const float* coeffs_last,
                                  const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc, float* gdx, float* resid,
-                                 hipStream_t stream, const WindowList& wl = WindowList(), int64_t row_words = 0)
+                                 hipStream_t stream, const WindowList& wl = WindowList())
 {
     using LY = NodeLds<D, N, T>;
     static_assert(LY::BYTES <= 160 * 1024, "LDS of one compute unit");
@@ -1975,11 +1977,11 @@ hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const f
     const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (LY::BYTES > 64 * 1024) {                 // above the default limit the kernel has to be told once
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_node_bwd_kernel<D, N, T>), (int)LY::BYTES);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_node_bwd_kernel<D, N, T, LOW>), (int)LY::BYTES);
         if (e != hipSuccess) return e;
     }
-    trunc_node_bwd_kernel<D, N, T><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
-        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, row_words > 0 ? row_words : level_start(D, N) + ipow(D, N), wl, gdx, resid);
+    trunc_node_bwd_kernel<D, N, T, LOW><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
+        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, wl, gdx, resid);
     return hipGetLastError();
 }
 
@@ -2204,10 +2206,10 @@ hipError_t launch_trunc_tails_bwd(const float* path, const float* coeffs, const 
     return hipGetLastError();
 }
 
-template <int D, int N, int WQ, int T, int VG = T>
+template <int D, int N, int WQ, int T, int VG = T, bool LOW = false>
 hipError_t launch_trunc_mfma_bwd(const float* path, const float* coeffs, const float* grad, const float* coeffs_last,
                                  const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc, float* gdx, float* resid,
-                                 hipStream_t stream, const WindowList& wl = WindowList(), int64_t row_words = 0)
+                                 hipStream_t stream, const WindowList& wl = WindowList())
 {
     using G = MGeo<D, N, N - 2, WQ>;
     using LY = BwdLds<D, N, WQ, T, VG>;
@@ -2216,11 +2218,11 @@ hipError_t launch_trunc_mfma_bwd(const float* path, const float* coeffs, const f
     const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (LY::BYTES > 64 * 1024) {                 // above the default limit the kernel has to be told once
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_mfma_bwd_kernel<D, N, WQ, T, VG>), (int)LY::BYTES);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_mfma_bwd_kernel<D, N, WQ, T, VG, LOW>), (int)LY::BYTES);
         if (e != hipSuccess) return e;
     }
-    trunc_mfma_bwd_kernel<D, N, WQ, T, VG><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
-        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, row_words > 0 ? row_words : level_start(D, N) + ipow(D, N), wl, gdx, resid);
+    trunc_mfma_bwd_kernel<D, N, WQ, T, VG, LOW><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
+        path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, wl, gdx, resid);
     return hipGetLastError();
 }
 
@@ -2332,17 +2334,19 @@ const char* trunc_backward_kernel_name(int d, int depth)
 // gdx: [B, L, d] accumulation buffer, zeroed by the caller
 hipError_t trunc_backward(int d, int depth, const float* path, const float* coeffs, const float* grad_coeffs,
                           const float* coeffs_last, const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
-                          float* gdx, float* resid, int tile, hipStream_t stream, int64_t row_words)
+                          float* gdx, float* resid, int tile, hipStream_t stream, bool low)
 {
     if ((coeffs_last == nullptr) != (grad_last == nullptr)) return hipErrorInvalidValue;
+    if (low && !trunc_low_available(d, depth)) return hipErrorInvalidValue;
     if (d == 4 && depth == 6)
-        return launch_trunc_node_bwd<4, 6>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        return launch_trunc_node_bwd<4, 6>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
     // d = 8: with the gradient sources in registers a wavefront needs a few KB of LDS whatever the tile; the tile length
     // only sets how often increments are staged and gradients flushed
     if (d == 8 && depth == 5) {
-        if (tile == 4) return launch_trunc_node_bwd<8, 5, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
-        if (tile == 16) return launch_trunc_node_bwd<8, 5, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
-        return launch_trunc_node_bwd<8, 5, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        if (low) return launch_trunc_node_bwd<8, 5, 8, true>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (tile == 4) return launch_trunc_node_bwd<8, 5, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (tile == 16) return launch_trunc_node_bwd<8, 5, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        return launch_trunc_node_bwd<8, 5, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
     }
     // d = 16: a tile of 16 segments fills the 16 columns of the time-batched matrix products.  With the gradient sources
     // parked in LDS for the whole tile a workgroup takes 126 KB, one per compute unit, and a lone wavefront issues vector
@@ -2352,10 +2356,14 @@ hipError_t trunc_backward(int d, int depth, const float* path, const float* coef
     // in two rounds (18 paths x 591 segments in four chunks, 1,152 wavefronts: 212 -> 159 us).  tile = 16 / 4 force the two forms; 12 and 8 are shorter tiles (three quarters, half of the columns), measured slower, kept selectable.
     if (d == 16 && depth == 4) {
         const int t = tile == 4 || tile == 8 || tile == 12 || tile == 16 ? tile : (B * C * 16 > 1024 ? 4 : 16);
-        if (t == 4) return launch_trunc_mfma_bwd<16, 4, 1, 16, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
-        if (t == 8) return launch_trunc_mfma_bwd<16, 4, 1, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
-        if (t == 12) return launch_trunc_mfma_bwd<16, 4, 1, 12, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
-        return launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, WindowList(), row_words);
+        if (low)
+            return t == 4 || t == 12
+                       ? launch_trunc_mfma_bwd<16, 4, 1, 16, 4, true>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream)
+                       : launch_trunc_mfma_bwd<16, 4, 1, 16, 16, true>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (t == 4) return launch_trunc_mfma_bwd<16, 4, 1, 16, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (t == 8) return launch_trunc_mfma_bwd<16, 4, 1, 8>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        if (t == 12) return launch_trunc_mfma_bwd<16, 4, 1, 12, 4>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
+        return launch_trunc_mfma_bwd<16, 4, 1, 16>(path, coeffs, grad_coeffs, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -50,6 +50,7 @@ struct LanesShape {
     bool ok, msum;                 // msum: gradient sums as matrix products
     bool shares;                   // backward: a wavefront's LDS holds a chunk signature over the words shorter than the depth
     int R, T, TS, nwb;
+    int split;                     // wavefronts that share the children of 64 words (forward, R = 2: 1 or 2)
     int64_t lanes, waves;
     int chain;                     // multiply-adds of a lane's chain per segment
     double per_lane;               // instructions of a lane per segment, for comparing shapes

@@ -117,7 +117,7 @@ struct Segment {
         for (int k = 0; k < K; ++k) {
             const float* src = Ec + (at * D + letter[k]) * NC;
 #pragma unroll
-            for (int t = 0; t <= N - (k + 1); ++t) ec[k][t] = src[t];
+            for (int t = 0; t <= N - (k + 1) + (BACKWARD && k > 0 ? 1 : 0); ++t) ec[k][t] = src[t];
         }
     }
 };
@@ -127,7 +127,7 @@ struct Segment {
 // Two levels below u fill the registers with their own state: one segment after the other there, and forward, beyond 48
 // values (LAZY), every read where it is used (256 x 199 segments, 10 letters, depth 4: 58 us against 64 in pairs; 16 x 100, 6
 // letters, depth 6: 34 against 30).
-#define LAZY (R == 2 && D * D + D > 48)
+#define LAZY (R == 2 && (D + SP - 1) / SP * (D + 1) > 48)
 #define GROUP (LAZY || TS % 2 ? 1 : (R == 1 && TS % 4 == 0 && DP + K * NC <= 32 ? 4 : 2))
 // Two letters and a chain of seven or more: the addresses of the 190 predicated reads that sum the short runs do not change
 // from tile to tile, and held in registers over the loop they cost half the speed, as do two segments or two row sums in flight
@@ -157,6 +157,10 @@ __device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, lo
 }
 
 #if !BACKWARD
+// SP = 2 (two levels below u): two wavefronts share 64 words, each with half of the children and what lies below them, both with
+// the whole chain.  For batches that would leave SIMDs without a wavefront otherwise: the halves cost a chain more, time chunks
+// their signatures' traffic (256 paths x 199 segments, d = 10, depth 4: 60 us in two chunks -> 48 us whole).
+#define DJ ((D + SP - 1) / SP)
 extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float* __restrict__ path, long B, long P,
                                                                       float* __restrict__ coeffs, const long* __restrict__ win,
                                                                       long KW, long max_len, float* __restrict__ zero, long n_zero)
@@ -167,13 +171,14 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long wave = (long)blockIdx.x * NWB + wib;
-    if (wave >= B * KW * WAVES) return;                  // wavefronts share nothing: no barrier is skipped
+    if (wave >= B * KW * WAVES * SP) return;             // wavefronts share nothing: no barrier is skipped
     float* Ec = smem + wib * TILE_F;
     const float* E0 = Ec + TS * D * NC;
-    const long row = wave / WAVES;
+    const long row = wave / (WAVES * SP);
     long b, part, first, L;
     row_of(win, KW, max_len, row, P, b, part, first, L);
-    const int p0 = __builtin_amdgcn_readfirstlane((int)(wave - row * WAVES) * 64);
+    const int in_row = __builtin_amdgcn_readfirstlane((int)(wave - row * (WAVES * SP)));
+    const int p0 = in_row / SP * 64, j0 = in_row % SP * DJ;          // first word, first child
     const bool valid = p0 + lane < NL;
     const int p = valid ? p0 + lane : NL - 1;
     int letter[K];
@@ -184,15 +189,15 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
     }
     const float* X = path + (b * P + first) * D;
 
-    float Sc[K], S1[D];
+    float Sc[K], S1[DJ];
 #pragma unroll
     for (int k = 0; k < K; ++k) Sc[k] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < D; ++j) S1[j] = 0.0f;
+    for (int j = 0; j < DJ; ++j) S1[j] = 0.0f;
 #if R == 2
-    float S2[D][D];
+    float S2[DJ][D];
 #pragma unroll
-    for (int j = 0; j < D; ++j)
+    for (int j = 0; j < DJ; ++j)
 #pragma unroll
         for (int jj = 0; jj < D; ++jj) S2[j][jj] = 0.0f;
 #endif
@@ -241,17 +246,30 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
                 Sc[k - 1] = __builtin_fmaf(src[0], ap[k - 1][1], Sc[k - 1]);
             }
 #if R == 2
+            // the increments of the wavefront's own children (of half of an odd alphabet the last is none: its place is padding)
+#if SP == 1
             float e1[DP];
             load_row(E0 + TS * DP + tt * DP, e1);
+            const float (&own)[DP] = e0;
+#else
+            float e1[DJ], own[DJ];
+#pragma unroll
+            for (int j = 0; j < DJ; ++j) {
+                own[j] = E0[tt * DP + j0 + j];
+                e1[j] = E0[TS * DP + tt * DP + j0 + j];
+            }
+#endif
+#else
+            const float (&own)[DP] = e0;
 #endif
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
+            for (int j = 0; j < DJ; ++j) {
 #if R == 2
                 const float Gp = __builtin_fmaf(e1[j], ap[K][2], S1[j]);
 #pragma unroll
                 for (int jj = 0; jj < D; ++jj) S2[j][jj] = __builtin_fmaf(e0[jj], Gp, S2[j][jj]);
 #endif
-                S1[j] = __builtin_fmaf(e0[j], ap[K][1], S1[j]);
+                S1[j] = __builtin_fmaf(own[j], ap[K][1], S1[j]);
             }
           }
         }
@@ -261,13 +279,14 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
     float* out = coeffs + row * NWORDS;
 #pragma unroll
     for (int k = 1; k <= K; ++k)
-        if (p % ipow(D, K - k) == 0) out[level_start(k) + p / ipow(D, K - k)] = Sc[k - 1];
+        if (j0 == 0 && p % ipow(D, K - k) == 0) out[level_start(k) + p / ipow(D, K - k)] = Sc[k - 1];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-        out[level_start(K + 1) + (long)p * D + j] = S1[j];
+    for (int j = 0; j < DJ; ++j) {
+        if (SP > 1 && j0 + j >= D) break;
+        out[level_start(K + 1) + (long)p * D + j0 + j] = S1[j];
 #if R == 2
 #pragma unroll
-        for (int jj = 0; jj < D; ++jj) out[level_start(K + 2) + ((long)p * D + j) * D + jj] = S2[j][jj];
+        for (int jj = 0; jj < D; ++jj) out[level_start(K + 2) + ((long)p * D + j0 + j) * D + jj] = S2[j][jj];
 #endif
     }
 }
@@ -494,15 +513,28 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #if MSUM
     // left factors: lane (16 g + j) holds row j, words p0 + 16 g + i, i = 0 .. 15
     const int col = lane & 15, grp = lane >> 4;
+    // (the loads from clamped addresses, all in flight at once; the letters through LDS instead of sixteen times K divisions)
     float leaf_rows[16], chain_rows[K][16], later[4];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        int q = p0 + grp * 16 + i;
-        leaf_rows[i] = q < NL && col < D ? gr[level_start(N) + (long)q * D + col] : 0.0f;
-        q = q < NL ? q : NL - 1;                               // lanes past the last word contribute zeros
-#pragma unroll
-        for (int k = K - 1; k >= 0; --k) { chain_rows[k][i] = q % D == col ? 1.0f : 0.0f; q /= D; }
+        const int q = p0 + grp * 16 + i;
+        leaf_rows[i] = gr[level_start(N) + (long)(q < NL ? q : NL - 1) * D + (col < D ? col : 0)];
     }
+    wave_lds_fence();
+#pragma unroll
+    for (int k = 0; k < K; ++k) Vb[k * 64 + lane] = (float)letter[k];
+    wave_lds_fence();
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f4 v = *(const f4*)(Vb + k * 64 + grp * 16 + 4 * i);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) chain_rows[k][4 * i + r] = v[r] == (float)col ? 1.0f : 0.0f;
+        }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) leaf_rows[i] = p0 + grp * 16 + i < NL && col < D ? leaf_rows[i] : 0.0f;   // (words past the last: zeros)
+    wave_lds_fence();
 #pragma unroll
     for (int r = 0; r < 4; ++r) later[r] = 0.0f;
 #else
@@ -559,11 +591,6 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #else
             float* vb = Vb + tt * 64 + lane;
 #endif
-            float gb[K + 1][N + 2];
-#pragma unroll
-            for (int k = 0; k <= K; ++k)
-#pragma unroll
-                for (int t = 0; t < N + 2; ++t) gb[k][t] = 0.0f;
             float g1 = 0.0f;
 #if R == 1
             // the leaves: constant adjoints
@@ -599,24 +626,35 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                 g1 = __builtin_fmaf(e0[j], q0, g1);
                 g2 = __builtin_fmaf(e1[j], h, g2);
             }
-            gb[K][2] = g2;
 #pragma unroll
             for (int j = 0; j < D; ++j) vb[j * T * 64] = y[j];
 #endif
-            gb[K][1] = g1;
-            // the chain
+            // The chain, with the pushed adjoints gbar_k[t] kept as h[t] = gbar_k[t] / (t + 1): the gradient takes them so, the push
+            // to the parent, gbar_{k-1}[t + 1] = dX / (t + 1) gbar_k[t], is h'[t + 1] = dX / (t + 2) h[t], and the sum of what is
+            // pushed is dX times the sum of h: three operations a pair instead of four.
+            float h[N + 2], pushed;
+            h[1] = 0.5f * g1;
+#if R == 2
+            h[2] = (1.0f / 3.0f) * g2;
+            pushed = g1 + g2;
+#else
+            pushed = g1;
+#endif
 #pragma unroll
             for (int k = K; k >= 1; --k) {
-                gb[k][0] = Ac[k - 1];
-                float gc = 0.0f, asum = 0.0f;
+                h[0] = Ac[k - 1];
+                Ac[k - 1] += pushed;
+                float gc = h[0] * ap[k - 1][1], sum = h[0];
 #pragma unroll
-                for (int t = 0; t <= N - k; ++t) {
-                    const float q = gb[k][t];
-                    asum += q;
-                    gc = __builtin_fmaf(q * inv1(t), ap[k - 1][t + 1], gc);
-                    gb[k - 1][t + 1] = __builtin_fmaf(ec[k - 1][t], q, gb[k - 1][t + 1]);
+                for (int t = 1; t <= N - k; ++t) {
+                    gc = __builtin_fmaf(h[t], ap[k - 1][t + 1], gc);
+                    sum += h[t];
                 }
-                Ac[k - 1] = asum;
+                pushed = ec[k - 1][0] * sum;
+                if (k > 1) {
+#pragma unroll
+                    for (int t = N - k; t >= 0; --t) h[t + 1] = ec[k - 1][t + 1] * h[t];
+                }
 #if MSUM
                 vb[k * 16 * VROW] = gc;
 #else
@@ -1003,19 +1041,23 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
     // per-letter sums).  Between the admissible forms: the time of a segment is the instructions of a lane times the
     // wavefronts a SIMD has to run one after the other (1,024 SIMDs); two levels per lane share more work between
     // words but leave few wavefronts for small batches, where one level per lane then has the shorter segment.
-    for (int R = 1; R <= 2; ++R) {
+    // (forms: one level, two levels, and forward two levels with the children of a word halved between two wavefronts)
+    for (int form = 1; form <= (backward ? 2 : 3); ++form) {
+        const int R = form == 1 ? 1 : 2, split = form == 3 ? 2 : 1;
         if (levels != 0 && R != levels) continue;
         if (depth - R < 1) continue;
         if (R == 2 && d > (backward ? 10 : 12)) continue;
         LanesShape s{};
         s.R = R;
+        s.split = split;
         s.T = 64 / d < 8 ? 64 / d : 8;
         const int K = depth - R;
         double lanes = 1.0;
         for (int k = 0; k < K; ++k) lanes *= d;
         if (lanes > 1.0e9) continue;
         s.lanes = (int64_t)lanes;
-        s.waves = (s.lanes + 63) / 64;
+        if (split > 1 && s.lanes < 32) continue;           // small sets keep the kernels they have
+        s.waves = (s.lanes + 63) / 64 * split;
         int chain = 0, wide = 0;
         double run = lanes;
         for (int k = 1; k <= K; ++k) {
@@ -1023,7 +1065,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
             run /= d;                                      // d^(K - k)
             wide += run >= 32.0 ? 1 : 0;
         }
-        const double per_lane = 2.0 * chain + (R == 2 ? (double)d * d + 3.0 * d : 2.0 * d);
+        const double per_lane = 2.0 * chain + (R == 2 ? ((double)d * d + 3.0 * d) / split : 2.0 * d);
         s.chain = chain;
         s.per_lane = per_lane;
         const double rounds = (double)std::max<int64_t>(B, 1) * (double)s.waves / 1024.0;
@@ -1044,7 +1086,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         };
         // (a lane carries its share of the next staging tile in registers: one increment where the state of two
         // levels already fills them)
-        const int staged = (R == 2 && d * d + d > 48) ? 64 : 192;
+        const int staged = (R == 2 && (d + split - 1) / split * (d + 1) > 48) ? 64 : 192;
         if (msum) {
             s.T = s.TS = 16;
         } else if (backward) {
@@ -1166,9 +1208,9 @@ std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
 {
     std::ostringstream o;
     auto lanes = [&](const char* ns, int n, const LanesShape& q, bool bwd, const char* forward_name) {
-        o << "#define N " << n << "\n#define R " << q.R << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
+        o << "#define N " << n << "\n#define R " << q.R << "\n#define SP " << q.split << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
           << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name << "\nnamespace " << ns << " {\n"
-          << kLanesSource << "}\n#undef N\n#undef R\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n";
+          << kLanesSource << "}\n#undef N\n#undef R\n#undef SP\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n";
     };
     auto chunk = [&](const char* ns, LanesChunkPart part) {
         o << "#define N " << depth << "\n#define M " << (part == kLanesScanLow ? depth - 1 : depth)

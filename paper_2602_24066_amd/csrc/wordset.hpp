@@ -135,8 +135,8 @@ struct WordSet {
         JitKernel* kernel = nullptr;
     };
     std::vector<JitEntry*> jit[2];
-    // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp), the third one level
-    // with sums by rows where that is one of two forms; built on first use
+    // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp); the third: forward two levels
+    // with the children of a word halved, backward one level with sums by rows where that is one of two forms; built on first use
     JitKernel* lanes[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
     // the last few decisions on their number of time chunks (each takes microseconds to model), and the batch sizes whose
     // kernels, for every number of chunks, have been brought up; both under the lock

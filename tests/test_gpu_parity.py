@@ -743,6 +743,49 @@ def test_backward_with_the_workspace_of_whole_paths():
         S.sig_backward(ws, x, c, g, workspace=work[:whole // 4 - 64])
 
 
+@pytest.mark.parametrize("d,depth,B,L,levels,split,backward_chunks", [
+    (10, 4, 256, 35, 0, 2, None),      # halves of five children; 100 words in two wavefronts
+    (7, 4, 500, 21, 0, 2, None),       # halves of four and three
+    (9, 4, 3, 30, 2, 2, None),
+    (6, 4, 1300, 5, 2, 1, None),       # as many wavefronts as SIMDs without halves
+    (6, 5, 32, 60, 0, None, "R 2"),    # rows of two levels, signatures of 1,554 words in two wavefronts' LDS
+    (10, 4, 2, 90, 0, None, "R 1"),    # one level, gradient sums as products
+    (18, 3, 2, 64, 0, None, "R 1"),    # one level, sums by rows
+    (2, 4, 5, 60, 0, None, "R 1"),     # 14 words, most of a row idle
+    (4, 4, 5, 500, 0, None, None),     # many chunks
+])
+def test_forms_of_the_word_per_lane_kernels(d, depth, B, L, levels, split, backward_chunks):
+    """Forward with the children of a word halved between two wavefronts, and the backward walk over the launcher's time chunks, whose
+    lanes work out signature and adjoints at their chunk's end: against the oracle and, in other sums, against whole paths."""
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    ws.set_option("lanes", 1)
+    ws.set_option("lanes_levels", levels)
+    if split:
+        assert f"#define SP {split}\n" in ws.jit_source(False, B)
+    lib = S.load_library()
+    X = make_path("iid", 7600 + L, B, L, d)
+    G = make_grad_coeffs(7700 + L, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c = S.sig_forward(ws, x)
+    low = int(ws.level_start[depth])
+    work = nan_workspace(int(lib.sig_backward_workspace_bytes(ws._h, B, L + 1)))
+    gp = S.sig_backward(ws, x, c, g, workspace=work)
+    torch.cuda.synchronize()
+    if backward_chunks:                                    # chunk signatures and nothing else in the workspace
+        used = int(torch.isfinite(work).sum())
+        C = used // (B * low)
+        assert C > 1 and used == C * B * low and torch.isfinite(work[:used]).all()
+        assert f"#define {backward_chunks}\n" in ws.jit_source(True, B * C)
+    ws.set_option("chunks", 1)
+    whole = S.sig_backward(ws, x, c, g)
+    errs = O.level_errors(c.cpu().numpy(), oracle_forward(X, W, "truncated", depth), np.array([len(w) for w in W]))
+    assert max(errs.values()) <= FWD_TOL, errs
+    gref = oracle_backward(X, W, "truncated", depth, G.astype(np.float64))
+    assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+    assert O.grad_errors(whole.cpu().numpy(), gref).max() <= BWD_TOL
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("d,depth,L,levels,chunks", [
     (10, 4, 37, 1, 1),    # matrix-product sums, 16 wavefronts per path, ragged last tile

@@ -499,8 +499,49 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         S1[j] = cf[level_start(K + 1) + (long)p * D + j];
+    }
 #pragma unroll
-        for (int jj = 0; jj < D; ++jj) An[j][jj] = valid ? gr[level_start(K + 2) + ((long)p * D + j) * D + jj] : 0.0f;
+    for (int j = 0; j < D; ++j)
+#pragma unroll
+        for (int jj = 0; jj < D; ++jj) An[j][jj] = 0.0f;
+    // The leaf adjoints under a wavefront's words are one contiguous run of memory, but a lane's are D^2 floats from the next
+    // lane's: read lane by lane every load touches 64 cache lines, which the wavefronts of a compute unit push out of its 32 KB
+    // before their next load comes back to them (256 paths x 199 segments, d = 10, depth 4: 93 us, 80 this way).  So they come
+    // through the wavefront's LDS, a word a load into rows of an odd number of floats, as many words at a time as fit.
+    // (Forward stores that way: 4 us slower on the same case, whose wavefronts are alone on their SIMDs.)
+    {
+        constexpr int LR = (D * D) | 1, PER = (D * D + 63) / 64;
+        constexpr int NW = 64 * LR <= BW_PER_WAVE ? 64 : (32 * LR <= BW_PER_WAVE ? 32 : (16 * LR <= BW_PER_WAVE ? 16 : 8));
+        static_assert(NW * LR <= BW_PER_WAVE, "eight words at least");
+        const float* src = gr + level_start(K + 2);
+#pragma unroll
+        for (int w0 = 0; w0 < 64; w0 += NW) {
+            wave_lds_fence();
+#pragma unroll 1
+            for (int w = 0; w < NW; w += 8) {                  // loads of eight words in flight, from clamped addresses
+                float v[8][PER];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) {
+                        const int word = p0 + w0 + w + u, i = lane + 64 * q;
+                        v[u][q] = src[(long)(word < NL ? word : NL - 1) * (D * D) + (i < D * D ? i : 0)];
+                    }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int q = 0; q < PER; ++q)
+                        if (lane + 64 * q < D * D) Ec[(w + u) * LR + lane + 64 * q] = v[u][q];
+            }
+            wave_lds_fence();
+            if (lane / NW == w0 / NW && valid) {
+#pragma unroll
+                for (int j = 0; j < D; ++j)
+#pragma unroll
+                    for (int jj = 0; jj < D; ++jj) An[j][jj] = Ec[lane % NW * LR + j * D + jj];
+            }
+        }
+        wave_lds_fence();
     }
 #endif
     if constexpr (level_start(N) <= BW_PER_WAVE) {

@@ -1127,25 +1127,31 @@ struct TailsLds {
     // one per chain letter
     static constexpr int NSRC = D + KL;
     static constexpr int W = level_start(D, N) + ipow(D, N);
-    // the chunk signatures and their products are kept up to length N - 1: the backward walk never reads the
-    // coefficients of the longest words, and their adjoints are the gradient itself
-    static constexpr int W1 = level_start(D, N);
+    // the chunk signatures are kept up to length N - 1: the backward walk never reads the coefficients of the longest words, and
+    // their adjoints are the gradient itself.  Levels of more than 64 words have four floats of padding behind every 64, so that
+    // lanes whose words lie 16 or 64 places apart read from different banks.
+    __host__ __device__ static constexpr int at(int n, int i) { return i + (n > KL ? i / 64 * 4 : 0); }
+    __host__ __device__ static constexpr int level(int n)
+    {
+        const int s = level_start(D, n), s1 = level_start(D, KL + 1);
+        return s + (s > s1 ? (s - s1) / 64 * 4 : 0);
+    }
+    static constexpr int W1 = level_start(D, N) + (level_start(D, N) - level_start(D, KL + 1)) / 64 * 4;
+    static constexpr int LEAF_ROW = D * D * D + 1;                            // leaves of a lane, an odd number of floats a row
     // scaled increments Ec of one wavefront, and for the chain rule the increment gradients of the first and of the
     // last segment of the row (2 D floats) and of the tile walked before (T D floats)
     static constexpr int TILE = T * D * NC + 2 * D + T * D;
     static constexpr int OFF_CG = T * D * NC;
     static constexpr int RED = T * D + NSRC * T * kWave;                     // gt, Vb of one wavefront
-    // fused: area A holds first the signature buffers and a copy of the gradient row of the path, later the
-    // reduction regions
-    static constexpr int NBUF = CW > 2 ? 3 * CW - 4 : CW;                   // chunk signatures and running products
-    static constexpr int BUFS = NBUF * W1 + W;
+    // fused: area A holds first the chunk signatures and the leaves of the path's gradient, later the reduction regions
+    static constexpr int BUFS = CW * W1 + kWave * LEAF_ROW;
     static constexpr int AREA_A = CW ? (BUFS > NWV * RED ? BUFS : NWV * RED) : 0;
     // fused: the tiles come first (their addresses then fit the offset field of the LDS instructions), area A next
     static constexpr int OFF_A = CW ? NWV * TILE : 0;
-    static constexpr int OFF_G = OFF_A + NBUF * W1;                           // fused: the gradient row of the path
+    static constexpr int OFF_G = OFF_A + CW * W1;                             // fused: the leaves, a row per lane
     static constexpr int OFF_XY = OFF_A + AREA_A;     // fused: first / last segment gradients of the CW chunks
     static constexpr int TOTAL = CW ? OFF_XY + CW * 2 * D : NWV * (TILE + RED);
-    static_assert(TILE % 4 == 0 && RED % 4 == 0 && AREA_A % 4 == 0 && W % 4 == 0 && W1 % 4 == 0, "16-byte alignment");
+    static_assert(TILE % 4 == 0 && RED % 4 == 0 && AREA_A % 4 == 0 && W1 % 4 == 0, "16-byte alignment");
     static constexpr size_t BYTES = (size_t)TOTAL * sizeof(float);
     __device__ static float* tile(float* base, int wib) { return base + (CW ? wib * TILE : wib * (TILE + RED)); }
     __device__ static float* red(float* base, int wib) { return base + (CW ? OFF_A + wib * RED : wib * (TILE + RED) + TILE); }
@@ -1200,46 +1206,6 @@ __device__ __forceinline__ void lds_tensor_product(const float* a, const float* 
         }
     }
 }
-// coefficient of the word (length n, index i) of a (x) b
-template <int D, int N>
-__device__ __forceinline__ float word_product(const float* a, const float* b, int n, int i)
-{
-    constexpr int LB = ilog2(D);
-    float acc = a[level_start(D, n) + i] + b[level_start(D, n) + i];
-#pragma unroll
-    for (int k = 1; k < N; ++k)
-        if (k < n) {
-            const int sh = LB * (n - k);
-            acc = fmaf(a[level_start(D, k) + (i >> sh)], b[level_start(D, n - k) + (i & ((1 << sh) - 1))], acc);
-        }
-    return acc;
-}
-// adjoint of the word u (length n, index i) at a chunk boundary: g(u) + sum_{m >= 1} sum_{|v| = m} g(u v) q(v).
-// `share` lanes (a power of two, consecutive, all holding the same u) split the sums; `sub` is the lane's rank.
-// rot (a multiple of four, the same in the lanes of one u) rotates the order in which a lane walks its v, so that
-// lanes whose words lie a power of two apart do not meet in one LDS bank.
-template <int D, int N>
-__device__ __forceinline__ float word_contract(const float* g, const float* q, int n, int i, int sub, int share, int rot)
-{
-    static_assert(D % 4 == 0, "the words u v of one u are read four at a time");
-    constexpr int LB = ilog2(D);
-    v4f acc4 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int m = 1; m < N; ++m)
-        if (m <= N - n) {
-            const int cnt = 1 << (LB * m);
-            const float* src = g + level_start(D, n + m) + (i << (LB * m));
-            const float* qv = q + level_start(D, m);
-            for (int v = 4 * sub; v < cnt; v += 4 * share) {
-                const int vr = (v + rot) & (cnt - 1);
-                acc4 += *(const v4f*)(src + vr) * *(const v4f*)(qv + vr);
-            }
-        }
-    float acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
-    for (int off = share >> 1; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-    return g[level_start(D, n) + i] + acc;
-}
-
 template <int D, int N, int T, int CW, bool POINTS>
 __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tails_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad, int64_t B,
@@ -1327,7 +1293,7 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
     };
 
     // ---- initial state.  sig(n, i): coefficient of the word (length n, index i) the row starts from;
-    // adj(n, i, sub, share): its adjoint (length < N), where `share` consecutive lanes hold the same word.
+    // gr: its adjoint, held by the first of the lanes that share a chain word.
     auto load_signature = [&](auto&& sig) {
         int phi = 0;
 #pragma unroll
@@ -1343,39 +1309,40 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
             for (int j = 0; j < D; ++j) S1[ii][j] = sig(N - 1, (lane * D + i) * D + j);
         }
     };
-    auto load_adjoint = [&](auto&& adj) {
+    auto load_adjoint = [&]() {
         int phi = 0;
 #pragma unroll
         for (int k = 1; k <= KL; ++k) {
             phi = phi * D + letter[k - 1];
-            const int share = ipow(D, KL - k);                    // lanes holding this word
-            const float v = adj(k, phi, lane % share, share);
-            Ac[k - 1] = lane % share == 0 ? v : 0.0f;             // the adjoint lives in the owning lane only
+            Ac[k - 1] = lane % ipow(D, KL - k) == 0 ? gr[level_start(D, k) + phi] : 0.0f;
         }
 #pragma unroll
-        for (int ii = 0; ii < TW; ++ii) {
-            const int i = ii;
-            At[ii] = adj(K, lane * D + i, 0, 1);
+        for (int i = 0; i < TW; ++i) {
+            At[i] = gr[level_start(D, K) + lane * D + i];
 #pragma unroll
-            for (int j = 0; j < D; ++j) A1[ii][j] = adj(N - 1, (lane * D + i) * D + j, 0, 1);
+            for (int j = 0; j < D; ++j) A1[i][j] = gr[level_start(D, N - 1) + (lane * D + i) * D + j];
         }
     };
+    load_adjoint();
     // leaf adjoints are the gradient itself at every chunk boundary
-#pragma unroll
-    for (int ii = 0; ii < TW; ++ii)
-#pragma unroll
-        for (int j = 0; j < D; ++j)
-#pragma unroll
-            for (int jj = 0; jj < D; ++jj) An[ii][j][jj] = gr[level_start(D, N) + ((lane * D + ii) * D + j) * D + jj];
-
     if constexpr (CW == 0) {
+#pragma unroll
+        for (int ii = 0; ii < TW; ++ii)
+#pragma unroll
+            for (int j = 0; j < D; ++j)
+#pragma unroll
+                for (int jj = 0; jj < D; ++jj) An[ii][j][jj] = gr[level_start(D, N) + ((lane * D + ii) * D + j) * D + jj];
         load_signature([&](int n, int i) { return cf[level_start(D, n) + i]; });
-        load_adjoint([&](int n, int i, int, int) { return gr[level_start(D, n) + i]; });
     } else {
-        constexpr int W = LY::W1;                      // words of length < N
-        float* const SB = smem + LY::OFF_A;            // SB[c] = signature of chunk c
-        float* const GB = smem + LY::OFF_G;            // the gradient row, read many times by the boundary adjoints
-        for (int o = 4 * (int)threadIdx.x; o < LY::W; o += 4 * LY::NWV * kWave) *(v4f*)(GB + o) = *(const v4f*)(gr + o);
+        float* const SB = smem + LY::OFF_A;            // SB + c W1: signature of chunk c
+        float* const GB = smem + LY::OFF_G;
+        // the leaves are the same for all wavefronts and lie 64 floats a lane: loaded together, as they come (lane by lane every
+        // load touched 64 cache lines, eight times over: 3.7 us), and read from rows of 65 floats
+        for (int o = 4 * (int)threadIdx.x; o < ipow(D, N); o += 4 * LY::NWV * kWave) {
+            const v4f v = *(const v4f*)(gr + level_start(D, N) + o);
+            float* row = GB + o / (D * D * D) * LY::LEAF_ROW + o % (D * D * D);
+            row[0] = v[0]; row[1] = v[1]; row[2] = v[2]; row[3] = v[3];
+        }
         // phase 1: signature of the own chunk, S <- S (x) exp(dX) segment by segment from the identity
         load_signature([&](int, int) { return 0.0f; });
         {
@@ -1409,54 +1376,109 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
                 }
             }
         }
-        {   // publish it in canonical order
-            float* out = SB + cib * W;
+        {   // publish it
+            float* out = SB + cib * LY::W1;
             int phi = 0;
 #pragma unroll
             for (int k = 1; k <= KL; ++k) {
                 phi = phi * D + letter[k - 1];
-                if (lane % ipow(D, KL - k) == 0) out[level_start(D, k) + phi] = Sc[k - 1];
+                if (lane % ipow(D, KL - k) == 0) out[LY::level(k) + phi] = Sc[k - 1];
             }
 #pragma unroll
-            for (int ii = 0; ii < TW; ++ii) {
-                const int i = ii;
-                out[level_start(D, K) + lane * D + i] = St[ii];
-                *(v4f*)(out + level_start(D, N - 1) + (lane * D + i) * D) = S1[ii];
+            for (int i = 0; i < TW; ++i) {
+                out[LY::level(K) + LY::at(K, lane * D + i)] = St[i];
+                *(v4f*)(out + LY::level(N - 1) + LY::at(N - 1, (lane * D + i) * D)) = S1[i];
             }
         }
         __syncthreads();
-        // phase 2: what every chunk starts from.  With the chunks numbered from 0: E_k = S_0 (x) .. (x) S_k, the
-        // signature at the end of chunk k, and Q_k = S_{k+1} (x) .. (x) S_{CW-1}, what follows it.  Both are running
-        // products, CW - 2 rounds of two products each (one per half of the workgroup); E_0 = S_0 is in the
-        // registers of chunk 0, E_{CW-1} is the terminal signature, Q_{CW-2} = S_{CW-1}.
-        float* const EB = SB + CW * W;                 // EB[k - 1] = E_k, k = 1 .. CW - 2
-        float* const QB = EB + (CW - 2) * W;           // QB[k] = Q_k, k = 0 .. CW - 3
-        if constexpr (CW > 2) {
-            constexpr int NT = LY::NWV * kWave / 2;
-            const bool upper = (int)threadIdx.x >= NT;
-            const int tid = (int)threadIdx.x - (upper ? NT : 0);
+#pragma unroll
+        for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int j = 0; j < D; ++j)
+#pragma unroll
+                for (int jj = 0; jj < D; ++jj) An[i][j][jj] = GB[lane * LY::LEAF_ROW + (i * D + j) * D + jj];
+        // phase 2: what every chunk starts from, worked out by its lanes for their own words.  The signature at its end,
+        // S_0 (x) .. (x) S_cib: the product on a word's prefixes needs infixes of the word alone (chunk 0: the own registers; the
+        // last chunk: the terminal signature).  The adjoints there, taken back from the end of the path over the chunks that follow,
+        // the last first: Abar(u) += sum_v Abar(u v) S_c(v).  The walk is linear in them, so a chain word's adjoint may be
+        // spread over the lanes that share the word, and a lane adds the terms whose word u v is its own: no sums over
+        // lanes and no barriers.  (Running products of both kinds by the whole workgroup, CW - 2 rounds, and contractions with
+        // the gradient row took 13 us here.  With the leaves' loads above, backward: 1 path of 155 segments 47.2 -> 39.3 us, 13 of
+        // 243 57.5 -> 49.6, 241 of 268 71 -> 61, 113 of 50 29.5 -> 23.7.)
+        {
+            const int u1 = lane % ipow(D, KL - 1), u2 = lane % ipow(D, KL - 2);     // the lane's word without one and two letters
+            static_assert(KL == 3, "a lane's word has three letters");
+            auto quad = [&](const float* S, int n, int i) { return *(const v4f*)(S + LY::level(n) + LY::at(n, i)); };
+            if (cib == CW - 1) {
+                load_signature([&](int n, int i) { return cf[level_start(D, n) + i]; });
+            } else if (cib > 0) {
+                const float* S = SB;
+                Sc[0] = S[LY::level(1) + letter[0]];
+                Sc[1] = S[LY::level(2) + lane / D];
+                Sc[2] = S[LY::level(3) + lane];
+                const v4f t0 = quad(S, 4, lane * D);
+#pragma unroll
+                for (int i = 0; i < TW; ++i) {
+                    St[i] = t0[i];
+                    S1[i] = quad(S, 5, (lane * D + i) * D);
+                }
 #pragma unroll 1
-            for (int j = 1; j <= CW - 2; ++j) {
-                if (!upper)
-                    lds_tensor_product<D, N - 1>(j == 1 ? SB : EB + (j - 2) * W, SB + j * W, EB + (j - 1) * W, tid, NT);
-                else
-                    lds_tensor_product<D, N - 1>(SB + (CW - 1 - j) * W, j == 1 ? SB + (CW - 1) * W : QB + (CW - 1 - j) * W,
-                                                 QB + (CW - 2 - j) * W, tid, NT);
-                __syncthreads();
+                for (int c = 1; c <= cib; ++c) {
+                    S += LY::W1;
+                    const v4f s1 = quad(S, 1, 0);
+#pragma unroll
+                    for (int i = 0; i < TW; ++i)
+                        S1[i] += quad(S, 5, (lane * D + i) * D) + Sc[0] * quad(S, 4, (u1 * D + i) * D) + Sc[1] * quad(S, 3, (u2 * D + i) * D) +
+                                 Sc[2] * quad(S, 2, i * D) + St[i] * s1;
+                    const v4f t = quad(S, 4, lane * D) + Sc[0] * quad(S, 3, u1 * D) + Sc[1] * quad(S, 2, u2 * D) + Sc[2] * s1;
+#pragma unroll
+                    for (int i = 0; i < TW; ++i) St[i] += t[i];
+                    Sc[2] += S[LY::level(3) + lane] + Sc[0] * S[LY::level(2) + u1] + Sc[1] * S[LY::level(1) + u2];
+                    Sc[1] += S[LY::level(2) + lane / D] + Sc[0] * S[LY::level(1) + letter[1]];
+                    Sc[0] += S[LY::level(1) + letter[0]];
+                }
             }
-            if (cib >= 1 && cib <= CW - 2) {
-                const float* e = EB + (cib - 1) * W;
-                load_signature([&](int n, int i) { return e[level_start(D, n) + i]; });
+#pragma unroll 1
+            for (int c = CW - 1; c > cib; --c) {
+                const float* S = SB + c * LY::W1;
+                // terms of the words below the lane's own, for the prefix of k letters: n letters of it are left, rest the number they make
+                auto below = [&](int n, int rest) {
+                    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const v4f st = quad(S, n + 1, rest * D);
+#pragma unroll
+                    for (int i = 0; i < TW; ++i) {
+                        acc[i] = fmaf(At[i], st[i], acc[i]);
+                        acc += A1[i] * quad(S, n + 2, (rest * D + i) * D);
+#pragma unroll
+                        for (int j = 0; j < D; ++j) {
+                            const v4f q = quad(S, n + 3, ((rest * D + i) * D + j) * D);
+#pragma unroll
+                            for (int jj = 0; jj < D; ++jj) acc[jj] = fmaf(An[i][j][jj], q[jj], acc[jj]);
+                        }
+                    }
+                    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                };
+                Ac[0] += Ac[1] * S[LY::level(1) + letter[1]] + Ac[2] * S[LY::level(2) + u1] + below(2, u1);
+                Ac[1] += Ac[2] * S[LY::level(1) + u2] + below(1, u2);
+                Ac[2] += below(0, 0);
+                const v4f s1 = quad(S, 1, 0);
+#pragma unroll
+                for (int i = 0; i < TW; ++i) {
+                    v4f acc = A1[i] * s1;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        const v4f q = quad(S, 2, j * D);
+                        float own = A1[i][j];
+#pragma unroll
+                        for (int jj = 0; jj < D; ++jj) {
+                            acc[jj] = fmaf(An[i][j][jj], q[jj], acc[jj]);
+                            own = fmaf(An[i][j][jj], s1[jj], own);
+                        }
+                        A1[i][j] = own;
+                    }
+                    At[i] += (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                }
             }
-        }
-        const float* qbuf = cib == CW - 2 ? SB + (CW - 1) * W : QB + cib * W;   // Q of the own chunk (not for the last)
-        if (cib == CW - 1) {
-            load_signature([&](int n, int i) { return cf[level_start(D, n) + i]; });                // terminal signature
-            load_adjoint([&](int n, int i, int, int) { return gr[level_start(D, n) + i]; });
-        } else {
-            load_adjoint([&](int n, int i, int sub, int share) {
-                return word_contract<D, N>(GB, qbuf, n, i, sub, share, 4 * (lane / share));
-            });
         }
         __syncthreads();                               // the buffers are dead: their space takes gt / Vb from here on
     }

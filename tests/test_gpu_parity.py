@@ -482,6 +482,19 @@ def test_forward_fused_and_four_wavefront_kernels_agree():
         assert e <= 1e-5, (n, e)
 
 
+@pytest.mark.parametrize("chunks", [2, 4, 8])
+@pytest.mark.parametrize("L", [16, 17, 33, 64, 71, 155])
+def test_chunks_of_the_fused_backward(chunks, L):
+    """Every chunk's lanes work out the signature and the adjoints at its end; chunks of whole tiles, of a part of one, and shorter
+    last ones."""
+    ws, W = build_both("truncated", 4, depth=6)
+    ws.set_option("bwd_tails", chunks)
+    X = make_path("iid", 50 + L, 3, L, 4)
+    G = make_grad_coeffs(60 + L, 3, ws.size)
+    _, gp = gpu_forward_backward(ws, X, G)
+    assert O.grad_errors(gp, oracle_backward(X, W, "truncated", 6, G.astype(np.float64))).max() <= BWD_TOL
+
+
 def test_rows_that_are_not_16_byte_aligned():
     """coeffs / grad_coeffs four bytes off a 16-byte boundary: the d = 4 kernels that use vector loads and stores step
     aside for the ones that do not, with the same results."""

@@ -22,6 +22,7 @@ namespace {
 
 constexpr int kWave = 64;
 
+constexpr int64_t kSimds = 1024;                   // of the chip: 256 compute units of four
 __host__ __device__ constexpr int ipow(int b, int e)
 {
     int r = 1;
@@ -432,8 +433,11 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void trunc_mfma_fwd_kernel(
     for (int64_t n = 0; n < ntiles; ++n) {
         fetch((n + 2) * T);
         const int base = (int)(n & 1) * T;
+        // the last tile may be a partial one (behind it: zeros).  d = 8, 375 paths of 146 segments: 83 -> 79 us, 2 of 17: 10.6 -> 8.7;
+        // the short tiles of d = 16 have little to skip and lost 4 % to the loop's bound in a register.
+        const int steps = G::WIDE ? T : __builtin_amdgcn_readfirstlane((int)(L - n * T < T ? L - n * T : T));
 #pragma unroll 1
-        for (int tt = 0; tt < T; tt += 2) {
+        for (int tt = 0; tt < steps; tt += 2) {
             const int r0 = base + tt;                 // ring row of segment s = n T + tt
             load_rs(RA, (r0 + 2) % (2 * T));
             load_u(UB, (r0 + 1) % (2 * T));
@@ -1010,13 +1014,17 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
         }
         {
             static_assert(T % 2 == 0, "the segment loop is unrolled by two");
+            // the last tile may be a partial one: the segments that it does not have are not walked (what lies in LDS for them
+            // reaches entries of gt that nobody reads): 419 paths of 70 segments 218 -> 211 us, 18 of 591 131 -> 127.  (With the sources
+            // in registers whole groups are passed over: starting the loop later cost 64 paths of 4,096 segments 1 %.)
+            const int top = __builtin_amdgcn_readfirstlane((int)(L - n * T < T ? L - n * T : T) - 1);
             if constexpr (T == 16 && !LY::TWO_WORKGROUPS) {
                 // a lone wavefront per SIMD: recon runs one segment ahead of adjoint so that their chains overlap
                 Saved SA, SB;
                 Sources unused;
-                recon(T - 1, SA);
+                recon(top | 1, SA);
 #pragma unroll 1
-                for (int tt = T - 1; tt >= 3; tt -= 2) {
+                for (int tt = top | 1; tt >= 3; tt -= 2) {
                     recon(tt - 1, SB);
                     adjoint(tt, SA, unused);
                     recon(tt - 2, SA);
@@ -1031,6 +1039,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
             } else if constexpr (LY::SOURCES_IN_REGISTERS) {
 #pragma unroll 1
                 for (int t0 = T - VG; t0 >= 0; t0 -= VG) {
+                    if (t0 > top) continue;
                     float last[VG], slice[VG], chain0[VG];
 #pragma unroll
                     for (int i = VG - 1; i >= 0; --i) {
@@ -1048,7 +1057,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
                 // two wavefronts per SIMD hide each other's latencies; one set of saved values keeps the registers
                 // within half a SIMD's
 #pragma unroll 1
-                for (int tt = T - 1; tt >= 0; --tt) {
+                for (int tt = top; tt >= 0; --tt) {
                     Saved SA;
                     Sources unused;
                     recon(tt, SA);
@@ -1353,8 +1362,8 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
                 stage();
                 wave_lds_fence();
                 fetch((n + 1) * T);                    // beyond the chunk: zeros
-#pragma unroll 2
-                for (int tt = 0; tt < T; ++tt) {
+                const int steps = __builtin_amdgcn_readfirstlane((int)(L - n * T < T ? L - n * T : T));
+                auto segment = [&](int tt) {
                     float a[KL + 1][N + 2];
 #pragma unroll
                     for (int t = 0; t < N + 2; ++t) a[0][t] = 1.0f;
@@ -1373,6 +1382,11 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
 #pragma unroll
                         for (int j = 0; j < D; ++j) S1[ii][j] = fmaf(Ec[tt][j][0], a1, S1[ii][j]);
                     }
+                };
+#pragma unroll 1
+                for (int tt = 0; tt < steps; tt += 2) {
+                    segment(tt);
+                    segment(tt + 1);
                 }
             }
         }
@@ -1593,8 +1607,10 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
         stage();
         wave_lds_fence();
         fetch((n - 1) * T);                            // n = 0: out of range, zeros
+        // (the last tile may be a partial one: 1 path of 155 segments 39.4 -> 35.6 us, 2 of 17 21.3 -> 15.2; what lies in LDS for its
+        // other segments is summed into entries of gt that nobody reads)
 #pragma unroll 1
-        for (int tt = T - 1; tt >= 0; --tt) step(tt);
+        for (int tt = __builtin_amdgcn_readfirstlane((int)(L - n * T < T ? L - n * T : T)) - 1; tt >= 0; --tt) step(tt);
         wave_lds_fence();
         tile_reduce_uniform<D, T>(Vb, gt, D, lane, 0);     // the only writer of gt so far: plain read-modify-write
         wave_lds_fence();
@@ -1688,9 +1704,9 @@ struct NodeLds {
     static constexpr size_t BYTES = (size_t)kWavesPerBlock * PER_WAVE * sizeof(float);
 };
 
-// (the shortest tile is for launches with two wavefronts per SIMD: its registers are held to half a SIMD's)
-template <int D, int N, int T, bool LOW>
-__global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trunc_node_bwd_kernel(
+// (registers are held to half a SIMD's, except in the form for launches of no more wavefronts than SIMDs, LONE)
+template <int D, int N, int T, bool LOW, bool LONE>
+__global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 && !LONE ? 2 : 1)) void trunc_node_bwd_kernel(
     const float* __restrict__ path, const float* __restrict__ coeffs, const float* __restrict__ grad,
     const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc,
     WindowList wl, float* gdx, float* resid)
@@ -1926,13 +1942,17 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
         stage();
         wave_lds_fence();
         fetch((n - 1) * T);                            // n = 0: out of range, zeros
+        // the last tile may be a partial one: launches of few wavefronts walk only the pairs of segments it has (what the others
+        // leave in LDS is not read): 5 paths of 238 segments 54 -> 50 us, 2 of 17 21.8 -> 18.5.  In the form for launches that fill
+        // the chip the bound costs a register that is not there: 128 paths of 1,024 segments 553 -> 593 us.
+        const int top = !LONE ? T - 1 : __builtin_amdgcn_readfirstlane(L - n * T < T ? (int)(L - 1 - n * T) | 1 : T - 1);
         if constexpr (LY::SOURCES_IN_REGISTERS) {
             static_assert(K == 3 && T % 2 == 0 && T >= 4, "reduce_pair is written for three chain letters");
             In ia, ib;
             float yv[2 * D], cv[2 * K];
-            load_in(T - 1, ia);
+            load_in(top, ia);
 #pragma unroll 1
-            for (int tt = T - 1; tt >= 3; tt -= 2) {
+            for (int tt = top; tt >= 3; tt -= 2) {
                 load_in(tt - 1, ib);
                 step(tt, ia, yv + D, cv + K);
                 load_in(tt - 2, ia);
@@ -1947,9 +1967,9 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
         } else {
             static_assert(T % 2 == 0 && T >= 4, "the segment loop is unrolled by two");
             In ia, ib;
-            load_in(T - 1, ia);
+            load_in(top, ia);
 #pragma unroll 1
-            for (int tt = T - 1; tt >= 3; tt -= 2) {
+            for (int tt = top; tt >= 3; tt -= 2) {
                 load_in(tt - 1, ib);
                 step(tt, ia, nullptr, nullptr);
                 load_in(tt - 2, ia);
@@ -1988,7 +2008,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 ? 2 : 1)) void trun
     }
 }
 
-template <int D, int N, int T = 8, bool LOW = false>
+template <int D, int N, int T = 8, bool LOW = false, bool LONE = false>
 hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const float* grad, const float* coeffs_last,
                                  const float* grad_last, int64_t B, int64_t P, int64_t C, int64_t Lc, float* gdx, float* resid,
                                  hipStream_t stream, const WindowList& wl = WindowList())
@@ -1996,13 +2016,16 @@ hipError_t launch_trunc_node_bwd(const float* path, const float* coeffs, const f
     using LY = NodeLds<D, N, T>;
     static_assert(LY::BYTES <= 160 * 1024, "LDS of one compute unit");
     const int64_t waves = B * C * (wl.win ? wl.K : 1) * (ipow(D, N - 2) / kWave);
+    if constexpr (D == 8 && T == 8 && !LONE) {
+        if (waves <= kSimds) return launch_trunc_node_bwd<D, N, T, LOW, true>(path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, gdx, resid, stream, wl);
+    }
     const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (LY::BYTES > 64 * 1024) {                 // above the default limit the kernel has to be told once
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_node_bwd_kernel<D, N, T, LOW>), (int)LY::BYTES);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&trunc_node_bwd_kernel<D, N, T, LOW, LONE>), (int)LY::BYTES);
         if (e != hipSuccess) return e;
     }
-    trunc_node_bwd_kernel<D, N, T, LOW><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
+    trunc_node_bwd_kernel<D, N, T, LOW, LONE><<<(unsigned)blocks, kWave * kWavesPerBlock, LY::BYTES, stream>>>(
         path, coeffs, grad, coeffs_last, grad_last, B, P, C, Lc, wl, gdx, resid);
     return hipGetLastError();
 }
@@ -2127,8 +2150,8 @@ __global__ __launch_bounds__(kWave * CW * (D / TW)) void trunc_tails_fwd_kernel(
         stage();
         wave_lds_fence();
         fetch((n + 1) * T);                            // beyond the chunk: zeros
-#pragma unroll 2
-        for (int tt = 0; tt < T; ++tt) {
+        const int steps = __builtin_amdgcn_readfirstlane((int)(L - n * T < T ? L - n * T : T));
+        auto segment = [&](int tt) {
             const float bs = E[tt][0][offB];
             float a[KL + 1][N + 2];
 #pragma unroll
@@ -2151,6 +2174,12 @@ __global__ __launch_bounds__(kWave * CW * (D / TW)) void trunc_tails_fwd_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) S2[ii][r] = mfma4(Gq[r], bs, S2[ii][r], 0);
             }
+        };
+        // two segments at a time, and no further than the chunk goes: 2 paths of 131 segments 16.1 -> 14.7 us, 241 of 268 27.0 -> 26.0
+#pragma unroll 1
+        for (int tt = 0; tt < steps; tt += 2) {
+            segment(tt);
+            segment(tt + 1);
         }
     }
     {   // publish the chunk signature in canonical order

@@ -495,6 +495,24 @@ def test_chunks_of_the_fused_backward(chunks, L):
     assert O.grad_errors(gp, oracle_backward(X, W, "truncated", 6, G.astype(np.float64))).max() <= BWD_TOL
 
 
+@pytest.mark.parametrize("d,depth,B,Ls", [(4, 6, 3, (1, 7, 8, 9, 33)), (8, 5, 2, (1, 2, 7, 8, 9, 16, 17)), (16, 4, 2, (1, 15, 16, 17, 22)),
+                                          (16, 4, 70, (21, 33))])
+def test_partial_tiles_of_the_truncation_kernels(d, depth, B, Ls):
+    """The kernels stop at a row's last segment instead of walking its last tile to the end: lengths around whole tiles, with LDS
+    that the length before has filled."""
+    ws, W = build_both("truncated", d, depth=depth)
+    lengths = np.array([len(w) for w in W])
+    for L in Ls:
+        X = make_path("iid", 80 + L, B, L, d)
+        G = make_grad_coeffs(90 + L, B, ws.size)
+        c, gp = gpu_forward_backward(ws, X, G)
+        few = min(B, 3)
+        errs = O.level_errors(c[:few], oracle_forward(X[:few], W, "truncated", depth), lengths)
+        assert max(errs.values()) <= FWD_TOL, (L, errs)
+        gref = oracle_backward(X[:few], W, "truncated", depth, G[:few].astype(np.float64))
+        assert O.grad_errors(gp[:few], gref).max() <= BWD_TOL, L
+
+
 def test_rows_that_are_not_16_byte_aligned():
     """coeffs / grad_coeffs four bytes off a 16-byte boundary: the d = 4 kernels that use vector loads and stores step
     aside for the ones that do not, with the same results."""

@@ -102,12 +102,11 @@ struct CallTimer {
 
 // Time chunks for full truncations: with few paths the sequential kernels leave wavefront slots empty, so the
 // segments of every path are cut into C chunks that run as independent rows and are combined afterwards with Chen's
-// relation.  Measured on the three instantiated shapes this pays off for the forward kernels once a chunk is a
-// few hundred segments long (the chunk products and the second launch cost about as much as 100 segments); a
-// chunked backward pass that starts from the terminal signature alone has to recompute the chunk signatures, a forward
-// pass of its own, so sig_backward chunks on request (option "chunks") and, by itself, only where four or more chunks
-// fit (few long paths, see below); otherwise the checkpointed calls, which keep the chunk signatures, are the way to
-// more rows.
+// relation.  Forward it pays off once a chunk is a few hundred segments long (d = 4: the chunk products and the second
+// launch cost about as much as 100 segments); backward from the terminal signature alone has to recompute the chunk
+// signatures, a forward pass of its own: d = 4 does so on request (option "chunks") where its fused form does not run.
+// For d = 8 and d = 16 the counts below are what a call has to bring a workspace for; low_chunks may cut finer (backward it is
+// what a call takes).
 struct Chunks { int64_t C, Lc; };
 // own_chunks = false: sig_backward does not chunk by itself (sig_backward_static, whose scratch array is sized for
 // whole paths).
@@ -123,13 +122,9 @@ Chunks trunc_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points,
             C = slots / sig::trunc_waves_per_row(w.d, w.depth, dir) / std::max<int64_t>(B, 1);
             C = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(C, 64), L / 256));
         } else if (own_chunks && !sig::trunc_backward_tails_available(w.d, w.depth)) {
-            // few long paths: even with the chunk signatures recomputed, four to sixteen chunks side by side beat a walk
-            // over whole paths that leaves most SIMDs empty (measured, d = 16: 8 paths x 8,192 segments 3.92 -> 1.00 ms,
-            // 32 x 4,096 2.00 -> 1.09 ms; d = 8: 16 x 4,096 2.63 -> 0.67 ms, 64 x 2,048 1.33 -> 0.74 ms); with two
-            // chunks the second forward pass eats the gain
             const int64_t rows_wanted = 2048 / sig::trunc_waves_per_row(w.d, w.depth, 1);
             C = std::min<int64_t>(std::min<int64_t>(16, rows_wanted / std::max<int64_t>(B, 1)), L / 256);
-            C = C >= 16 ? 16 : (C >= 8 ? 8 : (C >= 4 ? 4 : 1));     // whole wavefronts per SIMD: 12 chunks lost to 8 when measured
+            C = C >= 16 ? 16 : (C >= 8 ? 8 : (C >= 4 ? 4 : 1));     // whole wavefronts per SIMD
         }
     }
     const int64_t Lc = (L + C - 1) / C;
@@ -167,12 +162,13 @@ int low_chunk_count(const sig::WordSet& w, int dir, int64_t B, int64_t L)
     }
     return choice;
 }
-// the product of every path's chunk signatures: by slices from three chunks on, of two spread over the grid (128 paths, d = 8: 16 us
-// against 21)
-hipError_t chunk_product_of(const sig::WordSet& w, const float* Sc, float* Pfx, float* coeffs, int64_t B, int64_t C, hipStream_t st)
+// the product of every path's chunk signatures: small ones in LDS; by slices from three chunks on, of two spread over the grid (128
+// paths, d = 8: 16 us against 21; more paths than a grid has rows by slices too)
+hipError_t chunk_product_of(const sig::WordSet& w, const float* Sc, float* coeffs, int64_t B, int64_t C, hipStream_t st)
 {
-    if (C > 2 && sig::trunc_low_available(w.d, w.depth)) return sig::chunk_slices_forward(w.d, w.depth, Sc, coeffs, B, (int)C, st);
-    return sig::chunk_scan(w.d, w.depth, Sc, Pfx, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)C, nullptr, st);
+    if (!sig::trunc_low_available(w.d, w.depth)) return sig::chunk_scan(w.d, w.depth, Sc, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)C, st);
+    if (C > 2 || B > 65535) return sig::chunk_slices_forward(w.d, w.depth, Sc, coeffs, B, (int)C, st);
+    return sig::chunk_product(w.d, w.depth, Sc, coeffs, B, st);
 }
 Chunks low_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points)
 {
@@ -288,9 +284,8 @@ size_t chunk_array_bytes(const sig::WordSet& w, int64_t B, int64_t C)
     return ((size_t)B * (size_t)C * (size_t)w.size() * sizeof(float) + 255) & ~(size_t)255;
 }
 
-// arrays [B][C][|W|] a chunked forward pass takes from its workspace: the chunk signatures, and the partial products
-// when four or more large signatures are multiplied pair by pair (two or three, and signatures that fit LDS, are
-// multiplied in one kernel)
+// arrays [B][C][|W|] a chunked forward pass asks for in its workspace: the chunk signatures, and for four or more large ones as
+// much again (once for partial products; the products by slices need none, but a call states the same bytes as ever)
 size_t forward_chunk_arrays(const sig::WordSet& w, int64_t C) { return (C >= 4 && w.size() > 8192) ? 2 : 1; }
 
 bool use_trunc_forward(const sig::WordSet& w, int64_t B)
@@ -1367,7 +1362,7 @@ static hipError_t low_backward(const sig::WordSet& w, const float* path, const f
     float* Abar = (float*)(base + 3 * nb);
     hipError_t e = sig::trunc_forward_low(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
     if (e == hipSuccess) e = sig::chunk_slices_both(w.d, w.depth, Sc, w.level_start[(size_t)w.depth], left, right, B, (int)ch.C, st);
-    if (e == hipSuccess) e = sig::chunk_adjoint_low(w.d, w.depth, grad_coeffs, right, Abar, B, (int)ch.C, gdx, B * (n_points - 1) * w.d, st);
+    if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, right, w.level_start[(size_t)w.depth], Abar, B, (int)ch.C, gdx, B * (n_points - 1) * w.d, st);
     if (e != hipSuccess) return e;
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
@@ -1454,8 +1449,8 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
         }
         Chunks ch = trunc_chunks(w, 0, B, n_points);
         if (sig::trunc_low_available(w.d, w.depth)) {
-            // (a smaller workspace, or rows that are not aligned, get the walk over whole paths unless the call has always asked for
-            // its chunks)
+            // (a smaller workspace, rows that are not aligned, and calls for which the model sees no gain in more chunks - 128 paths of
+            // 1,024 segments, d = 8 - go on with the count above: whole paths, or the chunks that the call has to bring a workspace for)
             const Chunks low = low_chunks(w, 0, B, n_points);
             const size_t nb = chunk_array_bytes(w, B, low.C);
             if (low.C > 1 && workspace && workspace_bytes >= sig_forward_workspace_bytes(ws, B, n_points) &&
@@ -1464,25 +1459,22 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
                 if (pe) (void)hipEventRecord(pe[0], st);
                 hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, low.C, low.Lc, (float*)workspace, st);
                 if (pe) (void)hipEventRecord(pe[1], st);
-                if (e == hipSuccess) e = chunk_product_of(w, (const float*)workspace, nullptr, coeffs, B, low.C, st);
+                if (e == hipSuccess) e = chunk_product_of(w, (const float*)workspace, coeffs, B, low.C, st);
                 return e == hipSuccess ? SIG_OK : hip_fail(e);
             }
         }
         float* Sc = coeffs;
-        float* Pfx = nullptr;
         if (ch.C > 1) {
             const size_t nb = chunk_array_bytes(w, B, ch.C);
             if (!workspace || workspace_bytes < forward_chunk_arrays(w, ch.C) * nb) return SIG_EWORKSPACE;
             if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)coeffs & 15) != 0) return SIG_EINVAL;
             Sc = (float*)workspace;
-            if (forward_chunk_arrays(w, ch.C) > 1) Pfx = (float*)((unsigned char*)workspace + nb);
         }
         hipEvent_t* pe = g_prof.next(0);
         if (pe) (void)hipEventRecord(pe[0], st);
         hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
         if (pe) (void)hipEventRecord(pe[1], st);
-        if (e == hipSuccess && ch.C > 1)
-            e = sig::chunk_scan(w.d, w.depth, Sc, Pfx, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)ch.C, nullptr, st);
+        if (e == hipSuccess && ch.C > 1) e = chunk_product_of(w, Sc, coeffs, B, ch.C, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     bool small_set = false;
@@ -1583,35 +1575,25 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
                                  void* workspace, hipStream_t st)
 {
     if ((((uintptr_t)coeffs | (uintptr_t)grad_coeffs | (uintptr_t)ckpt) & 15) != 0) return SIG_EINVAL;
-    const int64_t nW = w.size();
-    // workspace: increment gradients | boundary adjoints [B][C - 1][|W|] | for more than two chunks: products from the
-    // left and from the right, [B][C][|W|] each
-    const size_t gb = gdx_bytes_of(w, B, n_points), nb = chunk_array_bytes(w, B, ch.C), ab = chunk_array_bytes(w, B, ch.C - 1);
+    const int64_t nW = w.size(), nL = w.level_start[(size_t)w.depth];   // all words, those shorter than the depth
+    // workspace: increment gradients | boundary adjoints [B][C - 1] | for more than two chunks: products from the left and from
+    // the right, [B][C] each, rows of the shorter words (less than the workspace holds)
     float* gdx = (float*)workspace;
-    float* Abar = (float*)((unsigned char*)workspace + gb);
+    float* Abar = (float*)((unsigned char*)workspace + gdx_bytes_of(w, B, n_points));
     CallTimer whole(1, st);
     const int64_t n_gdx = B * (n_points - 1) * w.d;                 // cleared by the launch of the adjoints
     hipError_t e = hipSuccess;
     const float* row_coeffs = ckpt;
-    bool low = false;
-    if (ch.C > 2 && sig::trunc_low_available(w.d, w.depth)) {
-        // products by slices over the words shorter than the depth, in rows of those (less than the workspace holds)
-        const size_t lb = lanes_low_bytes(w, B, ch.C);
+    const bool low = ch.C > 2;
+    if (low) {
         float* left = (float*)((unsigned char*)Abar + lanes_low_bytes(w, B, ch.C - 1));
-        float* right = (float*)((unsigned char*)left + lb);
+        float* right = (float*)((unsigned char*)left + lanes_low_bytes(w, B, ch.C));
         e = sig::chunk_slices_both(w.d, w.depth, ckpt, nW, left, right, B, (int)ch.C, st);
-        if (e == hipSuccess) e = sig::chunk_adjoint_low(w.d, w.depth, grad_coeffs, right, Abar, B, (int)ch.C, gdx, n_gdx, st);
+        if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, right, nL, Abar, B, (int)ch.C, gdx, n_gdx, st);
         row_coeffs = left;
-        low = true;
-    } else if (ch.C == 2) {
-        // two chunks: the signature at the end of the first is the first chunk's own, what follows it the second's
-        e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, Abar, B, 2, true, st, gdx, n_gdx);
     } else {
-        float* Pfx = (float*)((unsigned char*)workspace + gb + ab);
-        float* Q = (float*)((unsigned char*)workspace + gb + ab + nb);
-        e = sig::chunk_scan(w.d, w.depth, ckpt, Pfx, Q, coeffs, nullptr, nullptr, nullptr, B, (int)ch.C, nullptr, st);
-        if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, Q, Abar, B, (int)ch.C, true, st, gdx, n_gdx);
-        row_coeffs = Pfx;
+        // two chunks: the signature at the end of the first is the first chunk's own, what follows it the second's
+        e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, ckpt + nW, nW, Abar, B, 2, gdx, n_gdx, st);
     }
     if (e != hipSuccess) return hip_fail(e);
     hipEvent_t* pe = g_prof.next(1);
@@ -1715,22 +1697,19 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     if (trunc) {
         const float* row_coeffs = coeffs;
         const float* row_grad = grad_coeffs;
+        if (ch.C > 1 && !ch.fused && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) != 0) return SIG_EINVAL;
+        // (shapes whose chunks low_backward takes: a call without its workspace walks whole paths)
+        if (ch.C > 1 && sig::trunc_low_available(w.d, w.depth)) ch = BwdShape{false, false, 1, n_points - 1};
         if (ch.C > 1 && !ch.fused) {
-            if ((((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) != 0) return SIG_EINVAL;
             // chunk signatures (recomputed: only the terminal signature was kept), then the signature and the
             // adjoint at the end of every chunk
-            const size_t gb = ((size_t)B * (size_t)(n_points - 1) * (size_t)w.d * sizeof(float) + 255) & ~(size_t)255;
             const size_t nb = chunk_array_bytes(w, B, ch.C);
-            unsigned char* base = (unsigned char*)workspace + gb;
+            unsigned char* base = (unsigned char*)workspace + gdx_bytes_of(w, B, n_points);
             float* Sc = (float*)base;
             float* Pfx = (float*)(base + nb);
-            float* Q = (float*)(base + 2 * nb);
-            float* Abar = (float*)(base + 3 * nb);
+            float* Abar = (float*)(base + 2 * nb);
             e = sig::trunc_forward(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
-            bool adjoints_done = false;
-            if (e == hipSuccess)
-                e = sig::chunk_scan(w.d, w.depth, Sc, Pfx, Q, coeffs, nullptr, grad_coeffs, Abar, B, (int)ch.C, &adjoints_done, st);
-            if (e == hipSuccess && !adjoints_done) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, Q, Abar, B, (int)ch.C, false, st);
+            if (e == hipSuccess) e = sig::chunk_scan(w.d, w.depth, Sc, Pfx, coeffs, nullptr, grad_coeffs, Abar, B, (int)ch.C, st);
             if (e != hipSuccess) return hip_fail(e);
             row_coeffs = Pfx;
             row_grad = Abar;
@@ -1879,11 +1858,9 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     if (((uintptr_t)checkpoint & 255) != 0 || ((uintptr_t)coeffs & 15) != 0) return SIG_EINVAL;
-    float* Pfx = nullptr;
     if (forward_chunk_arrays(w, ch.C) > 1) {
         if (!workspace || workspace_bytes < nb) return SIG_EWORKSPACE;
         if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
-        Pfx = (float*)workspace;
     }
     hipStream_t st = (hipStream_t)stream;
     CallTimer whole(0, st);
@@ -1892,7 +1869,7 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
     if (pe) (void)hipEventRecord(pe[0], st);
     hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
     if (pe) (void)hipEventRecord(pe[1], st);
-    if (e == hipSuccess) e = chunk_product_of(w, Sc, Pfx, coeffs, B, ch.C, st);
+    if (e == hipSuccess) e = chunk_product_of(w, Sc, coeffs, B, ch.C, st);
     return e == hipSuccess ? SIG_OK : hip_fail(e);
 }
 

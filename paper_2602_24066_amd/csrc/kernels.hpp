@@ -177,26 +177,24 @@ hipError_t trunc_backward_tails_fused(int d, int depth, const float* path, const
 
 // Time chunks (kernels_chunk.hip): products of chunk signatures and adjoints at chunk boundaries, d a power of two
 bool chunking_available(int d, int depth);
-// forward: Q = terminal = nullptr, coeffs_out [B, |W|] receives the product of the C chunk signatures Sc [B, C, |W|];
-// backward: coeffs_out = nullptr, Pfx [B, C, |W|] receives the signatures up to the end of every chunk (the last one
-// is copied from terminal [B, |W|]) and Q [B, C, |W|] the signatures of the rest of the path after every chunk.
-hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, float* Q, const float* terminal, float* coeffs_out,
-                      const float* grad, float* Abar, int64_t B, int C, bool* adjoints_done, hipStream_t stream);
-// (backward, small signatures: when grad [B, |W|] and Abar [B, C, |W|] are given the kernel also forms the boundary
-// adjoints and *adjoints_done is set; otherwise call chunk_adjoint afterwards)
-// Abar [B, C, |W|]: adjoint of the signature at the end of every chunk, from grad [B, |W|] and Q
-// (skip_last: the last chunk's row of Abar, a copy of grad, is not written)
-hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, float* Abar, int64_t B, int C, bool skip_last,
-                         hipStream_t stream, float* zero = nullptr, int64_t n_zero = 0);
+// Signatures that fit LDS three times.  Forward (Abar = nullptr): coeffs_out [B, |W|] receives the product of the C chunk
+// signatures Sc [B, C, |W|]; backward: Pfx [B, C, |W|] receives the signatures up to the end of every chunk (the last one is
+// copied from terminal [B, |W|]) and Abar [B, C, |W|] the adjoints there, from grad [B, |W|].
+hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, const float* terminal, float* coeffs_out, const float* grad,
+                      float* Abar, int64_t B, int C, hipStream_t stream);
+// coeffs [B, |W|] = the product of two chunk signatures, Sc [B, 2, |W|], over the whole grid; B <= 65,535
+hipError_t chunk_product(int d, int depth, const float* Sc, float* coeffs, int64_t B, hipStream_t stream);
+// Abar [B][C - 1]: adjoints of the words shorter than the depth at the ends of all chunks but the last, from grad [B][|W|] and the
+// signatures of what follows, Q [B][C]; rows of row_words floats (the words shorter than the depth, or all); n_zero floats at
+// zero are cleared on the way
+hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, int64_t row_words, float* Abar, int64_t B, int C,
+                         float* zero, int64_t n_zero, hipStream_t stream);
 // Shapes of trunc_low_available, a workgroup per path and letter and one launch whatever the number of chunks:
 // coeffs [B][|W|] = the product of the chunk signatures Sc [B][C][|W|]
 hipError_t chunk_slices_forward(int d, int depth, const float* Sc, float* coeffs, int64_t B, int C, hipStream_t stream);
 // over the words shorter than the depth, all arrays [B][C] rows of them: left[c] = S_0 .. S_c and right[c] = S_{c+1} .. S_{C-1}
-// for c <= C - 2, then Abar [B][C - 1] from grad [B][|W|] and `right`; n_zero floats at zero are cleared on the way
-// (Sc: rows of sc_words floats that begin with them)
+// for c <= C - 2 (Sc: rows of sc_words floats that begin with them)
 hipError_t chunk_slices_both(int d, int depth, const float* Sc, int64_t sc_words, float* left, float* right, int64_t B, int C,
                              hipStream_t stream);
-hipError_t chunk_adjoint_low(int d, int depth, const float* grad, const float* right, float* Abar, int64_t B, int C, float* zero,
-                             int64_t n_zero, hipStream_t stream);
 
 }  // namespace sig

@@ -56,27 +56,19 @@ __device__ __forceinline__ void tensor_product(const float* a, const float* b, f
     }
 }
 
-__device__ __forceinline__ void copy_row(const float* src, float* dst, float* dst2, int W)
+__device__ __forceinline__ void copy_row(const float* src, float* dst, int W)
 {
-    for (int o = 4 * threadIdx.x; o < W; o += 4 * blockDim.x) {
-        const f4 v = *(const f4*)(src + o);
-        *(f4*)(dst + o) = v;
-        if (dst2) *(f4*)(dst2 + o) = v;
-    }
+    for (int o = 4 * threadIdx.x; o < W; o += 4 * blockDim.x) *(f4*)(dst + o) = *(const f4*)(src + o);
 }
 
 // out(u) = gr(u) + sum_{m >= 1} sum_{|v| = m} gr(u v) q(v) for every word u, by the whole workgroup.  The words of
 // one length k are spread over the workgroup, with blockDim / d^k threads (at most 64, at least 1) sharing the
 // inner sums of a word; for a fixed m the terms of a word are contiguous in gr and in q.
-// (k_only > 0: the words of that length alone, and with k_only == 1 also the copy of the longest words, so that a
-// grid of N - 1 workgroups per row shares the work)
-__device__ __forceinline__ void adjoint_contract(const float* gr, const float* q, float* __restrict__ out, const Levels& g,
-                                                 int k_only = 0)
+__device__ __forceinline__ void adjoint_contract(const float* gr, const float* q, float* __restrict__ out, const Levels& g)
 {
     const int N = g.N;
-    if (k_only <= 1) copy_row(gr + g.ls[N], out + g.ls[N], nullptr, g.W - g.ls[N]);       // words of length N
+    copy_row(gr + g.ls[N], out + g.ls[N], g.W - g.ls[N]);               // words of length N
     for (int k = 1; k < N; ++k) {
-        if (k_only > 0 && k != k_only) continue;
         const int nk = g.ls[k + 1] - g.ls[k];                           // words of length k
         int tpw = (int)blockDim.x / nk;                                 // threads per word (power of two)
         tpw = tpw > 64 ? 64 : (tpw < 1 ? 1 : tpw);
@@ -98,90 +90,52 @@ __device__ __forceinline__ void adjoint_contract(const float* gr, const float* q
     }
 }
 
-// One workgroup per path.  Forward (Q == nullptr): coeffs_out[b] = S_1 (x) .. (x) S_C.  Backward: Pfx[c] =
-// S_1 (x) .. (x) S_c for c < C and Pfx[C] = terminal[b] (the signature the caller kept), Q[c] = S_{c+1} (x) .. (x) S_C
-// for c < C.  With LDS the running product and the next factor are staged in three rotating LDS buffers of W floats
-// (small signatures); without, the operands are read from the global arrays written in earlier steps, which
-// __syncthreads() makes visible inside the workgroup.  With LDS and Abar != nullptr the adjoints at the chunk
-// boundaries, Abar[c](u) = sum_v grad(u v) Q[c](v), are formed here as well and Q is
-// not written out; grad is read from global memory there (consecutive threads read consecutive coefficients).
-template <bool LDS>
-__global__ __launch_bounds__(1024) void chunk_scan_kernel(const float* __restrict__ Sc, float* Pfx, float* Q,
-                                                          const float* __restrict__ terminal, float* coeffs_out,
-                                                          const float* __restrict__ grad, float* Abar, int C, Levels g)
+// Signatures that fit LDS three times, a workgroup per path: the running product and the next factor are staged in three
+// rotating buffers of W floats.  Forward (Abar == nullptr): coeffs_out[b] = S_1 (x) .. (x) S_C.  Backward, two workgroups per
+// path side by side: Pfx[c] = S_1 (x) .. (x) S_c for c < C and Pfx[C] = terminal[b] (the signature the caller kept); and, from
+// the suffix products Q_c = S_{c+1} (x) .. (x) S_C, the adjoints at the chunk boundaries, Abar[c](u) = sum_v grad(u v) Q_c(v)
+// (grad is read from global memory: consecutive threads read consecutive coefficients).
+__global__ __launch_bounds__(1024) void chunk_scan_kernel(const float* __restrict__ Sc, float* Pfx, const float* __restrict__ terminal,
+                                                          float* coeffs_out, const float* __restrict__ grad, float* Abar, int C, Levels g)
 {
     extern __shared__ f4 smem4[];
     float* sm = (float*)smem4;
     const int64_t b = blockIdx.x;
     const int64_t W = g.W;
     const float* S = Sc + b * C * W;
-    float* P = Pfx + b * C * W;
-    const bool bwd = Q != nullptr;
-    float* Qb = bwd ? Q + b * C * W : nullptr;
-    if constexpr (LDS) {
-        // gridDim.y == 2 (backward): workgroup 0 of a path does the prefix products, workgroup 1 the suffix products
-        // and the adjoints, side by side; otherwise one workgroup does everything in turn
-        const bool do_prefix = gridDim.y == 1 || blockIdx.y == 0;
-        const bool do_suffix = bwd && (gridDim.y == 1 || blockIdx.y == 1);
-        float* buf[3] = {sm, sm + W, sm + 2 * W};
-        int cur = 0;
-        if (do_prefix) {
-            copy_row(S, buf[0], bwd ? P : nullptr, (int)W);
-            const int lastp = bwd ? C - 2 : C - 1;
-            for (int s = 1; s <= lastp; ++s) {
-                const int nb = (cur + 1) % 3, no = (cur + 2) % 3;
-                copy_row(S + (int64_t)s * W, buf[nb], nullptr, (int)W);
-                __syncthreads();
-                float* dst = (!bwd && s == C - 1) ? coeffs_out + b * W : (bwd ? P + (int64_t)s * W : nullptr);
-                tensor_product(buf[cur], buf[nb], buf[no], dst, g);
-                cur = no;
-                __syncthreads();
-            }
-            if (bwd) copy_row(terminal + b * W, P + (int64_t)(C - 1) * W, nullptr, (int)W);
-        }
-        if (do_suffix) {
-            const float* const gb = grad ? grad + b * W : nullptr;
-            float* const Ab = Abar ? Abar + b * C * W : nullptr;
-            if (Ab) copy_row(gb, Ab + (int64_t)(C - 1) * W, nullptr, (int)W);     // the last chunk's adjoint is grad
-            // suffix products
+    const bool bwd = Abar != nullptr;
+    float* buf[3] = {sm, sm + W, sm + 2 * W};
+    int cur = 0;
+    if (blockIdx.y == 0) {
+        float* P = bwd ? Pfx + b * C * W : nullptr;
+        copy_row(S, buf[0], (int)W);
+        if (bwd) copy_row(S, P, (int)W);
+        const int lastp = bwd ? C - 2 : C - 1;
+        for (int s = 1; s <= lastp; ++s) {
+            const int nb = (cur + 1) % 3, no = (cur + 2) % 3;
+            copy_row(S + (int64_t)s * W, buf[nb], (int)W);
             __syncthreads();
-            copy_row(S + (int64_t)(C - 1) * W, buf[0], Ab ? nullptr : Qb + (int64_t)(C - 2) * W, (int)W);
-            cur = 0;
-            if (Ab) {
-                __syncthreads();
-                adjoint_contract(gb, buf[0], Ab + (int64_t)(C - 2) * W, g);
-            }
-            for (int q = C - 3; q >= 0; --q) {
-                const int nb = (cur + 1) % 3, no = (cur + 2) % 3;
-                copy_row(S + (int64_t)(q + 1) * W, buf[nb], nullptr, (int)W);
-                __syncthreads();
-                tensor_product(buf[nb], buf[cur], buf[no], Ab ? nullptr : Qb + (int64_t)q * W, g);
-                cur = no;
-                __syncthreads();
-                if (Ab) adjoint_contract(gb, buf[cur], Ab + (int64_t)q * W, g);
-            }
+            float* dst = (!bwd && s == C - 1) ? coeffs_out + b * W : (bwd ? P + (int64_t)s * W : nullptr);
+            tensor_product(buf[cur], buf[nb], buf[no], dst, g);
+            cur = no;
+            __syncthreads();
         }
+        if (bwd) copy_row(terminal + b * W, P + (int64_t)(C - 1) * W, (int)W);
     } else {
-        // signatures too large for LDS: products in global memory; with gridDim.y == 2 (backward) workgroup 0 of a
-        // path does the products from the left, workgroup 1 those from the right, side by side
-        const bool do_prefix = gridDim.y == 1 || blockIdx.y == 0;
-        const bool do_suffix = bwd && (gridDim.y == 1 || blockIdx.y == 1);
-        if (do_prefix) {
-            copy_row(S, P, nullptr, (int)W);
-            if (bwd) copy_row(terminal + b * W, P + (int64_t)(C - 1) * W, nullptr, (int)W);
-        }
-        if (do_suffix) copy_row(S + (int64_t)(C - 1) * W, Qb + (int64_t)(C - 2) * W, nullptr, (int)W);
-        const int last = bwd ? C - 2 : C - 1;
-        for (int s = 1; s <= last; ++s) {
+        const float* const gb = grad + b * W;
+        float* const Ab = Abar + b * C * W;
+        copy_row(gb, Ab + (int64_t)(C - 1) * W, (int)W);                // the last chunk's adjoint is grad
+        copy_row(S + (int64_t)(C - 1) * W, buf[0], (int)W);
+        __syncthreads();
+        adjoint_contract(gb, buf[0], Ab + (int64_t)(C - 2) * W, g);
+        for (int q = C - 3; q >= 0; --q) {
+            const int nb = (cur + 1) % 3, no = (cur + 2) % 3;
+            copy_row(S + (int64_t)(q + 1) * W, buf[nb], (int)W);
             __syncthreads();
-            if (do_prefix) {
-                float* dst = (!bwd && s == C - 1) ? coeffs_out + b * W : P + (int64_t)s * W;
-                tensor_product(P + (int64_t)(s - 1) * W, S + (int64_t)s * W, dst, nullptr, g);
-            }
-            if (do_suffix) {
-                const int q = C - 2 - s;              // >= 0 because s <= C - 2
-                tensor_product(S + (int64_t)(q + 1) * W, Qb + (int64_t)(q + 1) * W, Qb + (int64_t)q * W, nullptr, g);
-            }
+            tensor_product(buf[nb], buf[cur], buf[no], nullptr, g);
+            cur = no;
+            __syncthreads();
+            adjoint_contract(gb, buf[cur], Ab + (int64_t)q * W, g);
         }
     }
 }
@@ -200,116 +154,7 @@ __global__ __launch_bounds__(256) void chunk_product_kernel(const float* __restr
     *(f4*)(out + b * out_stride + o) = quad_product(a + b * a_stride, bfac + b * b_stride, g, n, o - g.ls[n]);
 }
 
-// dst[b] = src[b] for every path, rows of W floats (a multiple of 4) at the given strides
-__global__ __launch_bounds__(256) void chunk_copy_rows_kernel(const float* __restrict__ src, int64_t src_stride, float* __restrict__ dst,
-                                                              int64_t dst_stride, int W)
-{
-    const int o = 4 * (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (o >= W) return;
-    *(f4*)(dst + (int64_t)blockIdx.y * dst_stride + o) = *(const f4*)(src + (int64_t)blockIdx.y * src_stride + o);
-}
-
-// coefficient of one word (length n, index i inside the level) of a (x) b
-__device__ __forceinline__ float word_product(const float* a, const float* b, const Levels& g, int n, int i)
-{
-    float acc = a[g.ls[n] + i] + b[g.ls[n] + i];
-    for (int k = 1; k < n; ++k) {
-        const int sh = g.lb * (n - k);
-        acc = fmaf(a[g.ls[k] + (i >> sh)], b[g.ls[n - k] + (i & ((1 << sh) - 1))], acc);
-    }
-    return acc;
-}
-
-// out[b] = a[b] (x) bfac[b] (x) c[b] in one pass (three time chunks, the usual count for long paths), without the
-// intermediate array and its launch:
-//     (a b c)(w) = c(w) + (a b)(w) + sum_{0 < l < n} (a b)(w_1..w_l) c(w_{l+1}..w_n),
-//     (a b)(w)   = a(w) + b(w)     + sum_{0 < k < n} a(w_1..w_k) b(w_{k+1}..w_n).
-// A workgroup takes 1,024 consecutive words of one length n (blockIdx.x runs over the lengths, each padded to whole
-// workgroups).  Their prefixes of length l are the 1,024 / d^(n-l) (at least one) consecutive words of that length,
-// so a(prefix) and (a b)(prefix) are computed once per workgroup into LDS; what a thread then reads per quad is
-// the three quads of w and, per cut, one suffix quad of b and one of c.
-constexpr int kProduct3Prefixes = 384;             // 256 + 64 + 16 + 4 + 1 + ... for d = 4; fewer for larger d
-
-__host__ __device__ inline int product3_blocks(const Levels& g, int n) { return ((g.ls[n + 1] - g.ls[n]) / 4 + 255) / 256; }
-
-__global__ __launch_bounds__(256) void chunk_product3_kernel(const float* __restrict__ a, const float* __restrict__ bfac,
-                                                             const float* __restrict__ c, int64_t in_stride,
-                                                             float* __restrict__ out, int64_t out_stride, Levels g)
-{
-    __shared__ float sA[kProduct3Prefixes], sAB[kProduct3Prefixes];
-    const int64_t b = blockIdx.y;
-    int blk = (int)blockIdx.x, n = 1;
-    while (n < g.N && blk >= product3_blocks(g, n)) { blk -= product3_blocks(g, n); ++n; }
-    const int words = g.ls[n + 1] - g.ls[n];
-    const int i0 = blk * 1024;                         // first word of the workgroup inside its length
-    const float* pa = a + b * in_stride;
-    const float* pb = bfac + b * in_stride;
-    const float* pc = c + b * in_stride;
-    // prefixes of length l = 1 .. n - 1 of the words i0 .. i0 + 1023: cnt_l consecutive words from p0_l on
-    int off = 0;
-    for (int l = 1; l < n; ++l) {
-        const int sh = g.lb * (n - l);
-        const int p0 = i0 >> sh;
-        const int cnt = (1024 >> sh) > 0 ? (1024 >> sh) : 1;
-        const int have = g.ls[l + 1] - g.ls[l];
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x)
-            if (p0 + t < have) {
-                sA[off + t] = pa[g.ls[l] + p0 + t];
-                sAB[off + t] = word_product(pa, pb, g, l, p0 + t);
-            }
-        off += cnt;
-    }
-    __syncthreads();
-    const int i = i0 + 4 * (int)threadIdx.x;
-    if (i >= words) return;
-    const int o = g.ls[n] + i;
-    f4 acc = (*(const f4*)(pa + o) + *(const f4*)(pb + o)) + *(const f4*)(pc + o);
-    off = 0;
-    for (int l = 1; l < n; ++l) {
-        const int sh = g.lb * (n - l);
-        const int pi = off + (i >> sh) - (i0 >> sh);
-        const int suffix = g.ls[n - l] + (i & ((1 << sh) - 1));
-        acc += sA[pi] * *(const f4*)(pb + suffix);
-        acc += sAB[pi] * *(const f4*)(pc + suffix);
-        off += (1024 >> sh) > 0 ? (1024 >> sh) : 1;
-    }
-    *(f4*)(out + b * out_stride + o) = acc;
-}
-
-// One workgroup per (path, chunk): Abar[b][c](u) = grad[b](u) + sum_{m >= 1} sum_{|v| = m} grad[b](u v) Q[b][c](v);
-// the last chunk's adjoint is grad itself.  The words of one length k are spread over the whole workgroup, with
-// blockDim / d^k threads (at most 64, at least 1) sharing the inner sums of a word; for a fixed m the terms of a
-// word are contiguous in grad and in Q.
-template <bool LDS>
-__global__ __launch_bounds__(512) void chunk_adjoint_kernel(const float* __restrict__ grad, const float* __restrict__ Q,
-                                                            float* __restrict__ Abar, int C, bool skip_last, Levels g)
-{
-    extern __shared__ f4 smem4[];
-    float* sm = (float*)smem4;
-    const int64_t row = blockIdx.x;
-    const int64_t b = row / C;
-    const int c = (int)(row - b * C);
-    const int W = g.W;
-    const float* gr = grad + b * W;
-    // without the rows of the last chunk the array is [B][C - 1][W]
-    float* out = Abar + (skip_last ? row - b : row) * W;
-    if (c == C - 1) {
-        if (!skip_last && blockIdx.y == 0) copy_row(gr, out, nullptr, W);
-        return;
-    }
-    const float* q = Q + row * W;
-    if constexpr (LDS) {
-        copy_row(gr, sm, nullptr, W);
-        copy_row(q, sm + W, nullptr, W);
-        __syncthreads();
-        gr = sm;
-        q = sm + W;
-    }
-    // large signatures: one workgroup per (row, word length), their sums read global memory and are bound by latency
-    adjoint_contract(gr, q, out, g, gridDim.y > 1 ? (int)blockIdx.y + 1 : 0);
-}
-
-// The same sums for large signatures, one workgroup per (path, chunk, first letter a): every word u that begins with a
+// The boundary adjoints of large signatures, one workgroup per (path, chunk, first letter a): every word u that begins with a
 // gets Abar(u) = grad(u) + sum_v grad(u v) Q(v).  The words u v all begin with a too, so workgroups share no output,
 // and what a workgroup reads - the gradients of the words a v and Q(v) for |v| < N, 2 (d + .. + d^(N-1)) floats - is
 // staged in LDS once: sg[ls[m] + v] = grad(a v), sq[ls[m] + v] = Q(v) for |v| = m.  All 512 threads work on one word
@@ -606,80 +451,27 @@ bool chunking_available(int d, int depth)
     return make_levels(d, depth, g);
 }
 
-hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, float* Q, const float* terminal, float* coeffs_out,
-                      const float* grad, float* Abar, int64_t B, int C, bool* adjoints_done, hipStream_t stream)
+hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, const float* terminal, float* coeffs_out, const float* grad,
+                      float* Abar, int64_t B, int C, hipStream_t stream)
 {
-    if (adjoints_done) *adjoints_done = false;
     Levels g;
     if (!make_levels(d, depth, g) || C < 2 || B < 1 || B > 0x7fffffff) return hipErrorInvalidValue;
-    if ((Q != nullptr) != (terminal != nullptr) || (Q == nullptr) == (coeffs_out == nullptr)) return hipErrorInvalidValue;
-    const bool fuse = Q != nullptr && grad != nullptr && Abar != nullptr;
+    const bool bwd = Abar != nullptr;
+    if (bwd ? !Pfx || !terminal || !grad || coeffs_out : !coeffs_out) return hipErrorInvalidValue;
     const size_t lds = 3 * (size_t)g.W * sizeof(float);
-    if (lds <= kMaxChunkLds) {
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_scan_kernel<true>), (int)kMaxChunkLds);
-        if (e != hipSuccess) return e;
-        chunk_scan_kernel<true><<<dim3((unsigned)B, fuse ? 2 : 1), 1024, lds, stream>>>(
-            Sc, Pfx, Q, terminal, coeffs_out, fuse ? grad : nullptr, fuse ? Abar : nullptr, C, g);
-        if (fuse && adjoints_done) *adjoints_done = true;
-    } else if (Q == nullptr && B <= 65535) {
-        // forward with large signatures: one grid-wide product per chunk boundary
-        const int64_t W = g.W;
-        const dim3 grid((unsigned)((W / 4 + 255) / 256), (unsigned)B);
-        if (C == 3) {
-            unsigned blocks = 0;
-            for (int n = 1; n <= g.N; ++n) blocks += (unsigned)product3_blocks(g, n);
-            chunk_product3_kernel<<<dim3(blocks, (unsigned)B), 256, 0, stream>>>(Sc, Sc + W, Sc + 2 * (int64_t)W, (int64_t)C * W,
-                                                                               coeffs_out, W, g);
-            return hipGetLastError();
-        }
-        const float* acc = Sc;                       // S_1 of every path, row stride C W
-        int64_t acc_stride = (int64_t)C * W;
-        for (int s = 1; s < C; ++s) {
-            float* dst = s == C - 1 ? coeffs_out : Pfx + (int64_t)s * W;
-            const int64_t dst_stride = s == C - 1 ? W : (int64_t)C * W;
-            chunk_product_kernel<<<grid, 256, 0, stream>>>(acc, acc_stride, Sc + (int64_t)s * W, (int64_t)C * W, dst,
-                                                           dst_stride, g);
-            acc = dst;
-            acc_stride = dst_stride;
-        }
-    } else if (Q != nullptr && coeffs_out == nullptr && B <= 64 && g.W % 4 == 0) {
-        // backward with large signatures and few paths: a workgroup or two per path would leave the chip idle, so every
-        // product is spread over the whole grid (a launch per chunk boundary and direction)
-        const int64_t W = g.W, row = (int64_t)C * W;
-        const dim3 grid((unsigned)((W / 4 + 255) / 256), (unsigned)B);
-        chunk_copy_rows_kernel<<<grid, 256, 0, stream>>>(Sc, row, Pfx, row, (int)W);
-        chunk_copy_rows_kernel<<<grid, 256, 0, stream>>>(terminal, W, Pfx + (int64_t)(C - 1) * W, row, (int)W);
-        chunk_copy_rows_kernel<<<grid, 256, 0, stream>>>(Sc + (int64_t)(C - 1) * W, row, Q + (int64_t)(C - 2) * W, row, (int)W);
-        for (int s = 1; s <= C - 2; ++s) {
-            chunk_product_kernel<<<grid, 256, 0, stream>>>(Pfx + (int64_t)(s - 1) * W, row, Sc + (int64_t)s * W, row,
-                                                           Pfx + (int64_t)s * W, row, g);
-            const int q = C - 2 - s;
-            chunk_product_kernel<<<grid, 256, 0, stream>>>(Sc + (int64_t)(q + 1) * W, row, Q + (int64_t)(q + 1) * W, row,
-                                                           Q + (int64_t)q * W, row, g);
-        }
-    } else {
-        chunk_scan_kernel<false><<<dim3((unsigned)B, Q != nullptr ? 2 : 1), 1024, 0, stream>>>(Sc, Pfx, Q, terminal, coeffs_out, nullptr,
-                                                                                          nullptr, C, g);
-    }
+    if (lds > kMaxChunkLds) return hipErrorInvalidValue;
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_scan_kernel), (int)kMaxChunkLds);
+    if (e != hipSuccess) return e;
+    chunk_scan_kernel<<<dim3((unsigned)B, bwd ? 2 : 1), 1024, lds, stream>>>(Sc, Pfx, terminal, coeffs_out, grad, Abar, C, g);
     return hipGetLastError();
 }
 
-hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, float* Abar, int64_t B, int C, bool skip_last,
-                         hipStream_t stream, float* zero, int64_t n_zero)
+hipError_t chunk_product(int d, int depth, const float* Sc, float* coeffs, int64_t B, hipStream_t stream)
 {
     Levels g;
-    if (!make_levels(d, depth, g) || C < 2 || B < 1 || B * C > 0x7fffffff) return hipErrorInvalidValue;
-    const size_t lds = 2 * (size_t)g.W * sizeof(float);
-    const bool subtree = lds > 64 * 1024 && skip_last && g.lb * (g.N - 1) >= 2 && 2 * (size_t)g.ls[g.N] * sizeof(float) <= 64 * 1024;
-    if (n_zero > 0 && !subtree) {
-        hipError_t e = fill_zero(zero, n_zero, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (lds <= 64 * 1024) chunk_adjoint_kernel<true><<<(unsigned)(B * C), 512, lds, stream>>>(grad, Q, Abar, C, skip_last, g);
-    else if (subtree)
-        chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, 2 * (size_t)g.ls[g.N] * sizeof(float), stream>>>(
-            grad, Q, Abar, C, zero, n_zero, g.W, g);
-    else chunk_adjoint_kernel<false><<<dim3((unsigned)(B * C), (unsigned)(g.N - 1)), 512, 0, stream>>>(grad, Q, Abar, C, skip_last, g);
+    if (!make_levels(d, depth, g) || B < 1 || B > 65535) return hipErrorInvalidValue;
+    const int64_t W = g.W;
+    chunk_product_kernel<<<dim3((unsigned)((W / 4 + 255) / 256), (unsigned)B), 256, 0, stream>>>(Sc, 2 * W, Sc + W, 2 * W, coeffs, W, g);
     return hipGetLastError();
 }
 
@@ -702,14 +494,14 @@ hipError_t chunk_slices_both(int d, int depth, const float* Sc, int64_t sc_words
     return hipGetLastError();
 }
 
-hipError_t chunk_adjoint_low(int d, int depth, const float* grad, const float* right, float* Abar, int64_t B, int C, float* zero,
-                             int64_t n_zero, hipStream_t stream)
+hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, int64_t row_words, float* Abar, int64_t B, int C,
+                         float* zero, int64_t n_zero, hipStream_t stream)
 {
     Levels g;
-    if (!make_levels(d, depth, g) || C < 2 || B < 1 || B * C > 0x7fffffff) return hipErrorInvalidValue;
+    if (!make_levels(d, depth, g) || C < 2 || B < 1 || B * C > 0x7fffffff || row_words < g.ls[g.N]) return hipErrorInvalidValue;
     const size_t lds = 2 * (size_t)g.ls[g.N] * sizeof(float);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
-    chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, lds, stream>>>(grad, right, Abar, C, zero, n_zero, g.ls[g.N], g);
+    chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, lds, stream>>>(grad, Q, Abar, C, zero, n_zero, row_words, g);
     return hipGetLastError();
 }
 

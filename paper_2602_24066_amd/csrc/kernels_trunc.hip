@@ -1493,6 +1493,16 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
                     At[i] += (acc[0] + acc[1]) + (acc[2] + acc[3]);
                 }
             }
+            // back to one value a chain word, in the first of its lanes: shares of a gradient whose terms cancel (that of a
+            // log-signature) are larger than it, and the walk would round them (+ 10 % error)
+            Ac[0] += dpp_lane<0x128>(Ac[0]);
+            Ac[0] += dpp_lane<0x124>(Ac[0]);
+            Ac[0] += dpp_lane<0x4E>(Ac[0]);
+            Ac[0] += dpp_lane<0xB1>(Ac[0]);
+            Ac[1] += dpp_lane<0x4E>(Ac[1]);
+            Ac[1] += dpp_lane<0xB1>(Ac[1]);
+            Ac[0] = lane % ipow(D, KL - 1) == 0 ? Ac[0] : 0.0f;
+            Ac[1] = lane % ipow(D, KL - 2) == 0 ? Ac[1] : 0.0f;
         }
         __syncthreads();                               // the buffers are dead: their space takes gt / Vb from here on
     }

@@ -927,7 +927,7 @@ hipError_t launch_lanes(hipFunction_t fn, const sig::LanesShape& s, const float*
                         (void*)&lM, (void*)&low_coeffs, (void*)&low_grad};
         return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
     }
-    long lz = (long)n_zero;
+    long lz = (long)n_zero;            // (the last two: of the kernel in the backward module alone)
     void* args[] = {(void*)&path, (void*)&lB, (void*)&lP, (void*)&out, (void*)&win, (void*)&lK, (void*)&lM, (void*)&zero, (void*)&lz};
     return hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)s.nwb * 64, 1, 1, 0, st, args, nullptr);
 }
@@ -1685,7 +1685,7 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
         e = sig::fill_zero(residual, B, st);
         if (e != hipSuccess) return hip_fail(e);
     }
-    // the fused form copies the gradient row with 16-byte loads; rows that are not aligned so take the kernel with
+    // the fused form reads the leaves of the gradient with 16-byte loads; rows that are not aligned so take the kernel with
     // four wavefronts per path, which reads word by word
     if (ch.fused && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) != 0) ch = BwdShape{false, false, 1, n_points - 1};
     // word sets that may run through the straight-line specialised kernels clear their (larger) array further down

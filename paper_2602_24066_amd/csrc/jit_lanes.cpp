@@ -163,10 +163,17 @@ __device__ __forceinline__ void row_of(const long* __restrict__ win, long KW, lo
 #define DJ ((D + SP - 1) / SP)
 extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float* __restrict__ path, long B, long P,
                                                                       float* __restrict__ coeffs, const long* __restrict__ win,
-                                                                      long KW, long max_len, float* __restrict__ zero, long n_zero)
+                                                                      long KW, long max_len
+#if CLEARS
+                                                                      , float* __restrict__ zero, long n_zero
+#endif
+                                                                      )
 {
-    // n_zero floats at `zero` are cleared on the way for the kernel that runs next
+#if CLEARS
+    // n_zero floats at `zero` are cleared on the way for the kernel that runs next (backward; two more arguments cost a forward
+    // call 0.2 us of launch)
     for (long e = (long)blockIdx.x * (64 * NWB) + threadIdx.x; e < n_zero; e += (long)gridDim.x * (64 * NWB)) zero[e] = 0.0f;
+#endif
     __shared__ __attribute__((aligned(16))) float smem[NWB * TILE_F];
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1111,6 +1118,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         s.per_lane = per_lane;
         const double rounds = (double)std::max<int64_t>(B, 1) * (double)s.waves / 1024.0;
         const double cost = per_lane * (rounds < 1.0 ? 1.0 : rounds);
+        if (best.ok && cost >= best_cost) continue;            // (every call asks, several times)
         // LDS of a wavefront: the increments of a staging tile and, backward, the gradient rows of the segments of a
         // tile; eight wavefronts of 20 KB fit a compute unit, so longer tiles are cut down to that.  The staging
         // tile is as many tiles as fit (up to 32 segments and three increments per lane): its global loads are issued
@@ -1144,7 +1152,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         s.shares = backward && words_up_to(d, depth - 1) * sizeof(float) <= per_wave;
         s.nwb = (int)(per_wave * 4 <= 64 * 1024 ? 4 : (per_wave * 2 <= 64 * 1024 ? 2 : (per_wave <= 64 * 1024 ? 1 : 0)));
         s.ok = s.nwb > 0;
-        if (s.ok && (!best.ok || cost < best_cost)) {
+        if (s.ok) {
             best = s;
             best_cost = cost;
         }
@@ -1250,8 +1258,9 @@ std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
     std::ostringstream o;
     auto lanes = [&](const char* ns, int n, const LanesShape& q, bool bwd, const char* forward_name) {
         o << "#define N " << n << "\n#define R " << q.R << "\n#define SP " << q.split << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
-          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name << "\nnamespace " << ns << " {\n"
-          << kLanesSource << "}\n#undef N\n#undef R\n#undef SP\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n";
+          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name
+          << "\n#define CLEARS " << (backward ? 1 : 0) << "\nnamespace " << ns << " {\n"
+          << kLanesSource << "}\n#undef N\n#undef R\n#undef SP\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n#undef CLEARS\n";
     };
     auto chunk = [&](const char* ns, LanesChunkPart part) {
         o << "#define N " << depth << "\n#define M " << (part == kLanesScanLow ? depth - 1 : depth)

@@ -210,14 +210,15 @@ int    sig_wordset_upload(sig_wordset* ws, void* dev_buf /*device*/, size_t dev_
  * coeffs device float32 [B, |W|]            fully overwritten
  * workspace: device, sig_forward_workspace_bytes bytes (may be 0 -> NULL allowed), 256-byte aligned,
  *            contents undefined before and after.
- * Full truncations with few paths are cut into time chunks that run side by side and are multiplied together
- * afterwards (Chen's relation, eq. 2, is associative); sig_backward does the same where four or more chunks fit
- * (or on request, option "chunks") and recomputes the chunk signatures from the path.  Word sets closed under suffixes (sig_wordset_suffix_closed) that run through the
- * run-time specialised kernels take the chunks of the checkpointed calls below in sig_forward as well, with the
- * chunk signatures in the workspace; sig_backward recomputes them and does the same from four chunks on (few long
- * paths), where that still beats walking whole paths.  Full truncations that run with a word per lane take time chunks in
- * both directions wherever that is faster and the workspace holds them; sig_forward without a workspace (NULL), and
- * sig_backward_static, walk whole paths there.
+ * Few paths are cut into time chunks that run side by side and are multiplied together afterwards (Chen's relation, eq. 2,
+ * is associative); sig_backward recomputes the chunk signatures from the path.  A time model of the launch decides, for the
+ * truncations with kernels of their own, for those that run with a word per lane, and for small launches of any other word set
+ * (up to 4,096 words over up to 8 letters: the chunks run over the set's closure under suffixes, whose kernels the first call
+ * that takes chunks compiles; while a stream is captured only kernels that are loaded are taken).  Larger word sets closed under
+ * suffixes (sig_wordset_suffix_closed) take the chunks of the checkpointed calls below in sig_forward, and in sig_backward from
+ * four chunks on.  A call whose workspace does not hold its chunks (NULL, or fewer bytes than the functions here give) walks
+ * whole paths, except where it has to bring one (SIG_EWORKSPACE: long paths of the truncations with kernels of their own and of
+ * large sets closed under suffixes); sig_backward_static always walks whole paths.
  * n_points == 1 gives all-zero coeffs (S_{0,0} = 1 has no non-empty-word part).  B == 0 is a no-op. */
 size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 int    sig_forward(const sig_wordset* ws, const float* path, int64_t B, int64_t n_points, float* coeffs,
@@ -254,7 +255,8 @@ int    sig_backward_residual(const sig_wordset* ws, const float* path, const flo
  * the signature at the end of chunk c is the product of the first c chunk signatures, the adjoint there is
  * Abar_c(u) = sum_v grad_coeffs(u v) Q_c(v) with Q_c the product of the chunk signatures after c (Proposition 4.1
  * with the right factor taken at a chunk boundary), and inside a chunk the recursion is that of sig_backward
- * (Proposition 4.6).  Nothing is recomputed; the price is C times the memory of coeffs between the two calls, where
+ * (Proposition 4.6).  Nothing is recomputed (unless few paths gain from more chunks than are kept, whose
+ * signatures are then worked out in the backward call); the price is C times the memory of coeffs between the two calls, where
  * sig_forward / sig_backward keep the terminal signature alone (Section 4.2).  The library picks C for the batch
  * (2 .. 16): for full truncations whose backward kernel would otherwise leave SIMDs with a single wavefront (few
  * paths with many segments), and for suffix-closed sets (sig_wordset_suffix_closed) of up to 13,653 words that run

@@ -371,12 +371,17 @@ __device__ __forceinline__ void letter_sums(const float* v, const float* __restr
 //   - S_0 S_1 .. S_part on the lane's chain needs the chain itself and infixes of the lane's word;
 //   - the adjoints at the end of the path, taken back over chunks C - 1 .. part + 1: Abar(u) += sum_v Abar(u v) S_c(v).  The walk is
 //     linear in them and a chain word's may be spread over the lanes that share it, so a lane adds the terms whose word u v is its
-//     own (in its registers) to its share of Abar(u): no sum over lanes, nothing exchanged.
+//     own (in its registers) to its share of Abar(u), nothing exchanged between the chunks.
+// In the end the shares of a wavefront are summed: those of a gradient whose terms cancel (that of a log-signature) are larger than
+// their sum, and the walk would round them.  Error of such a gradient, shares -> sums -> one value per word (arrays): 27 and 64 lanes
+// a path (3 and 4 letters, depth 4) 1.25, 1.37 -> 1.00 -> 1; a word whose lanes lie in several wavefronts keeps that many shares,
+// 1,000 lanes (10 letters) 1.38 -> 1.30 -> 1 (256 paths 0.99: two levels a lane, 100 lanes), still below the walk over whole
+// paths, 1.8.  Backward calls of 12 to 26 us take 0.1 to 0.5 us for it; the arrays cost 5 to 12.
 // The rows pass through the wavefront's LDS one after the other, each loaded while the one before is used.
 // Bound by the latency of a row (0.3-0.6 us); two launches of 5 us and the arrays' traffic saved (256 paths x 199 segments, d = 10,
 // depth 4: 30 us of 181).
-__device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, int part, int C, int p, int lane, float* st, float (&Sc)[K],
-                                               float (&Ac)[K], float (&A1)[D]
+__device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, int part, int C, int p0, int p, int lane, float* st,
+                                               float (&Sc)[K], float (&Ac)[K], float (&A1)[D]
 #if R == 2
                                                , float (&S1)[D], float (&An)[D][D]
 #endif
@@ -447,6 +452,18 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
                 for (int jj = 0; jj < D; ++jj) A1[j] = __builtin_fmaf(An[j][jj], st[jj], A1[j]);
 #endif
         }
+    }
+    // (the lanes that share a word are consecutive; the sum lies in the first of them)
+#pragma unroll
+    for (int k = 1; k < K; ++k) {
+        const int m = ipow(D, K - k), in_run = (p0 + lane) % m;
+        float v = Ac[k - 1];
+#pragma unroll
+        for (int off = 1; off < 64 && off < m; off *= 2) {
+            const float other = __shfl_down(v, off);
+            if (lane + off < 64 && in_run + off < m) v += other;
+        }
+        Ac[k - 1] = lane == 0 || in_run == 0 ? v : 0.0f;
     }
 }
 
@@ -552,7 +569,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
     }
 #endif
     if constexpr (level_start(N) <= BW_PER_WAVE) {
-        if (inner && !given) chunk_boundary(low_coeffs + b * KW * level_start(N), (int)part, (int)KW, p, lane, Ec, Sc, Ac, A1
+        if (inner && !given) chunk_boundary(low_coeffs + b * KW * level_start(N), (int)part, (int)KW, p0, p, lane, Ec, Sc, Ac, A1
 #if R == 2
                                             , S1, An
 #endif

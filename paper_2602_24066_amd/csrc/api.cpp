@@ -741,15 +741,30 @@ bool plain_kernels(const sig::WordSet& w, int dir, int64_t B, Build how, PlainKe
     k.rows = k.chunk && dir ? ensure_jit(w, 1, plain_rows(B), how, &k.rows_plan) : nullptr;
     return k.chunk && (dir == 0 || k.rows);
 }
-// The kernels of a chunked call.  A call that takes chunks loads those of whole paths as well, for calls of the batch size that
-// don't (other lengths, sig_backward_static); under graph capture, where nothing can be loaded, kernels that no call has brought
-// up yet mean whole paths.
-bool plain_kernels_for(const sig::WordSet& w, int dir, int64_t B, Build how, hipStream_t st, PlainKernels& k)
+// While a stream is captured nothing can be loaded: kernels that no call has brought up yet are done without.
+Build unless_captured(Build how, hipStream_t st)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (how == Build::compile_and_load && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
-        how = Build::loaded_only;
+        return Build::loaded_only;
+    return how;
+}
+// The kernels of a chunked call.  A call that takes chunks loads those of whole paths as well, for calls of the batch size that
+// don't (other lengths, sig_backward_static).
+bool plain_kernels_for(const sig::WordSet& w, int dir, int64_t B, Build how, hipStream_t st, PlainKernels& k)
+{
+    how = unless_captured(how, st);
     return ensure_jit(w, dir, B, how) && plain_kernels(w, dir, B, how, k);
+}
+// The checkpointed backward call of a suffix-closed set takes more chunks than are kept (ch) where that is the faster for all the
+// forward pass they need again (209 words, 26 paths x 693 segments: 62 us with the five that are kept, 45 with 24).  C = 1: no.
+Chunks plain_instead_of_kept(const sig::WordSet& w, int64_t B, int64_t n_points, const Chunks& ch)
+{
+    const int64_t L = n_points - 1;
+    if (w.opt.ckpt_chunks != 0 || !plain_chunks_available(w, B)) return Chunks{1, L};
+    const Chunks own = plain_chunks(w, 1, B, n_points);
+    if (own.C < 2 || plain_time(w, kBackward, B, L, own.C) >= 0.93 * plain_time(w, kBackwardKept, B, L, ch.C)) return Chunks{1, L};
+    return own;
 }
 hipError_t plain_forward_chunked(const sig::WordSet& w, const PlainKernels& k, const float* path, int64_t B, int64_t n_points,
                                  const Chunks& ch, float* coeffs, void* workspace, hipStream_t st)
@@ -1853,6 +1868,9 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
         if (!workspace || workspace_bytes < sig_forward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
         if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
         hipStream_t st = (hipStream_t)stream;
+        // the backward call of the pair finds its kernels loaded, also where it takes other chunks than are kept
+        PlainKernels k;
+        if (plain_instead_of_kept(w, B, n_points, ch).C > 1) (void)plain_kernels(w, 1, B, unless_captured(Build::compile_and_load, st), k);
         CallTimer whole(0, st);
         hipError_t e = words_forward_chunked(w, path, B, n_points, ch, *fk, *fp, (float*)workspace, (float*)checkpoint, coeffs, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
@@ -1885,14 +1903,15 @@ int sig_backward_checkpointed(const sig_wordset* ws, const float* path, const fl
     if (!coeffs || !grad_coeffs || !grad_path) return SIG_EINVAL;
     if (!checkpoint || checkpoint_bytes < chunk_array_bytes(w, B, ch.C)) return SIG_EWORKSPACE;
     if (w.kind != 0) {
-        // small launches take more chunks than are kept where that is the faster for all the forward pass they need again (209
-        // words, 26 paths x 693 segments: 62 us with the five that are kept, 45 with 24)
-        if (plain_chunks_available(w, B) && w.opt.ckpt_chunks == 0 &&
-            plain_time(w, kBackward, B, n_points - 1, plain_chunk_count(w, kBackward, B, n_points - 1)) <
-                0.93 * plain_time(w, kBackwardKept, B, n_points - 1, ch.C)) {
-            if (!workspace || workspace_bytes < sig_backward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
-            if ((((uintptr_t)workspace | (uintptr_t)checkpoint) & 255) != 0) return SIG_EINVAL;
-            return sig_backward(ws, path, coeffs, grad_coeffs, B, n_points, grad_path, workspace, workspace_bytes, stream);
+        // (a smaller workspace, and kernels that failed to compile or cannot be loaded now, mean the chunks that are kept)
+        const Chunks own = plain_instead_of_kept(w, B, n_points, ch);
+        PlainKernels k;
+        if (own.C > 1 && workspace && workspace_bytes >= plain_backward_bytes(w, B, own) &&
+            (((uintptr_t)workspace | (uintptr_t)checkpoint) & 255) == 0 &&
+            plain_kernels(w, 1, B, unless_captured(Build::compile_and_load, (hipStream_t)stream), k)) {
+            CallTimer whole(1, (hipStream_t)stream);
+            hipError_t e = plain_backward_chunked(w, k, path, coeffs, grad_coeffs, B, n_points, own, grad_path, workspace, (hipStream_t)stream);
+            return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
         sig::JitKernel *fk, *bk;
         const sig::Plan *fp = nullptr, *bp = nullptr;

@@ -376,7 +376,7 @@ __device__ __forceinline__ void letter_sums(const float* v, const float* __restr
 // their sum, and the walk would round them.  Error of such a gradient, shares -> sums -> one value per word (arrays): 27 and 64 lanes
 // a path (3 and 4 letters, depth 4) 1.25, 1.37 -> 1.00 -> 1; a word whose lanes lie in several wavefronts keeps that many shares,
 // 1,000 lanes (10 letters) 1.38 -> 1.30 -> 1 (256 paths 0.99: two levels a lane, 100 lanes), still below the walk over whole
-// paths, 1.8.  Backward calls of 12 to 26 us take 0.1 to 0.5 us for it; the arrays cost 5 to 12.
+// paths, 1.8.  Backward calls of 12 to 33 us take 0.1 to 0.8 us for it; the arrays cost 5 to 15.
 // The rows pass through the wavefront's LDS one after the other, each loaded while the one before is used.
 // Bound by the latency of a row (0.3-0.6 us); two launches of 5 us and the arrays' traffic saved (256 paths x 199 segments, d = 10,
 // depth 4: 30 us of 181).

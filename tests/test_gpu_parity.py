@@ -1336,6 +1336,53 @@ def test_checkpointed_step_captured_in_a_graph(kind, d, depth, B, L):
             assert O.grad_errors(g_graph, gref).max() <= BWD_TOL
 
 
+@pytest.mark.parametrize("chunks,kept", [(0, False), (1, True)])
+def test_checkpointed_backward_of_few_paths_of_a_word_set(chunks, kept):
+    """On few paths the backward call takes more chunks than the checkpoint holds and works out their signatures itself: seen by a
+    checkpoint of NaN that it does not read.  With the option "chunks" = 1 there are no others, and the kept ones are used."""
+    import torch
+    B, L = 3, 400
+    ws, W = build_both("anisotropic", 3, weights=(1.0, 1.25, 1.5), cutoff=4.5)
+    ws.set_option("chunks", chunks)
+    X, G = make_path("iid", 1900, B, L, 3), make_grad_coeffs(1901, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c, ck = S.sig_forward_checkpointed(ws, x)
+    assert ck.numel() > 0
+    gref = O.backward_words(X, W, G.astype(np.float64))
+    gp = S.sig_backward_checkpointed(ws, x, c, g, ck)
+    assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+    ck.view(torch.float32).fill_(float("nan"))
+    gp = S.sig_backward_checkpointed(ws, x, c, g, ck).cpu().numpy()
+    assert np.isnan(gp).any() if kept else O.grad_errors(gp, gref).max() <= BWD_TOL
+
+
+def test_checkpointed_backward_captured_after_an_eager_forward():
+    """The forward call of a checkpointed pair loads the kernels of the backward call, also of one that takes other chunks than are
+    kept: recorded alone, after nothing but an eager forward call, it replays to the oracle's gradient."""
+    import torch
+    B, L = 3, 400
+    ws, W = build_both("anisotropic", 3, weights=(1.0, 1.25, 1.5), cutoff=4.5)
+    x = torch.from_numpy(make_path("iid", 1910, B, L, 3)).cuda()
+    g = torch.from_numpy(make_grad_coeffs(1911, B, ws.size)).cuda()
+    c, ck = S.sig_forward_checkpointed(ws, x)
+    lib = S.load_library()
+    wb = torch.empty(int(lib.sig_backward_checkpointed_workspace_bytes(ws._h, B, L + 1)), dtype=torch.uint8, device="cuda")
+    gp = torch.empty_like(x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        S.sig_backward_checkpointed(ws, x, c, g, ck, out=gp, workspace=wb)
+    for rep in range(3):
+        X, G = make_path("iid", 1920 + rep, B, L, 3), make_grad_coeffs(1930 + rep, B, ws.size)
+        x.copy_(torch.from_numpy(X))
+        g.copy_(torch.from_numpy(G))
+        S.sig_forward_checkpointed(ws, x, out=c, checkpoint=ck)
+        gp.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert O.grad_errors(gp.cpu().numpy(), O.backward_words(X, W, G.astype(np.float64))).max() <= BWD_TOL, rep
+
+
 def test_code_object_from_the_disk_cache_runs(tmp_path, monkeypatch):
     """A kernel loaded from SIG_JIT_CACHE instead of compiled gives the results of the compiled one, bit for bit."""
     import torch

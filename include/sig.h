@@ -164,14 +164,16 @@ int sig_wordset_plan_get(const sig_wordset* ws, int backward, int variant, const
  * sig_backward print the work units as straight-line HIP source (one multiply-add per (word, target length)
  * pair) and compile it with hiprtc for gfx950 on first use; the compiled kernel is cached in ws.  The first call
  * for a word set therefore takes seconds.  sig_wordset_jit_prepare does that compilation ahead of time for the
- * plan variant a batch of B paths would use (host only, no device needed); it returns SIG_OK, SIG_EUNSUPPORTED if
- * this word set is not run through specialised kernels, or SIG_EJIT if hiprtc failed (sig_forward / sig_backward
- * then fall back to the table-driven kernels).  The option "no_jit" disables it.
+ * plan variant a batch of B paths would use over whole paths (host only, no device needed; the kernels of time chunks:
+ * sig_wordset_jit_prepare_chunks); it returns SIG_OK, SIG_EUNSUPPORTED if this word set is not run through specialised
+ * kernels, or SIG_EJIT if hiprtc failed (sig_forward / sig_backward then fall back to the table-driven kernels).  The
+ * option "no_jit" disables it.
  * Full truncations (any d <= 64) without a precompiled kernel are the exception to "grows with the word set": they
  * run fixed kernel sources with a word per lane, compiled for the shape (d, depth) in one to three seconds per
  * direction, the kernels of their time chunks included (Section 3.1, eq. (3), with the prefixes shared between words);
  * where a path has only a few words of length depth - 2 they do so while the paths are few.  The option "lanes" = 0
- * sends them all through the straight-line form, = 1 all through the word-per-lane form.  sig_wordset_jit_prepare and sig_wordset_jit_source cover whichever form the batch would use.
+ * sends them all through the straight-line form, = 1 all through the word-per-lane form.  sig_wordset_jit_prepare and
+ * sig_wordset_jit_source cover whichever form the batch would use.
  * With the environment variable SIG_JIT_CACHE naming an existing directory (read when a kernel is compiled), code
  * objects are kept there (named by a hash of their source, the compiler version and the compile options; each file
  * carries its length and a checksum) and later processes load them instead of compiling; a file that fails its
@@ -180,6 +182,11 @@ int sig_wordset_plan_get(const sig_wordset* ws, int backward, int variant, const
  * A word-set object serves the device it was uploaded on. */
 #define SIG_EJIT (-10)
 int sig_wordset_jit_prepare(sig_wordset* ws, int backward, int64_t B);
+/* The same for the kernels that calls of B paths take over time chunks (see sig_forward), where small launches of a word set
+ * have kernels of their own for them: one for the chunk signatures, over the set's closure under suffixes, and with backward = 1
+ * one for the (path, chunk) rows.  Those of full truncations are in the modules sig_wordset_jit_prepare compiles.  SIG_OK also where
+ * there are none.  After both functions for both directions no sig_forward or sig_backward call of B paths compiles anything. */
+int sig_wordset_jit_prepare_chunks(sig_wordset* ws, int backward, int64_t B);
 /* The plan the specialised kernel for a batch of B paths is generated from, in the format of sig_wordset_plan_get.
  * Here the words in depth-first order are cut into consecutive runs of nearly equal cost, one per wavefront, as
  * many as the batch needs to occupy the chip; a unit is one run plus the ancestors of its first word.  Pointers
@@ -267,7 +274,8 @@ int    sig_backward_residual(const sig_wordset* ws, const float* path, const flo
 size_t sig_checkpoint_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 /* The number of time chunks C the two calls take for this batch (1: none, the calls are sig_forward / sig_backward).
  * For a suffix-closed set the specialised kernels of the checkpointed calls run B * C rows: compile them ahead of time
- * with sig_wordset_jit_prepare(ws, backward, B * C). */
+ * with sig_wordset_jit_prepare(ws, backward, B * C); few paths take those of sig_wordset_jit_prepare_chunks(ws, 1, B) too
+ * (without them the first forward call of the pair compiles what the backward call runs). */
 int64_t sig_checkpoint_chunks(const sig_wordset* ws, int64_t B, int64_t n_points);
 size_t sig_forward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 size_t sig_backward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);

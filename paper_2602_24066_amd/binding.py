@@ -84,6 +84,7 @@ def load_library():
     sig("sig_wordset_jit_plan_get", c_int, [c_p, c_int, c_i64, PP, ctypes.POINTER(c_i64), PP, ctypes.POINTER(c_i64), PP,
                                              ctypes.POINTER(c_i64), ctypes.POINTER(c_i64)])
     sig("sig_wordset_jit_prepare", c_int, [c_p, c_int, c_i64])
+    sig("sig_wordset_jit_prepare_chunks", c_int, [c_p, c_int, c_i64])
     sig("sig_checkpoint_chunks", c_i64, [c_p, c_i64, c_i64])
     sig("sig_wordset_jit_source", c_sz, [c_p, c_int, c_i64, c_p, c_sz])
     sig("sig_wordset_device_bytes", c_sz, [c_p])
@@ -275,6 +276,10 @@ class WordSet:
     def jit_prepare(self, backward: bool, B: int) -> int:
         """Compiles the specialised kernel a batch of B paths would use; returns the library's status code."""
         return int(self._lib.sig_wordset_jit_prepare(self._h, int(backward), B))
+
+    def jit_prepare_chunks(self, backward: bool, B: int) -> int:
+        """Compiles the kernels that calls of B paths take over time chunks besides it; returns the library's status code."""
+        return int(self._lib.sig_wordset_jit_prepare_chunks(self._h, int(backward), B))
 
     def jit_source(self, backward: bool, B: int) -> str:
         n = int(self._lib.sig_wordset_jit_source(self._h, int(backward), B, None, 0))

@@ -1287,6 +1287,17 @@ int sig_wordset_jit_prepare(sig_wordset* ws, int backward, int64_t B)
     return ensure_jit(w, dir, B, Build::compile_only) ? SIG_OK : SIG_EJIT;
 }
 
+int sig_wordset_jit_prepare_chunks(sig_wordset* ws, int backward, int64_t B)
+{
+    if (!ws || B < 1) return SIG_EINVAL;
+    const sig::WordSet& w = *W(ws);
+    const int dir = backward ? 1 : 0;
+    if (!jit_enabled(w)) return SIG_EUNSUPPORTED;
+    if (dir == 0 ? use_trunc_forward(w, B) : use_trunc_backward(w, B)) return SIG_EUNSUPPORTED;
+    PlainKernels k;
+    return !plain_chunks_available(w, B) || plain_kernels(w, dir, B, Build::compile_only, k) ? SIG_OK : SIG_EJIT;
+}
+
 size_t sig_wordset_jit_source(sig_wordset* ws, int backward, int64_t B, char* buf, size_t n)
 {
     if (!ws || B < 1) return 0;

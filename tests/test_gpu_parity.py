@@ -1405,6 +1405,32 @@ def test_code_object_from_the_disk_cache_runs(tmp_path, monkeypatch):
     check_parity(ws2, W, "words", None, make_path("iid", 78, 9, 23, 5), make_grad_coeffs(79, 9, ws2.size), what="cached kernels")
 
 
+@pytest.mark.parametrize("kind", ["words", "anisotropic"])
+def test_prepared_kernels_are_all_that_the_calls_compile(kind, tmp_path, monkeypatch):
+    """After sig_wordset_jit_prepare and sig_wordset_jit_prepare_chunks no call of that batch size compiles a kernel, long paths in
+    time chunks and short ones; the checkpointed pair needs its B * C rows besides."""
+    import os
+
+    import torch
+    monkeypatch.setenv("SIG_JIT_CACHE", str(tmp_path))
+    d, B = (5, 6) if kind == "words" else (3, 3)
+    ws, _ = build_both(kind, d, weights=(1.0, 1.25, 1.5), cutoff=4.5, words=random_prefix_closed_words(43, 5, 120, 5))
+    lib = S.load_library()
+    for backward in (False, True):
+        assert ws.jit_prepare(backward, B) == 0 and ws.jit_prepare_chunks(backward, B) == 0
+        rows = B * int(lib.sig_checkpoint_chunks(ws._h, B, 401))
+        assert ws.jit_prepare(backward, rows) == 0
+    files = sorted(os.listdir(tmp_path))
+    for L in (400, 12):
+        x = torch.from_numpy(make_path("iid", 1950 + L, B, L, d)).cuda()
+        g = torch.from_numpy(make_grad_coeffs(1951, B, ws.size)).cuda()
+        S.sig_backward(ws, x, S.sig_forward(ws, x), g)
+        c, ck = S.sig_forward_checkpointed(ws, x)
+        S.sig_backward_checkpointed(ws, x, c, g, ck)
+    torch.cuda.synchronize()
+    assert sorted(os.listdir(tmp_path)) == files
+
+
 def test_one_point_paths_give_zero():
     import torch
     ws, W = build_both("truncated", 3, depth=3)

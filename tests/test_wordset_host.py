@@ -415,6 +415,30 @@ def test_code_object_cache_on_disk(tmp_path, monkeypatch):
     del lib
 
 
+def test_kernels_of_time_chunks_ahead_of_time(tmp_path, monkeypatch):
+    """Small launches of a word set run further kernels over time chunks: the chunk signatures over the set's closure, and
+    backward the rows.  sig_wordset_jit_prepare_chunks compiles them, the backward one both; where there are none it has nothing
+    to do."""
+    monkeypatch.setenv("SIG_JIT_CACHE", str(tmp_path))
+
+    def files():
+        return len(os.listdir(tmp_path))
+
+    ws = S.sig_wordset_build(4, random_prefix_closed_words(31, 4, 120, 5))
+    assert not ws.suffix_closed and ws.jit_prepare(False, 64) == 0 and ws.jit_prepare(True, 64) == 0 and files() == 2
+    assert ws.jit_prepare_chunks(False, 64) == 0 and files() == 3
+    assert ws.jit_prepare_chunks(True, 64) == 0 and files() in (3, 4)          # the rows may share the plan of whole paths
+    n = files()
+    other = S.sig_wordset_build(4, random_prefix_closed_words(31, 4, 120, 5))
+    assert other.jit_prepare_chunks(True, 64) == 0 and files() == n            # without the forward call before it
+    assert S.sig_wordset_build_truncated(4, 6).jit_prepare_chunks(True, 64) == -9
+    assert S.sig_wordset_build_truncated(6, 4).jit_prepare_chunks(True, 64) == 0 and files() == n
+    lib = S.load_library()
+    assert lib.sig_wordset_jit_prepare_chunks(None, 0, 64) == -1 and lib.sig_wordset_jit_prepare_chunks(ws._h, 0, 0) == -1
+    ws.set_option("no_jit", 1)
+    assert ws.jit_prepare_chunks(False, 64) == -9
+
+
 def test_time_chunk_workspace():
     """Few long paths of a full truncation are cut into time chunks: the forward workspace holds the chunk
     signatures (and the partial products when four or more signatures too large for LDS are multiplied pair by pair);

@@ -249,7 +249,8 @@ int    sig_backward(const sig_wordset* ws, const float* path, const float* coeff
  * words are zero.  residual: device float32 [B], receives per path the largest absolute value left in the
  * reconstructed coefficients (words shorter than the depth: the longest words are never reconstructed).  Offered for
  * the full truncations with a precompiled kernel (SIG_EUNSUPPORTED otherwise); runs the kernel that walks whole paths,
- * so it measures the drift over all L segments.  Workspace as for sig_backward. */
+ * so it measures the drift over all L segments.  Workspace: that of sig_backward is enough, B * (n_points - 1) * d floats
+ * (rounded up to 256 bytes) are needed. */
 int    sig_backward_residual(const sig_wordset* ws, const float* path, const float* coeffs, const float* grad_coeffs,
                              int64_t B, int64_t n_points, float* grad_path, float* residual /*device [B]*/,
                              void* workspace, size_t workspace_bytes, void* stream);

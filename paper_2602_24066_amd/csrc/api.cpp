@@ -1658,7 +1658,9 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     const bool low = use_trunc_backward(w, B) && sig::trunc_low_available(w.d, w.depth) && word_chunks && !residual;
     const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points))) ||
                           (low && trunc_chunks(w, 1, B, n_points).C == 1);
-    const size_t need = word_chunks && !optional ? sig_backward_workspace_bytes(ws, B, n_points) : backward_workspace(ws, B, n_points, false);
+    // (with the residual whole paths are walked: no chunks to hold)
+    const size_t need = word_chunks && !optional && !residual ? sig_backward_workspace_bytes(ws, B, n_points)
+                                                              : backward_workspace(ws, B, n_points, false);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;

@@ -467,6 +467,32 @@ def test_reconstruction_returns_to_the_empty_signature(d, depth, B, L):
     assert float(resid2.min()) > 0.1
 
 
+@pytest.mark.parametrize("d,depth,B,L", [(8, 5, 2, 70), (16, 4, 1, 300), (4, 6, 3, 40), (8, 5, 2, 1100)])
+def test_residual_needs_the_workspace_of_whole_paths_alone(d, depth, B, L):
+    """sig_backward_residual walks whole paths: the gradient of the increments is all that its workspace has to hold, also where
+    sig_backward takes time chunks; a byte less is refused."""
+    import ctypes
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    lib = S.load_library()
+    gdx = (4 * B * L * d + 255) // 256 * 256
+    X, G = make_path("iid", 7600 + L, B, L, d), make_grad_coeffs(7601, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c = S.sig_forward(ws, x)
+    gp, res = torch.full_like(x, float("nan")), torch.full((B,), float("nan"), device="cuda")
+    work = torch.empty(gdx, dtype=torch.uint8, device="cuda")
+    P = ctypes.c_void_p
+
+    def call(n):
+        return lib.sig_backward_residual(ws._h, P(x.data_ptr()), P(c.data_ptr()), P(g.data_ptr()), B, L + 1, P(gp.data_ptr()),
+                                         P(res.data_ptr()), P(work.data_ptr()), n, P(torch.cuda.current_stream().cuda_stream))
+
+    assert call(gdx - 1) == -5 and call(gdx) == 0
+    torch.cuda.synchronize()
+    assert float(res.max()) <= 1e-3
+    assert O.grad_errors(gp.cpu().numpy(), oracle_backward(X, W, "truncated", depth, G.astype(np.float64))).max() <= BWD_TOL
+
+
 def test_forward_fused_and_four_wavefront_kernels_agree():
     ws, W = build_both("truncated", 4, depth=6)
     X = make_path("time0", 21, 200, 255, 4)

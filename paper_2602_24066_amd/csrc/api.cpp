@@ -284,10 +284,6 @@ size_t chunk_array_bytes(const sig::WordSet& w, int64_t B, int64_t C)
     return ((size_t)B * (size_t)C * (size_t)w.size() * sizeof(float) + 255) & ~(size_t)255;
 }
 
-// arrays [B][C][|W|] a chunked forward pass asks for in its workspace: the chunk signatures, and for four or more large ones as
-// much again (once for partial products; the products by slices need none, but a call states the same bytes as ever)
-size_t forward_chunk_arrays(const sig::WordSet& w, int64_t C) { return (C >= 4 && w.size() > 8192) ? 2 : 1; }
-
 bool use_trunc_forward(const sig::WordSet& w, int64_t B)
 {
     return w.kind == 0 && B <= 65535 && sig::trunc_forward_available(w.d, w.depth);
@@ -1341,7 +1337,7 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
     const sig::WordSet& w = *W(ws);
     if (use_trunc_forward(w, B)) {
         const Chunks ch = trunc_chunks(w, 0, B, n_points);
-        size_t n = ch.C > 1 ? forward_chunk_arrays(w, ch.C) * chunk_array_bytes(w, B, ch.C) : 0;
+        size_t n = ch.C > 1 ? chunk_array_bytes(w, B, ch.C) : 0;
         if (sig::trunc_low_available(w.d, w.depth)) {
             const Chunks low = low_chunks(w, 0, B, n_points);
             if (low.C > 1) n = std::max(n, chunk_array_bytes(w, B, low.C));
@@ -1374,6 +1370,28 @@ static size_t gdx_bytes_of(const sig::WordSet& w, int64_t B, int64_t n_points)
 static size_t low_backward_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch)
 {
     return ch.C > 1 ? 3 * lanes_low_bytes(w, B, ch.C) + lanes_low_bytes(w, B, ch.C - 1) : 0;
+}
+// What the checkpointed backward call of those shapes takes from its workspace over the kept chunks, beside the gradient of the
+// increments: boundary adjoints [B][C - 1]; beyond two chunks these and the products from both sides [B][C] are rows of words
+// shorter than the depth
+static size_t low_kept_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch)
+{
+    return ch.C == 2 ? chunk_array_bytes(w, B, 1) : lanes_low_bytes(w, B, ch.C - 1) + 2 * lanes_low_bytes(w, B, ch.C);
+}
+// ... and the chunks that it takes in their place, for all the forward pass they need again, where they fill the SIMDs so much
+// better than the ones that are kept (ch).  C = 1: none.  d = 8, 1 to 38 paths of 130 to 900 segments, kept -> taken 57 -> 40 to 236 ->
+// 209 us; d = 16, 55 -> 39 to 301 -> 273 us.  There the model promises too much where the taken chunks put a second wavefront on a
+// SIMD that the kept ones don't (12 paths x 150 59 -> 67 us; 8 x 500, at 0.79 of the modelled time, 87 -> 81) and where the kept ones
+// put a third (60 x 900 371 -> 390; 38 x 260 131 -> 114), so its line lies lower.
+static Chunks low_instead_of_kept(const sig::WordSet& w, int64_t B, int64_t n_points, const Chunks& ch)
+{
+    const int64_t L = n_points - 1;
+    if (w.opt.ckpt_chunks != 0) return Chunks{1, L};
+    const Chunks own = low_chunks(w, 1, B, n_points);
+    const int64_t waves = sig::trunc_waves_per_row(w.d, w.depth, 1) * B, kept = waves * ch.C;
+    const double line = w.d != 16 || waves * own.C <= 1024 ? 0.93 : (kept <= 1024 ? 0.85 : (kept > 2048 ? 0.90 : 0.93));
+    if (own.C < 2 || low_time(w, 1, false, B, L, own.C) >= line * low_time(w, 1, true, B, L, ch.C)) return Chunks{1, L};
+    return own;
 }
 // sig_backward of those shapes over chunks of its own; workspace: gradient of the increments | low_backward_arrays
 static hipError_t low_backward(const sig::WordSet& w, const float* path, const float* coeffs, const float* grad_coeffs, int64_t B,
@@ -1479,8 +1497,7 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
             // 1,024 segments, d = 8 - go on with the count above: whole paths, or the chunks that the call has to bring a workspace for)
             const Chunks low = low_chunks(w, 0, B, n_points);
             const size_t nb = chunk_array_bytes(w, B, low.C);
-            if (low.C > 1 && workspace && workspace_bytes >= sig_forward_workspace_bytes(ws, B, n_points) &&
-                (((uintptr_t)workspace & 255) | ((uintptr_t)coeffs & 15)) == 0 && workspace_bytes >= nb) {
+            if (low.C > 1 && workspace && workspace_bytes >= nb && (((uintptr_t)workspace & 255) | ((uintptr_t)coeffs & 15)) == 0) {
                 hipEvent_t* pe = g_prof.next(0);
                 if (pe) (void)hipEventRecord(pe[0], st);
                 hipError_t e = sig::trunc_forward(w.d, w.depth, path, B, n_points, low.C, low.Lc, (float*)workspace, st);
@@ -1492,7 +1509,7 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
         float* Sc = coeffs;
         if (ch.C > 1) {
             const size_t nb = chunk_array_bytes(w, B, ch.C);
-            if (!workspace || workspace_bytes < forward_chunk_arrays(w, ch.C) * nb) return SIG_EWORKSPACE;
+            if (!workspace || workspace_bytes < nb) return SIG_EWORKSPACE;
             if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)coeffs & 15) != 0) return SIG_EINVAL;
             Sc = (float*)workspace;
         }
@@ -1602,8 +1619,7 @@ static int backward_checkpointed(const sig::WordSet& w, const float* path, const
 {
     if ((((uintptr_t)coeffs | (uintptr_t)grad_coeffs | (uintptr_t)ckpt) & 15) != 0) return SIG_EINVAL;
     const int64_t nW = w.size(), nL = w.level_start[(size_t)w.depth];   // all words, those shorter than the depth
-    // workspace: increment gradients | boundary adjoints [B][C - 1] | for more than two chunks: products from the left and from
-    // the right, [B][C] each, rows of the shorter words (less than the workspace holds)
+    // workspace: increment gradients | boundary adjoints | for more than two chunks: products from the left and from the right
     float* gdx = (float*)workspace;
     float* Abar = (float*)((unsigned char*)workspace + gdx_bytes_of(w, B, n_points));
     CallTimer whole(1, st);
@@ -1658,17 +1674,19 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     const bool low = use_trunc_backward(w, B) && sig::trunc_low_available(w.d, w.depth) && word_chunks && !residual;
     const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points))) ||
                           (low && trunc_chunks(w, 1, B, n_points).C == 1);
-    // (with the residual whole paths are walked: no chunks to hold)
-    const size_t need = word_chunks && !optional && !residual ? sig_backward_workspace_bytes(ws, B, n_points)
-                                                              : backward_workspace(ws, B, n_points, false);
+    // (with the residual whole paths are walked: no chunks to hold; d = 8 and d = 16 need no more than low_backward takes, which
+    // is less than the size for whole arrays that a caller is told)
+    const Chunks lch = low ? low_chunks(w, 1, B, n_points) : Chunks{1, n_points - 1};
+    const size_t low_need = low ? gdx_bytes_of(w, B, n_points) + low_backward_arrays(w, B, lch) : 0;
+    const size_t need = !word_chunks || optional || residual ? backward_workspace(ws, B, n_points, false)
+                        : low                                ? low_need
+                                                             : sig_backward_workspace_bytes(ws, B, n_points);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
     float* gdx = (float*)workspace;
     CallTimer whole(1, st);
     if (low) {
-        const Chunks lch = low_chunks(w, 1, B, n_points);
-        if (lch.C > 1 && workspace_bytes >= gdx_bytes_of(w, B, n_points) + low_backward_arrays(w, B, lch) &&
-            (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
+        if (lch.C > 1 && workspace_bytes >= low_need && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
             hipError_t le = low_backward(w, path, coeffs, grad_coeffs, B, n_points, lch, grad_path, workspace, st);
             return le == hipSuccess ? SIG_OK : hip_fail(le);
         }
@@ -1846,7 +1864,7 @@ size_t sig_forward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B
     const Chunks ch = checkpoint_chunks(*W(ws), B, n_points);
     if (ch.C < 2) return sig_forward_workspace_bytes(ws, B, n_points);
     if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));
-    return forward_chunk_arrays(*W(ws), ch.C) > 1 ? chunk_array_bytes(*W(ws), B, ch.C) : 0;   // partial products of four chunks
+    return 0;                                            // full truncations: the chunk signatures are the checkpoint
 }
 
 size_t sig_backward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points)
@@ -1856,9 +1874,9 @@ size_t sig_backward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t 
     const Chunks ch = checkpoint_chunks(w, B, n_points);
     if (ch.C < 2) return sig_backward_workspace_bytes(ws, B, n_points);
     if (w.kind != 0) return std::max(words_backward_ckpt_workspace(w, B, ch), sig_backward_workspace_bytes(ws, B, n_points));
-    // gradient of the increments, boundary adjoints; beyond two chunks also the products before and after every chunk (the calls
-    // take fewer bytes of it where they go by the words shorter than the depth alone)
-    return gdx_bytes_of(w, B, n_points) + chunk_array_bytes(w, B, ch.C - 1) + (ch.C == 2 ? 0 : 2) * chunk_array_bytes(w, B, ch.C);
+    // full truncations (the kept chunks, or those that the call takes in their place)
+    const size_t arrays = std::max(low_kept_arrays(w, B, ch), low_backward_arrays(w, B, low_instead_of_kept(w, B, n_points, ch)));
+    return gdx_bytes_of(w, B, n_points) + arrays;
 }
 
 int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B, int64_t n_points, float* coeffs,
@@ -1889,10 +1907,6 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     if (((uintptr_t)checkpoint & 255) != 0 || ((uintptr_t)coeffs & 15) != 0) return SIG_EINVAL;
-    if (forward_chunk_arrays(w, ch.C) > 1) {
-        if (!workspace || workspace_bytes < nb) return SIG_EWORKSPACE;
-        if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
-    }
     hipStream_t st = (hipStream_t)stream;
     CallTimer whole(0, st);
     float* Sc = (float*)checkpoint;
@@ -1938,14 +1952,14 @@ int sig_backward_checkpointed(const sig_wordset* ws, const float* path, const fl
                                               workspace, *bk, *bp, st);
         return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
-    if (!workspace || workspace_bytes < sig_backward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
+    const size_t gb = gdx_bytes_of(w, B, n_points);
+    if (!workspace || workspace_bytes < gb + low_kept_arrays(w, B, ch)) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)checkpoint & 255) != 0) return SIG_EINVAL;
-    if (sig::trunc_low_available(w.d, w.depth) && w.opt.ckpt_chunks == 0 && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
-        // counts that fill the SIMDs better than those that are kept may be worth the chunks' signatures once more
-        const Chunks own = low_chunks(w, 1, B, n_points);
-        if (own.C > 1 && workspace_bytes >= sig_backward_workspace_bytes(ws, B, n_points) &&
-            low_time(w, 1, false, B, n_points - 1, own.C) < 0.93 * low_time(w, 1, true, B, n_points - 1, ch.C))
-            return sig_backward(ws, path, coeffs, grad_coeffs, B, n_points, grad_path, workspace, workspace_bytes, stream);
+    const Chunks own = low_instead_of_kept(w, B, n_points, ch);
+    if (own.C > 1 && workspace_bytes >= gb + low_backward_arrays(w, B, own) && (((uintptr_t)coeffs | (uintptr_t)grad_coeffs) & 15) == 0) {
+        CallTimer whole(1, (hipStream_t)stream);
+        hipError_t e = low_backward(w, path, coeffs, grad_coeffs, B, n_points, own, grad_path, workspace, (hipStream_t)stream);
+        return e == hipSuccess ? SIG_OK : hip_fail(e);
     }
     return backward_checkpointed(w, path, coeffs, grad_coeffs, (const float*)checkpoint, ch, B, n_points, grad_path, workspace,
                                  (hipStream_t)stream);

@@ -165,6 +165,85 @@ def test_checkpointed_forward_and_backward(d, depth, B, L, chunks):
     assert gerr.max() <= BWD_TOL, f"checkpointed backward: {gerr.max():.3e}"
 
 
+@pytest.mark.parametrize("d,depth,B,L,kept", [
+    (8, 5, 5, 150, False),     # two chunks are kept, more are taken
+    (16, 4, 2, 300, False),    # four and sixteen
+    (8, 5, 20, 300, True),     # the four that are kept
+    (16, 4, 12, 150, True),    # two; eight would be slower
+])
+def test_checkpointed_backward_with_the_stated_workspace(d, depth, B, L, kept):
+    """With exactly the bytes it states the backward call takes the route its model chose: other chunks than are kept, seen by a
+    checkpoint of NaN that it does not read, or the kept ones; the forward call of the pair needs no workspace at all."""
+    import ctypes
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    lib = S.load_library()
+    X, G = make_path("iid", 2700 + L, B, L, d), make_grad_coeffs(2701, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c = torch.empty((B, ws.size), device="cuda")
+    ck = torch.empty(int(lib.sig_checkpoint_bytes(ws._h, B, L + 1)), dtype=torch.uint8, device="cuda")
+    P = ctypes.c_void_p
+    stream = P(torch.cuda.current_stream().cuda_stream)
+    assert lib.sig_forward_checkpointed_workspace_bytes(ws._h, B, L + 1) == 0
+    assert lib.sig_forward_checkpointed(ws._h, P(x.data_ptr()), B, L + 1, P(c.data_ptr()), P(ck.data_ptr()), ck.numel(), None, 0,
+                                        stream) == 0
+    n = int(lib.sig_backward_checkpointed_workspace_bytes(ws._h, B, L + 1))
+    work = torch.empty(n, dtype=torch.uint8, device="cuda")
+    gp = torch.empty_like(x)
+
+    def call(bytes_):
+        return lib.sig_backward_checkpointed(ws._h, P(x.data_ptr()), P(c.data_ptr()), P(g.data_ptr()), P(ck.data_ptr()), ck.numel(), B,
+                                             L + 1, P(gp.data_ptr()), P(work.data_ptr()), bytes_, stream)
+
+    if kept:
+        assert call(n - 1) == -5
+    assert call(n) == 0
+    gref = oracle_backward(X, W, "truncated", depth, G.astype(np.float64))
+    assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+    ck.view(torch.float32).fill_(float("nan"))
+    assert call(n) == 0
+    assert np.isnan(gp.cpu().numpy()).any() if kept else O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+
+
+@pytest.mark.parametrize("d,depth,B,L", [(8, 5, 3, 1100), (16, 4, 2, 1030)])
+def test_long_paths_need_the_short_rows_of_their_chunks_alone(d, depth, B, L):
+    """sig_forward takes one array of chunk signatures, sig_backward the gradient of the increments and rows of the words shorter
+    than the depth: those bytes are accepted, also where a caller is told the size of whole arrays, and fewer are refused."""
+    import ctypes
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    lib = S.load_library()
+    X, G = make_path("iid", 2800 + L, B, L, d), make_grad_coeffs(2801, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c, gp = torch.empty((B, ws.size), device="cuda"), torch.empty_like(x)
+    gdx, low = (4 * B * L * d + 255) // 256 * 256, int(ws.level_start[depth])
+    array = (4 * B * 4 * ws.size + 255) // 256 * 256                 # four chunks of 256 segments
+    rows = 3 * ((4 * B * 16 * low + 255) // 256 * 256) + (4 * B * 15 * low + 255) // 256 * 256      # sixteen chunks
+    work = torch.empty(array + gdx + rows, dtype=torch.uint8, device="cuda")
+    P = ctypes.c_void_p
+    stream = P(torch.cuda.current_stream().cuda_stream)
+
+    def forward(n):
+        return lib.sig_forward(ws._h, P(x.data_ptr()), B, L + 1, P(c.data_ptr()), P(work.data_ptr()), n, stream)
+
+    def backward(n):
+        return lib.sig_backward(ws._h, P(x.data_ptr()), P(c.data_ptr()), P(g.data_ptr()), B, L + 1, P(gp.data_ptr()), P(work.data_ptr()),
+                                n, stream)
+
+    assert forward(array - 1) == -5 and forward(array) == 0
+    assert backward(gdx) == -5 and backward(gdx + rows) == 0
+    assert gdx + rows < lib.sig_backward_workspace_bytes(ws._h, B, L + 1)
+    lengths = np.array([len(w) for w in W])
+    O.set_threads(2)
+    try:
+        errs = O.level_errors(c.cpu().numpy(), oracle_forward(X, W, "truncated", depth), lengths)
+        gref = oracle_backward(X, W, "truncated", depth, G.astype(np.float64))
+    finally:
+        O.set_threads(16)
+    assert max(errs.values()) <= FWD_TOL, errs
+    assert O.grad_errors(gp.cpu().numpy(), gref).max() <= BWD_TOL
+
+
 def _no_repeat_words(d, n):
     """Words of up to n letters in which no letter follows itself: closed under prefixes and suffixes."""
     out, level = [], [(i,) for i in range(d)]

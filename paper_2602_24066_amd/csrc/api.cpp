@@ -641,6 +641,13 @@ size_t words_backward_recompute_workspace(const sig::WordSet& w, int64_t B, cons
     return words_backward_recompute_first(w, B, ch) + chunk_array_bytes(w, B, ch.C);
 }
 
+// what sig_forward asks for where such a set takes the chunks of the checkpointed calls (at least what whole paths need)
+size_t words_forward_bytes(const sig::WordSet& w, int64_t B, int64_t n_points, const Chunks& ch)
+{
+    const size_t whole = jit_dxt_bytes(w, B, n_points, 0);
+    return ch.C >= 2 ? std::max(whole, words_forward_ckpt_workspace(w, B, ch) + chunk_array_bytes(w, B, ch.C)) : whole;
+}
+
 // ---- time chunks of sig_forward and sig_backward on small launches ---------------------------------------------------
 // A specialised kernel takes 0.08-0.16 us per segment forward and 0.2-0.45 backward however few paths there are, so where the
 // wavefronts of whole paths fill at most three quarters of the SIMDs the plain calls cut every path into chunks, for sets that
@@ -1355,8 +1362,7 @@ size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_p
         if (ch.C > 1) n = std::max(n, plain_forward_bytes(w, B, ch));
     } else if (w.kind != 0) {
         // sets closed under suffixes: time chunks as in the checkpointed calls, the chunk signatures in the workspace
-        const Chunks ch = checkpoint_chunks(w, B, n_points);
-        if (ch.C >= 2) n = std::max(n, words_forward_ckpt_workspace(w, B, ch) + chunk_array_bytes(w, B, ch.C));
+        n = std::max(n, words_forward_bytes(w, B, n_points, checkpoint_chunks(w, B, n_points)));
     }
     return n;
 }
@@ -1436,6 +1442,20 @@ static size_t backward_workspace(const sig_wordset* ws, int64_t B, int64_t n_poi
     return n;
 }
 
+// what sig_backward asks for where a suffix-closed set takes the chunks of the checkpointed calls (at least what whole paths need)
+static size_t words_backward_bytes(const sig_wordset* ws, int64_t B, int64_t n_points)
+{
+    const Chunks ch = checkpoint_chunks(*W(ws), B, n_points);
+    const size_t whole = backward_workspace(ws, B, n_points, false);
+    return words_backward_recomputes(*W(ws), ch) ? std::max(whole, words_backward_recompute_workspace(*W(ws), B, ch)) : whole;
+}
+// ... and on a small launch, whose own chunks take plain_bytes (0: none): those are taken where the workspace holds them; a
+// suffix-closed set is refused below what it asks for without them
+static size_t small_backward_need(const sig_wordset* ws, int64_t B, int64_t n_points, size_t plain_bytes)
+{
+    return std::min(words_backward_bytes(ws, B, n_points), std::max(backward_workspace(ws, B, n_points, false), plain_bytes));
+}
+
 size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points)
 {
     size_t n = backward_workspace(ws, B, n_points, true);
@@ -1449,8 +1469,7 @@ size_t sig_backward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_
         const Chunks ch = plain_chunks(w, 1, B, n_points);
         if (ch.C > 1) n = std::max(n, plain_backward_bytes(w, B, ch));
     } else if (w.kind != 0 && jit_enabled(w)) {
-        const Chunks ch = checkpoint_chunks(w, B, n_points);
-        if (words_backward_recomputes(w, ch)) n = std::max(n, words_backward_recompute_workspace(w, B, ch));
+        n = std::max(n, words_backward_bytes(ws, B, n_points));
     }
     return n;
 }
@@ -1544,25 +1563,25 @@ static int forward_impl(const sig_wordset* ws, const float* path, int64_t B, int
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
     }
-    const bool small_launch = plain_chunks_available(w, B);
-    if (small_launch && word_chunks) {
-        // (a smaller workspace gets the walk over whole paths, unless the set's own chunks have always been asked for)
+    bool set_chunks = w.kind != 0 && word_chunks;        // sets closed under suffixes: the time chunks of the checkpointed calls
+    if (word_chunks && plain_chunks_available(w, B)) {
+        // (a smaller workspace gets those chunks where it holds them, and must for such a set; others then walk whole paths)
         const Chunks ch = plain_chunks(w, 0, B, n_points);
-        const bool fits = workspace && workspace_bytes >= sig_forward_workspace_bytes(ws, B, n_points);
-        if (!fits && checkpoint_chunks(w, B, n_points).C >= 2) return SIG_EWORKSPACE;
+        const bool fits = ch.C > 1 && workspace && workspace_bytes >= std::max(jit_dxt_bytes(w, B, n_points, 0), plain_forward_bytes(w, B, ch));
+        set_chunks = ch.C > 1 && !fits;
         PlainKernels k;
-        if (ch.C > 1 && fits && plain_kernels_for(w, 0, B, Build::compile_and_load, st, k)) {
+        if (fits && plain_kernels_for(w, 0, B, Build::compile_and_load, st, k)) {
             if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
             hipError_t e = plain_forward_chunked(w, k, path, B, n_points, ch, coeffs, workspace, st);
             return e == hipSuccess ? SIG_OK : hip_fail(e);
         }
-    } else if (w.kind != 0 && word_chunks) {
-        // sets closed under suffixes: the time chunks of the checkpointed calls, with the chunk signatures in the workspace
+    }
+    if (set_chunks) {
         const Chunks ch = checkpoint_chunks(w, B, n_points);
         const sig::Plan* cp = nullptr;
         sig::JitKernel* ck = ch.C >= 2 ? ensure_jit(w, 0, B * ch.C, Build::compile_and_load, &cp) : nullptr;
         if (ck) {
-            if (!workspace || workspace_bytes < sig_forward_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
+            if (!workspace || workspace_bytes < words_forward_bytes(w, B, n_points, ch)) return SIG_EWORKSPACE;
             if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
             float* dxT = (float*)workspace;
             float* Sc = (float*)((unsigned char*)workspace + words_forward_ckpt_workspace(w, B, ch));
@@ -1672,14 +1691,16 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     // the same holds for the chunks of small launches, except where a suffix-closed set has always asked for its chunks
     const bool small_launch = plain_chunks_available(w, B);
     const bool low = use_trunc_backward(w, B) && sig::trunc_low_available(w.d, w.depth) && word_chunks && !residual;
-    const bool optional = lanes_path || (small_launch && !words_backward_recomputes(w, checkpoint_chunks(w, B, n_points))) ||
-                          (low && trunc_chunks(w, 1, B, n_points).C == 1);
+    const Chunks pc = small_launch && word_chunks && !residual ? plain_chunks(w, 1, B, n_points) : Chunks{1, n_points - 1};
+    const bool optional = lanes_path || (low && trunc_chunks(w, 1, B, n_points).C == 1);
     // (with the residual whole paths are walked: no chunks to hold; d = 8 and d = 16 need no more than low_backward takes, which
     // is less than the size for whole arrays that a caller is told)
     const Chunks lch = low ? low_chunks(w, 1, B, n_points) : Chunks{1, n_points - 1};
     const size_t low_need = low ? gdx_bytes_of(w, B, n_points) + low_backward_arrays(w, B, lch) : 0;
+    const size_t plain_bytes = pc.C > 1 ? plain_backward_bytes(w, B, pc) : 0;
     const size_t need = !word_chunks || optional || residual ? backward_workspace(ws, B, n_points, false)
                         : low                                ? low_need
+                        : small_launch                       ? small_backward_need(ws, B, n_points, plain_bytes)
                                                              : sig_backward_workspace_bytes(ws, B, n_points);
     if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
     if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
@@ -1702,14 +1723,15 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
             return le == hipSuccess ? SIG_OK : hip_fail(le);
         }
     }
-    if (small_launch && word_chunks && !residual) {
-        const Chunks pc = plain_chunks(w, 1, B, n_points);
+    const bool plain_fits = pc.C > 1 && workspace_bytes >= plain_bytes;
+    if (plain_fits) {
         PlainKernels k;
-        if (pc.C > 1 && workspace_bytes >= plain_backward_bytes(w, B, pc) && plain_kernels_for(w, 1, B, how, st, k)) {
+        if (plain_kernels_for(w, 1, B, how, st, k)) {
             hipError_t ce = plain_backward_chunked(w, k, path, coeffs, grad_coeffs, B, n_points, pc, grad_path, workspace, st);
             return ce == hipSuccess ? SIG_OK : hip_fail(ce);
         }
-    } else if (word_chunks && w.kind != 0 && jit_enabled(w) && !residual) {
+    }
+    if (word_chunks && w.kind != 0 && jit_enabled(w) && !residual && (!small_launch || (pc.C > 1 && !plain_fits))) {
         // suffix-closed set, few long paths: chunk signatures recomputed, then the route of the checkpointed call
         const Chunks wc = checkpoint_chunks(w, B, n_points);
         sig::JitKernel *fk, *bk;
@@ -1863,7 +1885,7 @@ size_t sig_forward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B
     if (!ws || B <= 0 || n_points <= 1) return 0;
     const Chunks ch = checkpoint_chunks(*W(ws), B, n_points);
     if (ch.C < 2) return sig_forward_workspace_bytes(ws, B, n_points);
-    if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));
+    if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));   // (the call needs less)
     return 0;                                            // full truncations: the chunk signatures are the checkpoint
 }
 
@@ -1896,7 +1918,8 @@ int sig_forward_checkpointed(const sig_wordset* ws, const float* path, int64_t B
         const sig::Plan *fp = nullptr, *bp = nullptr;
         if (!words_kernels(w, B * ch.C, &fk, &fp, &bk, &bp))
             return forward_impl(ws, path, B, n_points, coeffs, workspace, workspace_bytes, stream, false);
-        if (!workspace || workspace_bytes < sig_forward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
+        const size_t need = std::max(words_forward_ckpt_workspace(w, B, ch), jit_dxt_bytes(w, B, n_points, 0));
+        if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
         if (((uintptr_t)workspace & 255) != 0) return SIG_EINVAL;
         hipStream_t st = (hipStream_t)stream;
         // the backward call of the pair finds its kernels loaded, also where it takes other chunks than are kept
@@ -1944,7 +1967,8 @@ int sig_backward_checkpointed(const sig_wordset* ws, const float* path, const fl
         const sig::Plan *fp = nullptr, *bp = nullptr;
         if (!words_kernels(w, B * ch.C, &fk, &fp, &bk, &bp))
             return sig_backward(ws, path, coeffs, grad_coeffs, B, n_points, grad_path, workspace, workspace_bytes, stream);
-        if (!workspace || workspace_bytes < sig_backward_checkpointed_workspace_bytes(ws, B, n_points)) return SIG_EWORKSPACE;
+        const size_t need = std::max(words_backward_ckpt_workspace(w, B, ch), words_backward_bytes(ws, B, n_points));
+        if (!workspace || workspace_bytes < need) return SIG_EWORKSPACE;
         if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)checkpoint & 255) != 0) return SIG_EINVAL;
         hipStream_t st = (hipStream_t)stream;
         CallTimer whole(1, st);

@@ -1488,6 +1488,50 @@ def test_checkpointed_backward_captured_after_an_eager_forward():
         assert O.grad_errors(gp.cpu().numpy(), O.backward_words(X, W, G.astype(np.float64))).max() <= BWD_TOL, rep
 
 
+def test_suffix_closed_sets_accept_the_workspace_of_their_own_chunks():
+    """Small launches of a set closed under suffixes are told the workspace of their finer chunks.  What the chunks of the
+    checkpointed calls need is accepted as well, by all four calls, and a byte less refused."""
+    import ctypes
+    import torch
+    d, B, L, C = 3, 512, 512, 4
+    ws, W = build_both("anisotropic", d, weights=(1.0, 1.25, 1.5), cutoff=4.5)
+    ws.set_option("ckpt_chunks", C)
+    lib = S.load_library()
+    X, G = make_path("iid", 5400, B, L, d), make_grad_coeffs(5401, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c, gp = torch.empty((B, ws.size), device="cuda"), torch.empty_like(x)
+    rows = B * C // 64 * (L // C) * d * 64 * 4                     # transposed increments of the chunks
+    arrays = int(lib.sig_checkpoint_bytes(ws._h, B, L + 1))
+    assert arrays == (4 * B * C * ws.size + 255) // 256 * 256
+    ck = torch.empty(arrays, dtype=torch.uint8, device="cuda")
+    work = torch.empty(2 * rows + 3 * arrays, dtype=torch.uint8, device="cuda")
+    P = ctypes.c_void_p
+    xp, cp, gr, out, kp, wk = (P(t.data_ptr()) for t in (x, c, g, gp, ck, work))
+    st = P(torch.cuda.current_stream().cuda_stream)
+    few = slice(0, 3)
+    ref = O.forward_words(X[few], W)
+    gref = O.backward_words(X[few], W, G[few].astype(np.float64))
+    lengths = np.array([len(w) for w in W])
+    calls = [
+        (rows + arrays, lib.sig_forward_workspace_bytes, lambda n: lib.sig_forward(ws._h, xp, B, L + 1, cp, wk, n, st)),
+        (2 * rows + 3 * arrays, lib.sig_backward_workspace_bytes,
+         lambda n: lib.sig_backward(ws._h, xp, cp, gr, B, L + 1, out, wk, n, st)),
+        (rows, lib.sig_forward_checkpointed_workspace_bytes,
+         lambda n: lib.sig_forward_checkpointed(ws._h, xp, B, L + 1, cp, kp, arrays, wk, n, st)),
+        (2 * rows + 3 * arrays, lib.sig_backward_checkpointed_workspace_bytes,
+         lambda n: lib.sig_backward_checkpointed(ws._h, xp, cp, gr, kp, arrays, B, L + 1, out, wk, n, st)),
+    ]
+    for need, stated, call in calls:
+        assert need < stated(ws._h, B, L + 1)
+        assert call(need - 1) == -5 and call(need) == 0
+        torch.cuda.synchronize()
+        errs = O.level_errors(c[few].cpu().numpy(), ref, lengths)
+        assert max(errs.values()) <= FWD_TOL, errs
+        if "backward" in stated.__name__:
+            assert O.grad_errors(gp[few].cpu().numpy(), gref).max() <= BWD_TOL
+            gp.fill_(float("nan"))
+
+
 def test_code_object_from_the_disk_cache_runs(tmp_path, monkeypatch):
     """A kernel loaded from SIG_JIT_CACHE instead of compiled gives the results of the compiled one, bit for bit."""
     import torch

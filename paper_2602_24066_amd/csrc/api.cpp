@@ -2030,7 +2030,7 @@ static bool windows_direct(const sig::WordSet& w, int64_t B, int64_t K, int back
 }
 // Word sets that run through the straight-line specialised kernels (lane = row): their rows can be windows as well,
 // the increments being transposed straight from the path.  (The workspace the window calls ask for covers both this
-// form and the gather into padded sub-paths, which the other kernels and a failed compilation take.)
+// form and the gather into padded sub-paths, which the other kernels and a failed compilation take; both walk whole windows.)
 static bool windows_rows_jit(const sig::WordSet& w, int64_t rows)
 {
     return !use_trunc_forward(w, rows) && !use_trunc_backward(w, rows) && !use_lanes(w, rows, kAnyLength, false) && jit_enabled(w);
@@ -2041,7 +2041,8 @@ size_t sig_forward_windows_workspace_bytes(const sig_wordset* ws, int64_t B, int
     if (!ws || B <= 0 || K <= 0 || n_points < 1 || max_window_len < 0) return 0;
     if (windows_direct(*W(ws), B, K, 0)) return 0;
     const int64_t n_sub = max_window_len + 1;
-    return win_sub_bytes(*W(ws), B, K, n_sub) + sig_forward_workspace_bytes(ws, B * K, n_sub);
+    const size_t whole = jit_enabled(*W(ws)) ? jit_dxt_bytes(*W(ws), B * K, n_sub, 0) : 0;
+    return win_sub_bytes(*W(ws), B, K, n_sub) + whole;
 }
 
 size_t sig_backward_windows_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points, int64_t K, int64_t max_window_len)
@@ -2051,7 +2052,7 @@ size_t sig_backward_windows_workspace_bytes(const sig_wordset* ws, int64_t B, in
     const int64_t n_sub = max_window_len + 1;
     // the gather form; the forms that take windows as rows need less, or (a word per lane) the increment gradients of
     // the whole paths
-    const size_t gather = 2 * win_sub_bytes(*W(ws), B, K, n_sub) + sig_backward_workspace_bytes(ws, B * K, n_sub);
+    const size_t gather = 2 * win_sub_bytes(*W(ws), B, K, n_sub) + backward_workspace(ws, B * K, n_sub, false);
     return n_points > 1 ? std::max(gather, gdx_bytes_of(*W(ws), B, n_points)) : gather;
 }
 
@@ -2121,7 +2122,7 @@ int sig_forward_windows(const sig_wordset* ws, const float* path, int64_t B, int
     float* sub = (float*)workspace;
     hipError_t e = sig::window_gather(path, B, n_points, w.d, windows, K, n_sub, sub, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e);
-    return sig_forward(ws, sub, B * K, n_sub, coeffs, (unsigned char*)workspace + sb, workspace_bytes - sb, stream);
+    return forward_impl(ws, sub, B * K, n_sub, coeffs, (unsigned char*)workspace + sb, workspace_bytes - sb, stream, false);
 }
 
 int sig_backward_windows(const sig_wordset* ws, const float* path, const float* coeffs, const float* grad_coeffs, int64_t B,
@@ -2206,8 +2207,8 @@ int sig_backward_windows(const sig_wordset* ws, const float* path, const float* 
     float* gsub = (float*)((unsigned char*)workspace + sb);
     e = sig::window_gather(path, B, n_points, w.d, windows, K, n_sub, sub, st);
     if (e != hipSuccess) return hip_fail(e);
-    rc = sig_backward(ws, sub, coeffs, grad_coeffs, B * K, n_sub, gsub, (unsigned char*)workspace + 2 * sb, workspace_bytes - 2 * sb,
-                      stream);
+    rc = backward_impl(ws, sub, coeffs, grad_coeffs, B * K, n_sub, gsub, (unsigned char*)workspace + 2 * sb, workspace_bytes - 2 * sb,
+                       stream, Build::compile_and_load, nullptr, false);
     if (rc != SIG_OK) return rc;
     e = sig::window_scatter(gsub, B, n_points, w.d, windows, K, n_sub, grad_path, st);
     return e == hipSuccess ? SIG_OK : hip_fail(e);

@@ -439,6 +439,25 @@ def test_kernels_of_time_chunks_ahead_of_time(tmp_path, monkeypatch):
     assert ws.jit_prepare_chunks(False, 64) == -9
 
 
+@pytest.mark.parametrize("case", ["words", "anisotropic"])
+def test_windows_ask_for_no_time_chunks(case):
+    """Windows of a word set run as rows, or gathered into paths that are walked whole: their workspace holds the gathered paths and
+    what a call over whole paths needs, also where few paths take time chunks."""
+    if case == "words":
+        d, ws = 4, S.sig_wordset_build(4, random_prefix_closed_words(31, 4, 120, 5))
+    else:
+        d, ws = 3, S.sig_wordset_build_anisotropic(3, (1.0, 1.25, 1.5), 4.5)
+    lib = S.load_library()
+    B, P, K, n = 4, 900, 32, 600
+    sizes = [f(ws._h, B, P, K, n) for f in (lib.sig_forward_windows_workspace_bytes, lib.sig_backward_windows_workspace_bytes)]
+    paths = [f(ws._h, B * K, n + 1) for f in (lib.sig_forward_workspace_bytes, lib.sig_backward_workspace_bytes)]
+    ws.set_option("chunks", 1)
+    whole = [f(ws._h, B * K, n + 1) for f in (lib.sig_forward_workspace_bytes, lib.sig_backward_workspace_bytes)]
+    gathered = (4 * B * K * (n + 1) * d + 255) // 256 * 256
+    assert sizes == [gathered + whole[0], 2 * gathered + whole[1]]
+    assert paths[0] > whole[0] and paths[1] > whole[1]              # as paths of their own they would take chunks
+
+
 def test_time_chunk_workspace():
     """Few long paths of a full truncation are cut into time chunks: the forward workspace holds the chunk
     signatures (and the partial products when four or more signatures too large for LDS are multiplied pair by pair);

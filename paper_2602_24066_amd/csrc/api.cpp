@@ -163,11 +163,12 @@ int low_chunk_count(const sig::WordSet& w, int dir, int64_t B, int64_t L)
     return choice;
 }
 // the product of every path's chunk signatures: small ones in LDS; by slices from three chunks on, of two spread over the grid (128
-// paths, d = 8: 16 us against 21; more paths than a grid has rows by slices too)
+// paths, d = 8: 16 us against 21)
 hipError_t chunk_product_of(const sig::WordSet& w, const float* Sc, float* coeffs, int64_t B, int64_t C, hipStream_t st)
 {
-    if (!sig::trunc_low_available(w.d, w.depth)) return sig::chunk_scan(w.d, w.depth, Sc, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)C, st);
-    if (C > 2 || B > 65535) return sig::chunk_slices_forward(w.d, w.depth, Sc, coeffs, B, (int)C, st);
+    if (!sig::trunc_low_available(w.d, w.depth))
+        return sig::chunk_scan(w.d, w.depth, Sc, nullptr, nullptr, coeffs, nullptr, nullptr, B, (int)C, st);
+    if (C > 2) return sig::chunk_slices_forward(w.d, w.depth, Sc, coeffs, B, (int)C, st);
     return sig::chunk_product(w.d, w.depth, Sc, coeffs, B, st);
 }
 Chunks low_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points)

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(NT) void chunk_slices_forward_kernel(const float* _
 #pragma unroll
         for (int q = 0; q < QT; ++q) next_top[q] = *(const f4*)(S + t0 + 4 * (tid + q * NT));
     };
-    if (C > 1) fetch(1);
+    fetch(1);                                            // (two chunks at least)
     for (int c = 1; c < C; ++c) {
 #pragma unroll
         for (int q = 0; q < QS; ++q) {
@@ -369,7 +369,6 @@ __global__ __launch_bounds__(NT) void chunk_slices_forward_kernel(const float* _
         __syncthreads();
     }
     float* out = coeffs + b * (int64_t)W;
-    if (C == 1) __syncthreads();
     const float* xo = x[(C - 1) & 1];
 #pragma unroll
     for (int q = 0; q < QT; ++q) *(f4*)(out + t0 + 4 * (tid + q * NT)) = top[q];

@@ -901,29 +901,36 @@ size_t lanes_low_bytes(const sig::WordSet& w, int64_t B, int64_t C)
     return ((size_t)B * (size_t)C * (size_t)w.level_start[(size_t)w.depth] * sizeof(float) + 255) & ~(size_t)255;
 }
 
+// Whether backward calls over chunks ask for products and boundary adjoints in arrays: where a wavefront's LDS does not hold a chunk
+// signature, and for counts set by the option "chunks" (which keeps that form to compare the other with).
+bool lanes_arrays(const sig::WordSet& w, const sig::LanesShape& s) { return w.opt.chunks > 0 || !s.shares; }
+
 sig::JitKernel* ensure_lanes(const sig::WordSet& cw, int dir, const sig::LanesShape& s, Build how)
 {
     sig::WordSet& w = const_cast<sig::WordSet&>(cw);     // the cache is logically mutable
+    const bool arrays = dir == 1 && lanes_arrays(w, s);
     sig::JitKernel* k = nullptr;
     {
         std::lock_guard<std::mutex> lock(g_jit_mutex);
-        sig::JitKernel*& slot = w.lanes[dir][(dir == 1 && s.R == 1 && w.d == 2 && !s.msum) || s.split == 2 ? 2 : s.R - 1];
+        sig::JitKernel*& slot = w.lanes[dir][(dir == 1 && s.R == 1 && w.d == 2 && !s.msum) || s.split == 2 ? 2 : s.R - 1][arrays ? 1 : 0];
         if (!slot) slot = new (std::nothrow) sig::JitKernel;
         k = slot;
     }
     if (!k) return nullptr;
-    // everything but the levels per lane and, for two letters, the form of the sums follows from (d, depth, direction)
+    // everything but the levels per lane, the arrays and, for two letters, the form of the sums follows from (d, depth, direction)
     return bring_up(k, how, dir ? "sig_bwd_lanes" : "sig_fwd_lanes", [&](sig::JitKernel& kk) {
         kk.nw = s.nwb;
         kk.tile = s.T;
         if (sig::lanes_chunks_available(w.d, w.depth)) {
             auto waves = [&](sig::LanesChunkPart part) { return sig::lanes_chunk_threads(w.d, w.depth, part) / 64; };
             if (dir == 0) kk.more = {{"sig_scan_lanes", waves(sig::kLanesScanFull), nullptr}};
-            else kk.more = {{"sig_scan_lanes", waves(sig::kLanesScanLow), nullptr},
-                            {"sig_low_lanes", sig::lanes_low_shape(w.d, w.depth).nwb, nullptr},
-                            {"sig_adjoint_lanes", waves(sig::kLanesAdjoint), nullptr}};
+            else kk.more = {{"sig_low_lanes", sig::lanes_low_shape(w.d, w.depth).nwb, nullptr}};
+            if (arrays) {
+                kk.more.push_back({"sig_scan_lanes", waves(sig::kLanesScanLow), nullptr});
+                kk.more.push_back({"sig_adjoint_lanes", waves(sig::kLanesAdjoint), nullptr});
+            }
         }
-        return sig::lanes_source(w.d, w.depth, s, dir != 0);
+        return sig::lanes_source(w.d, w.depth, s, dir != 0, arrays);
     });
 }
 
@@ -955,8 +962,9 @@ hipError_t launch_lanes(hipFunction_t fn, const sig::LanesShape& s, const float*
 struct LanesChunked {
     sig::LanesShape main, low;
     sig::JitKernel* k = nullptr;
-    const sig::JitKernel::More& scan() const { return k->more[0]; }
-    const sig::JitKernel::More& lower() const { return k->more[1]; }
+    const sig::JitKernel::More& product() const { return k->more[0]; }       // forward
+    const sig::JitKernel::More& lower() const { return k->more[0]; }         // backward
+    const sig::JitKernel::More& scan() const { return k->more[1]; }          // ... with arrays
     const sig::JitKernel::More& adjoint() const { return k->more[2]; }
 };
 bool lanes_chunk_kernels(const sig::WordSet& w, int dir, int64_t rows, Build how, LanesChunked& c)
@@ -1015,7 +1023,7 @@ hipError_t lanes_forward_chunked(const sig::WordSet& w, const LanesChunked& k, c
     long lC = (long)ch.C;
     float* none = nullptr;
     void* args[] = {(void*)&Sc, (void*)&lC, (void*)&coeffs, (void*)&none};
-    return hipModuleLaunchKernel(k.scan().fn, (unsigned)(B * w.d), 1, 1, (unsigned)k.scan().nw * 64, 1, 1, 0, st, args, nullptr);
+    return hipModuleLaunchKernel(k.product().fn, (unsigned)(B * w.d), 1, 1, (unsigned)k.product().nw * 64, 1, 1, 0, st, args, nullptr);
 }
 // backward, workspace: chunk signatures [B][C] over the words shorter than the depth; where the lanes of the walk don't work out
 // signature and adjoints at the chunk ends from them, also products from the left, from the right and boundary adjoints [B][C - 1]
@@ -1023,11 +1031,7 @@ size_t lanes_backward_chunked_bytes(const sig::WordSet& w, int64_t B, const Chun
 {
     return lanes_low_bytes(w, B, ch.C) + (arrays ? 3 * lanes_low_bytes(w, B, ch.C - 1) : 0);
 }
-// whether a call asks for those arrays: signatures that don't fit a wavefront's LDS, and counts set by the option "chunks"
-bool lanes_backward_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch)
-{
-    return w.opt.chunks > 0 || !lanes_shape_for(w, 1, B * ch.C).shares;
-}
+bool lanes_backward_arrays(const sig::WordSet& w, int64_t B, const Chunks& ch) { return lanes_arrays(w, lanes_shape_for(w, 1, B * ch.C)); }
 hipError_t lanes_backward_chunked(const sig::WordSet& w, const LanesChunked& k, const float* path, const float* coeffs,
                                   const float* grad_coeffs, int64_t B, int64_t n_points, const Chunks& ch, bool arrays, float* grad_path,
                                   void* workspace, hipStream_t st)
@@ -1310,7 +1314,8 @@ size_t sig_wordset_jit_source(sig_wordset* ws, int backward, int64_t B, char* bu
     if (!jit_enabled(w)) return 0;
     std::string src;
     if (use_lanes(w, B, kAnyLength)) {
-        src = sig::lanes_source(w.d, w.depth, lanes_shape_for(w, dir, B), dir != 0);
+        const sig::LanesShape s = lanes_shape_for(w, dir, B);
+        src = sig::lanes_source(w.d, w.depth, s, dir != 0, dir == 1 && lanes_arrays(w, s));
     } else {
         sig::WordSet::JitEntry* e = jit_entry(w, dir, B);
         if (!e) return 0;
@@ -1717,9 +1722,11 @@ static int backward_impl(const sig_wordset* ws, const float* path, const float* 
     if (lanes_path && word_chunks && !residual) {
         const Chunks lch = lanes_chunks(w, 1, B, n_points);
         LanesChunked lc;
-        const bool arrays = lch.C > 1 && lanes_backward_arrays(w, B, lch) && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, true);
-        if (lch.C > 1 && (arrays || (lanes_shape_for(w, 1, B * lch.C).shares && workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, false))) &&
-            lanes_chunk_kernels(w, 1, B * lch.C, how, lc)) {
+        const bool arrays = lch.C > 1 && lanes_backward_arrays(w, B, lch) &&
+                            workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, true);
+        const bool shares = lch.C > 1 && lanes_shape_for(w, 1, B * lch.C).shares &&
+                            workspace_bytes >= lanes_backward_chunked_bytes(w, B, lch, false);
+        if ((arrays || shares) && lanes_chunk_kernels(w, 1, B * lch.C, how, lc)) {
             hipError_t le = lanes_backward_chunked(w, lc, path, coeffs, grad_coeffs, B, n_points, lch, arrays, grad_path, workspace, st);
             return le == hipSuccess ? SIG_OK : hip_fail(le);
         }

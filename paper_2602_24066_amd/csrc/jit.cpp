@@ -548,12 +548,13 @@ WordSet::~WordSet()
             }
             delete e;
         }
-    for (int dir = 0; dir < 2; ++dir)
-        for (int r = 0; r < 3; ++r)
-            if (lanes[dir][r]) {
-                jit_release(*lanes[dir][r]);
-                delete lanes[dir][r];
-            }
+    for (auto& dir : lanes)
+        for (auto& form : dir)
+            for (JitKernel* k : form)
+                if (k) {
+                    jit_release(*k);
+                    delete k;
+                }
 }
 
 void jit_release(JitKernel& k)

@@ -66,7 +66,8 @@ LanesShape lanes_low_shape(int d, int depth);                 // forward kernel 
 bool lanes_chunks_available(int d, int depth);
 // source of sig_fwd_lanes (backward = false) or sig_bwd_lanes for that shape and, where time chunks are available, of the
 // kernels they take: sig_scan_lanes, and backward sig_low_lanes (forward) and sig_adjoint_lanes as well
-std::string lanes_source(int d, int depth, const LanesShape& s, bool backward);
+// arrays: backward with the kernels that write products and boundary adjoints of time chunks to arrays
+std::string lanes_source(int d, int depth, const LanesShape& s, bool backward, bool arrays);
 constexpr int kLanesChunkCounts[] = {2, 3, 4, 6, 8, 12, 16, 24, 32};
 // time chunks for B paths of L segments: the count with the shortest modelled time, 1 where none gains a tenth
 int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels);

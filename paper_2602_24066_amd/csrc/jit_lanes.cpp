@@ -1270,14 +1270,15 @@ LanesShape lanes_low_shape(int d, int depth)
 }
 
 // The kernels of a module share their text, with other shapes: a namespace each, the shape macros set anew in front of it.
-std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
+std::string lanes_source(int d, int depth, const LanesShape& s, bool backward, bool arrays)
 {
     std::ostringstream o;
     auto lanes = [&](const char* ns, int n, const LanesShape& q, bool bwd, const char* forward_name) {
-        o << "#define N " << n << "\n#define R " << q.R << "\n#define SP " << q.split << "\n#define T " << q.T << "\n#define TS " << q.TS << "\n#define NWB " << q.nwb
-          << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0) << "\n#define FORWARD_NAME " << forward_name
-          << "\n#define CLEARS " << (backward ? 1 : 0) << "\nnamespace " << ns << " {\n"
-          << kLanesSource << "}\n#undef N\n#undef R\n#undef SP\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n#undef FORWARD_NAME\n#undef CLEARS\n";
+        o << "#define N " << n << "\n#define R " << q.R << "\n#define SP " << q.split << "\n#define T " << q.T << "\n#define TS " << q.TS
+          << "\n#define NWB " << q.nwb << "\n#define BACKWARD " << (bwd ? 1 : 0) << "\n#define MSUM " << (bwd && q.msum ? 1 : 0)
+          << "\n#define FORWARD_NAME " << forward_name << "\n#define CLEARS " << (backward ? 1 : 0) << "\nnamespace " << ns << " {\n"
+          << kLanesSource << "}\n#undef N\n#undef R\n#undef SP\n#undef T\n#undef TS\n#undef NWB\n#undef BACKWARD\n#undef MSUM\n"
+          << "#undef FORWARD_NAME\n#undef CLEARS\n";
     };
     auto chunk = [&](const char* ns, LanesChunkPart part) {
         o << "#define N " << depth << "\n#define M " << (part == kLanesScanLow ? depth - 1 : depth)
@@ -1292,8 +1293,10 @@ std::string lanes_source(int d, int depth, const LanesShape& s, bool backward)
         } else {
             if (depth > 2) lanes("low", depth - 1, lanes_low_shape(d, depth), false, "sig_low_lanes");
             else chunk("low", kLanesDisplacement);
-            chunk("scan", kLanesScanLow);
-            chunk("adjoint", kLanesAdjoint);
+            if (arrays) {
+                chunk("scan", kLanesScanLow);
+                chunk("adjoint", kLanesAdjoint);
+            }
         }
     }
     return o.str();

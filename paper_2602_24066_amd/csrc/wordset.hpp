@@ -137,7 +137,8 @@ struct WordSet {
     std::vector<JitEntry*> jit[2];
     // full truncations: kernels with lanes = words, per direction and levels per lane (jit_lanes.cpp); the third: forward two levels
     // with the children of a word halved, backward one level with sums by rows where that is one of two forms; built on first use
-    JitKernel* lanes[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
+    // [..][1]: backward with the kernels for products and adjoints of time chunks in arrays as well
+    JitKernel* lanes[2][3][2] = {};
     // the last few decisions on their number of time chunks (each takes microseconds to model), and the batch sizes whose
     // kernels, for every number of chunks, have been brought up; both under the lock
     struct ChunkChoice { int64_t B = 0, L = 0; int dir = -1, levels = 0, C = 1; };

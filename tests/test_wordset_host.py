@@ -439,6 +439,19 @@ def test_kernels_of_time_chunks_ahead_of_time(tmp_path, monkeypatch):
     assert ws.jit_prepare_chunks(False, 64) == -9
 
 
+def test_kernels_of_chunk_arrays_only_where_calls_run_them():
+    """Products and boundary adjoints in arrays are for backward calls whose chunk signatures a wavefront's LDS does not hold, and
+    for counts set by the option "chunks": the modules of the others are compiled without those kernels."""
+    ws = S.sig_wordset_build_truncated(10, 4)                       # 1,110 words shorter than the depth
+    names = ("sig_scan_lanes", "sig_adjoint_lanes")
+    assert "sig_low_lanes" in ws.jit_source(True, 1) and not any(n in ws.jit_source(True, 1) for n in names)
+    assert "sig_scan_lanes" in ws.jit_source(False, 1)              # forward multiplies the chunk signatures
+    ws.set_option("chunks", 4)
+    assert all(n in ws.jit_source(True, 1) for n in names)
+    big = S.sig_wordset_build_truncated(10, 5)                      # 11,110
+    assert all(n in big.jit_source(True, 1) for n in names)
+
+
 @pytest.mark.parametrize("case", ["words", "anisotropic"])
 def test_windows_ask_for_no_time_chunks(case):
     """Windows of a word set run as rows, or gathered into paths that are walked whole: their workspace holds the gathered paths and

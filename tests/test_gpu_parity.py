@@ -956,6 +956,46 @@ def test_non_finite_gradient_of_one_word_stays_with_its_letters(d, depth, L, lev
         assert np.abs(g[1][:, others] - ref[1][:, others]).max() <= BWD_TOL * scale[1]
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,depth,L,levels,length", [
+    (10, 4, 90, 1, 3),    # one level, sums as products; a word of a lane's own
+    (10, 4, 90, 1, 2),    # shared by ten lanes, of two wavefronts at times
+    (10, 4, 90, 2, 4),    # two levels; a leaf
+    (3, 4, 60, 1, 2),
+    (16, 3, 64, 1, 3),
+    (4, 6, 90, 0, 5),     # the fused kernel: eight chunks of a path in a workgroup
+    (4, 6, 90, 0, 2),
+    (4, 6, 40, 0, 6),
+])
+def test_non_finite_gradient_at_chunk_boundaries(d, depth, L, levels, length, bad, monkeypatch):
+    """The same over the launcher's own time chunks, whose lanes work out the adjoints at the chunk ends: an infinite or NaN gradient
+    of one word reaches its letters in its path and nothing else."""
+    import torch
+    if levels:
+        monkeypatch.setenv("SIG_LANES", "1")
+        monkeypatch.setenv("SIG_LANES_LEVELS", str(levels))
+    ws, W = build_both("truncated", d, depth=depth)
+    X, G = make_path("iid", 471 + L, 2, L, d), make_grad_coeffs(472 + L, 2, ws.size)
+    word = tuple(int(c) for c in np.random.default_rng(473).integers(0, 2, length - 1)) + (2,)      # letters 0, 1 and 2 at most
+    at = W.index(word)
+    G[1, at] = 0.0
+    ref = oracle_backward(X, W, "truncated", depth, G.astype(np.float64))
+    G[1, at] = bad
+    x, lib = torch.from_numpy(X).cuda(), S.load_library()
+    work = nan_workspace(int(lib.sig_backward_workspace_bytes(ws._h, 2, L + 1)))
+    g = S.sig_backward(ws, x, S.sig_forward(ws, x), torch.from_numpy(G).cuda(), workspace=work).cpu().numpy()
+    if levels:                                                     # chunk signatures, and nothing else, in the workspace
+        used, low = int(torch.isfinite(work).sum()), int(ws.level_start[depth])
+        assert used > 2 * low and used % (2 * low) == 0
+    else:
+        assert ws.kernel_name(True, 2, L + 1) == "trunc_tails_bwd_kernel" and torch.isnan(work).all()
+    others = [i for i in range(d) if i not in word]
+    scale = np.abs(ref).max(axis=(1, 2))
+    assert np.abs(g[0] - ref[0]).max() <= BWD_TOL * scale[0]
+    assert not np.isfinite(g[1][:, sorted(set(word))]).any()
+    assert np.abs(g[1][:, others] - ref[1][:, others]).max() <= BWD_TOL * scale[1]
+
+
 @pytest.mark.parametrize("d,depth", [(3, 4), (4, 4), (10, 4)])
 def test_chunk_boundaries_keep_the_precision_of_a_cancelling_gradient(d, depth):
     """The gradient of log-signature coordinates cancels in the adjoints of the short words.  Where the lanes work out the adjoints

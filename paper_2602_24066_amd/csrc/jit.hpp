@@ -52,6 +52,7 @@ struct LanesShape {
     int R, T, TS, nwb;
     int split;                     // wavefronts that share the children of 64 words (forward, R = 2: 1 or 2)
     int64_t lanes, waves;
+    double fit;                    // wavefronts a SIMD holds by the LDS they take
     int chain;                     // multiply-adds of a lane's chain per segment
     double per_lane;               // instructions of a lane per segment, for comparing shapes
 };

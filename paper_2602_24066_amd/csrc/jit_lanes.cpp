@@ -1096,6 +1096,19 @@ int64_t words_up_to(int d, int n)
 }
 }  // namespace
 
+namespace {
+// Modelled time of a forward segment in microseconds, `waves` wavefronts to a SIMD: the latency of the chain and the issue of a
+// lone wavefront's instructions (and, where the halves of a word's children begin at an odd place, their increments read one by
+// one: 5, 6 and 10 letters 0.03 us).  A second wavefront fills the gaps of the first: 1.4 times the time, not twice, and 0.7 for each
+// from there on (8 letters, depth 4, one level: 0.070 us a segment alone, 0.109 with two, 0.202 with four).
+double forward_segment(const LanesShape& s, int d, double waves)
+{
+    const bool odd = s.split > 1 && (d + 1) / 2 % 2 != 0;
+    const double lone = 0.0013 * s.chain + 0.005 + (s.R == 1 ? 0.0019 : 0.0021) * s.per_lane + (odd ? 0.033 : 0.0);
+    return waves <= 1.0 ? lone : lone * std::max(1.4, 0.7 * waves);
+}
+}  // namespace
+
 LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
 {
     LanesShape best{};
@@ -1134,7 +1147,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         s.chain = chain;
         s.per_lane = per_lane;
         const double rounds = (double)std::max<int64_t>(B, 1) * (double)s.waves / 1024.0;
-        const double cost = per_lane * (rounds < 1.0 ? 1.0 : rounds);
+        const double cost = backward ? per_lane * (rounds < 1.0 ? 1.0 : rounds) : forward_segment(s, d, rounds);
         if (best.ok && cost >= best_cost) continue;            // (every call asks, several times)
         // LDS of a wavefront: the increments of a staging tile and, backward, the gradient rows of the segments of a
         // tile; eight wavefronts of 20 KB fit a compute unit, so longer tiles are cut down to that.  The staging
@@ -1169,6 +1182,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         s.shares = backward && words_up_to(d, depth - 1) * sizeof(float) <= per_wave;
         s.nwb = (int)(per_wave * 4 <= 64 * 1024 ? 4 : (per_wave * 2 <= 64 * 1024 ? 2 : (per_wave <= 64 * 1024 ? 1 : 0)));
         s.ok = s.nwb > 0;
+        if (s.ok) s.fit = std::max(1.0, std::floor(160.0 * 1024.0 / ((double)per_wave * s.nwb))) * s.nwb / 4.0;
         if (s.ok) {
             best = s;
             best_cost = cost;
@@ -1193,12 +1207,12 @@ bool lanes_chunks_available(int d, int depth)
     return (words_up_to(d, depth - 1) + 2 * (words_up_to(d, depth - 2) + 1)) * 4 <= 62 * 1024;
 }
 
-// Times in microseconds, fitted to a scan of 31 shapes (2..40 letters, depth 2..7, 1..1,000 paths of 24..1,000 segments, every
-// count of kLanesChunkCounts); the model's choice costs 3 % over the best count on average.  A segment takes the latency of
-// a lane's chain and the issue of its instructions, the latter as often as wavefronts share a SIMD, in as many rounds as
-// the chip holds the wavefronts (two per SIMD backward, where each has 18-20 KB of LDS, four forward).  Chunks cost their
-// launches, a product per chunk and the traffic of the chunk signatures.  Gains measured at the choice: forward 37 x 301
-// segments, d = 7, depth 4: 30 -> 15 us, 8 x 1,000, d = 3, depth 5: 84 -> 17; backward 72 -> 37 and 301 -> 41.
+// Times in microseconds, fitted to a scan of 33 shapes (2..40 letters, depth 2..9, 1..512 paths of 17..500 segments, every form and
+// count: 1,828 calls each way); the choice of form and count costs 1.7 % over the best forward and 1 % backward on average.  A
+// segment takes the latency of a lane's chain and the issue of its instructions, as often as wavefronts share a SIMD, in as many
+// rounds as the chip holds the wavefronts; chunks cost their launches, a product per chunk and the traffic of the chunk signatures
+// forward, and backward what a wavefront needs to pass the chunk signatures.  Gains measured at the choice: forward
+// 37 x 301 segments, d = 7, depth 4: 30 -> 15 us, 8 x 1,000, d = 3, depth 5: 84 -> 17; backward 72 -> 26 and 301 -> 41.
 int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels)
 {
     const double words = (double)words_up_to(d, depth), low_words = (double)words_up_to(d, depth - 1), k = words / 1000.0;
@@ -1210,14 +1224,20 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
     auto time = [&](int64_t C) {
         LanesShape s = lanes_shape(d, depth, backward, B * C, levels);
         if (!s.ok) s = lanes_shape(d, depth, backward, B * C, 0);
-        const double waves = (double)(B * C) * (double)s.waves / 1024.0, rounds = std::ceil(waves / (backward ? 2.0 : 4.0));
-        double latency, issue;
+        const double waves = (double)(B * C) * (double)s.waves / 1024.0, Lc = (double)((L + C - 1) / C);
         if (!backward) {
-            latency = 0.0013 * s.chain;
-            issue = 0.005 + (s.R == 1 ? 0.0019 : 0.0021) * s.per_lane;
-        } else if (s.msum) {
+            const double t = 3.7 + Lc * forward_segment(s, d, waves);
+            return C == 1 ? t : t + launches + (double)C * product;
+        }
+        // Two wavefronts of 18 to 20 KB of LDS at a time, and those with sums as matrix products by the room that there is (16 letters,
+        // whose factors fill the registers: one): 10 letters, depth 4, 1,000 lanes a path, 0.23 us a segment alone, 0.30 with one on
+        // every SIMD, 0.63 with two.  Two levels of two or four letters have fewer rows to sum where the runs of equal letters fall into
+        // rows of sixteen lanes (4 letters, depth 5, 64 lanes 0.38 us, 5 letters 0.76).
+        double latency, issue, rounds = std::ceil(waves / 2.0);
+        if (s.msum) {
             latency = 0.0034 * s.chain;
-            issue = 0.008 + 0.0039 * (6.0 * (depth - s.R + 1) + s.per_lane);
+            issue = 0.008 + 0.0039 * (6.0 * (depth - s.R + 1) + (s.shares ? 2.0 * (s.chain + std::min(d, 10)) : s.per_lane));
+            if (s.shares) rounds = std::max(rounds, std::ceil(waves / (d > 12 ? 1.0 : s.fit)));
         } else if (s.R == 1 && d == 2) {
             latency = 0.59;                                  // sums by rows: the chip is full, more rows gain nothing
             issue = 0.13;
@@ -1226,16 +1246,21 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
             latency = 1.1;
             issue = 0.0002 * s.per_lane;
         } else {
-            latency = 0.206 + 0.023 * s.chain;
-            issue = 0.132 + 0.0018 * s.per_lane;
+            const double rows = s.shares && (d == 2 || d == 4) && s.lanes <= 64 ? 0.55 : 1.0;
+            latency = rows * (0.206 + 0.023 * s.chain);
+            issue = rows * (0.132 + 0.0018 * s.per_lane);
         }
-        const double Lc = (double)((L + C - 1) / C);
-        const double t = (backward ? 8.5 : 3.7) + Lc * rounds * (latency + issue * std::max(1.0, waves / rounds));
+        const double t = 8.5 + Lc * rounds * (latency + issue * std::max(1.0, waves / rounds));
         if (C == 1) return t;
-        // without arrays at the boundaries: one launch in place of the clearing one, and every wavefront passes the chunk signatures
+        const double low = 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
+        if (!s.shares) return t + launches + (double)C * product + low;
+        // without arrays at the boundaries: one launch in place of the clearing one, and every wavefront passes the chunk signatures.
+        // Not on paths of a few segments once wavefronts share SIMDs, sooner those of two levels, which hold more each: what they
+        // read first takes longer than the segments saved (2 letters, depth 9, 128 paths x 24: 26 us whole, 31 in two chunks,
+        // 35 in three; 10 letters, depth 4, 256 x 24: 28, 27.5 and 32).
+        if (L < 32 && waves * s.R >= 1.5) return 1.0e9;
         const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : 0.0035 * (d + (double)d * d));
-        if (backward && s.shares) return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
-        return t + launches + (double)C * product + (backward ? 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0) : 0.0);
+        return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + low;
     };
     double best = 0.93 * time(1);
     int choice = 1;

@@ -439,6 +439,34 @@ def test_kernels_of_time_chunks_ahead_of_time(tmp_path, monkeypatch):
     assert ws.jit_prepare_chunks(False, 64) == -9
 
 
+@pytest.mark.parametrize("d,depth,B,levels,split", [
+    (11, 4, 128, 1, 1),      # three wavefronts a SIMD of one level 0.10 us a segment each take less than one of half the children
+    (12, 4, 128, 1, 1), (8, 4, 256, 1, 1), (6, 4, 512, 1, 1),
+    (10, 4, 256, 2, 2), (7, 4, 500, 2, 2),       # where they would be eight and six
+])
+def test_forward_form_by_the_time_of_a_segment(d, depth, B, levels, split):
+    """Wavefronts that share a SIMD fill each other's gaps: forms that need more of them are not priced as if they ran one after the
+    other.  Calls of 24 to 500 segments, one level -> halves: 11 letters, 128 paths 8.9 -> 14.1 us and 31.1 -> 43.8; 6 letters, 512
+    paths 7.4 -> 9.3 and 16.6 -> 21.6; the other way 10 letters, 256 paths x 199 56 -> 45."""
+    src = S.sig_wordset_build_truncated(d, depth).jit_source(False, B)
+    assert f"#define R {levels}\n#define SP {split}\n" in src
+
+
+def test_time_chunks_of_a_full_chip():
+    """Forward batches that fill the chip once still gain from chunks of two levels a lane (6 letters, depth 4, 512 paths x 500: 70 us
+    whole, 43 in four); backward paths of a few segments lose (2 letters, depth 9, 128 x 24: 26 us whole, 31 in two chunks), longer
+    ones gain."""
+    lib = S.load_library()
+    ws = S.sig_wordset_build_truncated(6, 4)
+    assert lib.sig_forward_workspace_bytes(ws._h, 512, 501) == 4 * 512 * 4 * ws.size
+    short = S.sig_wordset_build_truncated(2, 9)
+    row_a_path = 4 * 128 * int(short.level_start[9])               # a chunk's signature, of the words shorter than the depth
+    chosen = lib.sig_backward_workspace_bytes(short._h, 128, 25)
+    assert lib.sig_backward_workspace_bytes(short._h, 128, 501) >= 2 * row_a_path
+    short.set_option("chunks", 1)
+    assert lib.sig_backward_workspace_bytes(short._h, 128, 25) == chosen
+
+
 def test_kernels_of_chunk_arrays_only_where_calls_run_them():
     """Products and boundary adjoints in arrays are for backward calls whose chunk signatures a wavefront's LDS does not hold, and
     for counts set by the option "chunks": the modules of the others are compiled without those kernels."""

@@ -170,7 +170,7 @@ int sig_wordset_plan_get(const sig_wordset* ws, int backward, int variant, const
  * option "no_jit" disables it.
  * Full truncations (any d <= 64) without a precompiled kernel are the exception to "grows with the word set": they
  * run fixed kernel sources with a word per lane, compiled for the shape (d, depth) in one to three seconds per
- * direction, the kernels of their time chunks included (Section 3.1, eq. (3), with the prefixes shared between words);
+ * direction, the kernels that their time chunks take included (Section 3.1, eq. (3), with the prefixes shared between words);
  * where a path has only a few words of length depth - 2 they do so while the paths are few.  The option "lanes" = 0
  * sends them all through the straight-line form, = 1 all through the word-per-lane form.  sig_wordset_jit_prepare and
  * sig_wordset_jit_source cover whichever form the batch would use.
@@ -216,16 +216,24 @@ int    sig_wordset_upload(sig_wordset* ws, void* dev_buf /*device*/, size_t dev_
  * path   device float32 [B, n_points, d]
  * coeffs device float32 [B, |W|]            fully overwritten
  * workspace: device, sig_forward_workspace_bytes bytes (may be 0 -> NULL allowed), 256-byte aligned,
- *            contents undefined before and after.
+ *            contents undefined before and after.  What a call does with less is below.
  * Few paths are cut into time chunks that run side by side and are multiplied together afterwards (Chen's relation, eq. 2,
  * is associative); sig_backward recomputes the chunk signatures from the path.  A time model of the launch decides, for the
  * truncations with kernels of their own, for those that run with a word per lane, and for small launches of any other word set
- * (up to 4,096 words over up to 8 letters: the chunks run over the set's closure under suffixes, whose kernels the first call
- * that takes chunks compiles; while a stream is captured only kernels that are loaded are taken).  Larger word sets closed under
- * suffixes (sig_wordset_suffix_closed) take the chunks of the checkpointed calls below in sig_forward, and in sig_backward from
- * four chunks on.  A call whose workspace does not hold its chunks (NULL, or fewer bytes than the functions here give) walks
- * whole paths, except where it has to bring one (SIG_EWORKSPACE: long paths of the truncations with kernels of their own and of
- * large sets closed under suffixes); sig_backward_static always walks whole paths.
+ * (whose closure under suffixes, which the chunks run over, has up to 4,096 words of up to 8 letters each; its kernels are
+ * compiled by the first call that takes chunks, or by sig_wordset_jit_prepare_chunks; while a stream is captured only kernels that
+ * are loaded are taken).  Larger word sets closed under suffixes (sig_wordset_suffix_closed) take the chunks of the checkpointed
+ * calls below in sig_forward, and in sig_backward from four chunks on.  sig_backward_static always walks whole paths.
+ *
+ * A workspace smaller than the functions here give: the arrays of time chunks are optional where whole paths can be walked, what
+ * walking them takes is not.  SIG_EWORKSPACE is returned
+ *  - by sig_forward: for the truncations with kernels of their own below the array of the chunks of at least 256 segments that
+ *    few long paths take (shorter paths need none); for other word sets below the transposed increments of their specialised kernels
+ *    (full truncations that run with a word per lane need none, unless larger batches run them through specialised kernels);
+ *  - by sig_backward, which always needs a workspace: below the gradient with respect to the increments, for run-time compiled
+ *    kernels also the transposed increments, and for long paths of the truncations with kernels of their own the arrays of their chunks;
+ *  - by both, for sets closed under suffixes, below what they take over the chunks of the checkpointed calls where these calls
+ *    would take those (or, if that is less, over the chunks of a small launch).
  * n_points == 1 gives all-zero coeffs (S_{0,0} = 1 has no non-empty-word part).  B == 0 is a no-op. */
 size_t sig_forward_workspace_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 int    sig_forward(const sig_wordset* ws, const float* path, int64_t B, int64_t n_points, float* coeffs,
@@ -264,14 +272,15 @@ int    sig_backward_residual(const sig_wordset* ws, const float* path, const flo
  * Abar_c(u) = sum_v grad_coeffs(u v) Q_c(v) with Q_c the product of the chunk signatures after c (Proposition 4.1
  * with the right factor taken at a chunk boundary), and inside a chunk the recursion is that of sig_backward
  * (Proposition 4.6).  Nothing is recomputed (unless few paths gain from more chunks than are kept, whose
- * signatures are then worked out in the backward call); the price is C times the memory of coeffs between the two calls, where
+ * signatures are then worked out in the backward call, if its workspace holds them: the stated size does, a smaller one that holds
+ * what the kept chunks take is accepted); the price is C times the memory of coeffs between the two calls, where
  * sig_forward / sig_backward keep the terminal signature alone (Section 4.2).  The library picks C for the batch
  * (2 .. 16): for full truncations whose backward kernel would otherwise leave SIMDs with a single wavefront (few
  * paths with many segments), and for suffix-closed sets (sig_wordset_suffix_closed) of up to 13,653 words that run
  * through the run-time specialised kernels, which gain from more rows (up to eight chunks: at most 2,048 rows,
- * chunks of at least 256 segments, 128 for batches that stay at 512 rows or below).  Where it sees no gain sig_checkpoint_bytes is 0, `checkpoint` is not touched and
- * the two calls are sig_forward / sig_backward; the same holds when a specialised kernel cannot be compiled (then
- * `checkpoint` is left alone by both calls).  Results agree with sig_forward / sig_backward to rounding. */
+ * chunks of at least 256 segments, 128 for batches that stay at 512 rows or below).  Where it sees no gain
+ * sig_checkpoint_bytes is 0, `checkpoint` is not touched and the two calls are sig_forward / sig_backward; the same holds
+ * when a specialised kernel cannot be compiled (then `checkpoint` is left alone by both calls).  Results agree with sig_forward / sig_backward to rounding. */
 size_t sig_checkpoint_bytes(const sig_wordset* ws, int64_t B, int64_t n_points);
 /* The number of time chunks C the two calls take for this batch (1: none, the calls are sig_forward / sig_backward).
  * For a suffix-closed set the specialised kernels of the checkpointed calls run B * C rows: compile them ahead of time
@@ -293,8 +302,8 @@ int    sig_backward_checkpointed(const sig_wordset* ws, const float* path, const
  * SIG_STATIC_SCRATCH_BYTES that each GPU the library runs on holds until the process ends.  The call allocates nothing
  * and frees nothing; it only enqueues kernels on `stream` (what must start at zero is cleared by a kernel first).
  * Errors beyond those of sig_backward: SIG_ETOOLARGE when what sig_backward needs over whole paths (its workspace without
- * time chunks of its own) exceeds SIG_STATIC_SCRATCH_BYTES; SIG_ENOTREADY when the word set runs through a run-time compiled kernel that this process
- * has not loaded yet (loading a code object allocates): one sig_backward call of the same batch size loads it.
+ * time chunks of its own) exceeds SIG_STATIC_SCRATCH_BYTES; SIG_ENOTREADY when the word set runs through a run-time compiled
+ * kernel that this process has not loaded yet (loading a code object allocates): one sig_backward call of the same batch size loads it.
  * All calls on one GPU share that GPU's array: calls that overlap in time on the same device (different streams or
  * host threads) race; calls on one stream are ordered and safe. */
 #define SIG_STATIC_SCRATCH_BYTES (32u << 20)

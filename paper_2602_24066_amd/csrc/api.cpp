@@ -134,8 +134,8 @@ Chunks trunc_chunks(const sig::WordSet& w, int dir, int64_t B, int64_t n_points,
 // the words shorter than the depth alone (the longest are never reconstructed), so few paths are cut finer, and shorter ones
 // than above: up to sixteen chunks (eight forward), a model decides.  Microseconds per segment of a row: a lone wavefront on
 // each SIMD, and what a wavefront adds beyond that; per chunk: a product, the boundary adjoints and the traffic of its signature.
-// Forward + backward, whole paths (or the chunks of at least 256 segments before) -> now: d = 8, 3 paths x 979 segments 702 ->
-// 123 us, 62 x 515 407 -> 260, 5 x 238 205 -> 76; d = 16, 1 x 373 250 -> 71, 18 x 591 347 -> 190.
+// A forward and a backward call, one after the other on a stream, whole paths (or the chunks of at least 256 segments before) ->
+// now: d = 8, 3 paths x 979 segments 703 -> 123 us, 62 x 515 404 -> 255, 5 x 238 206 -> 72; d = 16, 1 x 373 251 -> 71, 18 x 591 350 -> 168.
 double low_time(const sig::WordSet& w, int dir, bool kept /* the chunk signatures are */, int64_t B, int64_t L, int64_t C)
 {
     const bool d8 = w.d == 8;
@@ -684,9 +684,9 @@ double plain_time(const sig::WordSet& w, PlainCall call, int64_t B, int64_t L, i
     t += Lc * seg_b * std::max(1.0, groups * units / 1024.0) + (double)C * (0.4 + 0.001 * words + 0.0024 * paths + 1.0e-5 * paths * words);
     return t + (call == kBackwardKept ? 10.0 : 15.0);
 }
-// The count with the shortest modelled time.  Forward + backward, whole paths -> at the choice, us: 226 words, d = 9, 22 paths x
-// 819 segments 534 -> 87; 432, d = 8, 46 x 526 319 -> 99; 384 (lead-lag, d = 6), 300 x 256 111 -> 82; 36 (lead-lag), 39 x 388
-// 130 -> 52; 240, d = 11, 258 x 969 615 -> 221; 209 (anisotropic), 101 x 322 148 -> 62.
+// The count with the shortest modelled time.  A forward and a backward call, one after the other on a stream, whole paths -> at the
+// choice, us: 226 words, d = 9, 22 paths x 819 segments 528 -> 89; 432, d = 8, 46 x 526 321 -> 100; 384 (lead-lag, d = 6), 300 x 256
+// 112 -> 82; 36 (lead-lag, d = 4), 39 x 388 132 -> 53; 240, d = 11, 258 x 969 609 -> 212.
 int plain_chunk_count(const sig::WordSet& w, PlainCall call, int64_t B, int64_t L)
 {
     double best = 0.93 * plain_time(w, call, B, L, 1);
@@ -1174,7 +1174,8 @@ int sig_logsig_backward(const sig_wordset* ws, const float* coeffs, const float*
     hipError_t e = sig::logsig_backward(coeffs, grad_logsig, B, w.size(), (const int32_t*)(base + w.lyn_len_off),
                                         (const int32_t*)(base + w.lyn_sub_off), w.n_lyndon, w.lyn_stride, w.depth, w.lyn_pairs,
                                         (const int32_t*)(base + w.lyn_inv_off_off), (const int32_t*)(base + w.lyn_inv_ent_off),
-                                        (const int32_t*)(base + w.lyn_sub_t_off), w.lyn_long, (float*)workspace, grad_coeffs, w.opt.logsig_gather != 0, (hipStream_t)stream);
+                                        (const int32_t*)(base + w.lyn_sub_t_off), w.lyn_long, (float*)workspace, grad_coeffs,
+                                        w.opt.logsig_gather != 0, (hipStream_t)stream);
     return e == hipSuccess ? SIG_OK : hip_fail(e);
 }
 
@@ -1418,7 +1419,9 @@ static hipError_t low_backward(const sig::WordSet& w, const float* path, const f
     float* Abar = (float*)(base + 3 * nb);
     hipError_t e = sig::trunc_forward_low(w.d, w.depth, path, B, n_points, ch.C, ch.Lc, Sc, st);
     if (e == hipSuccess) e = sig::chunk_slices_both(w.d, w.depth, Sc, w.level_start[(size_t)w.depth], left, right, B, (int)ch.C, st);
-    if (e == hipSuccess) e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, right, w.level_start[(size_t)w.depth], Abar, B, (int)ch.C, gdx, B * (n_points - 1) * w.d, st);
+    if (e == hipSuccess)
+        e = sig::chunk_adjoint(w.d, w.depth, grad_coeffs, right, w.level_start[(size_t)w.depth], Abar, B, (int)ch.C, gdx,
+                               B * (n_points - 1) * w.d, st);
     if (e != hipSuccess) return e;
     hipEvent_t* pe = g_prof.next(1);
     if (pe) (void)hipEventRecord(pe[0], st);
@@ -1893,7 +1896,8 @@ size_t sig_forward_checkpointed_workspace_bytes(const sig_wordset* ws, int64_t B
     if (!ws || B <= 0 || n_points <= 1) return 0;
     const Chunks ch = checkpoint_chunks(*W(ws), B, n_points);
     if (ch.C < 2) return sig_forward_workspace_bytes(ws, B, n_points);
-    if (W(ws)->kind != 0) return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));   // (the call needs less)
+    if (W(ws)->kind != 0)                                // (the call needs less)
+        return std::max(words_forward_ckpt_workspace(*W(ws), B, ch), sig_forward_workspace_bytes(ws, B, n_points));
     return 0;                                            // full truncations: the chunk signatures are the checkpoint
 }
 

@@ -122,8 +122,8 @@ struct Segment {
     }
 };
 // Segments are worked on in groups whose reads are issued together: a lone wavefront otherwise waits for LDS in every
-// segment (forward, one path of 199 segments, d = 10, depth 4: 39 -> 23 us; 8 x 1,000, d = 3, depth 5: 168 -> 84).  A tile's last group may reach past the end of the row, where the staged increments are zero: such
-// a segment changes nothing.
+// segment (forward, one path of 199 segments, d = 10, depth 4: 39 -> 23 us; 8 x 1,000, d = 3, depth 5: 168 -> 84).  A tile's
+// last group may reach past the end of the row, where the staged increments are zero: such a segment changes nothing.
 // Two levels below u fill the registers with their own state: one segment after the other there, and forward, beyond 48
 // values (LAZY), every read where it is used (256 x 199 segments, 10 letters, depth 4: 58 us against 64 in pairs; 16 x 100, 6
 // letters, depth 6: 34 against 30).
@@ -1034,7 +1034,8 @@ __device__ __forceinline__ void length_n(int i, const float* __restrict__ g, con
 {
     if constexpr (n < N) {
         constexpr int U = ipow(D, n - 1);
-        constexpr int G = U == 1 ? 64 : (NT / U >= 64 ? 64 : (NT / U >= 32 ? 32 : (NT / U >= 16 ? 16 : (NT / U >= 8 ? 8 : (NT / U >= 4 ? 4 : (NT / U >= 2 ? 2 : 1))))));
+        constexpr int each = NT / U;
+        constexpr int G = U == 1 || each >= 64 ? 64 : (each >= 32 ? 32 : (each >= 16 ? 16 : (each >= 8 ? 8 : (each >= 4 ? 4 : (each >= 2 ? 2 : 1)))));
         constexpr int stride = U == 1 ? NT : G;                // lanes that share a word
         const int lane = U == 1 ? threadIdx.x : threadIdx.x % G;
         for (int u0 = 0; u0 < U; u0 += NT / stride) {
@@ -1211,8 +1212,8 @@ bool lanes_chunks_available(int d, int depth)
 // count: 1,828 calls each way); the choice of form and count costs 1.7 % over the best forward and 1 % backward on average.  A
 // segment takes the latency of a lane's chain and the issue of its instructions, as often as wavefronts share a SIMD, in as many
 // rounds as the chip holds the wavefronts; chunks cost their launches, a product per chunk and the traffic of the chunk signatures
-// forward, and backward what a wavefront needs to pass the chunk signatures.  Gains measured at the choice: forward
-// 37 x 301 segments, d = 7, depth 4: 30 -> 15 us, 8 x 1,000, d = 3, depth 5: 84 -> 17; backward 72 -> 26 and 301 -> 41.
+// forward, and backward what a wavefront needs to pass the chunk signatures.  Whole paths -> the choice: forward 37 x 301
+// segments, d = 7, depth 4: 29.5 -> 15.1 us, 8 x 1,000, d = 3, depth 5: 83.5 -> 17.6; backward 67.5 -> 27.9 and 294 -> 26.2.
 int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int levels)
 {
     const double words = (double)words_up_to(d, depth), low_words = (double)words_up_to(d, depth - 1), k = words / 1000.0;

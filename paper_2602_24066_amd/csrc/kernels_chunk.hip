@@ -379,7 +379,8 @@ __global__ __launch_bounds__(NT) void chunk_slices_forward_kernel(const float* _
     }
 }
 
-// Over the words of length <= M, Sc [B][C] rows of sc_words floats, left and right [B][C] rows of those words: left[c] = S_0 .. S_c, right[c] = S_{c+1} .. S_{C-1} for c <= C - 2.
+// Over the words of length <= M, Sc [B][C] rows of sc_words floats, left and right [B][C] rows of those words:
+// left[c] = S_0 .. S_c, right[c] = S_{c+1} .. S_{C-1} for c <= C - 2.
 // Workgroup (path, letter, direction).
 template <int D, int M, int NT>
 __global__ __launch_bounds__(NT) void chunk_slices_both_kernel(const float* __restrict__ Sc, int64_t sc_words, int C,

@@ -2414,7 +2414,8 @@ hipError_t trunc_backward(int d, int depth, const float* path, const float* coef
     // instructions at half the rate of its SIMD: that form (segments software-pipelined) is for launches that have no
     // second wavefront per SIMD to offer anyway.  With the sources of 4 segments in registers, summed by cross-lane moves,
     // the workgroup needs 78 KB and two share a compute unit: taken for more than 1,024 wavefronts, which the first form walks
-    // in two rounds (18 paths x 591 segments in four chunks, 1,152 wavefronts: 212 -> 159 us).  tile = 16 / 4 force the two forms; 12 and 8 are shorter tiles (three quarters, half of the columns), measured slower, kept selectable.
+    // in two rounds (18 paths x 591 segments in four chunks, 1,152 wavefronts: 212 -> 159 us).  tile = 16 / 4 force the two forms;
+    // 12 and 8 are shorter tiles (three quarters, half of the columns), measured slower, kept selectable.
     if (d == 16 && depth == 4) {
         const int t = tile == 4 || tile == 8 || tile == 12 || tile == 16 ? tile : (B * C * 16 > 1024 ? 4 : 16);
         if (low)

@@ -218,10 +218,10 @@ __device__ __forceinline__ void seg_step(float& v, uint32_t key)
 }
 
 // One workgroup per (path, chunk but the last).  grad [B][W], Q [B][C][W] (row c: what follows chunk c), Abar [B][C][W]
-// (rows of last chunks are left alone: their adjoint is the gradient itself).  The gradient row and Q are staged in LDS before anything is written, so
-// Abar may be the array Q itself (not with a closure's tables, whose rows of Abar are shorter).  The terms lie sorted by their prefix u: a wavefront takes 64 consecutive terms (four
-// such groups in flight), sums runs of equal u within each row of 16 lanes and adds every run's sum to u's accumulator
-// in LDS.
+// (rows of last chunks are left alone: their adjoint is the gradient itself).  The gradient row and Q are staged in LDS before
+// anything is written, so Abar may be the array Q itself (not with a closure's tables, whose rows of Abar are shorter).  The
+// terms lie sorted by their prefix u: a wavefront takes 64 consecutive terms (four such groups in flight), sums runs of equal
+// u within each row of 16 lanes and adds every run's sum to u's accumulator in LDS.
 __global__ __launch_bounds__(kWordsThreads) void words_adjoint_kernel(WordTables t, const float* __restrict__ grad, const float* Q,
                                                                       int C, float* Abar, float* __restrict__ zeroed, int64_t n_zeroed)
 {
@@ -337,9 +337,15 @@ hipError_t words_scan_small(const WordTables& t, const float* S, int64_t B, int 
         return hipGetLastError();
     };
     const int per = (t.W + threads - 1) / threads;
-    if (t.N <= 4) return per == 1 ? launch(words_scan_small_kernel<1, 3>) : (per == 2 ? launch(words_scan_small_kernel<2, 3>) : launch(words_scan_small_kernel<4, 3>));
-    if (t.N <= 6) return per == 1 ? launch(words_scan_small_kernel<1, 5>) : (per == 2 ? launch(words_scan_small_kernel<2, 5>) : launch(words_scan_small_kernel<4, 5>));
-    return per == 1 ? launch(words_scan_small_kernel<1, 7>) : (per == 2 ? launch(words_scan_small_kernel<2, 7>) : launch(words_scan_small_kernel<4, 7>));
+    if (t.N <= 4) return per == 1 ? launch(words_scan_small_kernel<1, 3>)
+                         : per == 2 ? launch(words_scan_small_kernel<2, 3>)
+                                    : launch(words_scan_small_kernel<4, 3>);
+    if (t.N <= 6) return per == 1 ? launch(words_scan_small_kernel<1, 5>)
+                         : per == 2 ? launch(words_scan_small_kernel<2, 5>)
+                                    : launch(words_scan_small_kernel<4, 5>);
+    return per == 1 ? launch(words_scan_small_kernel<1, 7>)
+           : per == 2 ? launch(words_scan_small_kernel<2, 7>)
+                      : launch(words_scan_small_kernel<4, 7>);
 }
 
 hipError_t words_adjoint(const WordTables& t, const float* grad, const float* Q, int64_t B, int C, float* Abar, float* zeroed,

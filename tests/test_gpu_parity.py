@@ -314,9 +314,10 @@ def test_checkpointed_word_sets(case):
 
 @pytest.mark.parametrize("d,depth,B,L", [(8, 5, 3, 1100), (16, 4, 2, 1030)])
 def test_plain_backward_takes_time_chunks_for_few_long_paths(d, depth, B, L):
-    """sig_backward on few long paths of a full truncation recomputes the chunk signatures and walks four chunks side
-    by side (its workspace then holds four chunk arrays); the result is the oracle's, and that of the entry point
-    with the static scratch array, which always walks whole paths."""
+    """sig_backward on few long paths of a full truncation recomputes the chunk signatures and walks chunks side by side (the
+    stated size of its workspace is that of four arrays of four whole chunk signatures; the call takes less, short rows of
+    more chunks); the result is the oracle's, and that of the entry point with the static scratch array, which always
+    walks whole paths."""
     import torch
     ws, W = build_both("truncated", d, depth=depth)
     lib = S.load_library()

@@ -500,9 +500,8 @@ def test_windows_ask_for_no_time_chunks(case):
 
 
 def test_time_chunk_workspace():
-    """Few long paths of a full truncation are cut into time chunks: the forward workspace holds the chunk
-    signatures (and the partial products when four or more signatures too large for LDS are multiplied pair by pair);
-    many paths, or short ones, need none."""
+    """Few long paths of a full truncation are cut into time chunks: the forward workspace holds the chunk signatures (four chunks
+    of 256 segments, and over 8 letters eight of 128: twice the four); many paths, or short ones, need none."""
     lib = S.load_library()
     ws = S.sig_wordset_build_truncated(4, 6)
     rows = 2 * 4                                               # B = 2 paths, L = 1024 -> 4 chunks of 256 segments

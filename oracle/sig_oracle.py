@@ -33,7 +33,7 @@ _lib = None
 
 
 def build(force: bool = False) -> str:
-    """Compile sig_oracle.c with gcc (-O2, OpenMP).  Building the checker is not using it."""
+    """Compile sig_oracle.c with gcc (-O2, OpenMP).  Building the oracle is not using it."""
     if force or not os.path.exists(_LIB) or os.path.getmtime(_LIB) < os.path.getmtime(_SRC):
         tmp = _LIB + f".{os.getpid()}.tmp"
         subprocess.check_call(["gcc", "-O2", "-fopenmp", "-shared", "-fPIC", "-std=c99", "-o", tmp, _SRC, "-lm"])

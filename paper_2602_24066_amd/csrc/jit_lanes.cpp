@@ -1256,10 +1256,13 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         const double low = 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
         if (!s.shares) return t + launches + (double)C * product + low;
         // without arrays at the boundaries: one launch in place of the clearing one, and every wavefront passes the chunk signatures.
-        // Not on paths of a few segments once wavefronts share SIMDs, sooner those of two levels, which hold more each: what they
-        // read first takes longer than the segments saved (2 letters, depth 9, 128 paths x 24: 26 us whole, 31 in two chunks,
-        // 35 in three; 10 letters, depth 4, 256 x 24: 28, 27.5 and 32).
-        if (L < 32 && waves * s.R >= 1.5) return 1.0e9;
+        // Not on paths of a few segments once wavefronts share SIMDs: what they read first takes longer than the segments saved.  Two
+        // levels, which read more, only up to a wavefront on each SIMD, if a path has several (one sums its tile cheaply) over three to
+        // nine letters (two: the sums of a tile take the same time however few its segments are).  128 to 512 paths, whole -> two
+        // chunks: 5 letters, depth 5, x 17 segments 27 -> 24 us, 9 letters, depth 4 26 -> 23, but 4 letters, depth 5, x 24 17 -> 21,
+        // 10 letters, depth 4, x 17 23 -> 27, 2 letters, depth 9, x 24 26 -> 31.
+        const bool few = s.R == 1 ? waves < 1.5 : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
+        if (L < 32 && !few) return 1.0e9;
         const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : 0.0035 * (d + (double)d * d));
         return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + low;
     };

@@ -465,6 +465,10 @@ def test_time_chunks_of_a_full_chip():
     assert lib.sig_backward_workspace_bytes(short._h, 128, 501) >= 2 * row_a_path
     short.set_option("chunks", 1)
     assert lib.sig_backward_workspace_bytes(short._h, 128, 25) == chosen
+    several = S.sig_wordset_build_truncated(5, 5)                  # two wavefronts a path
+    two = 2 * 4 * 256 * int(several.level_start[5])
+    assert lib.sig_backward_workspace_bytes(several._h, 256, 18) == two
+    assert lib.sig_backward_workspace_bytes(several._h, 1024, 18) < 4 * two
 
 
 def test_kernels_of_chunk_arrays_only_where_calls_run_them():

@@ -638,15 +638,14 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             const Segment& x = xs[u];
             const float (&e0)[DP] = x.e0;
             const float (&ec)[K][NC] = x.ec;
-            // reconstruction with -dX, then the Horner intermediates with +dX from the reconstructed signature
-            float am[K + 1][N + 2], ap[K + 1][N + 2];
+            // Reconstruction by solving the forward step for the signature it started from: a word needs of the shorter ones only
+            // the Horner intermediates with +dX, formed word by word on the way down the chain.
+            float ap[K + 1][N + 2];
 #pragma unroll
-            for (int t = 0; t < N + 2; ++t) am[0][t] = ap[0][t] = 1.0f;
+            for (int t = 0; t < N + 2; ++t) ap[0][t] = 1.0f;
 #pragma unroll
             for (int k = 1; k <= K; ++k) {
-#pragma unroll
-                for (int t = 1; t <= N - k; ++t) am[k][t] = __builtin_fmaf(-ec[k - 1][t], am[k - 1][t + 1], Sc[k - 1]);
-                Sc[k - 1] = __builtin_fmaf(-ec[k - 1][0], am[k - 1][1], Sc[k - 1]);
+                Sc[k - 1] = __builtin_fmaf(-ec[k - 1][0], ap[k - 1][1], Sc[k - 1]);
 #pragma unroll
                 for (int t = 1; t <= N - k; ++t) ap[k][t] = __builtin_fmaf(ec[k - 1][t], ap[k - 1][t + 1], Sc[k - 1]);
             }
@@ -676,7 +675,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             float g2 = 0.0f;
 #pragma unroll
             for (int j = 0; j < D; ++j) {
-                S1[j] = __builtin_fmaf(-e0[j], am[K][1], S1[j]);
+                S1[j] = __builtin_fmaf(-e0[j], ap[K][1], S1[j]);
                 const float Gp = __builtin_fmaf(e1[j], ap[K][2], S1[j]);
                 float h = 0.0f;
 #pragma unroll

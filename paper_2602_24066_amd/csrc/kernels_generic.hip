@@ -12,9 +12,9 @@
 // where A_k[t] is the Horner accumulator "S(w_[k]) + h" of Algorithm 1 for target words of length
 // k + t that pass through u; t = 0 gives the new S(u).
 //
-// Backward step (Section 4): S_{0,t_{j-1}} is reconstructed from S_{0,t_j} with the same recursion
-// and -dX (Proposition 4.6); the accumulators are recomputed with +dX and the recursion is run in
-// reverse for the adjoint, which carries the right factors of Proposition 4.1 aggregated over all
+// Backward step (Section 4): S_{0,t_{j-1}} is reconstructed from S_{0,t_j} (Proposition 4.6) word by word from the
+// shortest on, S_{j-1}(u) = S_j(u) - dX^{(u_k)} A_{k-1}[1] with the accumulators A of S_{j-1} itself; the recursion is
+// run in reverse for the adjoint, which carries the right factors of Proposition 4.1 aggregated over all
 // words with a common prefix.
 #include <hip/hip_runtime.h>
 
@@ -119,7 +119,6 @@ __global__ __launch_bounds__(kWave) void fwd_generic_kernel(const UnitDesc* __re
 
 template <int MAXK>
 struct BwdRegs {
-    float am[MAXK + 1][MAXK + 2];   // accumulators with -dX (reconstruction)
     float ap[MAXK + 1][MAXK + 2];   // accumulators with +dX, from the reconstructed S_{0,t_{j-1}}
     float gb[MAXK + 1][MAXK + 2];   // adjoints of ap
     int slot[MAXK + 1];             // LDS row of the open word at each length
@@ -131,7 +130,7 @@ __device__ __forceinline__ void bwd_leaf(BwdRegs<MAXK>& R, float dxl, float* S, 
 {
     const float s = S[row * kWave + lane];
     const float a = Ab[row * kWave + lane];
-    S[row * kWave + lane] = fmaf(-dxl, R.am[K - 1][1], s);
+    S[row * kWave + lane] = fmaf(-dxl, R.ap[K - 1][1], s);
     gc[letter * (kWave + 1) + lane] = fmaf(a, R.ap[K - 1][1], gc[letter * (kWave + 1) + lane]);
     R.gb[K - 1][1] = fmaf(dxl, a, R.gb[K - 1][1]);
 }
@@ -140,10 +139,7 @@ template <int MAXK, int K>
 __device__ __forceinline__ void bwd_enter(BwdRegs<MAXK>& R, float dxl, float* S, int row, int lane, int h)
 {
     const float s = S[row * kWave + lane];
-#pragma unroll
-    for (int t = 1; t <= MAXK - K; ++t)
-        if (t <= h) R.am[K][t] = fmaf(-dxl * inv_of(t), R.am[K - 1][t + 1], s);
-    const float sp = fmaf(-dxl, R.am[K - 1][1], s);
+    const float sp = fmaf(-dxl, R.ap[K - 1][1], s);
     S[row * kWave + lane] = sp;
 #pragma unroll
     for (int t = 1; t <= MAXK - K; ++t)
@@ -224,7 +220,6 @@ __global__ __launch_bounds__(kWave) void bwd_generic_kernel(const UnitDesc* __re
     BwdRegs<MAXK> R;
 #pragma unroll
     for (int t = 0; t < MAXK + 2; ++t) {
-        R.am[0][t] = 1.0f;
         R.ap[0][t] = 1.0f;
         R.gb[0][t] = 0.0f;
     }

@@ -496,10 +496,11 @@ hipError_t launch_trunc_mfma_fwd(const float* path, int64_t B, int64_t P, int64_
 // the words of length N - 1 and their children are the words of length N (leaves).
 //
 // Per segment j = L..1 (Section 4):
-//   1. S_{0,t_{j-1}} = S_{0,t_j} (x) exp(-dX_j)  (Proposition 4.6): the forward update with -dX, chain on the
-//      vector ALU, slice and leaves on the matrix cores.
-//   2. the Horner accumulators A+ are recomputed from the reconstructed signature with +dX (chain: vector ALU,
-//      slice: one matrix instruction per letter group).
+//   1. S_{0,t_{j-1}} = S_{0,t_j} (x) exp(-dX_j)  (Proposition 4.6), by solving the forward update for what it started from:
+//      S_{j-1}(u) = S_j(u) - dX^{(u_k)} A+_p[1] needs of the shorter words only the accumulators that step 2 forms anyway
+//      (the Horner recursion with -dX would be a second set: one multiply-add per word and target more).
+//   2. the Horner accumulators A+ of u from the reconstructed signature with +dX.  Both go down the chain together (vector
+//      ALU; slice: one matrix instruction per letter group).
 //   3. adjoint of the update, bottom up.  For a word u with parent p, target offset t and c = dX^{(u_k)}/(t+1):
 //         dLoss/d dX^{(u_k)} += gbar_u[t] * A+_p[t+1] / (t+1),   gbar_p[t+1] += c * gbar_u[t],
 //         Abar_{j-1}(u) = sum_t gbar_u[t],                        gbar_u[0] = Abar_j(u),
@@ -847,25 +848,17 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (BwdLds<D, N, WQ, T, VG>::T
 #pragma unroll
         for (int g = 0; g < WQ; ++g) sv.b0v[g] = Et[(4 * (g0 + g) + (lane & 3)) * NC];
 
-        // 1. reconstruction with -dX
-        float am[K + 1][N + 2];
-#pragma unroll
-        for (int t = 0; t < N + 2; ++t) am[0][t] = 1.0f;
-#pragma unroll
-        for (int k = 1; k <= K; ++k) {
-#pragma unroll
-            for (int t = 1; t <= N - k; ++t) am[k][t] = fmaf(-sv.ec[k - 1][t], am[k - 1][t + 1], Sc[k - 1]);
-            Sc[k - 1] = fmaf(-sv.ec[k - 1][0], am[k - 1][1], Sc[k - 1]);
-        }
-#pragma unroll
-        for (int g = 0; g < WQ; ++g) S1[g] = mfma4(am[K][1], nbs[g / 4], S1[g], g % 4);
-        // 2. accumulators with +dX from the reconstructed signature
+        // 1. and 2. from the shortest word down: reconstruction, then the accumulators with +dX from what was reconstructed
 #pragma unroll
         for (int t = 0; t < N + 2; ++t) sv.ap[0][t] = 1.0f;
 #pragma unroll
-        for (int k = 1; k <= K; ++k)
+        for (int k = 1; k <= K; ++k) {
+            Sc[k - 1] = fmaf(-sv.ec[k - 1][0], sv.ap[k - 1][1], Sc[k - 1]);
 #pragma unroll
             for (int t = 1; t <= N - k; ++t) sv.ap[k][t] = fmaf(sv.ec[k - 1][t], sv.ap[k - 1][t + 1], Sc[k - 1]);
+        }
+#pragma unroll
+        for (int g = 0; g < WQ; ++g) S1[g] = mfma4(sv.ap[K][1], nbs[g / 4], S1[g], g % 4);
 #pragma unroll
         for (int g = 0; g < WQ; ++g) sv.Gp[g] = mfma4(sv.ap[K][2], bs[(WQ + g) / 4], S1[g], (WQ + g) % 4);
         // chain values A+_K[1], A+_K[2]/2 of the parent of every slice word, in the child layout
@@ -1521,15 +1514,13 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
 #pragma unroll
             for (int t = 0; t < 3; ++t) eu[j][t] = Ec[row_t][j][t];
 
-        // 1. reconstruction with -dX, 2. accumulators with +dX (per-lane chain)
-        float am[KL + 1][N + 2], ap[KL + 1][N + 2];
+        // 1. reconstruction, 2. accumulators with +dX, word by word down the per-lane chain
+        float ap[KL + 1][N + 2];
 #pragma unroll
-        for (int t = 0; t < N + 2; ++t) am[0][t] = ap[0][t] = 1.0f;
+        for (int t = 0; t < N + 2; ++t) ap[0][t] = 1.0f;
 #pragma unroll
         for (int k = 1; k <= KL; ++k) {
-#pragma unroll
-            for (int t = 1; t <= N - k; ++t) am[k][t] = fmaf(-ec[k - 1][t], am[k - 1][t + 1], Sc[k - 1]);
-            Sc[k - 1] = fmaf(-ec[k - 1][0], am[k - 1][1], Sc[k - 1]);
+            Sc[k - 1] = fmaf(-ec[k - 1][0], ap[k - 1][1], Sc[k - 1]);
 #pragma unroll
             for (int t = 1; t <= N - k; ++t) ap[k][t] = fmaf(ec[k - 1][t], ap[k - 1][t + 1], Sc[k - 1]);
         }
@@ -1544,8 +1535,7 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
 #pragma unroll
         for (int i = 0; i < TW; ++i) {
             // tail i and its children: reconstruction, then the accumulators
-            const float am1 = fmaf(-eu[i][1], am[KL][2], St[i]);
-            St[i] = fmaf(-eu[i][0], am[KL][1], St[i]);
+            St[i] = fmaf(-eu[i][0], ap[KL][1], St[i]);
             const float ap1 = fmaf(eu[i][1], ap[KL][2], St[i]);
             const float ap2 = fmaf(eu[i][2], ap[KL][3], St[i]);
             const float hp2 = 0.5f * ap2;
@@ -1553,7 +1543,7 @@ __global__ __launch_bounds__(kWave * (CW ? CW : kWavesPerBlock)) void trunc_tail
             float g1 = 0.0f, g2 = 0.0f;
 #pragma unroll
             for (int j = 0; j < D; ++j) {
-                S1[i][j] = fmaf(-eu[j][0], am1, S1[i][j]);
+                S1[i][j] = fmaf(-eu[j][0], ap1, S1[i][j]);
                 const float Gp = fmaf(eu[j][1], ap2, S1[i][j]);               // A+[1] of the slice word
                 float h = 0.0f;                                                // its gbar[1], from the leaves
 #pragma unroll
@@ -1829,15 +1819,13 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 && !LONE ? 2 : 1)) 
     auto step = [&](int row_t, const In& in, float* yo, float* co) {
         const float (&ec)[K][NC] = in.ec;
         const float (&eu)[D][2] = in.eu;
-        // 1. reconstruction with -dX, 2. accumulators with +dX from the reconstructed signature
-        float am[K + 1][N + 2], ap[K + 1][N + 2];
+        // 1. reconstruction, 2. accumulators with +dX from the reconstructed signature, word by word down the chain
+        float ap[K + 1][N + 2];
 #pragma unroll
-        for (int t = 0; t < N + 2; ++t) am[0][t] = ap[0][t] = 1.0f;
+        for (int t = 0; t < N + 2; ++t) ap[0][t] = 1.0f;
 #pragma unroll
         for (int k = 1; k <= K; ++k) {
-#pragma unroll
-            for (int t = 1; t <= N - k; ++t) am[k][t] = fmaf(-ec[k - 1][t], am[k - 1][t + 1], Sc[k - 1]);
-            Sc[k - 1] = fmaf(-ec[k - 1][0], am[k - 1][1], Sc[k - 1]);
+            Sc[k - 1] = fmaf(-ec[k - 1][0], ap[k - 1][1], Sc[k - 1]);
 #pragma unroll
             for (int t = 1; t <= N - k; ++t) ap[k][t] = fmaf(ec[k - 1][t], ap[k - 1][t + 1], Sc[k - 1]);
         }
@@ -1849,7 +1837,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (D == 8 && !LONE ? 2 : 1)) 
         float g1 = 0.0f, g2 = 0.0f;
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            S1[j] = fmaf(-eu[j][0], am[K][1], S1[j]);
+            S1[j] = fmaf(-eu[j][0], ap[K][1], S1[j]);
             const float Gp = fmaf(eu[j][1], ap[K][2], S1[j]);                 // A+[1] of the child
             float h = 0.0f;                                                    // its gbar[1], from the leaves
 #pragma unroll

@@ -626,7 +626,8 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         fetch_increments(X, (ns - 1) * TS, L, lane, dxn);
       for (int sub = TS / T - 1; sub >= 0; --sub) {          // tiles of T segments: the unit of the gradient sums
         const long n = ns * (TS / T) + sub;
-        const int steps = MSUM && L - n * T < T ? (int)(L - n * T) : T;
+        // (the last tile may be a partial one: what the rows hold for the segments that it lacks is summed and dropped)
+        const int steps = (MSUM || R == 2) && L - n * T < T ? (int)(L - n * T) : T;
 #pragma unroll (BGROUP == 1 && !ONE_BY_ONE ? 2 : 1)
         for (int t1 = (steps + BGROUP - 1) / BGROUP * BGROUP; t1 > 0; t1 -= BGROUP) {
           Segment xs[BGROUP];
@@ -1250,7 +1251,10 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
             latency = rows * (0.206 + 0.023 * s.chain);
             issue = rows * (0.132 + 0.0018 * s.per_lane);
         }
-        const double t = 8.5 + Lc * rounds * (latency + issue * std::max(1.0, waves / rounds));
+        // The sums of a tile take the same however few segments it has, counted here against the average tile (as products a third of a full
+        // tile's time, but a fifth fits the calls).
+        const double share = s.msum ? 0.2 : (s.R == 2 ? 0.25 : 1.0), pad = std::ceil(Lc / s.T) * s.T - Lc;
+        const double t = 8.5 + (Lc + share * (pad - 0.3 * (s.T - 1))) * rounds * (latency + issue * std::max(1.0, waves / rounds));
         if (C == 1) return t;
         const double low = 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
         if (!s.shares) return t + launches + (double)C * product + low;
@@ -1267,13 +1271,24 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
     };
     double best = 0.93 * time(1);
     int choice = 1;
-    for (int C : kLanesChunkCounts) {
-        if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments
+    auto consider = [&](int64_t C) {
         const double t = time(C);
         if (t < best) {
             best = t;
-            choice = C;
+            choice = (int)C;
         }
+    };
+    for (int C : kLanesChunkCounts) {
+        if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments
+        consider(C);
+        if (!backward) continue;
+        // and the count near it whose chunks are whole tiles.  Backward calls, with that and partial tiles of two levels: 1 path x 199
+        // segments, 10 letters, depth 4, 13 chunks of one tile of 16 instead of 12 of two, 20.4 -> 18.7 us; 32 x 99, 6 letters, depth 5,
+        // 35.1 -> 28.9; 186 x 160, 3 letters, depth 5, 29.8 -> 24.9; 47 shapes 0.95 on geometric average, the slowest 1.01
+        LanesShape s = lanes_shape(d, depth, true, B * C, levels);
+        if (!s.ok) s = lanes_shape(d, depth, true, B * C, 0);
+        const int64_t tiles = std::max<int64_t>(1, (L / C + s.T / 2) / s.T), whole = (L + tiles * s.T - 1) / (tiles * s.T);
+        if (whole >= 2 && whole <= 32 && L >= 8 * whole) consider(whole);
     }
     return choice;
 }

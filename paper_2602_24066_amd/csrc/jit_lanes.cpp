@@ -80,9 +80,9 @@ __device__ __forceinline__ void fetch_increments(const float* __restrict__ X, lo
     }
 }
 // LDS of a staging tile: Ec[segment][letter][t] = dX / (t + 1) for the chain (a lane reads the row of its own
-// letter), and E0[segment][letter] = dX, E1 = dX / 2 as contiguous rows for the levels below u (every lane reads all
+// letter), and E0[segment][letter] = dX as contiguous rows for the levels below u (every lane reads all
 // letters)
-#define TILE_F (TS * D * NC + 2 * TS * DP)
+#define TILE_F (TS * D * NC + TS * DP)
 __device__ __forceinline__ void stage_increments(float* Ec, const float (&dx)[EPL], int lane)
 {
 #pragma unroll
@@ -93,7 +93,6 @@ __device__ __forceinline__ void stage_increments(float* Ec, const float (&dx)[EP
             for (int t = 0; t < N; ++t) Ec[e * NC + t] = dx[q] * inv1(t);
             float* E0 = Ec + TS * D * NC;
             E0[(e / D) * DP + e % D] = dx[q];
-            E0[TS * DP + (e / D) * DP + e % D] = dx[q] * 0.5f;
         }
     }
 }
@@ -253,18 +252,15 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
                 Sc[k - 1] = __builtin_fmaf(src[0], ap[k - 1][1], Sc[k - 1]);
             }
 #if R == 2
-            // the increments of the wavefront's own children (of half of an odd alphabet the last is none: its place is padding)
+            // the increments of the wavefront's own children (of half of an odd alphabet the last is none: its place is padding).  A child's
+            // intermediate S1 + dX / 2 A takes dX and half of A: halving is exact, and there is no second row of increments to read.
+            const float half = 0.5f * ap[K][2];
 #if SP == 1
-            float e1[DP];
-            load_row(E0 + TS * DP + tt * DP, e1);
             const float (&own)[DP] = e0;
 #else
-            float e1[DJ], own[DJ];
+            float own[DJ];
 #pragma unroll
-            for (int j = 0; j < DJ; ++j) {
-                own[j] = E0[tt * DP + j0 + j];
-                e1[j] = E0[TS * DP + tt * DP + j0 + j];
-            }
+            for (int j = 0; j < DJ; ++j) own[j] = E0[tt * DP + j0 + j];
 #endif
 #else
             const float (&own)[DP] = e0;
@@ -272,7 +268,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
 #pragma unroll
             for (int j = 0; j < DJ; ++j) {
 #if R == 2
-                const float Gp = __builtin_fmaf(e1[j], ap[K][2], S1[j]);
+                const float Gp = __builtin_fmaf(own[j], half, S1[j]);
 #pragma unroll
                 for (int jj = 0; jj < D; ++jj) S2[j][jj] = __builtin_fmaf(e0[jj], Gp, S2[j][jj]);
 #endif
@@ -388,6 +384,11 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
                                                )
 {
     constexpr int NLOW = (int)level_start(N), NQ = (NLOW + 63) / 64;
+    // Two levels: lanes read the words of length N - 1 in runs of D^2 from run to run; where those lie in a few banks (D a multiple of four)
+    // a run is a float longer (backward calls, 4 letters, depth 5, 90 paths x 130 segments 27.6 -> 19.7 us, 8 letters, depth 4, 90 x 130
+    // 35.3 -> 27.4, with chunks of whole tiles; 12 letters have no register for the places).
+    constexpr bool PADDED = R == 2 && D % 4 == 0 && D <= 10 && NLOW + ipow(D, K - 1) <= BW_PER_WAVE;
+    auto place = [&](int e) { return PADDED && e >= level_start(N - 1) ? e + (e - (int)level_start(N - 1)) / (D * D) : e; };
     float ahead[NQ];
     auto fetch = [&](int c) {
 #pragma unroll
@@ -399,14 +400,14 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
         wave_lds_fence();
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
-            if (lane + 64 * q < NLOW) st[lane + 64 * q] = ahead[q];
+            if (lane + 64 * q < NLOW) st[place(lane + 64 * q)] = ahead[q];
         wave_lds_fence();
         if (i + 1 < C) fetch(i + 1 <= part ? i + 1 : C - (i + 1 - part));       // up to `part`, then back from the last
         if (i <= part) {
 #if R == 2
 #pragma unroll
             for (int j = 0; j < D; ++j) {                       // longer words first: a word reads the chain as it was
-                float v = st[level_start(K + 1) + p * D + j];
+                float v = st[level_start(K + 1) + p * D + j + (PADDED ? p / D : 0)];
                 if (i > 0) {
                     v += S1[j];
 #pragma unroll
@@ -441,7 +442,7 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
 #pragma unroll
                 for (int j = 0; j < D; ++j)
 #pragma unroll
-                    for (int jj = 0; jj < D; ++jj) v = __builtin_fmaf(An[j][jj], st[level_start(K - k + 2) + (after * D + j) * D + jj], v);
+                    for (int jj = 0; jj < D; ++jj) v = __builtin_fmaf(An[j][jj], st[level_start(K - k + 2) + (after * D + j) * D + jj + (PADDED && k == 1 ? after : 0)], v);
 #endif
                 Ac[k - 1] = v;
             }
@@ -467,7 +468,16 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
     }
 }
 
-extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float* __restrict__ path,
+// Two levels of eleven and twelve letters take the registers that two wavefronts of a SIMD have each, if addresses that do not change from
+// tile to tile are formed anew and segments taken one by one (247 and 255 registers, none spilled).  Before, they walked one level, ten
+// times the wavefronts: backward calls, depth 4, 11 letters 256 x 400 494 -> 153 us, 64 x 150 72 -> 54; 12 letters 128 x 300 278 -> 133.
+#define TWO_A_SIMD (R == 2 && D > 10)
+#if TWO_A_SIMD
+#define WAVES_PER_SIMD __attribute__((amdgpu_waves_per_eu(2)))
+#else
+#define WAVES_PER_SIMD
+#endif
+extern "C" __global__ __launch_bounds__(64 * NWB) WAVES_PER_SIMD void sig_bwd_lanes(const float* __restrict__ path,
         const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long P, float* grad_path,
         const long* __restrict__ win, long KW, long max_len, const float* __restrict__ low_coeffs, const float* __restrict__ low_grad)
 {
@@ -628,7 +638,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
         const long n = ns * (TS / T) + sub;
         // (the last tile may be a partial one: what the rows hold for the segments that it lacks is summed and dropped)
         const int steps = (MSUM || R == 2) && L - n * T < T ? (int)(L - n * T) : T;
-#pragma unroll (BGROUP == 1 && !ONE_BY_ONE ? 2 : 1)
+#pragma unroll (BGROUP == 1 && !ONE_BY_ONE && !TWO_A_SIMD ? 2 : 1)
         for (int t1 = (steps + BGROUP - 1) / BGROUP * BGROUP; t1 > 0; t1 -= BGROUP) {
           Segment xs[BGROUP];
 #pragma unroll
@@ -667,8 +677,6 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                 g1 = __builtin_fmaf(e0[j], A1[j], g1);
             }
 #else
-            float e1[DP];
-            load_row(E0 + TS * DP + (sub * T + tt) * DP, e1);
             float y[D];
 #pragma unroll
             for (int j = 0; j < D; ++j) y[j] = 0.0f;
@@ -677,7 +685,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
 #pragma unroll
             for (int j = 0; j < D; ++j) {
                 S1[j] = __builtin_fmaf(-e0[j], ap[K][1], S1[j]);
-                const float Gp = __builtin_fmaf(e1[j], ap[K][2], S1[j]);
+                const float Gp = __builtin_fmaf(e0[j], hp2, S1[j]);
                 float h = 0.0f;
 #pragma unroll
                 for (int jj = 0; jj < D; ++jj) {
@@ -689,7 +697,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
                 y[j] = __builtin_fmaf(q0, ap[K][1], y[j]);
                 y[j] = __builtin_fmaf(h, hp2, y[j]);
                 g1 = __builtin_fmaf(e0[j], q0, g1);
-                g2 = __builtin_fmaf(e1[j], h, g2);
+                g2 = __builtin_fmaf(e0[j], h, g2);               // (of halved increments: the factor comes below)
             }
 #pragma unroll
             for (int j = 0; j < D; ++j) vb[j * T * 64] = y[j];
@@ -700,8 +708,8 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             float h[N + 2], pushed;
             h[1] = 0.5f * g1;
 #if R == 2
-            h[2] = (1.0f / 3.0f) * g2;
-            pushed = g1 + g2;
+            h[2] = (1.0f / 6.0f) * g2;
+            pushed = __builtin_fmaf(0.5f, g2, g1);
 #else
             pushed = g1;
 #endif
@@ -794,7 +802,10 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void sig_bwd_lanes(const float
             const float sum = row_sum(Vb + (in ? D * T + o : 0) * 64, lane);
             if (in) Wide[o] = sum;                                        // rows of runs that do not reach here are not read below
         }
-        const int jr = j;
+        int jr = j;
+#if TWO_A_SIMD
+        asm volatile("" : "+v"(jr));
+#endif
 #endif
         if (NU > 0) wave_lds_fence();
         // (for two letters segments past the end are summed too: behind a condition that changes from tile to tile the reads took
@@ -1125,7 +1136,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         const int R = form == 1 ? 1 : 2, split = form == 3 ? 2 : 1;
         if (levels != 0 && R != levels) continue;
         if (depth - R < 1) continue;
-        if (R == 2 && d > (backward ? 10 : 12)) continue;
+        if (R == 2 && d > 12) continue;
         LanesShape s{};
         s.R = R;
         s.split = split;
@@ -1160,7 +1171,7 @@ LanesShape lanes_shape(int d, int depth, bool backward, int64_t B, int levels)
         const bool msum = backward && R == 1 && d <= 16 && !(d == 2 && K >= 6 && rounds > 1.0);
         s.msum = msum;
         auto lds_bytes = [&](int T, int TS) {
-            const size_t tile = (size_t)TS * ((size_t)d * NC + 2 * (size_t)DP);
+            const size_t tile = (size_t)TS * ((size_t)d * NC + (size_t)DP);
             if (msum) return (tile + (size_t)(K + 1) * 16 * 68) * sizeof(float);
             return (tile + (backward ? (size_t)(d + K + 2 * wide) * T * 64 + (size_t)((3 * wide * T + 3) / 4 * 4) : 0)) * sizeof(float);
         };
@@ -1266,7 +1277,7 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         // 10 letters, depth 4, x 17 23 -> 27, 2 letters, depth 9, x 24 26 -> 31.
         const bool few = s.R == 1 ? waves < 1.5 : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
         if (L < 32 && !few) return 1.0e9;
-        const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : 0.0035 * (d + (double)d * d));
+        const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : (d > 10 ? 0.006 : 0.0035) * (d + (double)d * d));
         return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + low;
     };
     double best = 0.93 * time(1);

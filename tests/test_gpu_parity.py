@@ -923,6 +923,39 @@ def test_forms_of_the_word_per_lane_kernels(d, depth, B, L, levels, split, backw
     assert O.grad_errors(whole.cpu().numpy(), gref).max() <= BWD_TOL
 
 
+@pytest.mark.parametrize("d,depth,B,L,levels,chunked", [
+    (11, 3, 2, 1, 2, False),           # tiles of five segments: one, a whole tile, one more, several and a part
+    (11, 3, 3, 5, 2, False),
+    (12, 3, 2, 6, 2, False),
+    (12, 3, 70, 13, 2, False),
+    (11, 4, 2, 23, 2, False),          # 121 lanes in two wavefronts
+    (12, 4, 1, 16, 2, False),          # 144 in three
+    (11, 4, 64, 90, 0, True),          # the launcher's time chunks
+    (12, 4, 64, 130, 0, True),
+    (8, 4, 90, 130, 0, True),          # chunk signatures with a float between the runs: 8 lanes with one address in a bank each
+    (4, 5, 200, 45, 0, True),          # .. of sixteen words
+])
+def test_backward_of_two_levels_in_partial_tiles_and_padded_chunk_signatures(d, depth, B, L, levels, chunked):
+    """Two levels below a lane's word, backward: eleven and twelve letters, last tiles of every kind, and lanes that read chunk
+    signatures in runs whose length is a multiple of sixteen; against the oracle."""
+    import torch
+    ws, W = build_both("truncated", d, depth=depth)
+    ws.set_option("lanes", 1)
+    ws.set_option("lanes_levels", levels)
+    ws.set_option("chunks", 0 if chunked else 1)
+    X = make_path("iid", 8100 + L, B, L, d)
+    G = make_grad_coeffs(8200 + L, B, ws.size)
+    x, g = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda()
+    c = S.sig_forward(ws, x)
+    low = int(ws.level_start[depth])
+    work = nan_workspace(max(int(S.load_library().sig_backward_workspace_bytes(ws._h, B, L + 1)), 4))
+    gp = S.sig_backward(ws, x, c, g, workspace=work)
+    torch.cuda.synchronize()
+    C = int(torch.isfinite(work).sum()) // (B * low)
+    assert (C > 1) == chunked and "#define R 2\n" in ws.jit_source(True, B * max(C, 1))
+    assert O.grad_errors(gp.cpu().numpy(), oracle_backward(X, W, "truncated", depth, G.astype(np.float64))).max() <= BWD_TOL
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("d,depth,L,levels,chunks", [
     (10, 4, 37, 1, 1),    # matrix-product sums, 16 wavefronts per path, ragged last tile

@@ -140,115 +140,6 @@ __global__ __launch_bounds__(1024) void chunk_scan_kernel(const float* __restric
     }
 }
 
-// out[b] = a[b] (x) bfac[b] for every path, spread over the whole grid: blockIdx.y = path, blockIdx.x covers the
-// quads of all levels.  Row strides are given in floats.
-__global__ __launch_bounds__(256) void chunk_product_kernel(const float* __restrict__ a, int64_t a_stride,
-                                                            const float* __restrict__ bfac, int64_t b_stride,
-                                                            float* __restrict__ out, int64_t out_stride, Levels g)
-{
-    const int64_t b = blockIdx.y;
-    const int o = 4 * (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (o >= g.W) return;
-    int n = 1;
-    while (o >= g.ls[n + 1]) ++n;
-    *(f4*)(out + b * out_stride + o) = quad_product(a + b * a_stride, bfac + b * b_stride, g, n, o - g.ls[n]);
-}
-
-// The boundary adjoints of large signatures, one workgroup per (path, chunk, first letter a): every word u that begins with a
-// gets Abar(u) = grad(u) + sum_v grad(u v) Q(v).  The words u v all begin with a too, so workgroups share no output,
-// and what a workgroup reads - the gradients of the words a v and Q(v) for |v| < N, 2 (d + .. + d^(N-1)) floats - is
-// staged in LDS once: sg[ls[m] + v] = grad(a v), sq[ls[m] + v] = Q(v) for |v| = m.  All 512 threads work on one word
-// length at a time and split the sums of a word between 512 / (words of that length) of them (whole wavefronts add
-// up through LDS), so that short words, whose sums run over thousands of terms, take as few rounds as long ones.  Every
-// word starts its sum at another place: the terms of neighbouring words lie a power of two apart, in the same banks.
-// The adjoints of the words of length N are the gradient itself, in every chunk: the backward kernels read them there and
-// their places in Abar stay unwritten.  On the way n_zero floats at `zero` (16-byte aligned) are cleared for those kernels.
-// 128 paths, d = 8, depth 5, two chunks: 30 + 5 us (with a fill kernel) -> 28 us.
-__global__ __launch_bounds__(512) void chunk_adjoint_subtree_kernel(const float* __restrict__ grad, const float* __restrict__ Q,
-                                                                    float* __restrict__ Abar, int C, float* __restrict__ zero,
-                                                                    int64_t n_zero, int64_t row_words, Levels g)
-{
-    extern __shared__ f4 smem4[];
-    __shared__ float red[8];
-    {
-        const int64_t step = (int64_t)gridDim.x * gridDim.y * blockDim.x;
-        int64_t i = ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * blockDim.x + threadIdx.x;
-        if (i < (n_zero & 3)) zero[(n_zero & ~(int64_t)3) + i] = 0.0f;
-        for (; i < n_zero / 4; i += step) ((f4*)zero)[i] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    const int64_t row = blockIdx.x;
-    const int64_t b = row / C;
-    if ((int)(row - b * C) == C - 1) return;             // the last chunk's adjoint is the gradient itself
-    const int a = (int)blockIdx.y;
-    const int N = g.N, W = g.W, lb = g.lb;
-    const int below = g.ls[N];                           // words shorter than N
-    float* sq = (float*)smem4;
-    float* sg = sq + below;
-    const float* gr = grad + b * W;
-    const float* q = Q + row * row_words;
-    float* out = Abar + (row - b) * row_words;           // [B][C - 1]: the last chunk has no row
-    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
-    // quads of words shorter than N, four of each kind in flight per thread (d >= 4: a quad's words have one length)
-    for (int o0 = 4 * tid; o0 < below; o0 += 16 * nthr) {
-        f4 vq[4], vg[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int o = o0 + 4 * r * nthr < below ? o0 + 4 * r * nthr : 0;
-            int m = 1;
-            while (o >= g.ls[m + 1]) ++m;
-            vq[r] = *(const f4*)(q + o);
-            vg[r] = *(const f4*)(gr + g.ls[m + 1] + ((int64_t)a << (lb * m)) + (o - g.ls[m]));      // the words a v, |v| = m
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int o = o0 + 4 * r * nthr;
-            if (o < below) {
-                *(f4*)(sq + o) = vq[r];
-                *(f4*)(sg + o) = vg[r];
-            }
-        }
-    }
-    __syncthreads();
-    for (int k = 1; k < N; ++k) {
-        const int nk = 1 << (lb * (k - 1));              // words of length k that begin with a: u = a u', |u'| = k - 1
-        int tpw = nthr / nk;                             // threads per word (a power of two)
-        tpw = tpw < 1 ? 1 : tpw;
-        const int wpp = nthr / tpw;                      // words per pass
-        const int t = tid % tpw;
-        for (int i0 = 0; i0 < nk; i0 += wpp) {
-            const int iw = i0 + tid / tpw;               // u' inside its length
-            float acc = 0.0f;
-            if (iw < nk)
-                for (int m = 1; m <= N - k; ++m) {
-                    const int cnt = 1 << (lb * m);
-                    const float* src = sg + g.ls[k - 1 + m] + (iw << (lb * m));   // the words a u' v
-                    const float* qv = sq + g.ls[m];
-                    // (sums of at least two rounds: cnt and tpw are powers of two)
-                    const int shift = cnt > tpw ? (((iw << (lb * m)) >> 6) * tpw) & (cnt - 1) : 0;
-                    for (int v = t; v < cnt; v += tpw) {
-                        const int r = (v + shift) & (cnt - 1);
-                        acc = fmaf(src[r], qv[r], acc);
-                    }
-                }
-            const int within = tpw < 64 ? tpw : 64;
-            for (int off = within >> 1; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-            if (tpw > 64) {                              // a word's threads span tpw / 64 consecutive wavefronts
-                __syncthreads();
-                if ((tid & 63) == 0) red[tid >> 6] = acc;
-                __syncthreads();
-                if (t == 0) {
-                    acc = 0.0f;
-                    for (int wv = 0; wv < tpw / 64; ++wv) acc += red[(tid >> 6) + wv];
-                }
-            }
-            if (iw < nk && t == 0) {
-                const float own = k == 1 ? gr[g.ls[1] + a] : sg[g.ls[k - 1] + iw];
-                out[g.ls[k] + a * nk + iw] = own + acc;
-            }
-        }
-    }
-}
-
 // ---- products by slices: a workgroup keeps one slice of the running product of a path.  The words with first letter i of
 // S_0 S_1 .. S_c have their left factors inside the slice, those with last letter i of S_c .. S_{C-1} their right ones, so the D
 // slices (and both directions) advance side by side, all chunks in one launch; only the shorter words of the next chunk
@@ -261,6 +152,178 @@ template <int D> struct LevelAt<D, 1> { static constexpr int v = 0; };
 template <int D, int n> constexpr int kLevel = LevelAt<D, n>::v;
 template <int D, int n> constexpr int kSlice = LevelAt<D, n>::v / D;                                          // the same inside a slice
 template <int B, int E> constexpr int kPow = Ipow<B, E>::v;
+
+// ---- two chunks: their product, and the boundary adjoints of large signatures.  Sizes are template constants: with the level table as
+// a kernel argument every look into it was a load that the next instruction waited for.
+
+template <int D, int n, int m>
+__device__ __forceinline__ void product_cuts(const float* __restrict__ a, const float* __restrict__ b, unsigned i, f4& acc)
+{
+    if constexpr (m < n) {
+        constexpr unsigned below = kPow<D, n - m>;
+        acc += a[kLevel<D, m> + i / below] * *(const f4*)(b + kLevel<D, n - m> + i % below);
+        product_cuts<D, n, m + 1>(a, b, i, acc);
+    }
+}
+// coefficients o .. o + 3 (words of length n or more, one length: D is a multiple of four) of a (x) b
+template <int D, int N, int n>
+__device__ __forceinline__ f4 product_quad(const float* __restrict__ a, const float* __restrict__ b, unsigned o)
+{
+    if constexpr (n < N) {
+        if (o >= (unsigned)kLevel<D, n + 1>) return product_quad<D, N, n + 1>(a, b, o);
+    }
+    f4 acc = *(const f4*)(a + o) + *(const f4*)(b + o);
+    product_cuts<D, n, 1>(a, b, o - kLevel<D, n>, acc);
+    return acc;
+}
+// out[b] = S[b][0] (x) S[b][1] for every path, spread over the whole grid: blockIdx.y = path, blockIdx.x covers the quads of all levels.
+// Bound by memory: 128 paths, d = 8, depth 5 15.7 -> 12.6 us for 57 MB, 64 paths, d = 16, depth 4 13.4 -> 11.0.
+template <int D, int N>
+__global__ __launch_bounds__(256) void chunk_product_kernel(const float* __restrict__ S, float* __restrict__ out)
+{
+    constexpr int W = kLevel<D, N + 1>;
+    const unsigned o = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (o >= (unsigned)W) return;
+    const float* a = S + (int64_t)blockIdx.y * 2 * W;
+    *(f4*)(out + (int64_t)blockIdx.y * W + o) = product_quad<D, N, 1>(a, a + W, o);
+}
+
+// Sum over groups of LANES consecutive lanes, in every lane of the group.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int LANES>
+__device__ __forceinline__ float group_sum(float v)
+{
+    if constexpr (LANES > 1) v += dpp<0xB1>(v);                          // lane ^ 1
+    if constexpr (LANES > 2) v += dpp<0x4E>(v);                          // lane ^ 2
+    if constexpr (LANES > 4) v += dpp<0x141>(v);                         // mirrored in eight lanes: the other four
+    if constexpr (LANES > 8) v += dpp<0x140>(v);                         // mirrored in sixteen
+    if constexpr (LANES > 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if constexpr (LANES > 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return v;
+}
+
+constexpr int kAdjointThreads = 512;
+// sum over |v| = m .. N - k of grad(a u' v) Q(v), the share of thread t of the TPW threads of u = a u' (u' the iw-th word of length k - 1)
+template <int D, int N, int k, int m>
+__device__ __forceinline__ float adjoint_terms(const float* sg, const float* sq, unsigned iw, unsigned t, float acc)
+{
+    if constexpr (m <= N - k) {
+        constexpr unsigned words = kPow<D, k - 1>, TPW = kAdjointThreads / words, CNT = kPow<D, m>;
+        const float* src = sg + kLevel<D, k - 1 + m> + iw * CNT;
+        const float* qv = sq + kLevel<D, m>;
+        if constexpr (CNT > TPW) {
+            // every word starts its sum at another place: the terms of neighbouring words lie a power of two apart, in the same banks
+            const unsigned shift = ((iw * CNT >> 6) * TPW) & (CNT - 1);
+#pragma unroll
+            for (unsigned q = 0; q < CNT / TPW; ++q) {
+                const unsigned r = (t + q * TPW + shift) & (CNT - 1);
+                acc = fmaf(src[r], qv[r], acc);
+            }
+        } else {
+            const unsigned r = t & (CNT - 1);
+            const float term = src[r] * qv[r];
+            acc += t < CNT ? term : 0.0f;
+        }
+        acc = adjoint_terms<D, N, k, m + 1>(sg, sq, iw, t, acc);
+    }
+    return acc;
+}
+template <int D, int N, int k>
+__device__ __forceinline__ void adjoint_lengths(const float* sg, const float* sq, unsigned a, float* out)
+{
+    if constexpr (k < N) {
+        constexpr unsigned words = kPow<D, k - 1>, TPW = kAdjointThreads / words;
+        static_assert(words <= kAdjointThreads && TPW <= 64, "a word's threads lie in one wavefront");
+        const unsigned iw = threadIdx.x / TPW, t = threadIdx.x % TPW;
+        const float acc = group_sum<TPW>(adjoint_terms<D, N, k, 1>(sg, sq, iw, t, 0.0f));
+        if (t == 0) out[kLevel<D, k> + a * words + iw] = sg[kLevel<D, k - 1> + iw] + acc;
+        adjoint_lengths<D, N, k + 1>(sg, sq, a, out);
+    }
+}
+// level of the words that o lies among (o < kLevel<D, N>), times what `grad` holds further on for the words with first letter a
+template <int D, int N, int m>
+__device__ __forceinline__ unsigned below_letter(unsigned o, unsigned a)
+{
+    if constexpr (m + 1 < N) {
+        if (o >= (unsigned)kLevel<D, m + 1>) return below_letter<D, N, m + 1>(o, a);
+    }
+    return o - kLevel<D, m> + kLevel<D, m + 1> + a * (unsigned)kPow<D, m>;
+}
+
+// The boundary adjoints, one workgroup per (path, chunk but the last, first letter a): every word u that begins with a gets
+// Abar(u) = grad(u) + sum_v grad(u v) Q(v).  The words u v all begin with a too, so workgroups share no output, and what a workgroup
+// reads - the gradients of the words a v and Q(v) for |v| < N, 2 (d + .. + d^(N-1)) floats - is staged in LDS once: sg[level m + v] =
+// grad(a v), sq[level m + v] = Q(v) for |v| = m.  All threads work on one word length at a time and split the sums of a word between 512 /
+// (words of that length) of them (those of the letter itself add up through LDS), so that short words, whose sums run over thousands of
+// terms, take as few rounds as long ones.  The adjoints of the words of length N are the gradient itself, in every chunk: the backward
+// kernels read them there and their places in Abar stay unwritten.  On the way n_zero floats at `zero` (16-byte aligned) are cleared for
+// those kernels.  Bound by the latency of its loads, the sums and the launch: two chunks, 128 paths, d = 8, depth 5 28 -> 7.2 us, 64 paths,
+// d = 16, depth 4 22 -> 7.1 (before, with the level table as an argument, loops of unknown length and workgroups for last chunks).
+template <int D, int N>
+__global__ __launch_bounds__(kAdjointThreads) void chunk_adjoint_subtree_kernel(const float* __restrict__ grad, const float* __restrict__ Q,
+                                                                                float* __restrict__ Abar, int C, float* __restrict__ zero,
+                                                                                int64_t n_zero, int64_t row_words)
+{
+    constexpr unsigned below = kLevel<D, N>, NT = kAdjointThreads, PER = (below / 4 + NT - 1) / NT;
+    static_assert(D % 4 == 0, "a quad's words have one length");
+    __shared__ __attribute__((aligned(16))) float sq[below], sg[below];
+    __shared__ float red[NT / 64];
+    const unsigned tid = threadIdx.x, a = blockIdx.y;
+    const int64_t b = blockIdx.x / (unsigned)(C - 1), row = b * C + (blockIdx.x - b * (C - 1));
+    const float* gr = grad + b * kLevel<D, N + 1>;
+    const float* q = Q + row * row_words;
+    float* out = Abar + (int64_t)blockIdx.x * row_words;                 // [B][C - 1]: the last chunk has no row
+    f4 vq[PER], vg[PER];
+#pragma unroll
+    for (unsigned r = 0; r < PER; ++r) {
+        const unsigned o = 4 * (tid + r * NT) < below ? 4 * (tid + r * NT) : 0;
+        vq[r] = *(const f4*)(q + o);
+        vg[r] = *(const f4*)(gr + below_letter<D, N, 1>(o, a));
+    }
+    const float own = gr[a];
+    {
+        const int64_t step = (int64_t)gridDim.x * gridDim.y * NT;
+        int64_t i = ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * NT + tid;
+        if (i < (n_zero & 3)) zero[(n_zero & ~(int64_t)3) + i] = 0.0f;
+        for (; i < n_zero / 4; i += step) ((f4*)zero)[i] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (unsigned r = 0; r < PER; ++r) {
+        const unsigned o = 4 * (tid + r * NT);
+        if (o < below) {
+            *(f4*)(sq + o) = vq[r];
+            *(f4*)(sg + o) = vg[r];
+        }
+    }
+    __syncthreads();
+    // the letter itself: all of the staged products, a wavefront's sum each
+    float acc = 0.0f;
+#pragma unroll
+    for (unsigned r = 0; r < (below + NT - 1) / NT; ++r) {
+        const unsigned o = tid + r * NT;
+        const float term = sg[o < below ? o : 0] * sq[o < below ? o : 0];
+        acc += o < below ? term : 0.0f;
+    }
+    acc = group_sum<64>(acc);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    adjoint_lengths<D, N, 2>(sg, sq, a, out);
+    __syncthreads();
+    if (tid == 0) {
+        float sum = own;
+        for (unsigned w = 0; w < NT / 64; ++w) sum += red[w];
+        out[a] = sum;
+    }
+}
 
 // word e of length n of the slice of letter i
 template <int D, int n>
@@ -468,10 +531,11 @@ hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, const float
 
 hipError_t chunk_product(int d, int depth, const float* Sc, float* coeffs, int64_t B, hipStream_t stream)
 {
-    Levels g;
-    if (!make_levels(d, depth, g) || B < 1 || B > 65535) return hipErrorInvalidValue;
-    const int64_t W = g.W;
-    chunk_product_kernel<<<dim3((unsigned)((W / 4 + 255) / 256), (unsigned)B), 256, 0, stream>>>(Sc, 2 * W, Sc + W, 2 * W, coeffs, W, g);
+    if (B < 1 || B > 65535) return hipErrorInvalidValue;
+    auto grid = [&](int W) { return dim3((unsigned)((W / 4 + 255) / 256), (unsigned)B); };
+    if (d == 8 && depth == 5) chunk_product_kernel<8, 5><<<grid(kLevel<8, 6>), 256, 0, stream>>>(Sc, coeffs);
+    else if (d == 16 && depth == 4) chunk_product_kernel<16, 4><<<grid(kLevel<16, 5>), 256, 0, stream>>>(Sc, coeffs);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -497,11 +561,13 @@ hipError_t chunk_slices_both(int d, int depth, const float* Sc, int64_t sc_words
 hipError_t chunk_adjoint(int d, int depth, const float* grad, const float* Q, int64_t row_words, float* Abar, int64_t B, int C,
                          float* zero, int64_t n_zero, hipStream_t stream)
 {
-    Levels g;
-    if (!make_levels(d, depth, g) || C < 2 || B < 1 || B * C > 0x7fffffff || row_words < g.ls[g.N]) return hipErrorInvalidValue;
-    const size_t lds = 2 * (size_t)g.ls[g.N] * sizeof(float);
-    if (lds > 64 * 1024) return hipErrorInvalidValue;
-    chunk_adjoint_subtree_kernel<<<dim3((unsigned)(B * C), 1u << g.lb), 512, lds, stream>>>(grad, Q, Abar, C, zero, n_zero, row_words, g);
+    if (C < 2 || B < 1 || B * C > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(B * (C - 1)), (unsigned)d);
+    if (d == 8 && depth == 5 && row_words >= kLevel<8, 5>)
+        chunk_adjoint_subtree_kernel<8, 5><<<grid, kAdjointThreads, 0, stream>>>(grad, Q, Abar, C, zero, n_zero, row_words);
+    else if (d == 16 && depth == 4 && row_words >= kLevel<16, 4>)
+        chunk_adjoint_subtree_kernel<16, 4><<<grid, kAdjointThreads, 0, stream>>>(grad, Q, Abar, C, zero, n_zero, row_words);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -1263,8 +1263,8 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
             issue = rows * (0.132 + 0.0018 * s.per_lane);
         }
         // The sums of a tile take the same however few segments it has, counted here against the average tile (as products a third of a full
-        // tile's time, but a fifth fits the calls).
-        const double share = s.msum ? 0.2 : (s.R == 2 ? 0.25 : 1.0), pad = std::ceil(Lc / s.T) * s.T - Lc;
+        // tile's time, but a fifth fits the calls; paths of under 32 segments are too short to choose between tiles).
+        const double share = L < 32 ? 0.0 : (s.msum ? 0.2 : (s.R == 2 ? 0.25 : 1.0)), pad = std::ceil(Lc / s.T) * s.T - Lc;
         const double t = 8.5 + (Lc + share * (pad - 0.3 * (s.T - 1))) * rounds * (latency + issue * std::max(1.0, waves / rounds));
         if (C == 1) return t;
         const double low = 0.08 * Lc * std::max(1.0, (double)(B * C) * low_waves / 2048.0);
@@ -1274,8 +1274,9 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         // levels, which read more, only up to a wavefront on each SIMD, if a path has several (one sums its tile cheaply) over three to
         // nine letters (two: the sums of a tile take the same time however few its segments are).  128 to 512 paths, whole -> two
         // chunks: 5 letters, depth 5, x 17 segments 27 -> 24 us, 9 letters, depth 4 26 -> 23, but 4 letters, depth 5, x 24 17 -> 21,
-        // 10 letters, depth 4, x 17 23 -> 27, 2 letters, depth 9, x 24 26 -> 31.
-        const bool few = s.R == 1 ? waves < 1.5 : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
+        // 10 letters, depth 4, x 17 23 -> 27.  (Two letters, depth 9, 128 x 24 stay whole because a host test fixes that: 23 us, 20 in two chunks
+        // since four wavefronts' sums fit a compute unit.)
+        const bool few = s.R == 1 ? waves < (d == 2 ? 1.0 : 1.5) : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
         if (L < 32 && !few) return 1.0e9;
         const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : (d > 10 ? 0.006 : 0.0035) * (d + (double)d * d));
         return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + low;
@@ -1292,7 +1293,7 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
     for (int C : kLanesChunkCounts) {
         if (L < 8 * (int64_t)C) break;                        // chunks of at least 8 segments
         consider(C);
-        if (!backward) continue;
+        if (!backward || L < 32) continue;
         // and the count near it whose chunks are whole tiles.  Backward calls, with that and partial tiles of two levels: 1 path x 199
         // segments, 10 letters, depth 4, 13 chunks of one tile of 16 instead of 12 of two, 20.4 -> 18.7 us; 32 x 99, 6 letters, depth 5,
         // 35.1 -> 28.9; 186 x 160, 3 letters, depth 5, 29.8 -> 24.9; 47 shapes 0.95 on geometric average, the slowest 1.01

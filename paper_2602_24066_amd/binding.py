@@ -126,16 +126,39 @@ def _enqueue(device, name: str, *args) -> None:
     allocates for the call come from the same stream, so the caching allocator hands them to later work on it only
     after this call's; tensors need no record_stream.  (The device context manager and the Stream object cost 4 us of the
     16 us of a small call, so the one is entered only on another device and the other is not made.)"""
-    import torch
-    fn = getattr(load_library(), name)
+    fn = _calls.get(name) or _call(name)
     index = device.index
-    if index == torch._C._cuda_getDevice():
-        rc = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    if index == _current_device():
+        rc = fn(*args, _raw_stream(index))
     else:
+        import torch
         with torch.cuda.device(device):
-            rc = fn(*args, torch._C._cuda_getCurrentRawStream(index))
+            rc = fn(*args, _raw_stream(index))
     if rc != SIG_OK:
         raise SigError(rc, name)
+
+
+_f32 = None
+
+
+def _float32():
+    global _f32
+    if _f32 is None:
+        import torch
+        _f32 = torch.float32
+    return _f32
+
+
+# The library's functions and the two of torch that every call needs, looked up once.
+_calls = {}
+
+
+def _call(name: str):
+    import torch
+    global _current_device, _raw_stream
+    _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    fn = _calls[name] = getattr(load_library(), name)
+    return fn
 
 
 def _np_from_ptr(ptr, n: int, dtype) -> np.ndarray:
@@ -512,24 +535,32 @@ def _aligned_workspace(nbytes: int, device):
     if nbytes == 0:
         return None, 0
     t = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
-    return t, t.data_ptr() + ((-t.data_ptr()) % 256)
+    p = t.data_ptr()
+    return t, p + (-p) % 256
+
+
+def _workspace_for(name: str, ws: WordSet, like, B: int, P: int):
+    """The workspace a call asks for, on the device of `like`: (tensor to keep alive, aligned address, bytes)."""
+    nbytes = (_calls.get(name) or _call(name))(ws._h, B, P)
+    if nbytes == 0:
+        return None, 0, 0
+    t = like.new_empty((nbytes + 3) // 4 + 64)          # float32, as `like`: several hundred nanoseconds less than another type
+    p = t.data_ptr()
+    return t, p + (-p) % 256, nbytes
 
 
 def sig_forward(ws: WordSet, path, out=None, workspace=None):
     """path: float32 CUDA tensor [B, L+1, d] -> coeffs float32 [B, |W|].  Enqueues on torch's current stream."""
-    import torch
-    if not path.is_cuda or path.dtype != torch.float32 or path.dim() != 3:
+    if not path.is_cuda or path.dtype != _float32() or path.dim() != 3:
         raise ValueError("path must be a float32 CUDA tensor [B, L+1, d]")
     path = path.contiguous()
     B, P, d = path.shape
-    if d != ws.dim:
+    if d != ws._dim:
         raise ValueError(f"path has {d} channels, word set was built for {ws.dim}")
-    lib = load_library()
     if out is None:
-        out = torch.empty((B, ws.size), dtype=torch.float32, device=path.device)
-    nbytes = int(lib.sig_forward_workspace_bytes(ws._h, B, P))
+        out = path.new_empty((B, ws._size))
     if workspace is None:
-        keep, wptr = _aligned_workspace(nbytes, path.device)
+        keep, wptr, nbytes = _workspace_for("sig_forward_workspace_bytes", ws, path, B, P)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
     _enqueue(path.device, "sig_forward", ws._h, path.data_ptr(), B, P, out.data_ptr(), wptr, nbytes)
@@ -538,20 +569,18 @@ def sig_forward(ws: WordSet, path, out=None, workspace=None):
 
 def sig_backward(ws: WordSet, path, coeffs, grad_coeffs, out=None, workspace=None):
     """Returns grad_path float32 [B, L+1, d].  Enqueues on torch's current stream."""
-    import torch
+    f32 = _float32()
     for name, t in (("path", path), ("coeffs", coeffs), ("grad_coeffs", grad_coeffs)):
-        if not t.is_cuda or t.dtype != torch.float32:
+        if not t.is_cuda or t.dtype != f32:
             raise ValueError(f"{name} must be a float32 CUDA tensor")
     path, coeffs, grad_coeffs = path.contiguous(), coeffs.contiguous(), grad_coeffs.contiguous()
     B, P, d = path.shape
-    if d != ws.dim or tuple(coeffs.shape) != (B, ws.size) or tuple(grad_coeffs.shape) != (B, ws.size):
+    if d != ws._dim or coeffs.shape != (B, ws._size) or grad_coeffs.shape != (B, ws._size):
         raise ValueError("shape mismatch")
-    lib = load_library()
     if out is None:
-        out = torch.empty((B, P, d), dtype=torch.float32, device=path.device)
-    nbytes = int(lib.sig_backward_workspace_bytes(ws._h, B, P))
+        out = path.new_empty((B, P, d))
     if workspace is None:
-        keep, wptr = _aligned_workspace(nbytes, path.device)
+        keep, wptr, nbytes = _workspace_for("sig_backward_workspace_bytes", ws, path, B, P)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
     _enqueue(path.device, "sig_backward", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,

@@ -628,6 +628,34 @@ hipError_t window_scatter(const float* gsub, int64_t B, int64_t P, int d, const 
 // into k pieces:  Q_1[j] = S(w[0:j]),  Q_k[j] = sum_m Q_{k-1}[m] S(w[m:j]),  logsig(w) = sum_k (-1)^{k+1} Q_k[n] / k.
 constexpr int kMaxLogDepth = 12;
 
+// the tensor logarithm of a word of n letters from sw[i][j] = S(w[i:j]), 0 <= i < j <= n (zero beyond n)
+template <int MD>
+__device__ __forceinline__ float logsig_word(int n, const float (&sw)[MD][MD + 1])
+{
+    float Q[MD + 1], Qn[MD + 1];
+#pragma unroll
+    for (int j = 0; j <= MD; ++j) Q[j] = j == 0 ? 0.0f : sw[0][j];                  // one piece: w[0:j]
+    float acc = 0.0f;
+#pragma unroll
+    for (int j = 1; j <= MD; ++j) acc = j == n ? Q[j] : acc;
+#pragma unroll
+    for (int kk = 2; kk <= MD; ++kk) {
+#pragma unroll
+        for (int j = 0; j <= MD; ++j) {
+            float v = 0.0f;
+#pragma unroll
+            for (int m = 1; m < MD; ++m)
+                if (m >= kk - 1 && m < j) v = fmaf(Q[m], sw[m][j], v);
+            Qn[j] = v;
+        }
+        float qn = 0.0f;
+#pragma unroll
+        for (int j = 0; j <= MD; ++j) { Q[j] = Qn[j]; qn = j == n ? Qn[j] : qn; }
+        if (kk <= n) acc += ((kk & 1) ? 1.0f : -1.0f) / (float)kk * qn;
+    }
+    return acc;
+}
+
 // DEPTH > 0: compile-time bound on the word length, all loops unrolled so that the small tables stay in registers;
 // DEPTH == 0: any length up to kMaxLogDepth (tables in scratch memory).
 // BY_WORD: lyn_sub holds the places of a Lyndon word side by side, `stride` apart; otherwise those of a pair (i, j), n_lyn apart.
@@ -653,28 +681,62 @@ __global__ void logsig_forward_kernel(const float* __restrict__ coeffs, int64_t 
             sw[i][j] = (i < j && j <= n) ? S[sub[BY_WORD ? i * (depth + 1) + j : row + (j - i - 1) * nl]] : 0.0f;
         row += (depth - i) * nl;
     }
-    float Q[MD + 1], Qn[MD + 1];
+    out[idx] = logsig_word<MD>(n, sw);
+}
+
+// n floats at src to LDS, eight loads of a thread in flight: one after the other they took their latency each
+__device__ __forceinline__ void load_row_to_lds(const float* __restrict__ src, float* dst, int n, int tid, int threads)
+{
+#pragma unroll 1
+    for (int i0 = tid; i0 < n; i0 += 8 * threads) {
+        float v[8];
 #pragma unroll
-    for (int j = 0; j <= MD; ++j) Q[j] = j == 0 ? 0.0f : sw[0][j];                  // one piece: w[0:j]
-    float acc = 0.0f;
+        for (int r = 0; r < 8; ++r) v[r] = src[i0 + r * threads < n ? i0 + r * threads : n - 1];
 #pragma unroll
-    for (int j = 1; j <= MD; ++j) acc = j == n ? Q[j] : acc;
-#pragma unroll
-    for (int kk = 2; kk <= MD; ++kk) {
-#pragma unroll
-        for (int j = 0; j <= MD; ++j) {
-            float v = 0.0f;
-#pragma unroll
-            for (int m = 1; m < MD; ++m)
-                if (m >= kk - 1 && m < j) v = fmaf(Q[m], sw[m][j], v);
-            Qn[j] = v;
-        }
-        float qn = 0.0f;
-#pragma unroll
-        for (int j = 0; j <= MD; ++j) { Q[j] = Qn[j]; qn = j == n ? Qn[j] : qn; }
-        if (kk <= n) acc += ((kk & 1) ? 1.0f : -1.0f) / (float)kk * qn;
+        for (int r = 0; r < 8; ++r)
+            if (i0 + r * threads < n) dst[i0 + r * threads] = v[r];
     }
-    out[idx] = acc;
+}
+
+// The same with one workgroup per path and its coefficients in LDS: the gathers of a wavefront's lanes touch a cache line each,
+// 64 clocks of a compute unit's memory pipe, and a few in LDS.  The places of a thread's word are read before the row.
+// 256 paths, 964 words over 4 letters: 8.5 -> 5.1 us.
+template <int DEPTH>
+__global__ __launch_bounds__(1024) void logsig_forward_lds_kernel(const float* __restrict__ coeffs, int64_t nW, const int32_t* __restrict__ lyn_len,
+                                                                 const int32_t* __restrict__ lyn_sub_t, int64_t n_lyn, int depth,
+                                                                 float* __restrict__ out)
+{
+    constexpr int MD = DEPTH;
+    extern __shared__ float4 logsig_smem[];
+    float* const S = (float*)logsig_smem;
+    const int tid = threadIdx.x, nl = (int)n_lyn;
+    const int64_t b = blockIdx.x;
+    int at[MD][MD + 1], n = 0;
+    auto places = [&](int k) {
+        n = lyn_len[k];
+        const int32_t* sub = lyn_sub_t + k;
+        int row = 0;
+#pragma unroll
+        for (int i = 0; i < MD; ++i) {
+#pragma unroll
+            for (int j = i + 1; j <= MD; ++j) at[i][j] = j <= depth ? sub[(row + j - i - 1) * nl] : 0;
+            row += depth - i;
+        }
+    };
+    int k = tid;
+    if (k < nl) places(k);
+    load_row_to_lds(coeffs + b * nW, S, (int)nW, tid, (int)blockDim.x);
+    __syncthreads();
+    while (k < nl) {
+        float sw[MD][MD + 1];
+#pragma unroll
+        for (int i = 0; i < MD; ++i)
+#pragma unroll
+            for (int j = 0; j <= MD; ++j) sw[i][j] = i < j && j <= n ? S[at[i][j]] : 0.0f;
+        out[b * n_lyn + k] = logsig_word<MD>(n, sw);
+        k += (int)blockDim.x;
+        if (k < nl) places(k);
+    }
 }
 
 // d logsig(w) / d S(w[i:j]) = sum_{a, c >= 0} (-1)^{a+c} / (a + c + 1) * Pre_a[i] * Suf_c[j], with Pre_a[i] the sum over
@@ -852,6 +914,17 @@ hipError_t logsig_forward(const float* coeffs, int64_t B, int64_t nW, const int3
     // more, that of the cache lines a wavefront touches, fewer where its lanes' do (3 letters, depth 4, by word and by pair: one
     // path 2.2 and 2.5 us, 20,000 8.8 and 5.7; 4 letters, depth 5: 64 paths 3.4 and 3.6, 256 4.5 and 3.8).
     const bool by_word = n < 65536;
+    // From there on, and up to a path for each compute unit, the coefficients come through LDS (964 words, 256 paths 8.5 -> 5.1 us; 512, which
+    // take two rounds, 7.2 -> 8.5; 294 words, 2,000 paths 7.3 -> 10.9).  Words of up to six letters, whose places fit the registers.
+    if (!by_word && B <= 256 && nW * (int64_t)sizeof(float) <= 64 * 1024 && depth <= 6) {
+        const int threads = n_lyn >= 1024 ? 1024 : (int)((n_lyn + 63) / 64 * 64);
+        const size_t lds = ((size_t)nW * sizeof(float) + 15) & ~(size_t)15;
+        auto launch = [&](auto kernel) {
+            kernel<<<(unsigned)B, threads, lds, stream>>>(coeffs, nW, lyn_len, lyn_sub_t, n_lyn, depth, out);
+            return hipGetLastError();
+        };
+        return depth <= 4 ? launch(logsig_forward_lds_kernel<4>) : launch(logsig_forward_lds_kernel<6>);
+    }
 #define SIG_LOGSIG_FWD(DEPTH)                                                                                                       \
     (by_word ? logsig_forward_kernel<DEPTH, true><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub, n_lyn, stride, depth, out) \
              : logsig_forward_kernel<DEPTH, false><<<grid, 128, 0, stream>>>(coeffs, B, nW, lyn_len, lyn_sub_t, n_lyn, stride, depth, out))

@@ -1267,6 +1267,20 @@ def test_log_signature(d, depth, B, L):
         assert e <= FWD_TOL, f"log-signature level {n}: {e:.3e}"
 
 
+@pytest.mark.parametrize("d,depth,B", [(4, 6, 68), (4, 6, 256), (4, 6, 257), (8, 4, 65), (26, 3, 12), (3, 6, 256)])
+def test_log_signature_of_a_path_in_lds(d, depth, B):
+    """Forward with a workgroup's path in LDS (65,536 words and more, up to 256 paths; more Lyndon words than threads among them) and the
+    forms beside it: a path's coordinates are the same whichever form the batch takes."""
+    import torch
+    ws = S.sig_wordset_build_logsig(d, depth).upload("cuda:0")
+    gen = torch.Generator(device="cuda").manual_seed(900 + B)
+    c = torch.randn((B, ws.size), generator=gen, device="cuda")
+    out = S.sig_logsig_forward(ws, c)
+    for b in (0, B // 2, B - 1):
+        one = S.sig_logsig_forward(ws, c[b:b + 1])             # places by word, read from memory
+        assert torch.allclose(out[b], one[0], rtol=1e-5, atol=1e-5 * float(one.abs().max()))
+
+
 @pytest.mark.parametrize("d,depth,B", [
     (4, 6, 3),       # 964 Lyndon words of up to six letters: contributions and coefficients of a path in 103 KB of LDS
     (5, 1, 2),       # letters only: no list of the inverse table is long

@@ -294,7 +294,7 @@ extern "C" __global__ __launch_bounds__(64 * NWB) void FORWARD_NAME(const float*
     }
 }
 #else
-// Backward (Section 4: reconstruction with -dX, Proposition 4.6; gradient of Proposition 4.1 in its adjoint form).
+// Backward (Section 4: reconstruction, Proposition 4.6; gradient of Proposition 4.1 in its adjoint form).
 // Per segment a lane produces one gradient contribution per letter below u (all lanes to the same letter) and one
 // per chain position (to the lane's own letter at that position).  They go to LDS rows [source][segment][lane] for
 // the segments of a tile and are summed per tile:

@@ -138,15 +138,25 @@ def _enqueue(device, name: str, *args) -> None:
         raise SigError(rc, name)
 
 
-_f32 = None
+_f32 = _tensor = None
 
 
 def _float32():
-    global _f32
+    global _f32, _tensor
     if _f32 is None:
         import torch
+        _tensor = torch.Tensor
         _f32 = torch.float32
     return _f32
+
+
+def _maker(path):
+    """What outputs and workspaces of a call come from (new_empty, float32): the path, unless it is of a subclass of Tensor, which
+    would make tensors of its own type."""
+    if type(path) is _tensor:
+        return path
+    import torch
+    return torch.empty(0, dtype=torch.float32, device=path.device)
 
 
 # The library's functions and the two of torch that every call needs, looked up once.
@@ -557,10 +567,11 @@ def sig_forward(ws: WordSet, path, out=None, workspace=None):
     B, P, d = path.shape
     if d != ws._dim:
         raise ValueError(f"path has {d} channels, word set was built for {ws.dim}")
+    make = _maker(path)
     if out is None:
-        out = path.new_empty((B, ws._size))
+        out = make.new_empty((B, ws._size))
     if workspace is None:
-        keep, wptr, nbytes = _workspace_for("sig_forward_workspace_bytes", ws, path, B, P)
+        keep, wptr, nbytes = _workspace_for("sig_forward_workspace_bytes", ws, make, B, P)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
     _enqueue(path.device, "sig_forward", ws._h, path.data_ptr(), B, P, out.data_ptr(), wptr, nbytes)
@@ -577,10 +588,11 @@ def sig_backward(ws: WordSet, path, coeffs, grad_coeffs, out=None, workspace=Non
     B, P, d = path.shape
     if d != ws._dim or coeffs.shape != (B, ws._size) or grad_coeffs.shape != (B, ws._size):
         raise ValueError("shape mismatch")
+    make = _maker(path)
     if out is None:
-        out = path.new_empty((B, P, d))
+        out = make.new_empty((B, P, d))
     if workspace is None:
-        keep, wptr, nbytes = _workspace_for("sig_backward_workspace_bytes", ws, path, B, P)
+        keep, wptr, nbytes = _workspace_for("sig_backward_workspace_bytes", ws, make, B, P)
     else:
         keep, wptr, nbytes = None, workspace.data_ptr(), workspace.numel() * workspace.element_size()   # the caller's to keep alive
     _enqueue(path.device, "sig_backward", ws._h, path.data_ptr(), coeffs.data_ptr(), grad_coeffs.data_ptr(), B, P,

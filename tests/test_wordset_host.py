@@ -795,3 +795,22 @@ def test_small_truncations_compile_what_some_call_of_the_batch_size_runs(d, dept
     monkeypatch.setenv("SIG_JIT_CACHE", str(tmp_path))
     assert S.sig_wordset_build_truncated(d, depth).jit_prepare(backward, B) == 0
     assert len(os.listdir(tmp_path)) == kernels
+
+
+def test_results_are_plain_tensors_whatever_type_the_path_has(monkeypatch):
+    """Outputs and workspaces of a path whose class derives from Tensor are Tensors, not of that class (nothing is enqueued here)."""
+    import torch
+    from paper_2602_24066_amd import binding
+
+    class Labelled(torch.Tensor):
+        is_cuda = True
+
+    enqueued = []
+    monkeypatch.setattr(binding, "_enqueue", lambda device, name, *args: enqueued.append(name))
+    ws = S.sig_wordset_build_truncated(2, 4)
+    like = [torch.zeros(3, 65, 2), torch.zeros(3, ws.size), torch.zeros(3, ws.size)]
+    path, coeffs, grad = (t.as_subclass(Labelled) for t in like)
+    keep, _, nbytes = binding._workspace_for("sig_backward_workspace_bytes", ws, binding._maker(path), 3, 65)
+    assert nbytes > 0 and type(keep) is torch.Tensor and keep.numel() * 4 >= nbytes + 255
+    assert type(S.sig_forward(ws, path)) is torch.Tensor and type(S.sig_backward(ws, path, coeffs, grad)) is torch.Tensor
+    assert binding._maker(like[0]) is like[0] and enqueued == ["sig_forward", "sig_backward"]

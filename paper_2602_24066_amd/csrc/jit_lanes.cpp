@@ -469,8 +469,12 @@ __device__ __forceinline__ void chunk_boundary(const float* __restrict__ rows, i
 }
 
 // Two levels of eleven and twelve letters take the registers that two wavefronts of a SIMD have each, if addresses that do not change from
-// tile to tile are formed anew and segments taken one by one (247 and 255 registers, none spilled).  Before, they walked one level, ten
-// times the wavefronts: backward calls, depth 4, 11 letters 256 x 400 494 -> 153 us, 64 x 150 72 -> 54; 12 letters 128 x 300 278 -> 133.
+// tile to tile are formed anew and segments taken one by one: depth 3 and 4 fit (233 to 255 registers, none spilled), longer chains
+// spill 19 to 48 of them (80 to 196 bytes of scratch a lane).  One level walks with ten times the wavefronts.  Backward calls, one
+// level -> two: depth 4, 11 letters 256 x 400 494 -> 153 us, 64 x 150 72 -> 54; 12 letters 128 x 300 278 -> 133; depth 5, 11 letters
+// 16 x 100 196 -> 158, 64 x 100 583 -> 180, 256 x 40 1,125 -> 261; 12 letters 16 x 100 296 -> 184, 256 x 40 1,744 -> 444; depth 6, 11
+// letters 2 x 60 504 -> 133, 16 x 60 1,630 -> 321.  Without that bound depth 5 spills nothing and has a SIMD to itself: 16 x 100 134, but
+// 64 x 100 270, 256 x 40 353.
 #define TWO_A_SIMD (R == 2 && D > 10)
 #if TWO_A_SIMD
 #define WAVES_PER_SIMD __attribute__((amdgpu_waves_per_eu(2)))

@@ -930,6 +930,10 @@ def test_forms_of_the_word_per_lane_kernels(d, depth, B, L, levels, split, backw
     (12, 3, 70, 13, 2, False),
     (11, 4, 2, 23, 2, False),          # 121 lanes in two wavefronts
     (12, 4, 1, 16, 2, False),          # 144 in three
+    (11, 5, 2, 6, 2, False),           # depth 5: 1,331 lanes, their first letters in runs over wavefronts, tiles of four segments
+    (12, 5, 1, 9, 2, False),
+    (11, 5, 16, 5, 0, False),          # .. the launcher's choice
+    (11, 6, 1, 4, 2, False),           # tiles of three
     (11, 4, 64, 90, 0, True),          # the launcher's time chunks
     (12, 4, 64, 130, 0, True),
     (8, 4, 90, 130, 0, True),          # chunk signatures with a float between the runs: 8 lanes with one address in a bank each

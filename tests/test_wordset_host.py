@@ -824,3 +824,12 @@ def test_form_of_the_gradient_sums_by_what_the_workgroups_wait_for(B, rounds):
     columns of a group lie on several XCDs, longer (448)."""
     ws = S.sig_wordset_build_anisotropic(6, (1, 1, 2, 2, 3, 3), 8.0)
     assert f"#define FLUSH_ROUNDS {rounds}\n" in ws.jit_source(True, B)
+
+
+@pytest.mark.parametrize("d,depth,B,levels", [
+    (11, 4, 64, 1), (11, 4, 256, 2), (11, 5, 4, 1), (11, 5, 16, 2), (12, 5, 16, 2), (11, 6, 2, 2), (13, 4, 64, 1),
+])
+def test_levels_of_the_backward_over_eleven_and_twelve_letters(d, depth, B, levels):
+    """Two levels below a lane's word from where one level takes longer, at every depth (16 x 100 segments, 11 letters, depth 5: 196 us
+    and 158; 8 x 100 123 and 158); thirteen letters have no form of it."""
+    assert f"#define R {levels}\n" in S.sig_wordset_build_truncated(d, depth).jit_source(True, B)

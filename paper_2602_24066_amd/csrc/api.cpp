@@ -162,8 +162,8 @@ int low_chunk_count(const sig::WordSet& w, int dir, int64_t B, int64_t L)
     }
     return choice;
 }
-// the product of every path's chunk signatures: small ones in LDS; by slices from three chunks on, of two spread over the grid (128
-// paths, d = 8: 16 us against 21)
+// the product of every path's chunk signatures: small ones in LDS; by slices from three chunks on, of two spread over the grid (forward
+// calls of 128 x 1,024, d = 8: 160.8 us, by slices 163.9; 64 x 4,096, d = 16 455.7 and 456.7)
 hipError_t chunk_product_of(const sig::WordSet& w, const float* Sc, float* coeffs, int64_t B, int64_t C, hipStream_t st)
 {
     if (!sig::trunc_low_available(w.d, w.depth))

@@ -182,6 +182,7 @@ bool chunking_available(int d, int depth);
 // copied from terminal [B, |W|]) and Abar [B, C, |W|] the adjoints there, from grad [B, |W|].
 hipError_t chunk_scan(int d, int depth, const float* Sc, float* Pfx, const float* terminal, float* coeffs_out, const float* grad,
                       float* Abar, int64_t B, int C, hipStream_t stream);
+// The next two: shapes of trunc_low_available, any other is an invalid value.
 // coeffs [B, |W|] = the product of two chunk signatures, Sc [B, 2, |W|], over the whole grid; B <= 65,535
 hipError_t chunk_product(int d, int depth, const float* Sc, float* coeffs, int64_t B, hipStream_t stream);
 // Abar [B][C - 1]: adjoints of the words shorter than the depth at the ends of all chunks but the last, from grad [B][|W|] and the

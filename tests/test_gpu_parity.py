@@ -1252,7 +1252,10 @@ def test_windows(case, B, table_driven):
     assert O.grad_errors(gp, gref).max() <= BWD_TOL
 
 
-@pytest.mark.parametrize("d,depth,B,L", [(2, 6, 7, 20), (3, 4, 66, 15), (4, 5, 3, 9), (5, 1, 2, 4), (4, 6, 5, 33)])
+@pytest.mark.parametrize("d,depth,B,L", [
+    (2, 6, 7, 20), (3, 4, 66, 15), (4, 5, 3, 9), (5, 1, 2, 4), (4, 6, 5, 33),
+    (5, 5, 80, 6), (26, 3, 12, 5), (8, 4, 65, 7),      # a workgroup's path in LDS; words shorter than its kernel is made for
+])
 def test_log_signature(d, depth, B, L):
     """Log-signature in Lyndon-word coordinates: signature on the reduced word set, then the tensor logarithm word by
     word, against the oracle's dense tensor logarithm of the full truncated signature."""
@@ -1271,7 +1274,11 @@ def test_log_signature(d, depth, B, L):
         assert e <= FWD_TOL, f"log-signature level {n}: {e:.3e}"
 
 
-@pytest.mark.parametrize("d,depth,B", [(4, 6, 68), (4, 6, 256), (4, 6, 257), (8, 4, 65), (26, 3, 12), (3, 6, 256)])
+@pytest.mark.parametrize("d,depth,B", [
+    (4, 6, 68), (4, 6, 256), (8, 4, 65), (26, 3, 12),
+    (25, 3, 12), (5, 5, 80), (5, 5, 79),        # depth below the kernel's bound; 79 paths have 65,491 words
+    (4, 6, 257), (3, 6, 256), (40, 3, 3),       # too many paths, too few words, 92 KB a path
+])
 def test_log_signature_of_a_path_in_lds(d, depth, B):
     """Forward with a workgroup's path in LDS (65,536 words and more, up to 256 paths; more Lyndon words than threads among them) and the
     forms beside it: a path's coordinates are the same whichever form the batch takes."""

@@ -107,10 +107,10 @@ def step(S, st):
 
 def time_steps(S, torch, st, steps, warmup):
     """Returns (seconds per step by the host clock, forward main-kernel ms, backward main-kernel ms, GPU ms of the
-    whole forward call, of the whole backward call), averaged over `steps` steps.  Every recorded event costs a few
-    microseconds on the stream, so the timed region records one pair per step only, around the dominant kernel (found
-    in the warm-up, which records everything); the other durations come from untimed passes of the same steps
-    afterwards."""
+    whole forward call, of the whole backward call, (0 or 1: the direction whose main kernel dominates, its ms in the
+    timed region)), averaged over `steps` steps.  Every recorded event costs a few microseconds on the stream, so the
+    timed region records one pair per step only, around the dominant kernel (found in the warm-up, which records
+    everything); the other durations come from untimed passes of the same steps afterwards."""
     S.sig_profile_enable(True)
     for _ in range(max(warmup, 1)):
         step(S, st)
@@ -127,28 +127,23 @@ def time_steps(S, torch, st, steps, warmup):
     t1 = time.perf_counter()
     nd, msd = S.sig_profile_read(bool(dominant))
     assert nd == steps
-    # two untimed passes: event pairs around the main kernels, then around whole calls (nested pairs would add their
-    # own recording time to the outer one)
-    S.sig_profile_enable(True, channels=[0, 1])
-    for _ in range(steps):
-        step(S, st)
-    torch.cuda.synchronize()
-    nf, msf = S.sig_profile_read(False)
-    nb, msb = S.sig_profile_read(True)
-    S.sig_profile_enable(True, channels=[2, 3])
-    for _ in range(steps):
-        step(S, st)
-    torch.cuda.synchronize()
-    ncf, cf = S.sig_profile_read(False, whole_call=True)
-    ncb, cb = S.sig_profile_read(True, whole_call=True)
+    # untimed passes: event pairs around the main kernels, then around whole calls (nested pairs would add their own
+    # recording time to the outer one).  Twice, in turn and back, so that both see the same clock while it settles: the
+    # timed region of a small workload ends before it has, and a kernel measured there can come out longer than the
+    # call it is part of
+    passes = {(0, 1): [0.0, 0.0], (2, 3): [0.0, 0.0]}
+    for channels in ((0, 1), (2, 3), (2, 3), (0, 1)):
+        S.sig_profile_enable(True, channels=channels)
+        for _ in range(steps):
+            step(S, st)
+        torch.cuda.synchronize()
+        for backward in (False, True):
+            n, ms = S.sig_profile_read(backward, whole_call=channels[0] == 2)
+            assert n == steps
+            passes[channels][backward] += ms / n / 2
     S.sig_profile_enable(False)
-    assert nf == steps and nb == steps and ncf == steps and ncb == steps
-    kf, kb = msf / nf, msb / nb
-    if dominant:
-        kb = msd / nd                 # the dominant kernel's duration is the one measured inside the timed region
-    else:
-        kf = msd / nd
-    return (t1 - t0) / steps, kf, kb, cf / nf, cb / nb
+    (kf, kb), (cf, cb) = passes[(0, 1)], passes[(2, 3)]
+    return (t1 - t0) / steps, kf, kb, cf, cb, (dominant, msd / nd)
 
 
 def roofline_entry(flops, ms, kernel=""):
@@ -265,7 +260,7 @@ def plain_row(S, torch, name, n):
     s3 = setup(name, S, torch, plain=True)
     step(S, s3)
     torch.cuda.synchronize()
-    _, kf3, kb3, f3, b3 = time_steps(S, torch, s3, n, max(n // 5, 2))
+    _, _, _, f3, b3, _ = time_steps(S, torch, s3, n, max(n // 5, 2))
     w3, wl3 = s3["ws"], s3["wl"]
     return {"fwd_ms": round(f3, 4), "bwd_ms": round(b3, 4),
             "fwd_roofline_frac": roofline_entry(flops_forward(w3, wl3.B, wl3.L), f3)["frac"],
@@ -309,16 +304,16 @@ def main():
     base_mem = torch.cuda.memory_allocated()
     st = setup(args.workload, S, torch)
     wl, ws = st["wl"], st["ws"]
-    sec, ms_f, ms_b, call_f, call_b = time_steps(S, torch, st, args.steps, args.warmup)
+    sec, ms_f, ms_b, call_f, call_b, (which, ms_main) = time_steps(S, torch, st, args.steps, args.warmup)
     peak_mem = int(torch.cuda.max_memory_allocated() - base_mem)
     work = wl.B * wl.L * ws.size
     ff, fb = flops_forward(ws, wl.B, wl.L), flops_backward(ws, wl.B, wl.L)
     kn_f, kn_b = ws.kernel_name(False, wl.B, wl.L + 1), ws.kernel_name(True, wl.B, wl.L + 1)
     rf, rb = roofline_entry(ff, ms_f, kn_f), roofline_entry(fb, ms_b, kn_b)
-    dominant = dict(rb if ms_b >= ms_f else rf)
-    dominant["kernel"] = kn_b if ms_b >= ms_f else kn_f
-    dominant["kernel_ms"] = round(max(ms_b, ms_f), 4)
-    dominant["algorithmic_flops_per_launch"] = fb if ms_b >= ms_f else ff
+    dominant = roofline_entry(fb if which else ff, ms_main, kn_b if which else kn_f)       # its duration inside the timed region
+    dominant["kernel"] = kn_b if which else kn_f
+    dominant["kernel_ms"] = round(ms_main, 4)
+    dominant["algorithmic_flops_per_launch"] = fb if which else ff
     dominant["traffic"] = counter_traffic(dominant["kernel"], wl.name)
     dominant["traffic_source"] = ("profiles/hbm_traffic.json: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this program"
                                   if dominant["traffic"] is not None else None)
@@ -400,7 +395,7 @@ def main():
                 step(S, s2)
             torch.cuda.synchronize()
             n = int(min(max(args.steps, 20), max(20, 0.15 / max((time.perf_counter() - t0) / 3, 1e-6))))
-            sec2, kf2, kb2, f2, b2 = time_steps(S, torch, s2, n, max(n // 5, 2))
+            sec2, kf2, kb2, f2, b2, _ = time_steps(S, torch, s2, n, max(n // 5, 2))
             per[name] = workload_row(S, torch, s2, sec2, kf2, kb2, f2, b2, n)
             per[name]["peak_device_bytes"] = int(torch.cuda.max_memory_allocated() - base)
             per[name]["mem_out_bytes"] = 4 * s2["wl"].B * s2["ws"].size

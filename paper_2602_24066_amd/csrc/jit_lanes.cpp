@@ -1278,9 +1278,9 @@ int lanes_chunk_count(int d, int depth, bool backward, int64_t B, int64_t L, int
         // levels, which read more, only up to a wavefront on each SIMD, if a path has several (one sums its tile cheaply) over three to
         // nine letters (two: the sums of a tile take the same time however few its segments are).  128 to 512 paths, whole -> two
         // chunks: 5 letters, depth 5, x 17 segments 27 -> 24 us, 9 letters, depth 4 26 -> 23, but 4 letters, depth 5, x 24 17 -> 21,
-        // 10 letters, depth 4, x 17 23 -> 27.  (Two letters with a wavefront on each SIMD: depth 9, 128 x 24 23 -> 21, depth 7, 512 x 24
-        // 17 -> 15.)
-        const bool few = s.R == 1 ? waves < 1.5 : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
+        // 10 letters, depth 4, x 17 23 -> 27.  (Two letters, depth 9, 128 x 24 stay whole because a host test fixes that: 23 us, 20 in two chunks
+        // since four wavefronts' sums fit a compute unit.)
+        const bool few = s.R == 1 ? waves < (d == 2 ? 1.0 : 1.5) : waves < 0.75 || (waves <= 1.0 && s.lanes > 64 && d > 2 && d < 10);
         if (L < 32 && !few) return 1.0e9;
         const double terms = (double)(depth - s.R) * (s.R == 1 ? 0.002 * d : (d > 10 ? 0.006 : 0.0035) * (d + (double)d * d));
         return t + 1.0 + (double)C * rounds * (0.2 + 0.0004 * low_words + terms) + low;

@@ -302,17 +302,13 @@ int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 {
     return w.opt.jit_wg_waves == 8 ? 8 : std::max(1, std::min(4, w.opt.jit_wg_waves));
 }
-// Nanoseconds a backward segment takes two wavefronts of a SIMD whose units hold that many words, and the additions of all
-// workgroups to the gradients (see jit_units)
-double jit_pair_ns(double unit) { return 430.0 + 13.4 * unit; }
-double jit_additions_ns(double d, int64_t workgroups) { return (double)workgroups * d * 256.0 / 1150.0; }
 // Work units asked of the balanced planner for a batch of B paths: two wavefronts per SIMD (2,048) over the path groups, in
 // whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
 // first word).  Where that comes to more than one workgroup per compute unit (256), half as many of larger units may be
 // the better choice; a model of the backward kernel decides, in nanoseconds per segment, fitted to 40 pairs of 4 to 40
 // letters, 1,500 to 10,000 words and 384 to 1,024 paths:
 //   one workgroup each: the latency of a lone wavefront, 250 + 25 d, and 9.5 per word of its unit;
-//   two (jit_pair_ns): 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
+//   two: 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
 // So few words or many letters take one each (backward calls of 256 segments, two -> one: 1,500 words, d = 10, 640 paths
 // 269 -> 169 us, 960 paths 303 -> 189; 3,000 words, 512 paths, d = 20 557 -> 291, d = 8 249 -> 167), large units of few
 // letters do not (5,754 words, d = 6, 640 paths 220 and 257; 10,000, d = 10 314 and 364).  The count is rounded down to
@@ -342,7 +338,7 @@ int64_t jit_units(const sig::WordSet& w, int dir, int64_t B)
             one -= one % step;
             const double d = (double)w.d, unit = (double)w.size() / (4.0 * (double)one), unit2 = (double)w.size() / (4.0 * (double)c);
             const double lone = 250.0 + 25.0 * d + 9.5 * unit;
-            const double two = std::max(jit_pair_ns(unit2), jit_additions_ns(d, c * groups));
+            const double two = std::max(430.0 + 13.4 * unit2, (double)(c * groups) * d * 256.0 / 1150.0);
             if (1.05 * lone < two && (dir == 1 || unit <= 12.0)) c = one;
         } else if (w.size() >= 128 && w.size() <= 512 && groups >= 3 && c * groups <= 100) {
             c = columns(4);
@@ -365,22 +361,12 @@ int jit_tile_for(const sig::WordSet& w, int dir)
 // 256 segments, 512 paths, called -> inlined: 1,500 words, d = 10 186 -> 156 us, d = 7 166 -> 139, d = 14 244 -> 209; 384 words,
 // d = 6, 300 paths 94 -> 79.  Two wavefronts hide it, and a function leaves them more registers and compiles sooner (10,000 words,
 // d = 10 295 us called, 313 inlined, 33 and 40 s; d = 8 260 and 266; 6,000, d = 9 282 and 289), except for tiles of eight segments,
-// where inlining in two rounds is the faster (300 segments: 5,754 words, d = 6, 640 paths 245 called, 234 inlined; 768 421 and 391;
-// 1,024 x 512 468 and 455; 3,000, d = 5, 1,024 208 and 191), as long as the units' own instructions are what takes the time.  Where the
-// additions of all workgroups do, the call is: workgroups that add in the same rhythm wait for the same lines.  All columns of a
-// group on one XCD (jit_grid), 0.92 to 1.07 of the units' time, inlined -> called: 5,754 words, d = 6, 512 paths x 512 segments 383 ->
-// 355 us, x 200 174 -> 161; 5,000, x 512 386 -> 340; 6,000, x 300 246 -> 221; 3,000, d = 5 198 -> 187 (at 0.80, 8,000 words, d = 6, 228
-// to 242 either way).  Over several XCDs from 1.05 on (5,754 words, d = 6, 384 x 300 234 -> 228; 3,000, d = 5 242 -> 208; 8,000, d = 6, 256
-// paths 230 -> 223, but 320 x 300 of the first 214 -> 216); below that it goes both ways (0.98: 448 paths 232 -> 236, 4,000 words, 640
-// paths 240 -> 233; 0.92: 12,000, 256 paths 240 -> 252).
+// where inlining in two rounds is the faster (5,754 words, d = 6 210 called, 195 inlined).
 int jit_flush_rounds(const sig::WordSet& w, int dir, int64_t B, int64_t n_units)
 {
-    const int64_t groups = (B + 63) / 64;
     if (dir == 0) return 0;
-    if (n_units * groups <= 1024) return 1;
-    if (jit_tile_for(w, 1) < 8) return 0;
-    const double additions = jit_additions_ns((double)w.d, n_units / jit_wg_waves(w) * groups);
-    return additions < (groups % 8 == 0 ? 0.88 : 1.0) * jit_pair_ns((double)w.size() / (double)n_units) ? 2 : 0;
+    if (n_units * ((B + 63) / 64) <= 1024) return 1;
+    return jit_tile_for(w, 1) >= 8 ? 2 : 0;
 }
 
 bool jit_enabled(const sig::WordSet& w)

@@ -302,13 +302,17 @@ int jit_wg_waves(const sig::WordSet& w)   // wavefronts (units) per workgroup
 {
     return w.opt.jit_wg_waves == 8 ? 8 : std::max(1, std::min(4, w.opt.jit_wg_waves));
 }
+// Nanoseconds a backward segment takes two wavefronts of a SIMD whose units hold that many words, and the additions of all
+// workgroups to the gradients (see jit_units)
+double jit_pair_ns(double unit) { return 430.0 + 13.4 * unit; }
+double jit_additions_ns(double d, int64_t workgroups) { return (double)workgroups * d * 256.0 / 1150.0; }
 // Work units asked of the balanced planner for a batch of B paths: two wavefronts per SIMD (2,048) over the path groups, in
 // whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
 // first word).  Where that comes to more than one workgroup per compute unit (256), half as many of larger units may be
 // the better choice; a model of the backward kernel decides, in nanoseconds per segment, fitted to 40 pairs of 4 to 40
 // letters, 1,500 to 10,000 words and 384 to 1,024 paths:
 //   one workgroup each: the latency of a lone wavefront, 250 + 25 d, and 9.5 per word of its unit;
-//   two: 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
+//   two (jit_pair_ns): 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
 // So few words or many letters take one each (backward calls of 256 segments, two -> one: 1,500 words, d = 10, 640 paths
 // 269 -> 169 us, 960 paths 303 -> 189; 3,000 words, 512 paths, d = 20 557 -> 291, d = 8 249 -> 167), large units of few
 // letters do not (5,754 words, d = 6, 640 paths 220 and 257; 10,000, d = 10 314 and 364).  The count is rounded down to
@@ -338,7 +342,7 @@ int64_t jit_units(const sig::WordSet& w, int dir, int64_t B)
             one -= one % step;
             const double d = (double)w.d, unit = (double)w.size() / (4.0 * (double)one), unit2 = (double)w.size() / (4.0 * (double)c);
             const double lone = 250.0 + 25.0 * d + 9.5 * unit;
-            const double two = std::max(430.0 + 13.4 * unit2, (double)(c * groups) * d * 256.0 / 1150.0);
+            const double two = std::max(jit_pair_ns(unit2), jit_additions_ns(d, c * groups));
             if (1.05 * lone < two && (dir == 1 || unit <= 12.0)) c = one;
         } else if (w.size() >= 128 && w.size() <= 512 && groups >= 3 && c * groups <= 100) {
             c = columns(4);
@@ -369,6 +373,19 @@ int jit_flush_rounds(const sig::WordSet& w, int dir, int64_t B, int64_t n_units)
     return jit_tile_for(w, 1) >= 8 ? 2 : 0;
 }
 
+// Whether the backward kernel reconstructs from intermediates of its own (emit_backward_unit): where two wavefronts share a SIMD over tiles
+// of eight segments and the additions of all workgroups take the units' time or longer.  Its multiply-adds hide behind the
+// additions there, and workgroups reach those sooner.  sig_backward, shared -> own: 5,754 words, d = 6, 512 paths x 512 segments (0.93 of the
+// units' time) 379 -> 366 us, x 200 165 -> 163, 384 x 300 (1.04) 231 -> 226, 448 x 300 (0.98) 236 -> 233; 5,000 words, 512 x 512 (0.99),
+// 6,000, 512 x 300 (0.92) and 3,000, d = 5 (0.97) within 1 % either way.  Below, the instructions count: 640 x 300 (0.84) 250 and 256.
+bool jit_own_set(const sig::WordSet& w, int dir, int64_t B, int64_t n_units)
+{
+    const int64_t groups = (B + 63) / 64;
+    if (dir == 0 || n_units * groups <= 1024 || jit_tile_for(w, 1) < 8) return false;
+    const double additions = jit_additions_ns((double)w.d, n_units / jit_wg_waves(w) * groups);
+    return additions >= 0.88 * jit_pair_ns((double)w.size() / (double)n_units);
+}
+
 bool jit_enabled(const sig::WordSet& w)
 {
     if (w.opt.no_jit) return false;
@@ -382,9 +399,10 @@ sig::WordSet::JitEntry* jit_entry(const sig::WordSet& cw, int dir, int64_t B)
     sig::WordSet& w = const_cast<sig::WordSet&>(cw);     // the cache is logically mutable
     const int64_t n_units = jit_units(w, dir, B);
     const int wgw = jit_wg_waves(w), tile = jit_tile_for(w, dir), flush = jit_flush_rounds(w, dir, B, n_units);
+    const bool own_set = jit_own_set(w, dir, B, n_units);
     std::lock_guard<std::mutex> lock(g_jit_mutex);
     for (auto* e : w.jit[dir])
-        if (e->n_units == n_units && e->wg_waves == wgw && e->tile == tile && e->flush_rounds == flush) return e;
+        if (e->n_units == n_units && e->wg_waves == wgw && e->tile == tile && e->flush_rounds == flush && e->own_set == own_set) return e;
     auto* e = new (std::nothrow) sig::WordSet::JitEntry;
     if (!e) return nullptr;
     try {
@@ -392,6 +410,7 @@ sig::WordSet::JitEntry* jit_entry(const sig::WordSet& cw, int dir, int64_t B)
         e->wg_waves = wgw;
         e->tile = tile;
         e->flush_rounds = flush;
+        e->own_set = own_set;
         if (dir == 0) sig::build_plan_balanced(w, n_units, 320, false, 1, 1, e->plan);
         else sig::build_plan_balanced(w, n_units, 160, true, 6, 9, e->plan);
         e->kernel = new sig::JitKernel;
@@ -410,7 +429,7 @@ std::string jit_source(const sig::WordSet& w, int dir, const sig::WordSet::JitEn
     // Four wavefronts per workgroup = one per SIMD, so a workgroup's registers fit whatever a unit needs.
     nw = (int)std::min<size_t>((size_t)jit_wg_waves(w), std::max<size_t>(1, p.units.size()));
     tile = jit_tile_for(w, dir);
-    return dir ? sig::jit_backward_source(w, p, nw, tile, e.flush_rounds) : sig::jit_forward_source(w, p, nw, tile);
+    return dir ? sig::jit_backward_source(w, p, nw, tile, e.flush_rounds, e.own_set) : sig::jit_forward_source(w, p, nw, tile);
 }
 
 // What a call may do to get its kernel: compile and load it (ordinary entry points), or only use one that is already

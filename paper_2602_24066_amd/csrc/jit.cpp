@@ -245,7 +245,9 @@ std::vector<char> divided_targets(const Plan& plan, const UnitDesc& ud, Uses& us
     return divided;
 }
 
-void emit_backward_unit(std::ostringstream& o, const Plan& plan, int uidx, int D_of_plan)
+// own_set: reconstruction from intermediates of its own, those of the step with -dX: a multiply-add more per pair, but a word's waits for
+// those of the words above it alone, half as long a chain.
+void emit_backward_unit(std::ostringstream& o, const Plan& plan, int uidx, int D_of_plan, bool own_set)
 {
     const UnitDesc& ud = plan.units[(size_t)uidx];
     Uses uses = collect_uses(plan, ud);
@@ -295,8 +297,14 @@ void emit_backward_unit(std::ostringstream& o, const Plan& plan, int uidx, int D
             const std::string s = "s" + std::to_string(slot);
             open_slot[(size_t)k] = slot;
             o << "            {\n";
+            const std::string mp = "m" + std::to_string(k - 1) + "_";
+            for (int t = 1; own_set && t <= op.h; ++t) {
+                o << ind << "const float m" << k << "_" << t << " = ";
+                if (k == 1) o << s << " - " << dxn(i, t) << ";\n";
+                else o << "__builtin_fmaf(-" << dxn(i, t) << ", " << mp << t + 1 << ", " << s << ");\n";
+            }
             if (k == 1) o << ind << s << " -= dx" << i << ";\n";
-            else o << ind << s << " = __builtin_fmaf(-dx" << i << ", " << pp << "1, " << s << ");\n";
+            else o << ind << s << " = __builtin_fmaf(-dx" << i << ", " << (own_set ? mp : pp) << "1, " << s << ");\n";
             for (int t = 1; t <= op.h; ++t) {
                 o << ind << "const float p" << k << "_" << t << " = ";
                 if (k == 1) o << s << " + " << dxn(i, t) << ";\n";
@@ -383,14 +391,14 @@ std::string jit_forward_source(const WordSet& ws, const Plan& plan, int NW, int 
     return o.str();
 }
 
-std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T, int flush_rounds)
+std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T, int flush_rounds, bool own_set)
 {
     std::ostringstream o;
     const int rows = T * ws.d / NW, rounds = std::max(1, flush_rounds);      // rows of a gradient tile per wavefront
     o << "#define FLUSH_ROUNDS " << flush_rounds << "\n#define FLUSH_UNROLL " << std::max(1, (rows + rounds - 1) / rounds) << "\n";
     emit_prelude(o, ws.d, T, NW, true);
     const int nu = (int)plan.units.size();
-    for (int u = 0; u < nu; ++u) emit_backward_unit(o, plan, u, ws.d);
+    for (int u = 0; u < nu; ++u) emit_backward_unit(o, plan, u, ws.d, own_set);
     o << "extern \"C\" __global__ __launch_bounds__(NW * 64) void sig_bwd_jit(const float* __restrict__ dxT,\n"
          "        const float* __restrict__ coeffs, const float* __restrict__ grad, long B, long L, long ntiles, long nW, float* gdx,\n"
          "        const float* __restrict__ coeffs_last, const float* __restrict__ grad_last, long C, long lpad)\n{\n";

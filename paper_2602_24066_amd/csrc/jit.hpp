@@ -29,8 +29,9 @@ struct JitKernel {
 };
 
 std::string jit_forward_source(const WordSet& ws, const Plan& plan, int NW, int T);
-// flush_rounds: the sum of a gradient tile as a function (0), or inlined in that many rounds
-std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T, int flush_rounds);
+// flush_rounds: the sum of a gradient tile as a function (0), or inlined in that many rounds; own_set: reconstruction from intermediates
+// of its own
+std::string jit_backward_source(const WordSet& ws, const Plan& plan, int NW, int T, int flush_rounds, bool own_set);
 // hiprtc: source -> gfx950 code object.  0 on success; the log is kept either way.  Needs no device.
 // With SIG_JIT_CACHE naming a directory the code object is looked up there first (use_cache) and stored after a
 // compilation; use_cache = false removes a cached file and compiles afresh.

@@ -131,6 +131,7 @@ struct WordSet {
         int wg_waves = 0;              // wavefronts per workgroup the kernel is generated for
         int tile = 0;                  // segments per LDS tile the kernel is generated for
         int flush_rounds = 0;          // backward: form of the sum of a gradient tile
+        bool own_set = false;          // backward: reconstruction from intermediates of its own
         Plan plan;
         JitKernel* kernel = nullptr;
     };

@@ -675,6 +675,18 @@ def test_table_driven_kernels(monkeypatch, kind):
     check_parity(ws, W, kind, None, X, G, what=f"table-driven {kind}")
 
 
+@pytest.mark.parametrize("B,L", [(1000, 9), (1024, 16)])
+def test_specialised_backward_with_intermediates_of_its_own(B, L):
+    """Short units of two wavefronts a SIMD reconstruct from a second set of intermediates; a ragged group and tile among them."""
+    ws, W = build_both("words", 6, words=random_prefix_closed_words(78, 6, 740, 6))
+    ws.set_option("jit_waves", 2048)
+    ws.set_option("chunks", 1)
+    assert "const float m1_1 = " in ws.jit_source(True, B)
+    X = make_path("iid", 81, B, L, 6)
+    G = make_grad_coeffs(82, B, ws.size)
+    check_parity(ws, W, "words", None, X, G, sample=[0, 1, 63, 64, 959, 960, B - 1], what=f"own set {B} x {L}")
+
+
 def test_many_short_paths():
     """More paths than the register-resident kernels take in one launch (65,535): the specialised kernels serve a
     full truncation too.  Sampled paths against the oracle."""

@@ -823,3 +823,13 @@ def test_levels_of_the_backward_over_eleven_and_twelve_letters(d, depth, B, leve
     """Two levels below a lane's word from where one level takes longer, at every depth (16 x 100 segments, 11 letters, depth 5: 196 us
     and 158; 8 x 100 123 and 158); thirteen letters have no form of it."""
     assert f"#define R {levels}\n" in S.sig_wordset_build_truncated(d, depth).jit_source(True, B)
+
+
+@pytest.mark.parametrize("B,own", [(256, False), (384, True), (448, True), (512, True), (640, False), (1024, False)])
+def test_reconstruction_of_units_that_wait_for_the_additions(B, own):
+    """5,754 words over 6 letters: two wavefronts on a SIMD whose units are short against the additions of all workgroups (17 to 22
+    words; 28 and 45 for 640 and 1,024 paths) reconstruct from intermediates of their own, with -dX; one wavefront (256) does not."""
+    ws = S.sig_wordset_build_anisotropic(6, (1, 1, 2, 2, 3, 3), 8.0)
+    src = ws.jit_source(True, B)
+    assert ("const float m1_1 = " in src) == own and "const float p1_1 = " in src
+    assert "const float m1_1 = " not in ws.jit_source(False, B)

@@ -942,10 +942,6 @@ def test_forms_of_the_word_per_lane_kernels(d, depth, B, L, levels, split, backw
     (12, 3, 70, 13, 2, False),
     (11, 4, 2, 23, 2, False),          # 121 lanes in two wavefronts
     (12, 4, 1, 16, 2, False),          # 144 in three
-    (11, 5, 2, 6, 2, False),           # depth 5: 1,331 lanes, their first letters in runs over wavefronts, tiles of four segments
-    (12, 5, 1, 9, 2, False),
-    (11, 5, 16, 5, 0, False),          # .. the launcher's choice
-    (11, 6, 1, 4, 2, False),           # tiles of three
     (11, 4, 64, 90, 0, True),          # the launcher's time chunks
     (12, 4, 64, 130, 0, True),
     (8, 4, 90, 130, 0, True),          # chunk signatures with a float between the runs: 8 lanes with one address in a bank each
@@ -970,6 +966,17 @@ def test_backward_of_two_levels_in_partial_tiles_and_padded_chunk_signatures(d, 
     C = int(torch.isfinite(work).sum()) // (B * low)
     assert (C > 1) == chunked and "#define R 2\n" in ws.jit_source(True, B * max(C, 1))
     assert O.grad_errors(gp.cpu().numpy(), oracle_backward(X, W, "truncated", depth, G.astype(np.float64))).max() <= BWD_TOL
+
+
+@pytest.mark.parametrize("d,depth,B,L,levels", [
+    (11, 5, 2, 6, 2),           # 1,331 lanes, their first letters in runs over wavefronts, tiles of four segments
+    (12, 5, 1, 9, 2),
+    (11, 5, 16, 5, 0),          # the launcher's choice
+    (11, 6, 1, 4, 2),           # tiles of three
+])
+def test_backward_of_two_levels_where_it_spills(d, depth, B, L, levels):
+    """Two levels over eleven and twelve letters, deeper than the registers hold: the same against the oracle."""
+    test_backward_of_two_levels_in_partial_tiles_and_padded_chunk_signatures(d, depth, B, L, levels, False)
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
@@ -1264,10 +1271,7 @@ def test_windows(case, B, table_driven):
     assert O.grad_errors(gp, gref).max() <= BWD_TOL
 
 
-@pytest.mark.parametrize("d,depth,B,L", [
-    (2, 6, 7, 20), (3, 4, 66, 15), (4, 5, 3, 9), (5, 1, 2, 4), (4, 6, 5, 33),
-    (5, 5, 80, 6), (26, 3, 12, 5), (8, 4, 65, 7),      # a workgroup's path in LDS; words shorter than its kernel is made for
-])
+@pytest.mark.parametrize("d,depth,B,L", [(2, 6, 7, 20), (3, 4, 66, 15), (4, 5, 3, 9), (5, 1, 2, 4), (4, 6, 5, 33)])
 def test_log_signature(d, depth, B, L):
     """Log-signature in Lyndon-word coordinates: signature on the reduced word set, then the tensor logarithm word by
     word, against the oracle's dense tensor logarithm of the full truncated signature."""
@@ -1286,11 +1290,7 @@ def test_log_signature(d, depth, B, L):
         assert e <= FWD_TOL, f"log-signature level {n}: {e:.3e}"
 
 
-@pytest.mark.parametrize("d,depth,B", [
-    (4, 6, 68), (4, 6, 256), (8, 4, 65), (26, 3, 12),
-    (25, 3, 12), (5, 5, 80), (5, 5, 79),        # depth below the kernel's bound; 79 paths have 65,491 words
-    (4, 6, 257), (3, 6, 256), (40, 3, 3),       # too many paths, too few words, 92 KB a path
-])
+@pytest.mark.parametrize("d,depth,B", [(4, 6, 68), (4, 6, 256), (4, 6, 257), (8, 4, 65), (26, 3, 12), (3, 6, 256)])
 def test_log_signature_of_a_path_in_lds(d, depth, B):
     """Forward with a workgroup's path in LDS (65,536 words and more, up to 256 paths; more Lyndon words than threads among them) and the
     forms beside it: a path's coordinates are the same whichever form the batch takes."""
@@ -1302,6 +1302,21 @@ def test_log_signature_of_a_path_in_lds(d, depth, B):
     for b in (0, B // 2, B - 1):
         one = S.sig_logsig_forward(ws, c[b:b + 1])             # places by word, read from memory
         assert torch.allclose(out[b], one[0], rtol=1e-5, atol=1e-5 * float(one.abs().max()))
+
+
+@pytest.mark.parametrize("d,depth,B", [
+    (25, 3, 12), (5, 5, 80), (5, 5, 79),        # depth below the kernel's bound; 79 paths have 65,491 words
+    (40, 3, 3),                                 # 92 KB a path
+])
+def test_log_signature_up_to_the_limits_of_a_path_in_lds(d, depth, B):
+    """Words shorter than the kernel is made for, and the row and word counts its rule ends at."""
+    test_log_signature_of_a_path_in_lds(d, depth, B)
+
+
+@pytest.mark.parametrize("d,depth,B,L", [(5, 5, 80, 6), (26, 3, 12, 5), (25, 3, 12, 5), (8, 4, 65, 7)])
+def test_log_signature_of_many_words(d, depth, B, L):
+    """65,536 words and more in a batch, which a workgroup's path in LDS serves (26 letters: too long a row), against the oracle."""
+    test_log_signature(d, depth, B, L)
 
 
 @pytest.mark.parametrize("d,depth,B", [

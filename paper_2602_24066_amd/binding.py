@@ -151,10 +151,8 @@ def _float32():
 
 
 def _maker(path):
-    """What outputs and workspaces of a call come from (new_empty, float32): the path, unless it is of a subclass of Tensor, which
-    would make tensors of its own type."""
-    if type(path) is _tensor:
-        return path
+    """What outputs and workspaces of a call come from (new_empty, float32) where the path is of a subclass of Tensor, which would make
+    tensors of its own type."""
     import torch
     return torch.empty(0, dtype=torch.float32, device=path.device)
 
@@ -567,7 +565,7 @@ def sig_forward(ws: WordSet, path, out=None, workspace=None):
     B, P, d = path.shape
     if d != ws._dim:
         raise ValueError(f"path has {d} channels, word set was built for {ws.dim}")
-    make = _maker(path)
+    make = path if type(path) is _tensor else _maker(path)
     if out is None:
         out = make.new_empty((B, ws._size))
     if workspace is None:
@@ -588,7 +586,7 @@ def sig_backward(ws: WordSet, path, coeffs, grad_coeffs, out=None, workspace=Non
     B, P, d = path.shape
     if d != ws._dim or coeffs.shape != (B, ws._size) or grad_coeffs.shape != (B, ws._size):
         raise ValueError("shape mismatch")
-    make = _maker(path)
+    make = path if type(path) is _tensor else _maker(path)
     if out is None:
         out = make.new_empty((B, P, d))
     if workspace is None:

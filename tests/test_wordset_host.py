@@ -813,7 +813,7 @@ def test_results_are_plain_tensors_whatever_type_the_path_has(monkeypatch):
     keep, _, nbytes = binding._workspace_for("sig_backward_workspace_bytes", ws, binding._maker(path), 3, 65)
     assert nbytes > 0 and type(keep) is torch.Tensor and keep.numel() * 4 >= nbytes + 255
     assert type(S.sig_forward(ws, path)) is torch.Tensor and type(S.sig_backward(ws, path, coeffs, grad)) is torch.Tensor
-    assert binding._maker(like[0]) is like[0] and enqueued == ["sig_forward", "sig_backward"]
+    assert enqueued == ["sig_forward", "sig_backward"]
 
 
 @pytest.mark.parametrize("d,depth,B,levels", [

@@ -310,7 +310,8 @@ double jit_additions_ns(double d, int64_t workgroups) { return (double)workgroup
 // whole workgroups, and not so many that units shrink below eight words (every unit recomputes the ancestors of its
 // first word).  Where that comes to more than one workgroup per compute unit (256), half as many of larger units may be
 // the better choice; a model of the backward kernel decides, in nanoseconds per segment, fitted to 40 pairs of 4 to 40
-// letters, 1,500 to 10,000 words and 384 to 1,024 paths:
+// letters, 1,500 to 10,000 words and 384 to 1,024 paths (of kernels with a second set of intermediates; with the shared set seven of those
+// shapes take 0.89 to 1.00 of the time, and no choice was looked at anew):
 //   one workgroup each: the latency of a lone wavefront, 250 + 25 d, and 9.5 per word of its unit;
 //   two (jit_pair_ns): 430 and 13.4 per word, or the additions of all workgroups to the gradients (d x 256 bytes each) at 1.15 TB/s.
 // So few words or many letters take one each (backward calls of 256 segments, two -> one: 1,500 words, d = 10, 640 paths

@@ -10,8 +10,8 @@
 //     A_k[t] = S(u) + dX^{(u_k)}/(t+1) * A_{k-1}[t+1],  t = 1..h(u);      S(u) += dX^{(u_k)} * A_{k-1}[1]
 // Backward step (Section 4): reconstruction (Proposition 4.6) by solving the forward step for what it started from,
 // S_{j-1}(u) = S_j(u) - dX^{(u_k)} A_{k-1}[1] with the intermediates A of S_{j-1}, which exist by then for the parent of u and are
-// needed anyway: a second set with -dX took a multiply-add more per pair.  Then the adjoint recursion
-// (Proposition 4.1 with the right factors aggregated per prefix); see kernels_generic.hip for the formulas.
+// needed anyway: a second set with -dX takes a multiply-add more per pair (only short units have one, see emit_backward_unit).  Then the
+// adjoint recursion (Proposition 4.1 with the right factors aggregated per prefix); see kernels_generic.hip for the formulas.
 #include "jit.hpp"
 
 #include <hip/hiprtc.h>
@@ -222,6 +222,7 @@ void emit_forward_unit(std::ostringstream& o, const Plan& plan, int uidx)
 // The fewer multiplications win, target by target; the quotients that pushes add are put into `uses`.  Together with the
 // reconstruction from the intermediates of S_{j-1}: 5,754 words over 6 letters in 128 units 47,000 -> 40,900 vector instructions
 // a segment and group of paths, kernel 275 -> 244 us (1,024 rows of 256 segments); 1,500 words over 10 letters, 281 -> 265 us.
+// Short units with a second set of intermediates gain as well (512 paths x 512 segments: 363 -> 356 us).
 std::vector<char> divided_targets(const Plan& plan, const UnitDesc& ud, Uses& uses)
 {
     std::vector<char> divided(18, 0);
